@@ -35,11 +35,15 @@ namespace {
 
 constexpr int WG = 256;
 constexpr int NWAVE = WG / 64;
+constexpr int kMaxWaves = 16;   // waves of the largest workgroup (1,024 threads)
 constexpr int NB = 2048;    // histogram bins of one radix-select step
 constexpr int CAP = 2048;   // keys sorted in LDS at once (power of two)
-static_assert(kSelCap * 64 >= 2 * CAP + 64, "the chosen-chunk list must hold 2 * budget points");
+constexpr int64_t kWideBudget = 196608;   // largest budget of the batched path
+constexpr int64_t kSelMax = 8192;         // most chunks the bound chooses per query
+static_assert(kSelMax * 64 >= 2 * kWideBudget + 128, "the chosen chunks must hold 2 * budget points");
 constexpr int MAX_LEVELS = 16;
 constexpr int MAX_ROUNDS = 1000;
+static_assert(kLeanBudget == CAP, "a lean budget's members fit the sorted LDS keys");
 constexpr int64_t kScanBlocks = 1024;   // scan workgroups if the occupancy query fails
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
@@ -89,8 +93,8 @@ struct AnnArgs {
     int64_t* out_ids;
     float* out_dist;
     int32_t* out_stats;
-    // leaf-major fast path (per query): radius bound, its square and test
-    // slack, fallback flag, candidate count, scanned points, candidate list
+    // leaf-major fast path (per query): members of L in the first ball (-1: the
+    // per-query kernel answers), candidate count, scanned points, candidate list
     int32_t* q_flag;
     uint32_t* pq_list;          // count, then the queries flagged for the per-query kernel
     uint32_t* l_count;          // candidates per query
@@ -131,6 +135,12 @@ struct AnnArgs {
     const float* d16_eps;
     int d16;
     float* ws_clo;
+    // pd^2 bits of the pool entries (or null: long lists compute them again in
+    // every pass), and the members of L per verify workgroup
+    uint32_t* l_val;
+    int vslice;
+    // bound kernel: points sampled per budget point, chunks it may choose
+    int sample, sel_cap;
 };
 
 // Element (query q, chunk c) of the blocked chunk-distance matrix.
@@ -148,7 +158,7 @@ __device__ __forceinline__ int64_t cmask_at(const AnnArgs& a, int64_t c, int64_t
 // them and keeps its row of centre distances in their place.
 struct Smem {
     uint32_t hist[NB];
-    int32_t red[NWAVE * 2];
+    int32_t red[kMaxWaves * 2];
     int32_t cnt0, cnt1, cnt2;
     int32_t thr_bin, thr_below, thr_in;
     int32_t pad_[2];
@@ -186,18 +196,20 @@ __device__ __forceinline__ int wave_append(bool take, int32_t* counter) {
     return base + __popcll(m & lanemask_lt());
 }
 
+template <int T = WG>
 __device__ __forceinline__ int block_sum(int v, Smem& sh) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
     if (lane_id() == 0) sh.red[threadIdx.x >> 6] = v;
     __syncthreads();
     int s = 0;
 #pragma unroll
-    for (int w = 0; w < NWAVE; ++w) s += sh.red[w];
+    for (int w = 0; w < (T / 64); ++w) s += sh.red[w];
     __syncthreads();
     return s;
 }
 
 // Exclusive prefix sum over the workgroup.
+template <int T = WG>
 __device__ __forceinline__ int block_exclusive_scan(int v, Smem& sh) {
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     int x = v;
@@ -205,10 +217,10 @@ __device__ __forceinline__ int block_exclusive_scan(int v, Smem& sh) {
         const int y = __shfl_up(x, off);
         if (lane >= off) x += y;
     }
-    if (lane == 63) sh.red[NWAVE + wave] = x;
+    if (lane == 63) sh.red[(T / 64) + wave] = x;
     __syncthreads();
     int before = 0;
-    for (int w = 0; w < wave; ++w) before += sh.red[NWAVE + w];
+    for (int w = 0; w < wave; ++w) before += sh.red[(T / 64) + w];
     __syncthreads();
     return before + x - v;
 }
@@ -269,20 +281,22 @@ __device__ __forceinline__ int shift_for(uint64_t lo, uint64_t hi) {
     return bits - 11;
 }
 
+template <int T = WG>
 __device__ __forceinline__ void clear_hist(Smem& sh) {
-    for (int i = threadIdx.x; i < NB; i += WG) sh.hist[i] = 0;
+    for (int i = threadIdx.x; i < NB; i += T) sh.hist[i] = 0;
     __syncthreads();
 }
 
 // Finds the bin where the running count of the histogram reaches `need`.
+template <int T = WG>
 __device__ void find_threshold(int need, Smem& sh) {
-    constexpr int PER = NB / WG;
+    constexpr int PER = NB / T;
     const int base = threadIdx.x * PER;
     int local[PER];
     int s = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) { local[j] = (int)sh.hist[base + j]; s += local[j]; }
-    const int excl = block_exclusive_scan(s, sh);
+    const int excl = block_exclusive_scan<T>(s, sh);
     if (excl < need && excl + s >= need) {
         int acc = excl;
 #pragma unroll
@@ -413,14 +427,15 @@ __device__ __forceinline__ void scan_leaves(const AnnArgs& a, const int32_t* lea
     }
 }
 
+template <int T = WG>
 __device__ void bitonic_sort(int count, Smem& sh) {
     int P = 1;
     while (P < count) P <<= 1;
-    for (int i = count + threadIdx.x; i < P; i += WG) { sh.skey[i] = ~0ull; sh.spos[i] = -1; }
+    for (int i = count + threadIdx.x; i < P; i += T) { sh.skey[i] = ~0ull; sh.spos[i] = -1; }
     __syncthreads();
     for (int k = 2; k <= P; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < P; i += WG) {
+            for (int i = threadIdx.x; i < P; i += T) {
                 const int ixj = i ^ j;
                 if (ixj > i) {
                     const bool up = (i & k) == 0;
@@ -439,9 +454,10 @@ __device__ void bitonic_sort(int count, Smem& sh) {
 // The need-th smallest (need in [1, n]) of the n <= CAP distinct 64-bit keys
 // in sh.skey: NB-bin histogram passes over LDS, each narrowing the key range
 // to the bin that holds it.
+template <int T = WG>
 __device__ uint64_t lds_select(int n, int need, Smem& sh) {
     uint64_t lo = ~0ull, hi = 0ull;
-    for (int i = threadIdx.x; i < n; i += WG) {
+    for (int i = threadIdx.x; i < n; i += T) {
         const uint64_t k = sh.skey[i];
         lo = k < lo ? k : lo;
         hi = k > hi ? k : hi;
@@ -454,35 +470,35 @@ __device__ uint64_t lds_select(int n, int need, Smem& sh) {
     uint64_t* red = reinterpret_cast<uint64_t*>(sh.hist);
     if (lane_id() == 0) {
         red[threadIdx.x >> 6] = lo;
-        red[NWAVE + (threadIdx.x >> 6)] = hi;
+        red[(T / 64) + (threadIdx.x >> 6)] = hi;
     }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < NWAVE; ++w) {
+    for (int w = 0; w < (T / 64); ++w) {
         lo = red[w] < lo ? red[w] : lo;
-        hi = red[NWAVE + w] > hi ? red[NWAVE + w] : hi;
+        hi = red[(T / 64) + w] > hi ? red[(T / 64) + w] : hi;
     }
     __syncthreads();
     for (;;) {
         const int sft = shift_for(lo, hi);
-        clear_hist(sh);
-        for (int i = threadIdx.x; i < n; i += WG) {
+        clear_hist<T>(sh);
+        for (int i = threadIdx.x; i < n; i += T) {
             const uint64_t k = sh.skey[i];
             if (k >= lo && k <= hi) atomicAdd(&sh.hist[(int)((k - lo) >> sft)], 1u);
         }
         __syncthreads();
         if (threadIdx.x == 0) sh.thr_bin = NB - 1;
         __syncthreads();
-        find_threshold(need, sh);
-        const int T = sh.thr_bin, below = sh.thr_below, inT = sh.thr_in;
-        const uint64_t nlo = lo + ((uint64_t)T << sft);
+        find_threshold<T>(need, sh);
+        const int tb = sh.thr_bin, below = sh.thr_below, inT = sh.thr_in;
+        const uint64_t nlo = lo + ((uint64_t)tb << sft);
         const uint64_t span = (1ull << sft) - 1ull;
         const uint64_t nhi = hi - nlo > span ? nlo + span : hi;
         __syncthreads();
         if (sft == 0) return nlo;
         if (inT == 1) {
             // the bin holds one key: that key
-            for (int i = threadIdx.x; i < n; i += WG) {
+            for (int i = threadIdx.x; i < n; i += T) {
                 const uint64_t k = sh.skey[i];
                 if (k >= nlo && k <= nhi) red[0] = k;
             }
@@ -503,21 +519,21 @@ __device__ uint64_t lds_select(int n, int need, Smem& sh) {
 // receives every selected payload exactly once, slot in [0, need).
 // If hist_ready, sh.hist already holds the histogram of [lo, hi] at
 // shift_for(lo, hi) and `total` is the member count in [lo, hi].
-template <class Src, class Emit>
+template <int T = WG, class Src, class Emit>
 __device__ void block_select(Src&& src, Emit&& emit, uint64_t lo, uint64_t hi, int need,
                              bool hist_ready, int total, Smem& sh) {
     int emitted = 0;
     for (;;) {
         const int shift = shift_for(lo, hi);
         if (!hist_ready) {
-            clear_hist(sh);
+            clear_hist<T>(sh);
             src([&](bool valid, uint64_t key, int32_t) {
                 if (valid && key >= lo && key <= hi) atomicAdd(&sh.hist[(key - lo) >> shift], 1u);
             });
             __syncthreads();
             int loc = 0;
-            for (int i = threadIdx.x; i < NB; i += WG) loc += (int)sh.hist[i];
-            total = block_sum(loc, sh);
+            for (int i = threadIdx.x; i < NB; i += T) loc += (int)sh.hist[i];
+            total = block_sum<T>(loc, sh);
         }
         hist_ready = false;
         if (total <= CAP) {
@@ -529,25 +545,25 @@ __device__ void block_select(Src&& src, Emit&& emit, uint64_t lo, uint64_t hi, i
                 if (take && slot < CAP) { sh.skey[slot] = key; sh.spos[slot] = payload; }
             });
             __syncthreads();
-            bitonic_sort(total, sh);
-            for (int i = threadIdx.x; i < need; i += WG) emit(sh.spos[i], emitted + i);
+            bitonic_sort<T>(total, sh);
+            for (int i = threadIdx.x; i < need; i += T) emit(sh.spos[i], emitted + i);
             __syncthreads();
             return;
         }
         if (threadIdx.x == 0) { sh.thr_bin = NB - 1; sh.thr_below = 0; sh.thr_in = 0; }
         __syncthreads();
-        find_threshold(need, sh);
-        const int T = sh.thr_bin, below = sh.thr_below, inT = sh.thr_in;
+        find_threshold<T>(need, sh);
+        const int tb = sh.thr_bin, below = sh.thr_below, inT = sh.thr_in;
         if (threadIdx.x == 0) { sh.cnt1 = 0; sh.cnt2 = 0; }
         __syncthreads();
         const bool gather_T = inT <= CAP;
         src([&](bool valid, uint64_t key, int32_t payload) {
             const bool in = valid && key >= lo && key <= hi;
             const int bin = in ? (int)((key - lo) >> shift) : NB;
-            const bool lower = in && bin < T;
+            const bool lower = in && bin < tb;
             const int s1 = wave_append(lower, &sh.cnt1);
             if (lower && s1 < below) emit(payload, emitted + s1);
-            const bool at = gather_T && in && bin == T;
+            const bool at = gather_T && in && bin == tb;
             const int s2 = wave_append(at, &sh.cnt2);
             if (at && s2 < CAP) { sh.skey[s2] = key; sh.spos[s2] = payload; }
         });
@@ -555,12 +571,12 @@ __device__ void block_select(Src&& src, Emit&& emit, uint64_t lo, uint64_t hi, i
         emitted += below;
         need -= below;
         if (gather_T) {
-            bitonic_sort(inT, sh);
-            for (int i = threadIdx.x; i < need; i += WG) emit(sh.spos[i], emitted + i);
+            bitonic_sort<T>(inT, sh);
+            for (int i = threadIdx.x; i < need; i += T) emit(sh.spos[i], emitted + i);
             __syncthreads();
             return;
         }
-        const uint64_t nlo = lo + ((uint64_t)T << shift);
+        const uint64_t nlo = lo + ((uint64_t)tb << shift);
         const uint64_t nhi = nlo + ((1ull << shift) - 1ull);
         lo = nlo;
         hi = nhi < hi ? nhi : hi;
@@ -572,12 +588,13 @@ __device__ void block_select(Src&& src, Emit&& emit, uint64_t lo, uint64_t hi, i
 // step) so the gather of 1 KB rows runs at HBM rate rather than at latency.
 constexpr int VR = 4;
 
+template <int T = WG>
 __device__ void verify(const AnnArgs& a, const float* qs, const int32_t* cpos, float* cdist,
                        int v0, int v1) {
     const int g = threadIdx.x >> 4, l16 = threadIdx.x & 15;
     const int d4 = a.d_pad >> 2;
     const float4* q4 = reinterpret_cast<const float4*>(qs);
-    constexpr int GROUPS = WG / 16;
+    constexpr int GROUPS = T / 16;
     for (int base = v0; base < v1; base += GROUPS * VR) {
         const float4* row[VR];
         bool ok[VR];
@@ -618,12 +635,13 @@ __device__ void verify(const AnnArgs& a, const float* qs, const int32_t* cpos, f
 
 // Exact squared distances (same operation sequence as verify) of the C
 // members listed in idx[0, cnt); both bounds of each become the exact value.
+template <int T = WG>
 __device__ void verify_list(const AnnArgs& a, const float* qs, const int32_t* cpos,
                             const int32_t* idx, int cnt, float* lo2, float* hi2) {
     const int g = threadIdx.x >> 4, l16 = threadIdx.x & 15;
     const int d4 = a.d_pad >> 2;
     const float4* q4 = reinterpret_cast<const float4*>(qs);
-    constexpr int GROUPS = WG / 16;
+    constexpr int GROUPS = T / 16;
     for (int base = 0; base < cnt; base += GROUPS * VR) {
         const float4* row[VR];
         bool ok[VR];
@@ -682,11 +700,12 @@ __device__ void verify_list(const AnnArgs& a, const float* qs, const int32_t* cp
 // the row's bound |x - s x16|, the true distance lies in [D16 - eps, D16 +
 // eps] and the FP32 value within a further factor (1 +- gamma); every
 // rounding of the bound arithmetic is covered by extra factors of a few u.
+template <int T = WG>
 __device__ void verify16(const AnnArgs& a, const float* qs, const int32_t* cpos,
                          float* lo2, float* hi2, int v0, int v1) {
     const int g = threadIdx.x >> 4, l16 = threadIdx.x & 15;
     const int d8 = a.d16 >> 3;
-    constexpr int GROUPS = WG / 16;
+    constexpr int GROUPS = T / 16;
     const float u = 5.9604645e-08f;
     const float gam = 2.f * u * (float)(a.d16 / 16 + 8);
     for (int base = v0; base < v1; base += GROUPS * VR) {
@@ -761,15 +780,20 @@ struct QueryCtx {
     float qn2;
 };
 
-__device__ __forceinline__ void load_query(const AnnArgs& a, int64_t qi, float* qs, QueryCtx& c) {
-    const float* qrow = a.q + qi * a.d;
-    if (qs)
-        for (int j = threadIdx.x; j < a.d16; j += WG) qs[j] = j < a.d ? qrow[j] : 0.f;
+__device__ __forceinline__ void load_projection(const AnnArgs& a, int64_t qi, QueryCtx& c) {
 #pragma unroll
     for (int j = 0; j < MP; ++j) c.qp[j] = a.qp[qi * MP + j];
     c.qn2 = 0.f;
 #pragma unroll
     for (int j = 0; j < MP; ++j) c.qn2 = fmaf(c.qp[j], c.qp[j], c.qn2);
+}
+
+template <int T = WG>
+__device__ __forceinline__ void load_query(const AnnArgs& a, int64_t qi, float* qs, QueryCtx& c) {
+    const float* qrow = a.q + qi * a.d;
+    if (qs)
+        for (int j = threadIdx.x; j < a.d16; j += T) qs[j] = j < a.d ? qrow[j] : 0.f;
+    load_projection(a, qi, c);
 #pragma unroll
     for (int i = 0; i < PMLSH_MAX_PIVOTS; ++i) {
         float acc = 0.f;
@@ -802,7 +826,7 @@ constexpr int kRerankCap = 512;   // members the FP64 re-rank takes at most
 // smallest (FP64 value, id) are written, each distance as the FP32 rounding
 // of the FP64 root. src(j, v32, member) gives the cnt candidates. Returns
 // false, writing nothing, when more than kRerankCap members qualify.
-template <class Src>
+template <int T = WG, class Src>
 __device__ bool rerank_topk64(const AnnArgs& a, int64_t qi, const float* qs, const int32_t* cpos,
                               int cnt, float kth32, Src&& src, Smem& sh) {
     const int k = query_params(a, qi).k;
@@ -814,7 +838,7 @@ __device__ bool rerank_topk64(const AnnArgs& a, int64_t qi, const float* qs, con
     __syncthreads();
     if (threadIdx.x == 0) sh.cnt2 = 0;
     __syncthreads();
-    for (int b0 = 0; b0 < cnt; b0 += WG) {
+    for (int b0 = 0; b0 < cnt; b0 += T) {
         const int j = b0 + threadIdx.x;
         float v = 0.f;
         int mi = 0;
@@ -835,7 +859,7 @@ __device__ bool rerank_topk64(const AnnArgs& a, int64_t qi, const float* qs, con
         const int g = threadIdx.x >> 4, l16 = threadIdx.x & 15;
         const int d4 = a.d_pad >> 2;
         const float4* q4 = reinterpret_cast<const float4*>(qs);
-        for (int base = 0; base < np; base += WG / 16) {
+        for (int base = 0; base < np; base += T / 16) {
             const int j = base + g;
             double acc = 0.0;
             if (j < np) {
@@ -867,7 +891,7 @@ __device__ bool rerank_topk64(const AnnArgs& a, int64_t qi, const float* qs, con
     }
     __syncthreads();
     // rank by (FP64 value, id); ids are distinct
-    for (int j = threadIdx.x; j < np; j += WG) {
+    for (int j = threadIdx.x; j < np; j += T) {
         const double v = d64[j];
         const int32_t id = pid[j];
         int rank = 0;
@@ -881,6 +905,7 @@ __device__ bool rerank_topk64(const AnnArgs& a, int64_t qi, const float* qs, con
     return true;
 }
 
+template <int T = WG>
 __device__ void write_topk(const AnnArgs& a, int64_t qi, const float* qs, const int32_t* cpos,
                            const float* cdist, int n_ver, int rounds, int exit_kind,
                            int64_t scanned, Smem& sh) {
@@ -891,48 +916,48 @@ __device__ void write_topk(const AnnArgs& a, int64_t qi, const float* qs, const 
         // the k-th smallest FP32 value, then the FP64 re-rank
         float kth32 = __int_as_float(0x7f800000);
         if (n_ver > k) {
-            for (int i = threadIdx.x; i < n_ver; i += WG)
+            for (int i = threadIdx.x; i < n_ver; i += T)
                 sh.skey[i] = ((uint64_t)__float_as_uint(cdist[i]) << 32) | (uint32_t)perm[cpos[i]];
             __syncthreads();
-            kth32 = __uint_as_float((uint32_t)(lds_select(n_ver, k, sh) >> 32));
+            kth32 = __uint_as_float((uint32_t)(lds_select<T>(n_ver, k, sh) >> 32));
         }
-        done = rerank_topk64(a, qi, qs, cpos, n_ver, kth32,
+        done = rerank_topk64<T>(a, qi, qs, cpos, n_ver, kth32,
                              [&](int j, float& v, int& mi) { v = cdist[j]; mi = j; }, sh);
     }
     if (done) {
     } else if (n_ver <= CAP) {
-        for (int i = threadIdx.x; i < n_ver; i += WG)
+        for (int i = threadIdx.x; i < n_ver; i += T)
             sh.skey[i] = ((uint64_t)__float_as_uint(cdist[i]) << 32) | (uint32_t)perm[cpos[i]];
         __syncthreads();
         int m = n_ver;
         if (n_ver > k) {
-            const uint64_t kth = lds_select(n_ver, k, sh);
+            const uint64_t kth = lds_select<T>(n_ver, k, sh);
             // the k smallest keys, gathered through the histogram space
             uint64_t* tmp = reinterpret_cast<uint64_t*>(sh.hist);
             static_assert(NB * sizeof(uint32_t) >= PMLSH_MAX_K * sizeof(uint64_t),
                           "top-k staging must fit the histogram");
             if (threadIdx.x == 0) sh.cnt1 = 0;
             __syncthreads();
-            for (int b0 = 0; b0 < n_ver; b0 += WG) {
+            for (int b0 = 0; b0 < n_ver; b0 += T) {
                 const int i = b0 + threadIdx.x;
                 const bool take = i < n_ver && sh.skey[i] <= kth;
                 const int slot = wave_append(take, &sh.cnt1);
                 if (take) tmp[slot] = sh.skey[i];
             }
             __syncthreads();
-            for (int j = threadIdx.x; j < k; j += WG) sh.skey[j] = tmp[j];
+            for (int j = threadIdx.x; j < k; j += T) sh.skey[j] = tmp[j];
             __syncthreads();
             m = k;
         }
-        bitonic_sort(m, sh);
-        for (int j = threadIdx.x; j < k; j += WG) {
+        bitonic_sort<T>(m, sh);
+        for (int j = threadIdx.x; j < k; j += T) {
             const uint64_t key = sh.skey[j];
             a.out_ids[qi * a.out_stride + j] = (int64_t)(uint32_t)key;
             a.out_dist[qi * a.out_stride + j] = sqrtf(__uint_as_float((uint32_t)(key >> 32)));
         }
     } else {
         auto c_src = [&](auto&& v) {
-            for (int base = 0; base < n_ver; base += WG) {
+            for (int base = 0; base < n_ver; base += T) {
                 const int i = base + threadIdx.x;
                 const bool valid = i < n_ver;
                 uint64_t key = 0;
@@ -941,32 +966,32 @@ __device__ void write_topk(const AnnArgs& a, int64_t qi, const float* qs, const 
             }
         };
         int32_t* topk = a.ws_topk + qi * 3 * (int64_t)a.k;
-        block_select(c_src, [&](int32_t i, int slot) { if (slot < k) topk[slot] = i; }, 0ull,
+        block_select<T>(c_src, [&](int32_t i, int slot) { if (slot < k) topk[slot] = i; }, 0ull,
                      ~0ull, k, false, 0, sh);
         __syncthreads();
         // the k-th smallest FP32 value (the largest of the k selected), then
         // the FP64 re-rank
         float kmax = 0.f;
-        for (int j = threadIdx.x; j < k; j += WG) kmax = fmaxf(kmax, cdist[topk[j]]);
+        for (int j = threadIdx.x; j < k; j += T) kmax = fmaxf(kmax, cdist[topk[j]]);
         for (int off = 32; off > 0; off >>= 1) kmax = fmaxf(kmax, __shfl_xor(kmax, off));
         if (lane_id() == 0) sh.red[threadIdx.x >> 6] = __float_as_int(kmax);
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < NWAVE; ++w) kmax = fmaxf(kmax, __int_as_float(sh.red[w]));
+        for (int w = 0; w < (T / 64); ++w) kmax = fmaxf(kmax, __int_as_float(sh.red[w]));
         __syncthreads();
-        if (rerank_topk64(a, qi, qs, cpos, n_ver, kmax,
+        if (rerank_topk64<T>(a, qi, qs, cpos, n_ver, kmax,
                           [&](int j, float& v, int& mi) { v = cdist[j]; mi = j; }, sh))
             done = true;
     }
     if (!done && n_ver > CAP) {
         const int32_t* topk = a.ws_topk + qi * 3 * (int64_t)a.k;
-        for (int j = threadIdx.x; j < k; j += WG) {
+        for (int j = threadIdx.x; j < k; j += T) {
             const int i = topk[j];
             sh.skey[j] = ((uint64_t)__float_as_uint(cdist[i]) << 32) | (uint32_t)perm[cpos[i]];
         }
         __syncthreads();
-        bitonic_sort(k, sh);
-        for (int j = threadIdx.x; j < k; j += WG) {
+        bitonic_sort<T>(k, sh);
+        for (int j = threadIdx.x; j < k; j += T) {
             const uint64_t key = sh.skey[j];
             a.out_ids[qi * a.out_stride + j] = (int64_t)(uint32_t)key;
             a.out_dist[qi * a.out_stride + j] = sqrtf(__uint_as_float((uint32_t)(key >> 32)));
@@ -1200,7 +1225,7 @@ __device__ void ann_one(const AnnArgs& a, int64_t qi, int32_t* fa, int32_t* fb, 
 }
 
 // ------------------------------------------------------------------------
-// Leaf-major fast path for B <= CAP.
+// Batched path, for B <= kWideBudget.
 //
 // Every candidate set of Algorithm 2 is a prefix of the order of the data by
 // (projected distance, id) (the ball of a round holds the points up to t*r;
@@ -1215,7 +1240,8 @@ __device__ void ann_one(const AnnArgs& a, int64_t qi, int32_t* fa, int32_t* fb, 
 //           range query (q', tau) reaches the leaf (Eq. 5); points with
 //           pd^2 <= tau^2 are appended to the query's candidate list;
 //   finish  per query: exact radix select of L from the list, the rounds of
-//           Algorithm 2 on L with incremental verification, the top-k.
+//           Algorithm 2 on L with incremental verification, the top-k; or the
+//           same in three kernels (pool_cut_kernel and its followers).
 // Queries whose list overflows (or that fall outside the path) are flagged
 // and answered by the per-query kernel above.
 
@@ -1422,8 +1448,8 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     const uint32_t hbase = kCenBinBase;
     auto cbin = [&](uint32_t h) { return min(max(h >> 3, hbase) - hbase, (uint32_t)(NB - 1)); };
     const int32_t budget = query_params(a, qi).budget;
-    const int64_t want = a.n < 2 * (int64_t)budget ? a.n : 2 * (int64_t)budget;
-    const int wc = (int)min<int64_t>(nch, (want + 63) / 64 + 1);
+    const int64_t want = min((int64_t)a.n, (int64_t)a.sample * budget);
+    const int wc = (int)min<int64_t>(min(nch, a.sel_cap), (want + 63) / 64 + 1);
 
     // b0 bounds the bin sought in step 1 from above: every group holds a
     // chunk at its minimum, so with wc groups whose minima lie in bins <= b0
@@ -1513,9 +1539,9 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     __syncthreads();
 
     // 2: the chosen chunks, and the largest distance bound over their points.
-    // The list holds kSelCap chunks: those of the bins below tbin (fewer than
-    // wc) come first, then as many of bin tbin's as fit; any kSelCap chunks
-    // hold at least 64 kSelCap >= 2 * budget points, so the bound stays valid
+    // The list holds sel_cap >= wc chunks: those of the bins below tbin (fewer
+    // than wc) come first, then as many of bin tbin's as fit, so its points
+    // are at least budget and the bound stays valid
     if (threadIdx.x == 0) sh.cnt2 = 0;
     __syncthreads();
     float rmax = 0.f;
@@ -1531,7 +1557,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
                     const uint32_t h = half_k(v, k);
                     const int slot = cbin(h) < tbin ? atomicAdd(&sh.cnt1, 1)
                                                     : nlow + atomicAdd(&sh.cnt2, 1);
-                    if (slot < kSelCap) {
+                    if (slot < a.sel_cap) {
                         // the stored distance is low by less than a factor 1 + 2^-7
                         const float d = sqrtf(__uint_as_float(h << 16)) * 1.0079f;
                         rmax = fmaxf(rmax, d + a.chunk_rad[i]);
@@ -1544,7 +1570,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     for (int off = 32; off > 0; off >>= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, off));
     if (lane == 0) sh.red[wave] = __float_as_int(rmax);
     __syncthreads();
-    const int nsel = min(nlow + sh.cnt2, kSelCap);
+    const int nsel = min(nlow + sh.cnt2, a.sel_cap);
     float R = 0.f;
 #pragma unroll
     for (int w = 0; w < NWAVE; ++w) R = fmaxf(R, __int_as_float(sh.red[w]));
@@ -2046,6 +2072,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE))) void 
 // projections: the entries below the band are in L, the first B - below of
 // the band by (FP64 pd^2, id) join them, everything else leaves (key ~0).
 // Returns false, marking nothing, when the band holds more than 512 entries.
+template <int T = WG>
 __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n, int B,
                          uint64_t kth, Smem& sh) {
     constexpr int kBandCap = 512;
@@ -2061,7 +2088,7 @@ __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n
     if (threadIdx.x == 0) sh.cnt2 = 0;
     __syncthreads();
     int below = 0;
-    for (int b0 = 0; b0 < n; b0 += WG) {
+    for (int b0 = 0; b0 < n; b0 += T) {
         const int i = b0 + threadIdx.x;
         const float v = i < n ? __uint_as_float((uint32_t)(sh.skey[i] >> 32)) : __int_as_float(0x7f800000);
         below += i < n && v < blo;
@@ -2072,17 +2099,17 @@ __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n
             bid[slot] = (uint32_t)sh.skey[i];
         }
     }
-    below = block_sum(below, sh);
+    below = block_sum<T>(below, sh);
     const int nb = sh.cnt2;
     if (nb > kBandCap || below >= B || below + nb < B) return false;
     if (below + nb == B) {
         // the whole band is in L whatever its FP64 order
-        for (int i = threadIdx.x; i < n; i += WG)
+        for (int i = threadIdx.x; i < n; i += T)
             if (__uint_as_float((uint32_t)(sh.skey[i] >> 32)) > bhi) sh.skey[i] = ~0ull;
         __syncthreads();
         return true;
     }
-    for (int j = threadIdx.x; j < nb; j += WG) {
+    for (int j = threadIdx.x; j < nb; j += T) {
         const int64_t pos = sh.spos[band[j]];
         double acc = 0.0;
 #pragma unroll
@@ -2096,7 +2123,7 @@ __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n
     }
     __syncthreads();
     const int need = B - below;
-    for (int j = threadIdx.x; j < nb; j += WG) {
+    for (int j = threadIdx.x; j < nb; j += T) {
         const double v = b64[j];
         const uint32_t id = bid[j];
         int rank = 0;
@@ -2104,15 +2131,153 @@ __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n
         if (rank >= need) band[j] = ~band[j];
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < nb; j += WG)
+    for (int j = threadIdx.x; j < nb; j += T)
         if (band[j] < 0) sh.skey[~band[j]] = ~0ull;
-    for (int i = threadIdx.x; i < n; i += WG)
+    for (int i = threadIdx.x; i < n; i += T)
         if (__uint_as_float((uint32_t)(sh.skey[i] >> 32)) > bhi) sh.skey[i] = ~0ull;
     __syncthreads();
     return true;
 }
 
-__global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
+// The need-th smallest (from 1) of the values get(i) in [lo, hi], i < n, of
+// which there are at least need: histogram passes over ever narrower ranges,
+// four values per thread in flight.
+template <int T, class Get>
+__device__ uint32_t select_u32(int n, int need, uint32_t lo, uint32_t hi, Get&& get, Smem& sh) {
+    for (;;) {
+        const uint32_t span = hi - lo;
+        const int shift = span < (uint32_t)NB ? 0 : 32 - __clz((int)span) - 11;
+        clear_hist<T>(sh);
+        if (threadIdx.x == 0) {
+            sh.thr_bin = NB - 1;
+            sh.thr_below = sh.thr_in = 0;
+        }
+        for (int i0 = threadIdx.x; i0 < n; i0 += 4 * T) {
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = get(min(i0 + u * T, n - 1));
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u * T < n && v[u] >= lo && v[u] <= hi)
+                    atomicAdd(&sh.hist[(v[u] - lo) >> shift], 1u);
+        }
+        __syncthreads();
+        find_threshold<T>(need, sh);
+        const uint32_t nlo = lo + ((uint32_t)sh.thr_bin << shift);
+        const bool one = sh.thr_in == 1;
+        need -= sh.thr_below;
+        __syncthreads();
+        if (shift == 0) return nlo;
+        const uint32_t top = (1u << shift) - 1u;
+        hi = hi - nlo > top ? nlo + top : hi;
+        lo = nlo;
+        if (one) {
+            // the bin holds one value: that value
+            for (int i = threadIdx.x; i < n; i += T) {
+                const uint32_t v = get(i);
+                if (v >= lo && v <= hi) sh.hist[0] = v;
+            }
+            __syncthreads();
+            const uint32_t v = sh.hist[0];
+            __syncthreads();
+            return v;
+        }
+    }
+}
+
+// The answer from the bounds lo2 <= exact <= hi2 of the n_ver members i < lim of
+// C with member(i): the top-k and the statistics.
+template <int T, class Member>
+__device__ void answer_members(const AnnArgs& a, int64_t qi, const float* qs, int32_t* cpos,
+                               const float* lo2, float* hi2, int lim, Member&& member, int n_ver,
+                               int rounds, int exit_kind, Smem& sh) {
+    const int k = query_params(a, qi).k;
+    __syncthreads();
+    // Top-k: the k-th smallest upper bound hk; only members whose lower bound
+    // is within a factor 1 + 4 gamma of it can be placed among the k nearest
+    // by the FP64 order.
+    float hk = __int_as_float(0x7f800000);
+    if (n_ver > k) {
+        // the bounds' bits, in LDS when they fit
+        uint32_t* cache = reinterpret_cast<uint32_t*>(sh.skey);
+        const bool cached = lim <= 2 * CAP;
+        auto bits = [&](int i) { return member(i) ? __float_as_uint(hi2[i]) : 0xffffffffu; };
+        uint32_t lo = 0xffffffffu, hi = 0u;
+        for (int i = threadIdx.x; i < lim; i += T) {
+            const uint32_t b = bits(i);
+            if (cached) cache[i] = b;
+            lo = min(lo, b);
+            hi = b == 0xffffffffu ? hi : max(hi, b);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+            hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+        }
+        if (lane_id() == 0) {
+            sh.red[threadIdx.x >> 6] = (int32_t)lo;
+            sh.red[T / 64 + (threadIdx.x >> 6)] = (int32_t)hi;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < T / 64; ++w) {
+            lo = min(lo, (uint32_t)sh.red[w]);
+            hi = max(hi, (uint32_t)sh.red[T / 64 + w]);
+        }
+        hk = __uint_as_float(cached ? select_u32<T>(lim, k, lo, hi, [&](int i) { return cache[i]; }, sh)
+                                    : select_u32<T>(lim, k, lo, hi, bits, sh));
+    }
+    const float hkw = (float)((double)hk * (1.0 + 4.0 * (double)verify_gamma(a)) * (1.0 + 1e-7));
+    __syncthreads();
+    if (threadIdx.x == 0) sh.cnt1 = 0;
+    __syncthreads();
+    for (int b0 = 0; b0 < lim; b0 += T) {
+        const int i = b0 + threadIdx.x;
+        const bool take = i < lim && member(i) && lo2[i] <= hkw;
+        const int slot = wave_append(take, &sh.cnt1);
+        if (take && slot < kRerankCap) sh.spos[slot] = i;
+    }
+    __syncthreads();
+    const int m = sh.cnt1;
+    if (m <= kRerankCap) {
+        // the FP64 re-rank decides their order from their rows (no FP32 value
+        // is needed)
+        rerank_topk64<T>(
+            a, qi, qs, cpos, m, __int_as_float(0x7f800000),
+            [&](int j, float& v, int& mi) {
+                v = 0.f;
+                mi = sh.spos[j];
+            },
+            sh);
+        if (a.out_stats && threadIdx.x == 0) {
+            int32_t* st = a.out_stats + qi * 4;
+            st[0] = rounds;
+            st[2] = exit_kind;
+            st[3] = (int32_t)a.q_scanned[qi];
+        }
+    } else {
+        // too many: their exact FP32 values, moved to the front (a step reads
+        // its T entries before any of them is written, and writes only slots
+        // that have been read), then the top-k of exact values
+        if (threadIdx.x == 0) sh.cnt1 = 0;
+        __syncthreads();
+        for (int b0 = 0; b0 < lim; b0 += T) {
+            const int i = b0 + threadIdx.x;
+            const bool take = i < lim && member(i) && lo2[i] <= hkw;
+            const int32_t pos = take ? cpos[i] : 0;
+            const int slot = wave_append(take, &sh.cnt1);
+            __syncthreads();
+            if (take) cpos[slot] = pos;
+        }
+        __syncthreads();
+        verify<T>(a, qs, cpos, hi2, 0, m);
+        __syncthreads();
+        write_topk<T>(a, qi, qs, cpos, hi2, m, rounds, exit_kind, (int64_t)a.q_scanned[qi], sh);
+    }
+    if (a.out_stats && threadIdx.x == 0) a.out_stats[qi * 4 + 1] = n_ver;
+}
+
+template <int T>
+__global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
     float* qs = reinterpret_cast<float*>(smem_raw + ((sizeof(Smem) + 15) & ~size_t(15)));
@@ -2124,13 +2289,13 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
     if (cnt > (uint32_t)a.q_cap || cnt < (uint32_t)B) {
         // list overflow, or the bound fell short: the per-query kernel answers
         if (threadIdx.x == 0) {
-            a.q_flag[qi] = 1;
+            a.q_flag[qi] = -1;
             a.pq_list[1 + atomicAdd(&a.pq_list[0], 1u)] = (uint32_t)qi;
         }
         return;
     }
     QueryCtx qc;
-    load_query(a, qi, qs, qc);
+    load_query<T>(a, qi, qs, qc);
     int32_t* cpos = a.ws_cpos + qi * (int64_t)a.budget;
     float* cdist = a.ws_cdist + qi * (int64_t)a.budget;
     const uint32_t* list = a.l_list + qi * a.q_cap;
@@ -2147,11 +2312,11 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
         // four entries per thread in flight: their list, projection and id
         // loads are issued together
         constexpr int PU = 4;
-        for (int i0 = threadIdx.x; i0 < n; i0 += PU * WG) {
+        for (int i0 = threadIdx.x; i0 < n; i0 += PU * T) {
             int32_t pos[PU];
 #pragma unroll
             for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * WG;
+                const int i = i0 + u * T;
                 pos[u] = (int32_t)list[i < n ? i : i0];
             }
             float pd2[PU];
@@ -2163,7 +2328,7 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
             }
 #pragma unroll
             for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * WG;
+                const int i = i0 + u * T;
                 if (i < n) {
                     sh.skey[i] = ((uint64_t)__float_as_uint(pd2[u]) << 32) | (uint32_t)id[u];
                     sh.spos[i] = pos[u];
@@ -2172,9 +2337,9 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
         }
         __syncthreads();
         if (n > B) {
-            const uint64_t kth = lds_select(n, B, sh);
-            if (!cut_fp64(a, qi, qc, n, B, kth, sh)) {
-                for (int i = threadIdx.x; i < n; i += WG)
+            const uint64_t kth = lds_select<T>(n, B, sh);
+            if (!cut_fp64<T>(a, qi, qc, n, B, kth, sh)) {
+                for (int i = threadIdx.x; i < n; i += T)
                     if (sh.skey[i] > kth) sh.skey[i] = ~0ull;
                 __syncthreads();
             }
@@ -2182,7 +2347,7 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
         nl = n;
     } else {
         auto list_src = [&](auto&& v) {
-            for (int base = 0; base < n; base += WG) {
+            for (int base = 0; base < n; base += T) {
                 const int i = base + threadIdx.x;
                 const bool valid = i < n;
                 uint64_t key = 0;
@@ -2195,10 +2360,10 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
                 v(valid, key, pos);
             }
         };
-        block_select(list_src, [&](int32_t pos, int slot) { if (slot < B) cpos[slot] = pos; },
+        block_select<T>(list_src, [&](int32_t pos, int slot) { if (slot < B) cpos[slot] = pos; },
                      0ull, ~0ull, B, false, 0, sh);
         __syncthreads();
-        for (int j = threadIdx.x; j < B; j += WG) {
+        for (int j = threadIdx.x; j < B; j += T) {
             const int32_t pos = cpos[j];
             sh.skey[j] = ((uint64_t)__float_as_uint(proj_dist2(a.proj + (int64_t)pos * MP, qc.qp)) << 32) |
                          (uint32_t)perm[pos];
@@ -2225,27 +2390,27 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
             const double cr = qpar.c * r;
             const float thr2 = (float)(cr * cr);
             int sure = 0, maybe = 0;
-            for (int i = threadIdx.x; i < n_ver; i += WG) {
+            for (int i = threadIdx.x; i < n_ver; i += T) {
                 sure += hi2[i] <= thr2;
                 maybe += lo2[i] <= thr2 && hi2[i] > thr2;
             }
-            sure = block_sum(sure, sh);
-            maybe = block_sum(maybe, sh);
+            sure = block_sum<T>(sure, sh);
+            maybe = block_sum<T>(maybe, sh);
             if (sure < k && sure + maybe >= k) {
                 if (threadIdx.x == 0) sh.cnt1 = 0;
                 __syncthreads();
-                for (int b0 = 0; b0 < n_ver; b0 += WG) {
+                for (int b0 = 0; b0 < n_ver; b0 += T) {
                     const int i = b0 + threadIdx.x;
                     const bool take = i < n_ver && lo2[i] <= thr2 && hi2[i] > thr2;
                     const int slot = wave_append(take, &sh.cnt1);
                     if (take) ilist[slot] = i;
                 }
                 __syncthreads();
-                verify_list(a, qs, cpos, ilist, sh.cnt1, lo2, hi2);
+                verify_list<T>(a, qs, cpos, ilist, sh.cnt1, lo2, hi2);
                 __syncthreads();
                 int loc = 0;
-                for (int i = threadIdx.x; i < n_ver; i += WG) loc += hi2[i] <= thr2;
-                sure = block_sum(loc, sh);
+                for (int i = threadIdx.x; i < n_ver; i += T) loc += hi2[i] <= thr2;
+                sure = block_sum<T>(loc, sh);
             }
             if (sure >= k) { exit_kind = PMLSH_EXIT_NEAR; break; }
         }
@@ -2256,7 +2421,7 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
         // n_ver verified ones
         if (threadIdx.x == 0) sh.cnt1 = n_ver;
         __syncthreads();
-        for (int b0 = 0; b0 < nl; b0 += WG) {
+        for (int b0 = 0; b0 < nl; b0 += T) {
             const int i = b0 + threadIdx.x;
             bool take = false;
             if (i < nl) {
@@ -2270,7 +2435,7 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
         __syncthreads();
         const int nb = sh.cnt1 < B ? sh.cnt1 : B;
         ++rounds;
-        verify16(a, qs, cpos, lo2, hi2, n_ver, nb);
+        verify16<T>(a, qs, cpos, lo2, hi2, n_ver, nb);
         n_ver = nb;
         prev_bits = r2bits;
         __syncthreads();
@@ -2279,105 +2444,348 @@ __global__ __launch_bounds__(WG) void finish_kernel(AnnArgs a) {
         r = qpar.c * r;
     }
 
-    // Top-k: the k smallest upper bounds give hk; only members with lo2 <= hk
-    // can be among the k nearest, and those are verified exactly.
-    __syncthreads();
-    for (int i = threadIdx.x; i < n_ver; i += WG)
-        sh.skey[i] = ((uint64_t)__float_as_uint(hi2[i]) << 32) | (uint32_t)i;
-    __syncthreads();
-    const float hk = n_ver > k ? __uint_as_float((uint32_t)(lds_select(n_ver, k, sh) >> 32))
-                                 : __int_as_float(0x7f800000);
-    // members that the FP64 order of the re-rank could still place among the
-    // k nearest: lower bound within a factor 1 + 4 gamma of hk
-    const float hkw = (float)((double)hk * (1.0 + 4.0 * (double)verify_gamma(a)) * (1.0 + 1e-7));
-    if (threadIdx.x == 0) sh.cnt1 = 0;
-    __syncthreads();
-    for (int b0 = 0; b0 < n_ver; b0 += WG) {
-        const int i = b0 + threadIdx.x;
-        const bool take = i < n_ver && lo2[i] <= hkw;
-        const int slot = wave_append(take, &sh.cnt1);
-        if (take) sh.spos[slot] = i;
-    }
-    __syncthreads();
-    const int m = sh.cnt1;
-    // all of them go to the FP64 re-rank, which decides their order from
-    // their rows (no FP32 value is needed; the set holds every member the
-    // FP64 order can place among the k nearest)
-    bool done = false;
-    if (m <= kRerankCap)
-        done = rerank_topk64(
-            a, qi, qs, cpos, m, __int_as_float(0x7f800000),
-            [&](int j, float& v, int& mi) {
-                v = 0.f;
-                mi = sh.spos[j];
-            },
-            sh);
-    if (!done) {
-        // the FP32 order: exact values for the members still bounded, then
-        // keys (distance^2 bits, id)
-        if (threadIdx.x == 0) sh.cnt2 = 0;
-        __syncthreads();
-        for (int b0 = 0; b0 < m; b0 += WG) {
-            const int j = b0 + threadIdx.x;
-            const int i = j < m ? sh.spos[j] : 0;
-            const bool take = j < m && lo2[i] != hi2[i];
-            const int slot = wave_append(take, &sh.cnt2);
-            if (take) ilist[slot] = i;
+    answer_members<T>(a, qi, qs, cpos, lo2, hi2, n_ver, [](int) { return true; }, n_ver, rounds,
+                       exit_kind, sh);
+}
+
+// ---- The candidate list in three kernels ----
+//
+// The pool of a query becomes its answer in three steps of different shape:
+//   cut     one workgroup per query: L, the B pool entries of smallest
+//           (pd^2, id), written as positions and pd^2 bits, the members of
+//           the first round's ball in front;
+//   verify  one workgroup per slice of a query's members: distance bounds
+//           from the FP16 rows, with no step that waits for another slice;
+//   answer  one workgroup per query: the rounds of Algorithm 2 on the bounds,
+//           the top-k.
+// No step holds a whole list in LDS, so they take any budget up to
+// kWideBudget. Budgets above kLeanBudget used to go to the per-query kernel,
+// whose tree walk and leaf scans run query by query: 1M x 256, 1,024 queries
+// of B = 4,810 26.6 ms (now cut 136 us, verify 390 us, answer 84 us, 0.89 ms
+// in all); 200,000 x 128, 256 queries of B = 19,200 4.7 ms (75, 203, 46 us,
+// 0.48 ms). The cut is bound by the 64-byte projection rows of the pool
+// (gathered through 128-byte lines), the verification by HBM (the FP16 rows of
+// all members), the answer by the latency of its passes.
+
+// Bits of the squared radius of the first range query.
+__device__ __forceinline__ uint32_t first_radius_bits(const AnnQueryParams& p) {
+    const double rd = p.t * p.r_min;
+    return __float_as_uint((float)(rd * rd));
+}
+
+template <int T>
+__global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
+    const int64_t qi = blockIdx.x;
+    const AnnQueryParams qpar = query_params(a, qi);
+    const int B = qpar.budget;
+    const uint32_t cnt = a.l_count[qi];
+    if (cnt > (uint32_t)a.q_cap || cnt < (uint32_t)B) {
+        // list overflow, or the bound fell short: the per-query kernel answers
+        if (threadIdx.x == 0) {
+            a.q_flag[qi] = -1;
+            a.pq_list[1 + atomicAdd(&a.pq_list[0], 1u)] = (uint32_t)qi;
         }
-        __syncthreads();
-        verify_list(a, qs, cpos, ilist, sh.cnt2, lo2, hi2);
-        __syncthreads();
-        for (int j = threadIdx.x; j < m; j += WG) {
-            const int i = sh.spos[j];
-            sh.skey[j] = ((uint64_t)__float_as_uint(hi2[i]) << 32) | (uint32_t)perm[cpos[i]];
-        }
-        __syncthreads();
+        return;
     }
-    if (done) {
-    } else if (m <= WG) {
-        // keys are distinct (ids): the rank of each among the m is its slot
-        if (threadIdx.x < m) {
-            const uint64_t key = sh.skey[threadIdx.x];
-            int rank = 0;
-            for (int y = 0; y < m; ++y) rank += sh.skey[y] < key;
-            if (rank < k) {
-                a.out_ids[qi * a.out_stride + rank] = (int64_t)(uint32_t)key;
-                a.out_dist[qi * a.out_stride + rank] = sqrtf(__uint_as_float((uint32_t)(key >> 32)));
+    QueryCtx qc;
+    load_projection(a, qi, qc);
+    int32_t* cpos = a.ws_cpos + qi * (int64_t)a.budget;
+    const uint32_t* list = a.l_list + qi * a.q_cap;
+    const int n = (int)cnt;
+    const uint32_t first = first_radius_bits(qpar);
+    // members of L: the first ball's from the front, the others from the back
+    auto emit = [&](bool take, int32_t pos, uint32_t bits) {
+        const bool in = take && bits <= first;
+        const int s0 = wave_append(in, &sh.cnt0);
+        const int s1 = wave_append(take && !in, &sh.cnt1);
+        const int slot = in ? s0 : B - 1 - s1;
+        if (take && slot >= 0 && slot < B) cpos[slot] = pos;
+    };
+    if (n <= CAP) {
+        // keys and positions in LDS; four entries per thread in flight: their
+        // list, projection and id loads are issued together
+        constexpr int PU = 4;
+        for (int i0 = threadIdx.x; i0 < n; i0 += PU * T) {
+            int32_t pos[PU];
+#pragma unroll
+            for (int u = 0; u < PU; ++u) {
+                const int i = i0 + u * T;
+                pos[u] = (int32_t)list[i < n ? i : i0];
+            }
+            float pd2[PU];
+            int32_t id[PU];
+#pragma unroll
+            for (int u = 0; u < PU; ++u) {
+                pd2[u] = proj_dist2(a.proj + (int64_t)pos[u] * MP, qc.qp);
+                id[u] = a.perm[pos[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < PU; ++u) {
+                const int i = i0 + u * T;
+                if (i < n) {
+                    sh.skey[i] = ((uint64_t)__float_as_uint(pd2[u]) << 32) | (uint32_t)id[u];
+                    sh.spos[i] = pos[u];
+                }
             }
         }
-    } else {
-        const uint64_t kth = lds_select(m, k, sh);
-        uint64_t* tmp = reinterpret_cast<uint64_t*>(sh.hist);
-        if (threadIdx.x == 0) sh.cnt1 = 0;
         __syncthreads();
-        for (int b0 = 0; b0 < m; b0 += WG) {
+        if (n > B) {
+            const uint64_t kth = lds_select<T>(n, B, sh);
+            if (!cut_fp64<T>(a, qi, qc, n, B, kth, sh)) {
+                for (int i = threadIdx.x; i < n; i += T)
+                    if (sh.skey[i] > kth) sh.skey[i] = ~0ull;
+                __syncthreads();
+            }
+        }
+        if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
+        __syncthreads();
+        for (int b0 = 0; b0 < n; b0 += T) {
             const int i = b0 + threadIdx.x;
-            const bool take = i < m && sh.skey[i] <= kth;
-            const int slot = wave_append(take, &sh.cnt1);
-            if (take) tmp[slot] = sh.skey[i];
+            const uint64_t key = i < n ? sh.skey[i] : ~0ull;
+            emit(key != ~0ull, i < n ? sh.spos[i] : 0, (uint32_t)(key >> 32));
         }
         __syncthreads();
-        for (int j2 = threadIdx.x; j2 < k; j2 += WG) sh.skey[j2] = tmp[j2];
-        __syncthreads();
-        bitonic_sort(k, sh);
-        for (int j2 = threadIdx.x; j2 < k; j2 += WG) {
-            const uint64_t key = sh.skey[j2];
-            a.out_ids[qi * a.out_stride + j2] = (int64_t)(uint32_t)key;
-            a.out_dist[qi * a.out_stride + j2] = sqrtf(__uint_as_float((uint32_t)(key >> 32)));
+        if (threadIdx.x == 0) a.q_flag[qi] = sh.cnt0;
+        return;
+    }
+    // A longer list stays in memory: its pd^2 bits are computed once into
+    // l_val (or again in every pass, where the workspace has no room for them).
+    uint32_t* val = a.l_val ? a.l_val + qi * a.q_cap : nullptr;
+    auto compute = [&](int i) {
+        return __float_as_uint(proj_dist2(a.proj + (int64_t)(int32_t)list[i] * MP, qc.qp));
+    };
+    auto get = [&](int i) { return val ? val[i] : compute(i); };
+    // f(valid, entry, bits) for every entry, wave-uniform, four loads in flight
+    auto for_pool = [&](auto&& f) {
+        for (int b0 = 0; b0 < n; b0 += 4 * T) {
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = get(min(b0 + u * T + (int)threadIdx.x, n - 1));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = b0 + u * T + threadIdx.x;
+                f(i < n, min(i, n - 1), v[u]);
+            }
+        }
+    };
+    // the bin of the B-th: 256 bins per octave up to the test radius, which at
+    // least B entries do not exceed
+    const float tq = a.qtest[qi].x;
+    const uint32_t hb = __float_as_uint(tq * tq) >> 15;
+    const uint32_t base = hb > (uint32_t)(NB - 1) ? hb - (uint32_t)(NB - 1) : 0u;
+    clear_hist<T>(sh);
+    if (threadIdx.x == 0) {
+        sh.thr_bin = NB - 1;
+        sh.thr_below = 0;
+    }
+    for (int b0 = 0; b0 < n; b0 += 4 * T) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = compute(min(b0 + u * T + (int)threadIdx.x, n - 1));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = b0 + u * T + threadIdx.x;
+            if (i >= n) break;
+            if (val) val[i] = v[u];
+            atomicAdd(&sh.hist[min(radius_bin(__uint_as_float(v[u]), base), NB - 1)], 1u);
         }
     }
-    if (a.out_stats && threadIdx.x == 0) {
-        int32_t* st = a.out_stats + qi * 4;
-        st[0] = rounds;
-        st[1] = n_ver;
-        st[2] = exit_kind;
-        st[3] = (int32_t)a.q_scanned[qi];
+    __syncthreads();
+    find_threshold<T>(B, sh);
+    const uint32_t tb = (uint32_t)sh.thr_bin;
+    const int before = sh.thr_below;
+    __syncthreads();
+    const uint32_t k2 = select_u32<T>(
+        n, B - before, tb == 0u ? 0u : (base + tb) << 15,
+        tb == (uint32_t)(NB - 1) ? 0xffffffffu : ((base + tb + 1u) << 15) - 1u, get, sh);
+    // the FP64 order decides inside the band of cut_fp64
+    constexpr int kBandCap = 512;
+    int32_t* band = reinterpret_cast<int32_t*>(sh.hist);              // entry
+    uint32_t* bid = reinterpret_cast<uint32_t*>(sh.hist + kBandCap);  // its id
+    double* b64 = reinterpret_cast<double*>(sh.hist + 2 * kBandCap);  // its FP64 pd^2
+    const float kf = __uint_as_float(k2);
+    const float big = sqrtf(qc.qn2) + a.coord_scale;
+    const float e = 2.f * (2.384185791015625e-07f * sqrtf(kf) * big + 1.9073486328125e-06f * kf);
+    const float blo = kf - 2.f * e, bhi = kf + 2.f * e;
+    if (threadIdx.x == 0) sh.cnt2 = 0;
+    __syncthreads();
+    int below = 0, less = 0, equal = 0;
+    for_pool([&](bool ok, int i, uint32_t b) {
+        const float v = __uint_as_float(b);
+        below += ok && v < blo;
+        less += ok && b < k2;
+        equal += ok && b == k2;
+        const bool inb = ok && v >= blo && v <= bhi;
+        const int slot = wave_append(inb, &sh.cnt2);
+        if (inb && slot < kBandCap) {
+            band[slot] = i;
+            bid[slot] = (uint32_t)a.perm[list[i]];
+        }
+    });
+    below = block_sum<T>(below, sh);
+    less = block_sum<T>(less, sh);
+    equal = block_sum<T>(equal, sh);
+    const int nb = sh.cnt2;
+    const bool by64 = nb <= kBandCap && below < B && below + nb >= B;
+    float flim = bhi;          // by64: everything below blo, and the band or part of it
+    uint32_t idlim = 0xffffffffu;
+    if (by64 && below + nb > B) {
+        for (int j = threadIdx.x; j < nb; j += T) {
+            const int64_t pos = list[band[j]];
+            double acc = 0.0;
+#pragma unroll
+            for (int t = 0; t < MP; ++t) {
+                const double o = (double)a.proj[pos * MP + t] + (double)a.proj_lo[pos * MP + t];
+                const double q = (double)a.qp[qi * MP + t] + (double)a.qp_lo[qi * MP + t];
+                const double dd = q - o;
+                acc = fma(dd, dd, acc);
+            }
+            b64[j] = acc;
+        }
+        flim = -1.f;   // the band's members are emitted from the list below
+    } else if (!by64 && less + equal > B) {
+        // more entries than wanted at the B-th value: the smallest ids of them
+        idlim = select_u32<T>(
+            n, B - less, 0u, 0x7fffffffu,
+            [&](int i) { return get(i) == k2 ? (uint32_t)a.perm[list[i]] : 0xffffffffu; }, sh);
     }
+    __syncthreads();
+    if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
+    __syncthreads();
+    for_pool([&](bool ok, int i, uint32_t b) {
+        const float v = __uint_as_float(b);
+        bool take = ok && (by64 ? v < blo || v <= flim : b <= k2);
+        if (idlim != 0xffffffffu && take && b == k2) take = (uint32_t)a.perm[list[i]] <= idlim;
+        emit(take, take ? (int32_t)list[i] : 0, b);
+    });
+    if (by64 && flim < 0.f) {
+        const int want = B - below;
+        for (int b0 = 0; b0 < nb; b0 += T) {
+            const int j = b0 + threadIdx.x;
+            int rank = want;
+            if (j < nb) {
+                const double v = b64[j];
+                const uint32_t id = bid[j];
+                rank = 0;
+                for (int y = 0; y < nb; ++y) rank += b64[y] < v || (b64[y] == v && bid[y] < id);
+            }
+            const bool take = rank < want;
+            emit(take, take ? (int32_t)list[band[j]] : 0, take ? get(band[j]) : 0u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) a.q_flag[qi] = sh.cnt0;
+}
+
+// Distance bounds of the members in the first ball: blockIdx.y the query,
+// blockIdx.x the slice of a.vslice members.
+__global__ __launch_bounds__(WG) void pool_verify_kernel(AnnArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    float* qs = reinterpret_cast<float*>(smem_raw);
+    const int64_t qi = blockIdx.y;
+    const int n1 = a.q_flag[qi];
+    const int v0 = (int)blockIdx.x * a.vslice;
+    if (v0 >= n1) return;
+    const float* qrow = a.q + qi * a.d;
+    for (int j = threadIdx.x; j < a.d16; j += WG) qs[j] = j < a.d ? qrow[j] : 0.f;
+    __syncthreads();
+    const int64_t row = qi * (int64_t)a.budget;
+    verify16(a, qs, a.ws_cpos + row, a.ws_clo + row, a.ws_cdist + row, v0, min(n1, v0 + a.vslice));
+}
+
+template <int T>
+__global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
+    float* qs = reinterpret_cast<float*>(smem_raw + ((sizeof(Smem) + 15) & ~size_t(15)));
+    const int64_t qi = blockIdx.x;
+    const int n1 = a.q_flag[qi];
+    if (n1 < 0) return;   // the per-query kernel's
+    const AnnQueryParams qpar = query_params(a, qi);
+    const int B = qpar.budget;
+    const int k = qpar.k;
+    const float* qrow = a.q + qi * a.d;
+    for (int j = threadIdx.x; j < a.d16; j += T) qs[j] = j < a.d ? qrow[j] : 0.f;
+    const int64_t row = qi * (int64_t)a.budget;
+    int32_t* cpos = a.ws_cpos + row;
+    float* lo2 = a.ws_clo + row;
+    float* hi2 = a.ws_cdist + row;
+    int32_t* ilist = reinterpret_cast<int32_t*>(sh.hist);
+    __syncthreads();
+
+    // The rounds. C is the members of L with pd^2 bits <= cbits: after the
+    // first range query the n1 in front, whose bounds the verify kernel wrote;
+    // the others get theirs here when a second one is needed, and their pd^2
+    // is computed again where it is asked for.
+    double r = qpar.r_min;
+    uint32_t cbits = first_radius_bits(qpar);
+    int lim = n1, n_ver = n1, rounds = 1, exit_kind = n1 == B ? PMLSH_EXIT_BUDGET : 0;
+    auto member = [&](int i) {
+        return i < n1 ||
+               __float_as_uint(proj_dist2(a.proj + (int64_t)cpos[i] * MP, a.qp + qi * MP)) <= cbits;
+    };
+    while (exit_kind == 0 && rounds < a.max_rounds) {
+        r = qpar.c * r;
+        // the c r stop: at least k verified members within c r; a decision
+        // that the bounds leave open reads the FP32 rows of the members
+        // concerned, so it equals the one taken on exact values
+        const double cr = qpar.c * r;
+        const float thr2 = (float)(cr * cr);
+        int sure = 0, maybe = 0;
+        for (int i = threadIdx.x; i < lim; i += T) {
+            const bool in = member(i);
+            sure += in && hi2[i] <= thr2;
+            maybe += in && lo2[i] <= thr2 && hi2[i] > thr2;
+        }
+        sure = block_sum<T>(sure, sh);
+        maybe = block_sum<T>(maybe, sh);
+        if (sure < k && sure + maybe >= k) {
+            for (int b0 = 0; b0 < lim; b0 += NB) {
+                if (threadIdx.x == 0) sh.cnt1 = 0;
+                __syncthreads();
+                for (int i0 = b0; i0 < min(lim, b0 + NB); i0 += T) {
+                    const int i = i0 + threadIdx.x;
+                    const bool take = i < lim && member(i) && lo2[i] <= thr2 && hi2[i] > thr2;
+                    const int slot = wave_append(take, &sh.cnt1);
+                    if (take) ilist[slot] = i;
+                }
+                __syncthreads();
+                verify_list<T>(a, qs, cpos, ilist, sh.cnt1, lo2, hi2);
+                __syncthreads();
+            }
+            int loc = 0;
+            for (int i = threadIdx.x; i < lim; i += T) loc += member(i) && hi2[i] <= thr2;
+            sure = block_sum<T>(loc, sh);
+        }
+        if (sure >= k) { exit_kind = PMLSH_EXIT_NEAR; break; }
+        if (rounds >= MAX_ROUNDS) r = __longlong_as_double(0x7ff0000000000000ll);
+        const double rd = qpar.t * r;
+        cbits = __float_as_uint((float)(rd * rd));
+        if (lim < B) {
+            verify16<T>(a, qs, cpos, lo2, hi2, lim, B);
+            lim = B;
+            __syncthreads();
+        }
+        int loc = 0;
+        for (int i = threadIdx.x; i < B; i += T) loc += member(i);
+        n_ver = block_sum<T>(loc, sh);
+        ++rounds;
+        if (n_ver == B) exit_kind = PMLSH_EXIT_BUDGET;
+    }
+
+    answer_members<T>(a, qi, qs, cpos, lo2, hi2, lim, member, n_ver, rounds, exit_kind, sh);
 }
 
 }  // namespace
 
-int64_t ann_pool_per_query(int64_t n) { return n < 16384 ? n : 16384; }
+// Pool entries per query: the bound leaves up to about 1.3 B candidates on
+// clustered data and 5 to 8 B on data without contrast (fewer for large B).
+int64_t ann_pool_per_query(int64_t n, int64_t budget) {
+    const int64_t want = std::max(std::min<int64_t>(8 * budget, 65536), 3 * budget);
+    return std::min(n, std::max<int64_t>(want, 16384));
+}
 
 namespace {
 
@@ -2408,11 +2816,62 @@ void launch_bc_finalize(int64_t* ids, float* dist, const int32_t* stats, int64_t
     PMLSH_HIP(hipGetLastError());
 }
 
-bool ann_fast_path(int64_t budget) { return budget <= CAP; }
+bool ann_fast_path(int64_t budget) { return budget <= kWideBudget; }
 
 int ann_lds_bytes(int d_pad) {
     return (int)(((sizeof(Smem) + 15) & ~size_t(15)) + (size_t)d_pad * sizeof(float));
 }
+
+namespace {
+
+// Members of L per verify workgroup: enough workgroups to fill the chip a few
+// times over, at least the 64 rows that one has in flight.
+template <int T>
+void launch_pool(AnnArgs& a, const AnnLaunch& L, int lds_cut, int lds_answer, hipStream_t stream) {
+    const int64_t per = (L.budget * L.nq + 4095) / 4096;
+    a.vslice = (int)std::min<int64_t>(512, std::max<int64_t>(64, (per + 63) / 64 * 64));
+    PMLSH_HIP(hipFuncSetAttribute((const void*)pool_cut_kernel<T>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds_cut));
+    PMLSH_HIP(hipFuncSetAttribute((const void*)pool_answer_kernel<T>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds_answer));
+    hipLaunchKernelGGL(pool_cut_kernel<T>, dim3((unsigned)L.nq), dim3(T), (unsigned)lds_cut, stream, a);
+    const dim3 vgrid((unsigned)((L.budget + a.vslice - 1) / a.vslice), (unsigned)L.nq);
+    hipLaunchKernelGGL(pool_verify_kernel, vgrid, dim3(WG), (unsigned)(4 * a.d16), stream, a);
+    hipLaunchKernelGGL(pool_answer_kernel<T>, dim3((unsigned)L.nq), dim3(T), (unsigned)lds_answer,
+                       stream, a);
+}
+
+template <int T>
+void launch_finish(const AnnArgs& a, const AnnLaunch& L, int lds, hipStream_t stream) {
+    PMLSH_HIP(hipFuncSetAttribute((const void*)finish_kernel<T>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    hipLaunchKernelGGL(finish_kernel<T>, dim3((unsigned)L.nq), dim3(T), (unsigned)lds, stream, a);
+}
+
+// Which kernels finish a budget of at most kLeanBudget. One workgroup of 256
+// threads per query suits more than 512 queries: four are resident per compute
+// unit. With fewer queries the chip has room, and a query's chain of row gathers
+// (64 rows in flight per 256 threads) sets the time: 512 threads up to 512
+// queries, 1,024 up to 256 queries. The three kernels spread one query's rows
+// over many workgroups, at the cost of two launches: for a few queries, for
+// budgets whose lists (1.0 to 1.3 B) outgrow the LDS keys, and without contrast,
+// where the lists are longer still. us per call at 1M x 256, threads 256 / 512 /
+// 1,024 / three kernels:
+//   1 query      B = 160  67 /  68 /  72 /  73    900 110 /  98 /  90 /  86
+//   256 queries  B = 160  91 /  89 /  91 / 103    900 134 / 119 / 113 / 125
+//   512          B = 160 106 / 106 / 131 / 120    900 175 / 159 / 180 / 174
+//   1,024        B = 900 241 / 269 / 307 / 262   1,900 492 / 526 / 609 / 433
+// and at 1M x 960 without contrast, 1,024 queries of B = 1,010: 1,085 with 256
+// threads, 873 with three kernels.
+
+// Points sampled per budget point by the bound kernel. Where the chunks are
+// wider than the spread of their centres, points of every chunk lie inside the
+// ball and the nearest chunks' 2 B points bound its radius poorly: at 1M
+// points and B = 1,000 the ball then holds 14 B (up to 25 B) candidates, from
+// 4 B points 5 B (up to 8 B). On clustered data 2 B points leave 1.0 to 1.3 B.
+int ann_bound_sample(const pmlsh_index& x) { return x.low_contrast ? 4 : 2; }
+
+}  // namespace
 
 void launch_ann(const AnnLaunch& L, hipStream_t stream) {
     const pmlsh_index& x = *L.idx;
@@ -2488,6 +2947,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         a.cgroups = cdist_groups(x.n_pad16 / 64);
         a.gld = cdist_gmin_len(x.n_pad16 / 64);
         a.ws_clo = L.ws_clo;
+        a.l_val = L.l_val;
         a.q_flag = L.q_flag;
         a.pq_list = L.pq_list;
         a.l_count = L.l_count;
@@ -2505,13 +2965,15 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         {
             StageTimer tm(PMLSH_STAGE_TAU, stream);
             const int64_t ngr = (nchunk + 63) / 64;
+            a.sample = ann_bound_sample(x);
+            a.sel_cap = (int)std::min<int64_t>(kSelMax, std::max<int64_t>(kSelCap, (a.sample * L.budget + 63) / 64 + 1));
             a.grp_cap = (int)std::min<int64_t>(kGrpCap, std::max<int64_t>(0, tune_get(PMLSH_TUNE_GROUP_LIST)));
             const size_t min_bytes = 2 * (size_t)((ngr + 7) & ~7);
             a.glds = tune_get(PMLSH_TUNE_GROUP_MINIMA_LDS) != 0 &&
-                     min_bytes + 4 * (size_t)kGrpCap <= kTauGroupLds;
+                     min_bytes + 4 * (size_t)(kGrpCap + a.sel_cap - kSelCap) <= kTauGroupLds;
             const size_t lds_t = std::max((size_t)lds0, offsetof(Smem, skey) +
                                           (a.glds ? min_bytes : 0) +
-                                          4 * (size_t)(kGrpCap + kSelCap));
+                                          4 * (size_t)(kGrpCap + a.sel_cap));
             PMLSH_HIP(hipFuncSetAttribute((const void*)tau_kernel,
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_t));
             hipLaunchKernelGGL(tau_kernel, dim3((unsigned)L.nq), dim3(WG), (unsigned)lds_t, stream, a);
@@ -2550,13 +3012,19 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
                                    dim3(WG), 0, stream, a);
             PMLSH_HIP(hipGetLastError());
         }
-        PMLSH_HIP(hipFuncSetAttribute((const void*)finish_kernel,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        {
-            StageTimer tm(PMLSH_STAGE_FINISH, stream);
-            hipLaunchKernelGGL(finish_kernel, dim3((unsigned)L.nq), dim3(WG), lds, stream, a);
-            PMLSH_HIP(hipGetLastError());
-        }
+        StageTimer tm(PMLSH_STAGE_FINISH, stream);
+        const int64_t B = L.budget, nq = L.nq;
+        if (B > kLeanBudget)
+            launch_pool<1024>(a, L, lds0, lds, stream);
+        else if (B >= 1536 || x.low_contrast || (nq <= 32 && B >= 768))
+            launch_pool<WG>(a, L, lds0, lds, stream);
+        else if (nq > 512)
+            launch_finish<WG>(a, L, lds, stream);
+        else if (nq > 256 || B < 512)
+            launch_finish<512>(a, L, lds, stream);
+        else
+            launch_finish<1024>(a, L, lds, stream);
+        PMLSH_HIP(hipGetLastError());
     }
     // per-query path: every query when the fast path does not apply, else only
     // the queries the fast path flagged

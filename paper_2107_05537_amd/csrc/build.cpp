@@ -215,7 +215,7 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
             for (int t = 0; t < MP; ++t) mu64[t] += w * (double)ccen[(size_t)(c * MP + t)];
         }
         for (int t = 0; t < MP; ++t) x->scan_centre[t] = (float)(mu64[t] / (double)n);
-        double smax = 0.0;
+        double smax = 0.0, spread = 0.0, width = 0.0;
         for (int64_t c = 0; c < nch; ++c) {
             double s2 = 0.0;
             for (int t = 0; t < MP; ++t) {
@@ -223,7 +223,12 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
                 s2 += dd * dd;
             }
             smax = std::max(smax, std::sqrt(s2) + (double)crad[(size_t)c]);
+            spread += s2;
+            width += (double)crad[(size_t)c] * (double)crad[(size_t)c];
         }
+        // chunks as wide as the spread of their centres: the bound of the range
+        // filter needs more points, and its pools grow
+        x->low_contrast = width > spread;
         x->scan_scale = std::nextafter((float)(smax * (1.0 + 1e-6)), INFINITY);
 
         // FP16 rows scaled by a power of two s with s * S < 32, so every

@@ -48,6 +48,7 @@ namespace {
 struct AnnWorkspace {
     int64_t B, pool_q, per_query, nchunk, batch, slots, bytes;
     bool fast;
+    bool vals;   // pd^2 bits kept per pool entry
 };
 
 // Workgroups of the per-query kernel, each with its own pair of frontier
@@ -69,15 +70,18 @@ int64_t ann_layout_bytes(const pmlsh_index* x, const AnnWorkspace& w, int64_t ba
     return batch * w.per_query + mask_bytes + slots * 2 * x->n_leaves * 4;
 }
 
-AnnWorkspace ann_workspace_base(const pmlsh_index* x, int k, int64_t B) {
+// wide: budgets above kLeanBudget take the batched path too, and long candidate
+// lists keep their pd^2 bits in memory.
+AnnWorkspace ann_workspace_base(const pmlsh_index* x, int k, int64_t B, bool wide = true) {
     AnnWorkspace w{};
     w.B = B;
     // the batched path, unless the budget exceeds its limit or the plain
     // FP32 path is switched on (read once per call: layout and launch agree)
-    w.fast = ann_fast_path(B) && tune_get(PMLSH_TUNE_FP32_PATH) == 0;
-    w.pool_q = w.fast ? ann_pool_per_query(x->n) : 0;
+    w.fast = ann_fast_path(B) && tune_get(PMLSH_TUNE_FP32_PATH) == 0 && (wide || B <= kLeanBudget);
+    w.vals = w.fast && wide;
+    w.pool_q = w.fast ? ann_pool_per_query(x->n, B) : 0;
     w.per_query = (int64_t)MP * 8 + 64 + B * 8 + 3 * (int64_t)k * 4 +
-                  (w.fast ? 4 * 4 + w.pool_q * 4 + B * 4 : 0) +
+                  (w.fast ? 4 * 4 + w.pool_q * (w.vals ? 8 : 4) + B * 4 : 0) +
                   (w.fast && x->filter_gemm ? (MP + 1) * 4 : 0);
     w.nchunk = x->n_pad16 / 64;
     return w;
@@ -104,8 +108,9 @@ AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B) {
 // Layout that fits a fixed region of cap bytes: at most a quarter of it for
 // the frontier lists, the largest batch that fits in the rest. batch = 0
 // when not even one query fits.
-AnnWorkspace ann_workspace_in(const pmlsh_index* x, int64_t nq, int k, int64_t B, int64_t cap) {
-    AnnWorkspace w = ann_workspace_base(x, k, B);
+AnnWorkspace ann_workspace_in(const pmlsh_index* x, int64_t nq, int k, int64_t B, int64_t cap,
+                              bool wide = true) {
+    AnnWorkspace w = ann_workspace_base(x, k, B, wide);
     const int64_t per_slot = 2 * x->n_leaves * 4;
     int64_t slots = std::min<int64_t>(w.fast ? 256 : 2048, (cap / 4) / per_slot);
     slots = std::max<int64_t>(slots, 1);
@@ -176,7 +181,8 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
     uint64_t* cmask = reinterpret_cast<uint64_t*>(qtest + (fast ? batch : 0));
     uint32_t* list = reinterpret_cast<uint32_t*>(
         cmask + (fast ? (nchunk + 255) / 256 * 256 * ((batch + 63) / 64) : 0));
-    int32_t* front = reinterpret_cast<int32_t*>(list + batch * pool_q);
+    uint32_t* vals = list + batch * pool_q;
+    int32_t* front = reinterpret_cast<int32_t*>(vals + (w.vals ? batch * pool_q : 0));
     int32_t* cpos = front + w.slots * 2 * x->n_leaves;
     float* cdist = reinterpret_cast<float*>(cpos + batch * B);
     int32_t* topk = reinterpret_cast<int32_t*>(cdist + batch * B);
@@ -233,6 +239,7 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
             L.ws_qeps = lp ? qeps : nullptr;
             L.l_list = list;
             L.pool_cap = pool_q;
+            L.l_val = w.vals ? vals : nullptr;
         }
         L.out_ids = out_ids + q0 * stride;
         L.out_dist = out_dist + q0 * stride;
@@ -277,9 +284,13 @@ void run_ann_in(const pmlsh_index* x, const float* queries, int64_t nq, int k, d
     pmlsh_plan plan;
     r_min = ann_plan(x, k, c, confidence, beta, r_min, &plan);
     if (nq == 0) return;
-    const AnnWorkspace w = ann_workspace_in(x, nq, k, plan.budget, region_bytes);
+    // a small fixed region holds most queries without the lists' pd^2 bits; a
+    // large budget whose candidate pool does not fit takes the per-query path
+    AnnWorkspace w = ann_workspace_in(x, nq, k, plan.budget, region_bytes,
+                                      plan.budget > kLeanBudget);
+    if (w.batch < 1) w = ann_workspace_in(x, nq, k, plan.budget, region_bytes, false);
     if (w.batch < 1) {
-        const AnnWorkspace one = ann_workspace_in(x, 1, k, plan.budget, int64_t(1) << 62);
+        const AnnWorkspace one = ann_workspace_in(x, 1, k, plan.budget, int64_t(1) << 62, false);
         fail(PMLSH_EUNSUPPORTED,
              "one query of this index needs " + std::to_string(one.bytes) +
                  " bytes of workspace; the fixed region holds " + std::to_string(region_bytes));

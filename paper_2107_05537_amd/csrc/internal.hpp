@@ -28,9 +28,12 @@ constexpr float kScanMarginWeight = 0.001953125f + 0.00006103515625f;
 // a multiple of eight; the eight halves the 32-deep MFMA reads beyond them
 // are zero and are not stored
 constexpr int kScanRow = 24;
-// Chunks the ANN bound may choose per query (64 points each; at least twice
-// the largest budget of the batched path).
+// Chunks the ANN bound may choose per query at least (64 points each; larger
+// budgets get a longer list).
 constexpr int kSelCap = 1024;
+// Largest budget whose members fit the LDS lists of one workgroup; larger ones
+// use workgroups of 1,024 threads and lists in memory.
+constexpr int64_t kLeanBudget = 2048;
 
 // The batch's chunk-distance matrix (bf16 values) is stored in blocks of 64
 // queries x 64 chunks (8 KB, a query's 64 chunks contiguous inside), the
@@ -260,6 +263,7 @@ struct pmlsh_index {
     int filter_gemm = 0;
     float eps_max = 0.f;
     float scan_scale = 0.f;      // bound on |o' - scan_centre| over the scan rows
+    bool low_contrast = false;   // chunks about as wide as the spread of their centres
     float scan_centre[pmlsh::MP] = {};  // centre of the scan rows (mean projected point)
     // (c,k)-ACP workspace kept between calls: one device buffer per role,
     // grown on demand, freed with the index; calls on one index serialise on
@@ -365,6 +369,7 @@ struct AnnLaunch {
                             // blocks of 64 queries x 64 chunks
     uint16_t* ws_cgmin;     // nq x cdist_gmin_len: their minimum per group of 64 chunks
     int64_t pool_cap;       // candidate region per query
+    uint32_t* l_val;        // nq x pool_cap pd^2 bits of its entries, or null
     int64_t* out_ids;
     float* out_dist;
     int32_t* out_stats;
@@ -374,7 +379,7 @@ struct AnnLaunch {
 };
 void launch_ann(const AnnLaunch& a, hipStream_t stream);
 int ann_lds_bytes(int d_pad);
-int64_t ann_pool_per_query(int64_t n);
+int64_t ann_pool_per_query(int64_t n, int64_t budget);
 bool ann_fast_path(int64_t budget);
 
 }  // namespace pmlsh
