@@ -11,11 +11,11 @@
 // centred second moments over pieces of at most kPiece points (one
 // workgroup per piece, reduced per node in a fixed order, so a build is
 // deterministic), one wave per node for the power iteration, FP64 keys
-// (direction . point), a segmented radix sort of the nodes' points by key
-// (stable, so equal keys keep their order), and one wave per node for the
-// cut. The host only keeps the list of nodes and their children.
+// (direction . point), a sort of the nodes' points by (key, position), so
+// equal keys keep their order, and one wave per node for the cut. The host
+// only keeps the list of nodes and their children.
 
-#include <hipcub/hipcub.hpp>
+#include <algorithm>
 
 #include "internal.hpp"
 
@@ -184,6 +184,237 @@ __global__ __launch_bounds__(256) void bl_keys_kernel(const float* __restrict__ 
 #pragma unroll
         for (int j = 0; j < MP; ++j) v += dv[j] * (double)p[j];
         key[i] = v;
+    }
+}
+
+// ---- The sort of a level: every node's positions by (key, position) ----
+//
+// A range of at most kSortCap positions is sorted by one workgroup in LDS. A
+// longer one is first cut into about one bucket per kBucket positions: splitters
+// from a sorted sample of kOver positions per bucket, a count of every bucket,
+// and a scatter of (key, position) in any order within the bucket. Buckets above
+// kSortCap (ranges of more than kMaxBuckets buckets) go through this again.
+// Keys are compared together with their positions, so all are distinct: the
+// result does not depend on the scatter's order, equal keys keep theirs and
+// never gather in one bucket. One workgroup per node, as a segmented sort has
+// it, leaves the chip idle at the top of the tree: at 1M points it took 5.4 ms
+// per level on average (146 of the build's 195 ms); this takes 0.15 ms (sorting
+// 0.09, samples 0.025, buckets and scatter 0.03), bound by the LDS passes of the
+// bitonic network (256 / 512 / 1,024 threads: 91 / 66 / 64 us per launch;
+// ranges of 2,048 cost more bucket passes than they save). 10M points: 1.74 s
+// of sorts per build before.
+constexpr int kSortCap = 4096;
+constexpr int kBucket = 1536;
+constexpr int kOver = 16;
+constexpr int kMaxBuckets = 512;
+constexpr int kSampleWg = 1024;
+constexpr int kSortWg = 512;
+
+// A range of positions to sort, from the scattered copies (or the keys).
+struct SortRange {
+    int32_t b, e;
+    int32_t scattered;
+};
+// A range to cut into k buckets, whose splitters, counts and cursors start at
+// entry first (k entries; the last splitter is not used).
+struct CutRange {
+    int32_t b, e;
+    int32_t scattered;
+    int32_t k, first;
+};
+
+struct SortKey {
+    uint64_t k;   // ordered like the FP64 key
+    uint32_t p;   // position before the sort
+};
+__device__ __forceinline__ bool key_less(uint64_t ak, uint32_t ap, uint64_t bk, uint32_t bp) {
+    return ak < bk || (ak == bk && ap < bp);
+}
+__device__ __forceinline__ uint64_t ordered_bits(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    return (u >> 63) ? ~u : u | (1ull << 63);
+}
+__device__ __forceinline__ double from_ordered_bits(uint64_t u) {
+    return __longlong_as_double((long long)((u >> 63) ? u & ~(1ull << 63) : ~u));
+}
+__device__ __forceinline__ SortKey load_key(const double* key, const uint64_t* skey,
+                                            const uint32_t* spos, int32_t scattered, int32_t i) {
+    SortKey r;
+    if (scattered) {
+        r.k = skey[i];
+        r.p = spos[i];
+    } else {
+        r.k = ordered_bits(key[i]);
+        r.p = (uint32_t)i;
+    }
+    return r;
+}
+
+// Bitonic sort of the n <= capacity keys in LDS (padded to a power of two).
+template <int T>
+__device__ void sort_lds(uint64_t* sk, uint32_t* sp, int n) {
+    int P = 2;
+    while (P < n) P <<= 1;
+    for (int i = n + (int)threadIdx.x; i < P; i += T) {
+        sk[i] = ~0ull;
+        sp[i] = ~0u;
+    }
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = threadIdx.x; t < P / 2; t += T) {
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+                const int x = i | j;
+                const bool up = (i & k) == 0;
+                const uint64_t a = sk[i], b = sk[x];
+                const uint32_t pa = sp[i], pb = sp[x];
+                if (key_less(b, pb, a, pa) == up) {
+                    sk[i] = b;
+                    sk[x] = a;
+                    sp[i] = pb;
+                    sp[x] = pa;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Splitters of one range per workgroup, and its counters cleared.
+__global__ __launch_bounds__(kSampleWg) void bl_sample_kernel(
+    const CutRange* __restrict__ ranges, const double* __restrict__ key,
+    const uint64_t* __restrict__ skey, const uint32_t* __restrict__ spos,
+    uint64_t* __restrict__ split_k, uint32_t* __restrict__ split_p, int32_t* __restrict__ count) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const CutRange r = ranges[blockIdx.x];
+    const int ns = r.k * kOver;
+    uint64_t* sk = reinterpret_cast<uint64_t*>(smem);
+    uint32_t* sp = reinterpret_cast<uint32_t*>(sk + kMaxBuckets * kOver);
+    const int64_t len = r.e - r.b;
+    for (int i = threadIdx.x; i < ns; i += kSampleWg) {
+        const SortKey v = load_key(key, skey, spos, r.scattered, r.b + (int32_t)(i * len / ns));
+        sk[i] = v.k;
+        sp[i] = v.p;
+    }
+    __syncthreads();
+    sort_lds<kSampleWg>(sk, sp, ns);
+    for (int i = threadIdx.x; i < r.k; i += kSampleWg) {
+        const int at = min((i + 1) * kOver, ns - 1);
+        split_k[r.first + i] = sk[at];
+        split_p[r.first + i] = sp[at];
+        count[r.first + i] = 0;
+    }
+}
+
+// Bucket of a key: the number of splitters (of the first k - 1) not above it.
+__device__ __forceinline__ int bucket_of(const uint64_t* sk, const uint32_t* sp, int k,
+                                         const SortKey& v) {
+    int lo = 0, hi = k - 1;
+    while (lo < hi) {
+        const int m = (lo + hi) >> 1;
+        if (key_less(v.k, v.p, sk[m], sp[m])) hi = m;
+        else lo = m + 1;
+    }
+    return lo;
+}
+
+// Per piece: the bucket of every position, and the buckets' counts.
+__global__ __launch_bounds__(256) void bl_bucket_kernel(
+    const CutRange* __restrict__ ranges, const Piece* __restrict__ pieces,
+    const double* __restrict__ key, const uint64_t* __restrict__ skey,
+    const uint32_t* __restrict__ spos, const uint64_t* __restrict__ split_k,
+    const uint32_t* __restrict__ split_p, uint16_t* __restrict__ bucket,
+    int32_t* __restrict__ count) {
+    __shared__ uint64_t sk[kMaxBuckets];
+    __shared__ uint32_t sp[kMaxBuckets];
+    __shared__ int32_t cnt[kMaxBuckets];
+    const Piece pc = pieces[blockIdx.x];
+    const CutRange r = ranges[pc.seg];
+    for (int i = threadIdx.x; i < r.k; i += 256) {
+        sk[i] = split_k[r.first + i];
+        sp[i] = split_p[r.first + i];
+        cnt[i] = 0;
+    }
+    __syncthreads();
+    for (int i = pc.b + (int)threadIdx.x; i < pc.e; i += 256) {
+        const SortKey v = load_key(key, skey, spos, r.scattered, i);
+        const int g = bucket_of(sk, sp, r.k, v);
+        bucket[i] = (uint16_t)g;
+        atomicAdd(&cnt[g], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < r.k; i += 256)
+        if (cnt[i]) atomicAdd(&count[r.first + i], cnt[i]);
+}
+
+// Exclusive sums of each range's counts: the buckets' first positions, twice
+// (kept, and as the scatter's cursors).
+__global__ __launch_bounds__(kMaxBuckets) void bl_offset_kernel(
+    const CutRange* __restrict__ ranges, const int32_t* __restrict__ count,
+    int32_t* __restrict__ start, int32_t* __restrict__ cursor) {
+    __shared__ int32_t s[kMaxBuckets];
+    const CutRange r = ranges[blockIdx.x];
+    const int i = threadIdx.x;
+    const int own = i < r.k ? count[r.first + i] : 0;
+    s[i] = own;
+    __syncthreads();
+    for (int off = 1; off < kMaxBuckets; off <<= 1) {
+        const int v = i >= off ? s[i - off] : 0;
+        __syncthreads();
+        s[i] += v;
+        __syncthreads();
+    }
+    if (i < r.k) {
+        start[r.first + i] = r.b + s[i] - own;
+        cursor[r.first + i] = r.b + s[i] - own;
+    }
+}
+
+// Every (key, position) of a piece to its bucket, one reservation per piece
+// and bucket.
+__global__ __launch_bounds__(256) void bl_scatter_kernel(
+    const CutRange* __restrict__ ranges, const Piece* __restrict__ pieces,
+    const double* __restrict__ key, const uint64_t* __restrict__ skey,
+    const uint32_t* __restrict__ spos, const uint16_t* __restrict__ bucket,
+    int32_t* __restrict__ cursor, uint64_t* __restrict__ okey, uint32_t* __restrict__ opos) {
+    __shared__ int32_t cnt[kMaxBuckets];
+    const Piece pc = pieces[blockIdx.x];
+    const CutRange r = ranges[pc.seg];
+    for (int i = threadIdx.x; i < r.k; i += 256) cnt[i] = 0;
+    __syncthreads();
+    for (int i = pc.b + (int)threadIdx.x; i < pc.e; i += 256) atomicAdd(&cnt[bucket[i]], 1);
+    __syncthreads();
+    for (int i = threadIdx.x; i < r.k; i += 256)
+        if (cnt[i]) cnt[i] = atomicAdd(&cursor[r.first + i], cnt[i]);
+    __syncthreads();
+    for (int i = pc.b + (int)threadIdx.x; i < pc.e; i += 256) {
+        const SortKey v = load_key(key, skey, spos, r.scattered, i);
+        const int32_t at = atomicAdd(&cnt[bucket[i]], 1);
+        okey[at] = v.k;
+        opos[at] = v.p;
+    }
+}
+
+// One range per workgroup: sorted keys, and the ids at the sorted positions.
+__global__ __launch_bounds__(kSortWg) void bl_sort_kernel(
+    const SortRange* __restrict__ ranges, const double* __restrict__ key,
+    const uint64_t* __restrict__ skey, const uint32_t* __restrict__ spos,
+    const int32_t* __restrict__ perm, double* __restrict__ key_out,
+    int32_t* __restrict__ perm_out) {
+    __shared__ uint64_t sk[kSortCap];
+    __shared__ uint32_t sp[kSortCap];
+    const SortRange r = ranges[blockIdx.x];
+    const int n = r.e - r.b;
+    for (int i = threadIdx.x; i < n; i += kSortWg) {
+        const SortKey v = load_key(key, skey, spos, r.scattered, r.b + i);
+        sk[i] = v.k;
+        sp[i] = v.p;
+    }
+    __syncthreads();
+    sort_lds<kSortWg>(sk, sp, n);
+    for (int i = threadIdx.x; i < n; i += kSortWg) {
+        key_out[r.b + i] = from_ordered_bits(sk[i]);
+        perm_out[r.b + i] = perm[sp[i]];
     }
 }
 
@@ -438,6 +669,110 @@ struct DevVec {
 
 }  // namespace
 
+namespace {
+
+// Device buffers of the level sorts, and their host lists.
+struct LevelSort {
+    DevVec<uint64_t> skey[2], split_k;
+    DevVec<uint32_t> spos[2], split_p;
+    DevVec<uint16_t> bucket;
+    DevVec<int32_t> count;           // counts, starts and cursors of the buckets
+    DevVec<CutRange> d_cut;
+    DevVec<SortRange> d_sort;
+    DevVec<Piece> d_pieces;
+    std::vector<CutRange> cut, next;
+    std::vector<SortRange> ready;
+    std::vector<Piece> pieces;
+    std::vector<int32_t> start;
+
+    // Sorts [sb[s], se[s]) for every s < m by (key, position); ids and keys of
+    // the sorted ranges go to perm_out and key_out.
+    void run(const double* key, const int32_t* perm, int64_t n, const int32_t* sb,
+             const int32_t* se, int m, double* key_out, int32_t* perm_out, hipStream_t st) {
+        cut.clear();
+        ready.clear();
+        auto place = [&](int32_t b, int32_t e, int32_t scattered, std::vector<CutRange>& to) {
+            if (e - b <= kSortCap) {
+                if (e > b) ready.push_back({b, e, scattered});
+            } else {
+                to.push_back({b, e, scattered, std::min(kMaxBuckets, (e - b + kBucket - 1) / kBucket), 0});
+            }
+        };
+        for (int s = 0; s < m; ++s) place(sb[s], se[s], 0, cut);
+        int from = 1;   // the scattered copies read by this round are side `from`
+        while (!cut.empty()) {
+            sort_ready(key, perm, key_out, perm_out, from, st);
+            const int to = from ^ 1;
+            int32_t total = 0;
+            pieces.clear();
+            for (size_t s = 0; s < cut.size(); ++s) {
+                cut[s].first = total;
+                total += cut[s].k;
+                for (int32_t x = cut[s].b; x < cut[s].e; x += kPiece)
+                    pieces.push_back({(int32_t)s, x, std::min(cut[s].e, x + kPiece)});
+            }
+            uint64_t* ik = skey[from].get((size_t)n);
+            uint32_t* ip = spos[from].get((size_t)n);
+            uint64_t* ok = skey[to].get((size_t)n);
+            uint32_t* op = spos[to].get((size_t)n);
+            uint64_t* pk = split_k.get((size_t)total);
+            uint32_t* pp = split_p.get((size_t)total);
+            uint16_t* bk = bucket.get((size_t)n);
+            int32_t* cn = count.get((size_t)total * 3);
+            CutRange* dc = d_cut.get(cut.size());
+            Piece* dp = d_pieces.get(pieces.size());
+            PMLSH_HIP(hipMemcpyAsync(dc, cut.data(), cut.size() * sizeof(CutRange),
+                                     hipMemcpyHostToDevice, st));
+            PMLSH_HIP(hipMemcpyAsync(dp, pieces.data(), pieces.size() * sizeof(Piece),
+                                     hipMemcpyHostToDevice, st));
+            constexpr int lds = kMaxBuckets * kOver * (int)(sizeof(uint64_t) + sizeof(uint32_t));
+            PMLSH_HIP(hipFuncSetAttribute((const void*)bl_sample_kernel,
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+            const dim3 gr((unsigned)cut.size()), gp((unsigned)pieces.size());
+            hipLaunchKernelGGL(bl_sample_kernel, gr, dim3(kSampleWg), lds, st, dc, key, ik, ip, pk,
+                               pp, cn);
+            hipLaunchKernelGGL(bl_bucket_kernel, gp, dim3(256), 0, st, dc, dp, key, ik, ip, pk, pp,
+                               bk, cn);
+            hipLaunchKernelGGL(bl_offset_kernel, gr, dim3(kMaxBuckets), 0, st, dc, cn, cn + total,
+                               cn + 2 * total);
+            hipLaunchKernelGGL(bl_scatter_kernel, gp, dim3(256), 0, st, dc, dp, key, ik, ip, bk,
+                               cn + 2 * total, ok, op);
+            PMLSH_HIP(hipGetLastError());
+            start.resize((size_t)total);
+            PMLSH_HIP(hipMemcpyAsync(start.data(), cn + total, (size_t)total * sizeof(int32_t),
+                                     hipMemcpyDeviceToHost, st));
+            PMLSH_HIP(hipStreamSynchronize(st));
+            next.clear();
+            for (const CutRange& r : cut)
+                for (int g = 0; g < r.k; ++g) {
+                    const int32_t b = start[(size_t)(r.first + g)];
+                    const int32_t e = g + 1 < r.k ? start[(size_t)(r.first + g + 1)] : r.e;
+                    if (b < r.b || e < b || e > r.e)
+                        fail(PMLSH_EDEVICE, "device sort produced an invalid bucket");
+                    place(b, e, 1, next);
+                }
+            cut.swap(next);
+            from = to;
+        }
+        sort_ready(key, perm, key_out, perm_out, from, st);
+        PMLSH_HIP(hipGetLastError());
+    }
+
+private:
+    void sort_ready(const double* key, const int32_t* perm, double* key_out, int32_t* perm_out,
+                    int from, hipStream_t st) {
+        if (ready.empty()) return;
+        SortRange* dr = d_sort.get(ready.size());
+        PMLSH_HIP(hipMemcpyAsync(dr, ready.data(), ready.size() * sizeof(SortRange),
+                                 hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL(bl_sort_kernel, dim3((unsigned)ready.size()), dim3(kSortWg), 0, st, dr,
+                           key, skey[from].p, spos[from].p, perm, key_out, perm_out);
+        ready.clear();
+    }
+};
+
+}  // namespace
+
 void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
                   std::vector<int32_t>* perm_out, std::vector<SplitNode>* nodes_out) {
     if (n <= 0 || n > 0x7fffffffLL - kPiece) fail(PMLSH_EUNSUPPORTED, "point count out of range");
@@ -451,7 +786,7 @@ void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
     DevVec<int32_t> perm, perm_alt, d_idx;
     DevVec<double> key, key_alt, part, mean, cov, dir;
     DevVec<Piece> d_pieces;
-    DevVec<unsigned char> temp;
+    LevelSort sorter;
     {
         std::vector<int32_t> iota((size_t)n);
         for (int64_t i = 0; i < n; ++i) iota[(size_t)i] = (int32_t)i;
@@ -511,15 +846,7 @@ void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
                            ddir, key.p);
         PMLSH_HIP(hipGetLastError());
 
-        // stable sort of every node's points by key
-        size_t tbytes = 0;
-        PMLSH_HIP(hipcub::DeviceSegmentedRadixSort::SortPairs(
-            nullptr, tbytes, key.p, key_alt.p, perm.p, perm_alt.p, (int)n, m, dsb, dse, 0,
-            (int)(sizeof(double) * 8), st));
-        void* tp = temp.get(tbytes);
-        PMLSH_HIP(hipcub::DeviceSegmentedRadixSort::SortPairs(
-            tp, tbytes, key.p, key_alt.p, perm.p, perm_alt.p, (int)n, m, dsb, dse, 0,
-            (int)(sizeof(double) * 8), st));
+        sorter.run(key.p, perm.p, n, sb, se, m, key_alt.p, perm_alt.p, st);
         hipLaunchKernelGGL(bl_copy_kernel, dim3((unsigned)np), dim3(256), 0, st, dp, perm_alt.p,
                            perm.p);
         // the cuts, from the sorted keys
