@@ -395,7 +395,8 @@ __global__ __launch_bounds__(256) void bl_scatter_kernel(
     }
 }
 
-// One range per workgroup: sorted keys, and the ids at the sorted positions.
+// One range per workgroup: sorted keys, and the ids at the sorted positions
+// (unless perm is null).
 __global__ __launch_bounds__(kSortWg) void bl_sort_kernel(
     const SortRange* __restrict__ ranges, const double* __restrict__ key,
     const uint64_t* __restrict__ skey, const uint32_t* __restrict__ spos,
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(kSortWg) void bl_sort_kernel(
     sort_lds<kSortWg>(sk, sp, n);
     for (int i = threadIdx.x; i < n; i += kSortWg) {
         key_out[r.b + i] = from_ordered_bits(sk[i]);
-        perm_out[r.b + i] = perm[sp[i]];
+        if (perm) perm_out[r.b + i] = perm[sp[i]];
     }
 }
 
@@ -650,18 +651,41 @@ __global__ void bl_fill_kernel(double* __restrict__ x, int64_t count, double v) 
         x[i] = v;
 }
 
+// perm[i] = i.
+__global__ void bl_iota_kernel(int32_t* __restrict__ perm, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        perm[i] = (int32_t)i;
+}
+
+// inv[perm[i]] = i.
+__global__ void bl_invert_kernel(const int32_t* __restrict__ perm, int64_t n,
+                                 int32_t* __restrict__ inv) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        inv[perm[i]] = (int32_t)i;
+}
+
+dim3 grid_of(int64_t n) {
+    return dim3((unsigned)std::min<int64_t>(4096, std::max<int64_t>(1, (n + 255) / 256)));
+}
+
+// Device buffer that grows to at least twice its size, so that the levels of a
+// build, each a little larger than the one before, do not free and allocate in
+// turn (a free waits for the device).
 template <class T>
 struct DevVec {
     T* p = nullptr;
     size_t cap = 0;
     ~DevVec() { if (p) (void)hipFree(p); }
     T* get(size_t count) {
-        if (count > cap) {
+        if (count > cap || !p) {
+            const size_t want = std::max<size_t>(count, std::max<size_t>(2 * cap, 1));
             if (p) PMLSH_HIP(hipFree(p));
             p = nullptr;
             cap = 0;
-            PMLSH_HIP(hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T)));
-            cap = std::max<size_t>(count, 1);
+            PMLSH_HIP(hipMalloc(&p, want * sizeof(T)));
+            cap = want;
         }
         return p;
     }
@@ -774,7 +798,7 @@ private:
 }  // namespace
 
 void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
-                  std::vector<int32_t>* perm_out, std::vector<SplitNode>* nodes_out) {
+                  int32_t* perm, std::vector<SplitNode>* nodes_out) {
     if (n <= 0 || n > 0x7fffffffLL - kPiece) fail(PMLSH_EUNSUPPORTED, "point count out of range");
     std::vector<SplitNode>& nodes = *nodes_out;
     nodes.clear();
@@ -783,17 +807,12 @@ void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
     std::vector<int32_t> nb{0}, ne{(int32_t)n};        // their point ranges
     if (n > leaf) cur.push_back(0);
 
-    DevVec<int32_t> perm, perm_alt, d_idx;
+    DevVec<int32_t> perm_alt, d_idx;
     DevVec<double> key, key_alt, part, mean, cov, dir;
     DevVec<Piece> d_pieces;
     LevelSort sorter;
-    {
-        std::vector<int32_t> iota((size_t)n);
-        for (int64_t i = 0; i < n; ++i) iota[(size_t)i] = (int32_t)i;
-        PMLSH_HIP(hipMemcpyAsync(perm.get((size_t)n), iota.data(), (size_t)n * sizeof(int32_t),
-                                 hipMemcpyHostToDevice, st));
-        PMLSH_HIP(hipStreamSynchronize(st));
-    }
+    hipLaunchKernelGGL(bl_iota_kernel, grid_of(n), dim3(256), 0, st, perm, n);
+    PMLSH_HIP(hipGetLastError());
     key.get((size_t)n);
     key_alt.get((size_t)n);
     perm_alt.get((size_t)n);
@@ -832,23 +851,23 @@ void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
         double* dmean = mean.get((size_t)m * MP);
         double* dcov = cov.get((size_t)m * kCov);
         double* ddir = dir.get((size_t)m * MP);
-        hipLaunchKernelGGL(bl_sum_kernel, dim3((unsigned)np), dim3(256), 0, st, proj, perm.p, dp,
+        hipLaunchKernelGGL(bl_sum_kernel, dim3((unsigned)np), dim3(256), 0, st, proj, perm, dp,
                            dpart);
         hipLaunchKernelGGL(bl_reduce_kernel, dim3((unsigned)(((int64_t)m * MP + 255) / 256)),
                            dim3(256), 0, st, dpart, MP, dpb, m, dcnt, dmean);
-        hipLaunchKernelGGL(bl_cov_kernel, dim3((unsigned)np), dim3(256), 0, st, proj, perm.p, dp,
+        hipLaunchKernelGGL(bl_cov_kernel, dim3((unsigned)np), dim3(256), 0, st, proj, perm, dp,
                            dmean, dpart);
         hipLaunchKernelGGL(bl_reduce_kernel, dim3((unsigned)(((int64_t)m * kCov + 255) / 256)),
                            dim3(256), 0, st, dpart, kCov, dpb, m, nullptr, dcov);
         hipLaunchKernelGGL(bl_direction_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st,
                            dcov, m, ddir);
-        hipLaunchKernelGGL(bl_keys_kernel, dim3((unsigned)np), dim3(256), 0, st, proj, perm.p, dp,
+        hipLaunchKernelGGL(bl_keys_kernel, dim3((unsigned)np), dim3(256), 0, st, proj, perm, dp,
                            ddir, key.p);
         PMLSH_HIP(hipGetLastError());
 
-        sorter.run(key.p, perm.p, n, sb, se, m, key_alt.p, perm_alt.p, st);
+        sorter.run(key.p, perm, n, sb, se, m, key_alt.p, perm_alt.p, st);
         hipLaunchKernelGGL(bl_copy_kernel, dim3((unsigned)np), dim3(256), 0, st, dp, perm_alt.p,
-                           perm.p);
+                           perm);
         // the cuts, from the sorted keys
         int32_t* dmid = reinterpret_cast<int32_t*>(dcov);   // free after the directions
         hipLaunchKernelGGL(bl_cut_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, dsb,
@@ -879,8 +898,20 @@ void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
         }
         cur.swap(next);
     }
-    perm_out->resize((size_t)n);
-    PMLSH_HIP(hipMemcpyAsync(perm_out->data(), perm.p, (size_t)n * sizeof(int32_t),
+}
+
+void device_invert(const int32_t* perm, int64_t n, int32_t* inv, hipStream_t st) {
+    hipLaunchKernelGGL(bl_invert_kernel, grid_of(n), dim3(256), 0, st, perm, n, inv);
+    PMLSH_HIP(hipGetLastError());
+}
+
+void device_sorted(const double* x, int64_t n, hipStream_t st, std::vector<double>* out) {
+    LevelSort sorter;
+    DevVec<double> sorted;
+    const int32_t b = 0, e = (int32_t)n;
+    out->resize((size_t)n);
+    sorter.run(x, nullptr, n, &b, &e, 1, sorted.get((size_t)n), nullptr, st);
+    PMLSH_HIP(hipMemcpyAsync(out->data(), sorted.p, (size_t)n * sizeof(double),
                              hipMemcpyDeviceToHost, st));
     PMLSH_HIP(hipStreamSynchronize(st));
 }

@@ -173,7 +173,6 @@ struct HostTree {
     std::vector<int32_t> child_begin, child_end;
     std::vector<int32_t> npts;            // points in the subtree of each node
     std::vector<float> pivots;            // s x MP
-    std::vector<int32_t> perm;            // leaf position -> original id
     float coord_scale = 0.f;              // max ||o'|| + max ||p_i||
 };
 
@@ -186,9 +185,13 @@ struct SplitNode {
 
 // Recursive gap-aware splits of the leaf order on the device, level by level
 // (bulkload.hip): proj is the device projection (n x MP, original order);
-// returns the leaf order (leaf position -> id) and the split tree.
-void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
-                  std::vector<int32_t>* perm, std::vector<SplitNode>* nodes);
+// writes the leaf order (leaf position -> id) to the device array perm and
+// returns the split tree. device_invert: inv[perm[i]] = i. device_sorted: the
+// n doubles (no NaN) of a device array in ascending order, on the host.
+void device_split(const float* proj, int64_t n, int leaf, hipStream_t st, int32_t* perm,
+                  std::vector<SplitNode>* nodes);
+void device_invert(const int32_t* perm, int64_t n, int32_t* inv, hipStream_t st);
+void device_sorted(const double* x, int64_t n, hipStream_t st, std::vector<double>* out);
 
 // Device reductions of the bulk-load (bulkload.hip). device_all_finite:
 // whether count floats are all finite. device_pivots: s pivots by
@@ -207,11 +210,11 @@ void device_ball_summaries(const float* proj, const int32_t* perm, const std::ve
                            std::vector<double>* ring);
 
 // Bulk-loads the tree over the device projection proj (n x MP, original
-// order) from the leaf order (host perm, and its device copy perm_dev) and
-// the split tree of device_split.
+// order) from the leaf order (perm_dev, on the device) and the split tree of
+// device_split.
 void build_tree(const float* proj, int64_t n, int leaf_size, int fanout, int num_pivots,
-                std::vector<int32_t> perm, const int32_t* perm_dev,
-                const std::vector<SplitNode>& split, hipStream_t st, HostTree* out);
+                const int32_t* perm_dev, const std::vector<SplitNode>& split, hipStream_t st,
+                HostTree* out);
 
 // ---------------------------------------------------------------- index
 struct DeviceTree {
@@ -335,7 +338,10 @@ void launch_augment16(const float* proj, int64_t n, int64_t n_pad, float s, floa
                       uint16_t* out, hipStream_t stream);
 void launch_half_rows(const float* data, int64_t n, int d_pad, int d16, uint16_t* out,
                       float* scale, float* eps, hipStream_t stream);
-void launch_pair_dist_f64(const float* x, int d, int64_t ld, const int64_t* pairs,
+// FP64 Euclidean distances of the count sampled pairs of rows of x (n rows):
+// pair j is row i = sm(seed + j) mod n and row (i + 1 + sm(seed + count + j)
+// mod (n - 1)) mod n, sm the SplitMix64 output of a state.
+void launch_pair_dist_f64(const float* x, int64_t n, int d, int64_t ld, uint64_t seed,
                           int64_t count, double* out, hipStream_t stream);
 
 struct AnnLaunch {

@@ -334,15 +334,25 @@ __global__ __launch_bounds__(256) void half_rows_kernel(
     }
 }
 
-// FP64 Euclidean distance of row pairs (one wave per pair).
+__device__ __forceinline__ uint64_t splitmix64_dev(uint64_t x) {
+    uint64_t z = x + 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+
+// FP64 Euclidean distance of sampled row pairs (one wave per pair).
 __global__ __launch_bounds__(256) void pair_dist_f64_kernel(
-    const float* __restrict__ x, int d, int64_t ld,
-    const int64_t* __restrict__ pairs, int64_t count, double* __restrict__ out) {
+    const float* __restrict__ x, int64_t n, int d, int64_t ld, uint64_t seed, int64_t count,
+    double* __restrict__ out) {
     const int lane = threadIdx.x & 63;
     const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (p >= count) return;
-    const float* a = x + pairs[2 * p] * ld;
-    const float* b = x + pairs[2 * p + 1] * ld;
+    const uint64_t i = splitmix64_dev(seed + (uint64_t)p) % (uint64_t)n;
+    const uint64_t l =
+        (i + 1 + splitmix64_dev(seed + (uint64_t)(count + p)) % (uint64_t)(n - 1)) % (uint64_t)n;
+    const float* a = x + (int64_t)i * ld;
+    const float* b = x + (int64_t)l * ld;
     double s = 0.0;
     for (int c = lane; c < d; c += 64) {
         const double t = (double)a[c] - (double)b[c];
@@ -425,11 +435,11 @@ void launch_half_rows(const float* data, int64_t n, int d_pad, int d16, uint16_t
     PMLSH_HIP(hipGetLastError());
 }
 
-void launch_pair_dist_f64(const float* x, int d, int64_t ld, const int64_t* pairs,
+void launch_pair_dist_f64(const float* x, int64_t n, int d, int64_t ld, uint64_t seed,
                           int64_t count, double* out, hipStream_t stream) {
     if (count <= 0) return;
     hipLaunchKernelGGL(pair_dist_f64_kernel, dim3((unsigned)((count + 3) / 4)), dim3(256),
-                       0, stream, x, d, ld, pairs, count, out);
+                       0, stream, x, n, d, ld, seed, count, out);
     PMLSH_HIP(hipGetLastError());
 }
 

@@ -41,8 +41,8 @@ float round_down(double v) {
 }  // namespace
 
 void build_tree(const float* proj, int64_t n, int leaf_size, int fanout, int num_pivots,
-                std::vector<int32_t> perm_in, const int32_t* perm_dev,
-                const std::vector<SplitNode>& bt, hipStream_t st, HostTree* out) {
+                const int32_t* perm_dev, const std::vector<SplitNode>& bt, hipStream_t st,
+                HostTree* out) {
     HostTree& T = *out;
     const int s = num_pivots;
 
@@ -53,7 +53,6 @@ void build_tree(const float* proj, int64_t n, int leaf_size, int fanout, int num
 
     // ---- leaf order and binary split tree (leaf ranges) of the recursive
     // gap-aware splits; the inner levels are derived from the split tree
-    T.perm = std::move(perm_in);
     const int64_t n_leaves = (n + leaf_size - 1) / leaf_size;
 
     // Level l (of H) holds the maximal binary subtrees with at most
