@@ -919,7 +919,7 @@ static_assert(SG_DEPTH >= 2 && SG_X0 % 32 == 0, "at least two steps in flight; w
 
 template <bool X0L>
 __global__ __launch_bounds__(WG) void acp_seed_gram_kernel(
-    const float* __restrict__ data, int d_pad, const float* __restrict__ row_scale, int64_t n,
+    const float* __restrict__ data, int d_pad, const float2* __restrict__ row_se, int64_t n,
     int L, float gk, uint32_t* __restrict__ hi_out,
     uint32_t* __restrict__ lo_out, uint32_t* __restrict__ ghist) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
@@ -960,7 +960,7 @@ __global__ __launch_bounds__(WG) void acp_seed_gram_kernel(
     // steps padded to whole rounds of the ring: the extra steps stage zeros
     const int nsp = (nst + SG_DEPTH - 1) / SG_DEPTH * SG_DEPTH;
     // the power-of-two scale, in every wave: sc = 1 / (2 S)
-    float smax = row_scale[p0 + (lane < cnt ? lane : 0)];
+    float smax = row_se[p0 + (lane < cnt ? lane : 0)].x;
     // the first row into LDS (its loads before the ring's, 2 * 4 WG = 2,048
     // floats at most, zero past d_pad)
     float4 xa = make_float4(0.f, 0.f, 0.f, 0.f), xb = xa;
@@ -2188,11 +2188,11 @@ void run_acp(const pmlsh_index* x, int k, double c, double confidence, double be
             StageTimer tm(PMLSH_STAGE_ACP_SELFJOIN, st);
             if (x->d_pad <= SG_X0)
                 hipLaunchKernelGGL(acp_seed_gram_kernel<true>, dim3((unsigned)NL), dim3(WG), 0, st,
-                                   x->data, x->d_pad, x->data16_scale, n, L, gk,
+                                   x->data, x->d_pad, x->data16_se, n, L, gk,
                                    seeds.k0.as<uint32_t>(), slo.as<uint32_t>(), ghist.as<uint32_t>());
             else
                 hipLaunchKernelGGL(acp_seed_gram_kernel<false>, dim3((unsigned)NL), dim3(WG), 0, st,
-                                   x->data, x->d_pad, x->data16_scale, n, L, gk,
+                                   x->data, x->d_pad, x->data16_se, n, L, gk,
                                    seeds.k0.as<uint32_t>(), slo.as<uint32_t>(), ghist.as<uint32_t>());
             PMLSH_HIP(hipGetLastError());
         }

@@ -131,8 +131,7 @@ struct AnnArgs {
     // bounds, and per C member a lower bound of its squared distance (the
     // upper bound goes to ws_cdist; equal bounds mean the exact value)
     const uint16_t* data16;
-    const float* d16_scale;
-    const float* d16_eps;
+    const float2* d16_se;       // per row its scale and error bound
     int d16;
     float* ws_clo;
     // pd^2 bits of the pool entries (or null: long lists compute them again in
@@ -708,18 +707,25 @@ __device__ void verify16(const AnnArgs& a, const float* qs, const int32_t* cpos,
     constexpr int GROUPS = T / 16;
     const float u = 5.9604645e-08f;
     const float gam = 2.f * u * (float)(a.d16 / 16 + 8);
+    // the positions of a step are loaded one step ahead, and a row's scale and
+    // bound with the row, so a step waits for one memory round trip (with the
+    // positions and, at its end, the bounds loaded in it, for three)
+    if (v0 >= v1) return;
+    int nx[VR];
+#pragma unroll
+    for (int r = 0; r < VR; ++r) nx[r] = cpos[min(v0 + g + GROUPS * r, v1 - 1)];
     for (int base = v0; base < v1; base += GROUPS * VR) {
         const uint4* row[VR];
         bool ok[VR];
-        float acc[VR], sc[VR];
-        int pr[VR];
+        float acc[VR];
+        float2 se[VR];
 #pragma unroll
         for (int r = 0; r < VR; ++r) {
             const int i = base + g + GROUPS * r;
             ok[r] = i < v1;
-            pr[r] = cpos[ok[r] ? i : v0];
-            row[r] = reinterpret_cast<const uint4*>(a.data16 + (int64_t)pr[r] * a.d16);
-            sc[r] = a.d16_scale[pr[r]];
+            row[r] = reinterpret_cast<const uint4*>(a.data16 + (int64_t)nx[r] * a.d16);
+            se[r] = a.d16_se[nx[r]];
+            nx[r] = cpos[min(i + GROUPS * VR, v1 - 1)];
             acc[r] = 0.f;
         }
         // two 16-byte words of every row per lane and step, all loads issued
@@ -746,7 +752,7 @@ __device__ void verify16(const AnnArgs& a, const float* qs, const int32_t* cpos,
                     for (int e = 0; e < 8; ++e) {
                         const uint16_t bits = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
                         const float xv = (float)__builtin_bit_cast(_Float16, bits);
-                        const float t = __fmaf_rn(-sc[r], xv, y[e]);
+                        const float t = __fmaf_rn(-se[r].x, xv, y[e]);
                         acc[r] = __fmaf_rn(t, t, acc[r]);
                     }
                 }
@@ -760,7 +766,7 @@ __device__ void verify16(const AnnArgs& a, const float* qs, const int32_t* cpos,
             v += __shfl_xor(v, 2, 16);
             v += __shfl_xor(v, 1, 16);
             if (ok[r] && l16 == 0) {
-                const float eps = a.d16_eps[pr[r]];
+                const float eps = se[r].y;
                 const float dlo = sqrtf(v * (1.f - gam)) * (1.f - 4.f * u);
                 const float dhi = sqrtf(v * (1.f + 2.f * gam)) * (1.f + 4.f * u);
                 const float tlo = fmaxf((dlo - eps) * (1.f - 2.f * u), 0.f);
@@ -2094,10 +2100,7 @@ __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n
         below += i < n && v < blo;
         const bool inb = i < n && v >= blo && v <= bhi;
         const int slot = wave_append(inb, &sh.cnt2);
-        if (inb && slot < kBandCap) {
-            band[slot] = i;
-            bid[slot] = (uint32_t)sh.skey[i];
-        }
+        if (inb && slot < kBandCap) band[slot] = i;
     }
     below = block_sum<T>(below, sh);
     const int nb = sh.cnt2;
@@ -2111,6 +2114,7 @@ __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n
     }
     for (int j = threadIdx.x; j < nb; j += T) {
         const int64_t pos = sh.spos[band[j]];
+        bid[j] = (uint32_t)a.perm[pos];
         double acc = 0.0;
 #pragma unroll
         for (int t = 0; t < MP; ++t) {
@@ -2137,6 +2141,50 @@ __device__ bool cut_fp64(const AnnArgs& a, int64_t qi, const QueryCtx& qc, int n
         if (__uint_as_float((uint32_t)(sh.skey[i] >> 32)) > bhi) sh.skey[i] = ~0ull;
     __syncthreads();
     return true;
+}
+
+// L in LDS from a list of n <= CAP entries, B <= n: sh.skey holds the entries'
+// keys (pd^2 bits above, the entry's number below, or ~0 outside L), sh.spos
+// their positions. Ids are read only where they decide, in the FP64 band and
+// for equal FP32 values at the cut when the band is too long (reading all of
+// them costs a random 4-byte access per entry).
+template <int T>
+__device__ void lds_cut(const AnnArgs& a, int64_t qi, const QueryCtx& qc, const uint32_t* list,
+                        int n, int B, Smem& sh) {
+    // four entries per thread in flight: their list and projection loads are
+    // issued together
+    constexpr int PU = 4;
+    for (int i0 = threadIdx.x; i0 < n; i0 += PU * T) {
+        int32_t pos[PU];
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+            const int i = i0 + u * T;
+            pos[u] = (int32_t)list[i < n ? i : i0];
+        }
+        float pd2[PU];
+#pragma unroll
+        for (int u = 0; u < PU; ++u) pd2[u] = proj_dist2(a.proj + (int64_t)pos[u] * MP, qc.qp);
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+            const int i = i0 + u * T;
+            if (i < n) {
+                sh.skey[i] = ((uint64_t)__float_as_uint(pd2[u]) << 32) | (uint32_t)i;
+                sh.spos[i] = pos[u];
+            }
+        }
+    }
+    __syncthreads();
+    if (n == B) return;
+    uint64_t kth = lds_select<T>(n, B, sh);
+    if (cut_fp64<T>(a, qi, qc, n, B, kth, sh)) return;
+    // the FP32 order, ties by id
+    for (int i = threadIdx.x; i < n; i += T)
+        sh.skey[i] = (sh.skey[i] & 0xffffffff00000000ull) | (uint32_t)a.perm[sh.spos[i]];
+    __syncthreads();
+    kth = lds_select<T>(n, B, sh);
+    for (int i = threadIdx.x; i < n; i += T)
+        if (sh.skey[i] > kth) sh.skey[i] = ~0ull;
+    __syncthreads();
 }
 
 // The need-th smallest (from 1) of the values get(i) in [lo, hi], i < n, of
@@ -2309,41 +2357,7 @@ __global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
     int nl;
     __syncthreads();
     if (n <= CAP) {
-        // four entries per thread in flight: their list, projection and id
-        // loads are issued together
-        constexpr int PU = 4;
-        for (int i0 = threadIdx.x; i0 < n; i0 += PU * T) {
-            int32_t pos[PU];
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * T;
-                pos[u] = (int32_t)list[i < n ? i : i0];
-            }
-            float pd2[PU];
-            int32_t id[PU];
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                pd2[u] = proj_dist2(a.proj + (int64_t)pos[u] * MP, qc.qp);
-                id[u] = perm[pos[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * T;
-                if (i < n) {
-                    sh.skey[i] = ((uint64_t)__float_as_uint(pd2[u]) << 32) | (uint32_t)id[u];
-                    sh.spos[i] = pos[u];
-                }
-            }
-        }
-        __syncthreads();
-        if (n > B) {
-            const uint64_t kth = lds_select<T>(n, B, sh);
-            if (!cut_fp64<T>(a, qi, qc, n, B, kth, sh)) {
-                for (int i = threadIdx.x; i < n; i += T)
-                    if (sh.skey[i] > kth) sh.skey[i] = ~0ull;
-                __syncthreads();
-            }
-        }
+        lds_cut<T>(a, qi, qc, list, n, B, sh);
         nl = n;
     } else {
         auto list_src = [&](auto&& v) {
@@ -2504,41 +2518,7 @@ __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
         if (take && slot >= 0 && slot < B) cpos[slot] = pos;
     };
     if (n <= CAP) {
-        // keys and positions in LDS; four entries per thread in flight: their
-        // list, projection and id loads are issued together
-        constexpr int PU = 4;
-        for (int i0 = threadIdx.x; i0 < n; i0 += PU * T) {
-            int32_t pos[PU];
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * T;
-                pos[u] = (int32_t)list[i < n ? i : i0];
-            }
-            float pd2[PU];
-            int32_t id[PU];
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                pd2[u] = proj_dist2(a.proj + (int64_t)pos[u] * MP, qc.qp);
-                id[u] = a.perm[pos[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * T;
-                if (i < n) {
-                    sh.skey[i] = ((uint64_t)__float_as_uint(pd2[u]) << 32) | (uint32_t)id[u];
-                    sh.spos[i] = pos[u];
-                }
-            }
-        }
-        __syncthreads();
-        if (n > B) {
-            const uint64_t kth = lds_select<T>(n, B, sh);
-            if (!cut_fp64<T>(a, qi, qc, n, B, kth, sh)) {
-                for (int i = threadIdx.x; i < n; i += T)
-                    if (sh.skey[i] > kth) sh.skey[i] = ~0ull;
-                __syncthreads();
-            }
-        }
+        lds_cut<T>(a, qi, qc, list, n, B, sh);
         if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
         __syncthreads();
         for (int b0 = 0; b0 < n; b0 += T) {
@@ -2929,8 +2909,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
     a.chunk_cen = x.chunk_cen;
     a.chunk_rad = x.chunk_rad;
     a.data16 = x.data16;
-    a.d16_scale = x.data16_scale;
-    a.d16_eps = x.data16_eps;
+    a.d16_se = x.data16_se;
     a.d16 = x.d16;
     const int lds = ann_lds_bytes(x.d16);
     PMLSH_HIP(hipFuncSetAttribute((const void*)ann_kernel,

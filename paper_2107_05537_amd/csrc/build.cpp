@@ -39,7 +39,7 @@ struct TmpBuf {
 void index_release(pmlsh_index* x) {
     if (!x) return;
     void* bufs[] = {x->data, x->proj_hi, x->proj_lo, x->proj16, x->chunk_cen, x->chunk_rad,
-                    x->data16, x->data16_scale, x->data16_eps, x->perm, x->inv_perm, x->hash,
+                    x->data16, x->data16_se, x->perm, x->inv_perm, x->hash,
                     x->tree.centre, x->tree.radius, x->tree.hr_min, x->tree.hr_max,
                     x->tree.child_begin, x->tree.child_end, x->tree.npts,
                     x->tree.pivots};
@@ -170,9 +170,8 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
     // FP16 copy for the bounded verification
     x->d16 = (x->d + 7) / 8 * 8;
     x->data16 = dev_alloc<uint16_t>(x, n * x->d16);
-    x->data16_scale = dev_alloc<float>(x, n);
-    x->data16_eps = dev_alloc<float>(x, n);
-    launch_half_rows(x->data, n, x->d_pad, x->d16, x->data16, x->data16_scale, x->data16_eps, st);
+    x->data16_se = dev_alloc<float2>(x, n);
+    launch_half_rows(x->data, n, x->d_pad, x->d16, x->data16, x->data16_se, st);
 
     // ---- chunk balls, then the FP16 rows of the matrix-core scan
     {

@@ -246,8 +246,7 @@ struct pmlsh_index {
     float* chunk_cen = nullptr;  // n_pad16 / 64 x MP: centre of each 64-point chunk
     float* chunk_rad = nullptr;  // n_pad16 / 64: radius covering the chunk's points
     uint16_t* data16 = nullptr;  // n x d16 FP16 copy of D_leaf, rows scaled by a power of two
-    float* data16_scale = nullptr;  // n: that power of two
-    float* data16_eps = nullptr;    // n: bound on |row - scale * FP16 row|
+    float2* data16_se = nullptr;    // n: that power of two, and a bound on |row - scale * FP16 row|
     int d16 = 0;                    // d rounded up to a multiple of 8
     int32_t* perm = nullptr;     // leaf position -> id
     int32_t* inv_perm = nullptr; // id -> leaf position
@@ -337,7 +336,7 @@ void launch_project_lp(const float* x, int64_t rows, int d, int64_t ld, const fl
 void launch_augment16(const float* proj, int64_t n, int64_t n_pad, float s, float cm, const float* centre,
                       uint16_t* out, hipStream_t stream);
 void launch_half_rows(const float* data, int64_t n, int d_pad, int d16, uint16_t* out,
-                      float* scale, float* eps, hipStream_t stream);
+                      float2* scale_eps, hipStream_t stream);
 // FP64 Euclidean distances of the count sampled pairs of rows of x (n rows):
 // pair j is row i = sm(seed + j) mod n and row (i + 1 + sm(seed + count + j)
 // mod (n - 1)) mod n, sm the SplitMix64 output of a state.

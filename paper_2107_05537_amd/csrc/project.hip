@@ -306,7 +306,7 @@ __global__ __launch_bounds__(256) void augment16_kernel(
 // query to the FP16 row then lies within eps of the distance to x.
 __global__ __launch_bounds__(256) void half_rows_kernel(
     const float* __restrict__ data, int64_t n, int d_pad, int d16,
-    uint16_t* __restrict__ out, float* __restrict__ scale, float* __restrict__ eps) {
+    uint16_t* __restrict__ out, float2* __restrict__ scale_eps) {
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= n) return;
@@ -328,9 +328,8 @@ __global__ __launch_bounds__(256) void half_rows_kernel(
     }
     for (int off = 32; off > 0; off >>= 1) err += __shfl_xor(err, off);
     if (lane == 0) {
-        scale[row] = s;
         const float ef = (float)sqrt(err);
-        eps[row] = nextafterf(ef * (1.f + 9.5367431640625e-07f), INFINITY);
+        scale_eps[row] = make_float2(s, nextafterf(ef * (1.f + 9.5367431640625e-07f), INFINITY));
     }
 }
 
@@ -428,10 +427,10 @@ void launch_augment16(const float* proj, int64_t n, int64_t n_pad, float s, floa
 }
 
 void launch_half_rows(const float* data, int64_t n, int d_pad, int d16, uint16_t* out,
-                      float* scale, float* eps, hipStream_t stream) {
+                      float2* scale_eps, hipStream_t stream) {
     if (n <= 0) return;
     hipLaunchKernelGGL(half_rows_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream,
-                       data, n, d_pad, d16, out, scale, eps);
+                       data, n, d_pad, d16, out, scale_eps);
     PMLSH_HIP(hipGetLastError());
 }
 
