@@ -1794,8 +1794,8 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
 // a processor that compares one pair at a time, while the matrix cores
 // compare all pairs of a batch at 16 x 16 x 32 per instruction.
 //
-// Grid: x strides over 64-point chunks, y over blocks of 1,024 queries; wave
-// w of a workgroup owns a quarter of the block's mask words (256 queries).
+// Grid: x strides over 64-point chunks, y over blocks of 512 or 1,024 queries;
+// each wave of a workgroup owns up to two of the block's mask words (128 queries).
 // For each chunk a wave packs the queries whose chunk-ball test passed (the
 // set bits of its mask words) into a list and runs the MFMA on groups of 16
 // listed queries, so a group's 16 columns are all queries that may hold
@@ -1808,52 +1808,42 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
 // result register r of lane l holds point 4 (l / 16) + r of the tile and
 // listed query l % 16.
 
-// Two block shapes of the scan: 512 queries per workgroup (128 per wave,
-// three workgroups per compute unit) for indexes of fewer than
-// kScanLargeChunks chunks, 1,024 (256 per wave, two per compute unit) above:
+// Two block shapes of the scan, 128 queries per wave in both: 512 queries in
+// four waves (four workgroups per compute unit) for indexes of fewer than
+// kScanLargeChunks chunks, 1,024 in eight waves (two per compute unit) above:
 // staging a block's query rows is a fixed cost per workgroup, paid back only
-// when a workgroup has many chunks to scan, and a wave's list of passing
-// queries then fills more of each 16-query group.
-#ifndef PMLSH_SCAN_QB
-#define PMLSH_SCAN_QB 512
-#endif
-#ifndef PMLSH_SCAN_QB_LARGE
-#define PMLSH_SCAN_QB_LARGE 1024
-#endif
-#ifndef PMLSH_SCAN_STAGE
-#define PMLSH_SCAN_STAGE 1024
-#endif
-#ifndef PMLSH_SCAN_WAVES_PER_EU
-#define PMLSH_SCAN_WAVES_PER_EU 3
-#endif
-#ifndef PMLSH_SCAN_WAVES_PER_EU_LARGE
-#define PMLSH_SCAN_WAVES_PER_EU_LARGE 2
-#endif
+// when a workgroup has many chunks to scan. Four waves per SIMD in either
+// (128 VGPRs, two chunk slots in flight): the loop's query lists, matrix products
+// and ballots wait on one another, and more waves hide more of that than deeper
+// slots did. 1M x 256, 1,024 queries, us, three waves with four slots / four
+// with three / four with two / four with one: B = 885 54 / 70 / 48 / 52;
+// B = 4,810 139 / 145 / 127 / 132; 1M x 960 without contrast 284 / 239 / 226 / 230.
+struct ScanSmall { static constexpr int QB = 512, QW = 128, NW = 4, WGS = 4, STG = 512; };
+struct ScanLarge { static constexpr int QB = 1024, QW = 256, NW = 16, WGS = 1, STG = 512; };
 constexpr int64_t kScanLargeChunks = 32768;   // 2,097,152 points
-constexpr int SSTG = PMLSH_SCAN_STAGE;        // candidates staged per wave
 
 // Query rows, then per-wave candidate stages: every wave packs, stages,
 // counts and flushes its own candidates, so after the rows are loaded the
-// scan needs no workgroup barrier. QB queries per block.
-template <int QB>
+// scan needs no workgroup barrier. QB queries per block and NW waves of QW
+// queries each, STG candidates staged per wave.
+template <class S>
 struct __align__(16) ScanShared {
-    uint16_t qrow[QB + 1][kScanRow];    // FP16 query rows of the block, padding row last
-    uint32_t pos[NWAVE][SSTG];          // staged candidates: leaf position
-    uint8_t qid[NWAVE][SSTG];           // and query within the wave's range
-    uint32_t hits[NWAVE][QB / NWAVE], base[NWAVE][QB / NWAVE];
+    uint16_t qrow[S::QB + 1][kScanRow];   // FP16 query rows of the block, padding row last
+    uint32_t pos[S::NW][S::STG];          // staged candidates: leaf position
+    uint8_t qid[S::NW][S::STG];           // and query within the wave's range
+    uint32_t hits[S::NW][S::QW], base[S::NW][S::QW];
     // queries of the wave passing the chunk, by column: slot 16 g + j of the
     // list is lcol[j][g]
-    uint8_t lcol[NWAVE][16][QB / NWAVE / 16];
+    uint8_t lcol[S::NW][16][S::QW / 16];
 };
-template <int QB, int WPE>
+template <class S>
 constexpr bool scan_shape_ok() {
-    return (QB / NWAVE) % 64 == 0 && QB / NWAVE / 64 <= 4 && QB / NWAVE <= 256 &&
-           sizeof(ScanShared<QB>) * WPE <= 160 * 1024;
+    return S::QW % 64 == 0 && S::QW <= 256 && S::QB % S::QW == 0 && S::NW % (S::QB / S::QW) == 0 &&
+           sizeof(ScanShared<S>) * S::WGS <= 160 * 1024;
 }
-static_assert(scan_shape_ok<PMLSH_SCAN_QB, PMLSH_SCAN_WAVES_PER_EU>() &&
-                  scan_shape_ok<PMLSH_SCAN_QB_LARGE, PMLSH_SCAN_WAVES_PER_EU_LARGE>(),
-              "a wave's queries are whole mask words (ids below 256), and the scan "
-              "workgroups of a compute unit fit its LDS");
+static_assert(scan_shape_ok<ScanSmall>() && scan_shape_ok<ScanLarge>(),
+              "a wave's queries are whole mask words (ids below 256), every query has the same "
+              "number of waves, and the scan workgroups of a compute unit fit its LDS");
 
 __device__ __forceinline__ half8_t load_half8(const uint16_t* p) {
     return __builtin_bit_cast(half8_t, *reinterpret_cast<const uint4*>(p));
@@ -1868,8 +1858,8 @@ __device__ __forceinline__ void scan_mfma(const half8_t (&av)[4], half8_t b, flo
 // Writes the wave's staged candidates to the pool with one reservation per
 // query (queries qw0 .. qw0 + nqw - 1 of the batch) and empties the stage.
 // Only this wave touches its part of the shared memory.
-template <int QB>
-__device__ __forceinline__ void scan_flush(const AnnArgs& a, ScanShared<QB>& ss, int wave, int lane,
+template <class S>
+__device__ __forceinline__ void scan_flush(const AnnArgs& a, ScanShared<S>& ss, int wave, int lane,
                                            uint32_t& wn, int64_t qw0, int nqw) {
     uint32_t* hits = ss.hits[wave];
     uint32_t* base = ss.base[wave];
@@ -1897,8 +1887,8 @@ __device__ __forceinline__ void scan_flush(const AnnArgs& a, ScanShared<QB>& ss,
 // a ballot's candidates would not fit, so no candidate is lost. The group is
 // skipped when no result is negative; otherwise register r of the four tiles
 // is tested together first, since most register positions hold no candidate.
-template <int QB>
-__device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<QB>& ss, int wave, int lane,
+template <class S>
+__device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<S>& ss, int wave, int lane,
                                           uint32_t& wn, const float4_t (&cc)[4], int64_t p0, int q,
                                           int64_t qw0, int nqw) {
     // a result is a candidate when its sign bit is set
@@ -1920,7 +1910,7 @@ __device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<QB>& ss, 
             const uint32_t nh = (uint32_t)__popcll(m);
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            if (wn + nh > (uint32_t)SSTG) scan_flush(a, ss, wave, lane, wn, qw0, nqw);
+            if (wn + nh > (uint32_t)S::STG) scan_flush(a, ss, wave, lane, wn, qw0, nqw);
             if (c) {
                 ss.pos[wave][wn + rank] = prow + (uint32_t)(mt * 16 + r);
                 ss.qid[wave][wn + rank] = (uint8_t)q;
@@ -1930,13 +1920,16 @@ __device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<QB>& ss, 
     }
 }
 
-template <int QB, int WPE>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE))) void scan_kernel(AnnArgs a) {
-    constexpr int SQB = QB;           // queries per scan block
-    constexpr int SQW = SQB / NWAVE;  // queries per wave
+template <class S>
+__global__ __launch_bounds__(64 * S::NW)
+    __attribute__((amdgpu_waves_per_eu(S::NW * S::WGS / 4))) void scan_kernel(AnnArgs a) {
+    constexpr int SQB = S::QB;        // queries per scan block
+    constexpr int SQW = S::QW;        // queries per wave
+    constexpr int NQ = SQB / SQW;     // waves that cover the block's queries
+    constexpr int NC = S::NW / NQ;    // chunks in work at once
     constexpr int QPL = SQW / 64;     // queries per lane in the list building
     constexpr int SPAD = SQB;         // index of the padding row
-    __shared__ ScanShared<QB> ss;
+    __shared__ ScanShared<S> ss;
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lq = lane >> 4;
@@ -1944,14 +1937,14 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     const int nqb = min(SQB, a.nq - q0);
     const int nwq = (nqb + 63) >> 6;            // mask words of this query block
     // mask words per wave: the block's words split evenly, whole words each
-    const int wpw = (nwq + NWAVE - 1) / NWAVE;
-    const int w0 = wave * wpw;                  // first word of this wave
+    const int wpw = (nwq + NQ - 1) / NQ;
+    const int w0 = wave % NQ * wpw;             // first word of this wave
     const int nw = max(0, min(nwq - w0, wpw));
     const int64_t qw0 = (int64_t)q0 + w0 * 64;  // first query of this wave
     const int nqw = max(0, min(nqb - w0 * 64, nw * 64));   // its queries
 
     // the block's query rows (halves 0..23; 16 bytes per thread and step)
-    for (int e = threadIdx.x; e < (SQB + 1) * 3; e += WG) {
+    for (int e = threadIdx.x; e < (SQB + 1) * 3; e += 64 * S::NW) {
         const int r = e / 3, part = e - 3 * r;
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
         if (r < nqb) {
@@ -1965,11 +1958,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     __syncthreads();
 
     uint32_t wn = 0;
-    // Point chunks, strided over the workgroups. Four slots of FP16 rows and
-    // mask words are in flight per wave (12 KB of rows); the loop is unrolled
+    // Point chunks, strided over the workgroups. Two slots of FP16 rows and
+    // mask words are in flight per wave (6 KB of rows); the loop is unrolled
     // over the slots so that each is refilled in place after its chunk.
     const int64_t nchunk = a.n_pad16 >> 6;
-    const int64_t G = gridDim.x;
+    const int64_t G = (int64_t)gridDim.x * NC;
     const int l16 = lane & 15;
     // lane i packs the QPL queries QPL i .. QPL i + QPL - 1 of the wave's
     // range, held in mask word i / (64 / QPL) (those lanes load it together)
@@ -2026,7 +2019,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         // room for a chunk's typical candidates (a fuller chunk flushes
         // inside the emit)
-        if (wn > (uint32_t)(SSTG - 256)) scan_flush(a, ss, wave, lane, wn, qw0, nqw);
+        if (wn > (uint32_t)(S::STG - 256)) scan_flush(a, ss, wave, lane, wn, qw0, nqw);
         const uint8_t* mycol = lcol[l16];
         // two groups per step: their row reads and matrix products go out
         // before either result is examined
@@ -2046,24 +2039,16 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE))) void 
             if (two) scan_emit(a, ss, wave, lane, wn, cb, cc << 6, qb, qw0, nqw);
         }
     };
-    int64_t c = blockIdx.x;
-    Slot s0, s1, s2, s3;
-    load(c, s0);
-    load(c + G, s1);
-    load(c + 2 * G, s2);
-    load(c + 3 * G, s3);
-    for (; c < nchunk; c += 4 * G) {
-        chunk(s0, c);
-        load(c + 4 * G, s0);
-        if (c + G >= nchunk) break;
-        chunk(s1, c + G);
-        load(c + 5 * G, s1);
-        if (c + 2 * G >= nchunk) break;
-        chunk(s2, c + 2 * G);
-        load(c + 6 * G, s2);
-        if (c + 3 * G >= nchunk) break;
-        chunk(s3, c + 3 * G);
-        load(c + 7 * G, s3);
+    int64_t c = (int64_t)blockIdx.x * NC + wave / NQ;
+    Slot s0, s1;
+    load(c + 0 * G, s0);
+    load(c + 1 * G, s1);
+    for (; c < nchunk; c += 2 * G) {
+        chunk(s0, c + 0 * G);
+        load(c + 2 * G, s0);
+        if (c + 1 * G >= nchunk) break;
+        chunk(s1, c + 1 * G);
+        load(c + 3 * G, s1);
     }
     scan_flush(a, ss, wave, lane, wn, qw0, nqw);
 }
@@ -2965,15 +2950,14 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         // block shape that suits the index's size
         const int64_t shape = tune_get(PMLSH_TUNE_SCAN_SHAPE);
         const bool large = shape == 0 ? nchunk >= kScanLargeChunks : shape == 2;
-        const void* scan_fn =
-            large ? (const void*)scan_kernel<PMLSH_SCAN_QB_LARGE, PMLSH_SCAN_WAVES_PER_EU_LARGE>
-                  : (const void*)scan_kernel<PMLSH_SCAN_QB, PMLSH_SCAN_WAVES_PER_EU>;
-        const int sqb = large ? PMLSH_SCAN_QB_LARGE : PMLSH_SCAN_QB;
+        auto* scan_fn = large ? scan_kernel<ScanLarge> : scan_kernel<ScanSmall>;
+        const int sqb = large ? ScanLarge::QB : ScanSmall::QB;
+        const int swg = 64 * (large ? ScanLarge::NW : ScanSmall::NW);
         static thread_local int scan_slots[64][2] = {};
         int& slots = scan_slots[x.device & 63][large ? 1 : 0];
         if (slots == 0) {
             int per_cu = 0, cus = 0;
-            PMLSH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_fn, WG, 0));
+            PMLSH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)scan_fn, swg, 0));
             PMLSH_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, x.device));
             slots = per_cu > 0 && cus > 0 ? per_cu * cus : (int)kScanBlocks;
         }
@@ -2983,12 +2967,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         dim3 sgrid((unsigned)gx, (unsigned)ny);
         {
             StageTimer tm(PMLSH_STAGE_FILTER, stream);
-            if (large)
-                hipLaunchKernelGGL((scan_kernel<PMLSH_SCAN_QB_LARGE, PMLSH_SCAN_WAVES_PER_EU_LARGE>),
-                                   sgrid, dim3(WG), 0, stream, a);
-            else
-                hipLaunchKernelGGL((scan_kernel<PMLSH_SCAN_QB, PMLSH_SCAN_WAVES_PER_EU>), sgrid,
-                                   dim3(WG), 0, stream, a);
+            hipLaunchKernelGGL(scan_fn, sgrid, dim3((unsigned)swg), 0, stream, a);
             PMLSH_HIP(hipGetLastError());
         }
         StageTimer tm(PMLSH_STAGE_FINISH, stream);
