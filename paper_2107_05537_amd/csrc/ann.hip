@@ -97,7 +97,8 @@ struct AnnArgs {
     // per-query kernel answers), candidate count, scanned points, candidate list
     int32_t* q_flag;
     uint32_t* pq_list;          // count, then the queries flagged for the per-query kernel
-    uint32_t* l_count;          // candidates per query
+    uint32_t* l_count;          // candidates per query: entry q * l_stride
+    int64_t l_stride;
     uint32_t* q_scanned;
     uint32_t* l_list;           // nq x q_cap leaf positions (candidate pool)
     int q_cap;
@@ -1636,7 +1637,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     }
 
     if (threadIdx.x == 0) {
-        a.l_count[qi] = 0u;
+        a.l_count[qi * a.l_stride] = 0u;
         a.q_scanned[qi] = 0u;   // mask_kernel adds 64 per passing chunk
         a.q_flag[qi] = 0;
         if (qi == 0) a.pq_list[0] = 0u;   // the flagged list of the batch starts empty
@@ -1771,7 +1772,7 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
         for (int o = 0; o < MQB / 8; ++o) wd |= (uint64_t)lb[o][i] << (8 * o);
         if (c < nch) a.cmask[cmask_at(a, c, blockIdx.y)] = wd;
     }
-    if ((int)threadIdx.x < nqb && cnt[threadIdx.x])
+    if (a.out_stats && (int)threadIdx.x < nqb && cnt[threadIdx.x])
         atomicAdd(&a.q_scanned[q0 + threadIdx.x], 64u * cnt[threadIdx.x]);
 }
 
@@ -1838,7 +1839,8 @@ struct __align__(16) ScanShared {
 };
 template <class S>
 constexpr bool scan_shape_ok() {
-    return S::QW % 64 == 0 && S::QW <= 256 && S::QB % S::QW == 0 && S::NW % (S::QB / S::QW) == 0 &&
+    return S::QW % 64 == 0 && S::QW <= 256 && S::QB % S::QW == 0 &&
+           (S::QB / S::QW & (S::QB / S::QW - 1)) == 0 && S::NW % (S::QB / S::QW) == 0 &&
            sizeof(ScanShared<S>) * S::WGS <= 160 * 1024;
 }
 static_assert(scan_shape_ok<ScanSmall>() && scan_shape_ok<ScanLarge>(),
@@ -1867,7 +1869,7 @@ __device__ __forceinline__ void scan_flush(const AnnArgs& a, ScanShared<S>& ss, 
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     for (int e = lane; e < nqw; e += 64) {
         const uint32_t h = hits[e];
-        if (h) base[e] = atomicAdd(&a.l_count[qw0 + e], h);
+        if (h) base[e] = atomicAdd(&a.l_count[(qw0 + e) * a.l_stride], h);
         hits[e] = 0u;
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1891,32 +1893,28 @@ template <class S>
 __device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<S>& ss, int wave, int lane,
                                           uint32_t& wn, const float4_t (&cc)[4], int64_t p0, int q,
                                           int64_t qw0, int nqw) {
-    // a result is a candidate when its sign bit is set
-    uint32_t z[4];
+    // a result is a candidate when its sign bit is set: bit 4 t + r of the
+    // lane's mask is register r of tile t
+    uint32_t mk = 0u;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        z[r] = __float_as_uint(cc[0][r]) | __float_as_uint(cc[1][r]) | __float_as_uint(cc[2][r]) |
-               __float_as_uint(cc[3][r]);
-    if (!__builtin_amdgcn_ballot_w64((int32_t)(z[0] | z[1] | z[2] | z[3]) < 0)) return;
+    for (int b = 15; b >= 0; --b)
+        mk = __builtin_amdgcn_alignbit(mk, __float_as_uint(cc[b >> 2][b & 3]), 31);
     const uint32_t prow = (uint32_t)p0 + 4u * (uint32_t)(lane >> 4);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        if (!__builtin_amdgcn_ballot_w64((int32_t)z[r] < 0)) continue;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const bool c = __float_as_int(cc[mt][r]) < 0;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(c);
-            if (!m) continue;
-            const uint32_t nh = (uint32_t)__popcll(m);
-            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
-                (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            if (wn + nh > (uint32_t)S::STG) scan_flush(a, ss, wave, lane, wn, qw0, nqw);
-            if (c) {
-                ss.pos[wave][wn + rank] = prow + (uint32_t)(mt * 16 + r);
-                ss.qid[wave][wn + rank] = (uint8_t)q;
-            }
-            wn += nh;
+    // one candidate of every lane that has any left per step
+    for (;;) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(mk != 0u);
+        if (!m) return;
+        const uint32_t nh = (uint32_t)__popcll(m);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (wn + nh > (uint32_t)S::STG) scan_flush(a, ss, wave, lane, wn, qw0, nqw);
+        if (mk) {
+            const uint32_t b = (uint32_t)__builtin_ctz(mk);
+            ss.pos[wave][wn + rank] = prow + ((b >> 2) << 4) + (b & 3u);
+            ss.qid[wave][wn + rank] = (uint8_t)q;
+            mk &= mk - 1u;
         }
+        wn += nh;
     }
 }
 
@@ -1926,7 +1924,6 @@ __global__ __launch_bounds__(64 * S::NW)
     constexpr int SQB = S::QB;        // queries per scan block
     constexpr int SQW = S::QW;        // queries per wave
     constexpr int NQ = SQB / SQW;     // waves that cover the block's queries
-    constexpr int NC = S::NW / NQ;    // chunks in work at once
     constexpr int QPL = SQW / 64;     // queries per lane in the list building
     constexpr int SPAD = SQB;         // index of the padding row
     __shared__ ScanShared<S> ss;
@@ -1936,9 +1933,12 @@ __global__ __launch_bounds__(64 * S::NW)
     const int q0 = blockIdx.y * SQB;
     const int nqb = min(SQB, a.nq - q0);
     const int nwq = (nqb + 63) >> 6;            // mask words of this query block
-    // mask words per wave: the block's words split evenly, whole words each
-    const int wpw = (nwq + NQ - 1) / NQ;
-    const int w0 = wave % NQ * wpw;             // first word of this wave
+    // the waves that share the block's words (fewer when there are fewer words),
+    // whole words each, and the chunks in work at once
+    const int nqg = nwq >= NQ ? NQ : nwq <= 1 ? 1 : 1 << (32 - __builtin_clz(nwq - 1));
+    const int nc = S::NW / nqg;
+    const int wpw = (nwq + nqg - 1) / nqg;
+    const int w0 = wave % nqg * wpw;            // first word of this wave
     const int nw = max(0, min(nwq - w0, wpw));
     const int64_t qw0 = (int64_t)q0 + w0 * 64;  // first query of this wave
     const int nqw = max(0, min(nqb - w0 * 64, nw * 64));   // its queries
@@ -1958,42 +1958,37 @@ __global__ __launch_bounds__(64 * S::NW)
     __syncthreads();
 
     uint32_t wn = 0;
-    // Point chunks, strided over the workgroups. Two slots of FP16 rows and
-    // mask words are in flight per wave (6 KB of rows); the loop is unrolled
-    // over the slots so that each is refilled in place after its chunk.
+    // Point chunks, strided over the waves of a query range. Most chunks hold
+    // points near none of a wave's queries (1M x 256, B = 885: 69 % of the
+    // pairs of a chunk and 128 queries; 10M x 128: 75 % with 256), so a wave
+    // loads the mask words of 64 of its chunks at once, one chunk per lane, and
+    // visits the non-empty ones only. The rows of the next one are in flight
+    // while one is in work.
     const int64_t nchunk = a.n_pad16 >> 6;
-    const int64_t G = (int64_t)gridDim.x * NC;
+    const int64_t G = (int64_t)gridDim.x * nc;
     const int l16 = lane & 15;
     // lane i packs the QPL queries QPL i .. QPL i + QPL - 1 of the wave's
-    // range, held in mask word i / (64 / QPL) (those lanes load it together)
+    // range, held in mask word i / (64 / QPL)
     const int pk_word = lane / (64 / QPL), pk_shift = QPL * (lane % (64 / QPL));
-    const bool mword = pk_word < nw;
-    // Every slot load is unconditional, so that the compiler waits for the
-    // slot in use only (a load under a branch makes it wait for every slot in
-    // flight): a chunk past the end reads the last chunk (such a slot is never
-    // used), a lane without a mask word reads the block's first word, and
-    // lanes 48..63, whose halves 24..31 of the A operand are zero, read halves
-    // 16..23. What is not the chunk's is cleared where the slot is used.
-    const int64_t mband = (q0 >> 6) + (mword ? w0 + pk_word : 0);
+    // Every row load is unconditional (a load under a branch makes the compiler
+    // wait for every load in flight): lanes 48..63, whose halves 24..31 of the A
+    // operand are zero, read halves 16..23, cleared where the rows are used.
     const uint16_t* rbase = a.proj16 + (l16 * kScanRow + (lq < 3 ? lq : 2) * 8);
     const uint32_t rkeep = lq < 3 ? 0xffffffffu : 0u;
 
     struct Slot {
         half8_t r[4];
-        uint64_t m;
     };
     auto load = [&](int64_t cc, Slot& dst) {
-        const int64_t ccl = cc < nchunk ? cc : nchunk - 1;
-        dst.m = a.cmask[cmask_at(a, ccl, mband)];
-        const uint16_t* rp = rbase + ccl * (64 * kScanRow);
+        const uint16_t* rp = rbase + cc * (64 * kScanRow);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) dst.r[mt] = load_half8(rp + mt * 16 * kScanRow);
     };
     uint8_t (*lcol)[SQW / 16] = ss.lcol[wave];
-    auto chunk = [&](const Slot& cur, int64_t cc) {
+    // cm: the mask word that holds the lane's queries
+    auto chunk = [&](const Slot& cur, uint64_t cm, int64_t cc) {
         // the list of passing queries: each lane's set bits at the count of
         // set bits in the lanes below it
-        const uint64_t cm = mword ? cur.m : 0ull;
         const uint32_t pk = (uint32_t)(cm >> pk_shift) & ((1u << QPL) - 1u);
         int total = 0;
         uint32_t at = 0;
@@ -2004,7 +1999,6 @@ __global__ __launch_bounds__(64 * S::NW)
             at += __builtin_amdgcn_mbcnt_hi((uint32_t)(bb >> 32),
                                             __builtin_amdgcn_mbcnt_lo((uint32_t)bb, 0u));
         }
-        if (total == 0) return;
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         half8_t av[4];
 #pragma unroll
@@ -2039,16 +2033,45 @@ __global__ __launch_bounds__(64 * S::NW)
             if (two) scan_emit(a, ss, wave, lane, wn, cb, cc << 6, qb, qw0, nqw);
         }
     };
-    int64_t c = (int64_t)blockIdx.x * NC + wave / NQ;
-    Slot s0, s1;
-    load(c + 0 * G, s0);
-    load(c + 1 * G, s1);
-    for (; c < nchunk; c += 2 * G) {
-        chunk(s0, c + 0 * G);
-        load(c + 2 * G, s0);
-        if (c + 1 * G >= nchunk) break;
-        chunk(s1, c + 1 * G);
-        load(c + 3 * G, s1);
+    const int64_t mband = (q0 >> 6) + (nw > 0 ? w0 : 0);
+    for (int64_t cb = (int64_t)blockIdx.x * nc + wave / nqg; cb < nchunk; cb += 64 * G) {
+        const int64_t mine = cb + lane * G;
+        uint64_t m[QPL];
+        uint64_t any = 0ull;
+#pragma unroll
+        for (int k = 0; k < QPL; ++k) {
+            const uint64_t v = a.cmask[cmask_at(a, mine < nchunk ? mine : cb, mband + (k < nw ? k : 0))];
+            m[k] = mine < nchunk && k < nw ? v : 0ull;
+            any |= m[k];
+        }
+        uint64_t nz = __builtin_amdgcn_ballot_w64(any != 0ull);
+        if (!nz) continue;
+        // the lane's mask word of the chunk that lane b loaded
+        auto word_of = [&](int b) {
+            uint64_t cm = 0ull;
+#pragma unroll
+            for (int k = 0; k < QPL; ++k) {
+                const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)m[k], b);
+                const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(m[k] >> 32), b);
+                if (pk_word == k) cm = ((uint64_t)hi << 32) | lo;
+            }
+            return cm;
+        };
+        int b = __builtin_ctzll(nz);
+        Slot s0, s1;
+        load(cb + b * G, s0);
+        for (;;) {
+            nz &= nz - 1;
+            const int b1 = nz ? __builtin_ctzll(nz) : b;
+            load(cb + b1 * G, s1);
+            chunk(s0, word_of(b), cb + b * G);
+            if (!nz) break;
+            nz &= nz - 1;
+            b = nz ? __builtin_ctzll(nz) : b1;
+            load(cb + b * G, s0);
+            chunk(s1, word_of(b1), cb + b1 * G);
+            if (!nz) break;
+        }
     }
     scan_flush(a, ss, wave, lane, wn, qw0, nqw);
 }
@@ -2318,7 +2341,7 @@ __global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
     const AnnQueryParams qpar = query_params(a, qi);
     const int B = qpar.budget;
     const int k = qpar.k;
-    const uint32_t cnt = a.l_count[qi];
+    const uint32_t cnt = a.l_count[qi * a.l_stride];
     if (cnt > (uint32_t)a.q_cap || cnt < (uint32_t)B) {
         // list overflow, or the bound fell short: the per-query kernel answers
         if (threadIdx.x == 0) {
@@ -2479,7 +2502,7 @@ __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
     const int64_t qi = blockIdx.x;
     const AnnQueryParams qpar = query_params(a, qi);
     const int B = qpar.budget;
-    const uint32_t cnt = a.l_count[qi];
+    const uint32_t cnt = a.l_count[qi * a.l_stride];
     if (cnt > (uint32_t)a.q_cap || cnt < (uint32_t)B) {
         // list overflow, or the bound fell short: the per-query kernel answers
         if (threadIdx.x == 0) {
@@ -2914,7 +2937,11 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         a.l_val = L.l_val;
         a.q_flag = L.q_flag;
         a.pq_list = L.pq_list;
-        a.l_count = L.l_count;
+        // A query's candidate count sits where its members go later, so that
+        // the counts of different queries are on lines of their own: the
+        // scan's reservations on packed counts queued up at 64 lines.
+        a.l_count = reinterpret_cast<uint32_t*>(L.ws_cpos);
+        a.l_stride = L.budget;
         a.q_scanned = L.q_scanned;
         a.l_list = L.l_list;
         a.q_cap = (int)L.pool_cap;
