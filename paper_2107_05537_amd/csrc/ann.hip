@@ -208,6 +208,17 @@ __device__ __forceinline__ int block_sum(int v, Smem& sh) {
     return s;
 }
 
+// Inclusive prefix sum over the wave (row shifts, then the row totals).
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 to rows 1, 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 to rows 2, 3
+    return x;
+}
+
 // Exclusive prefix sum over the workgroup.
 template <int T = WG>
 __device__ __forceinline__ int block_exclusive_scan(int v, Smem& sh) {
@@ -1900,10 +1911,32 @@ __device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<S>& ss, i
     for (int b = 15; b >= 0; --b)
         mk = __builtin_amdgcn_alignbit(mk, __float_as_uint(cc[b >> 2][b & 3]), 31);
     const uint32_t prow = (uint32_t)p0 + 4u * (uint32_t)(lane >> 4);
-    // one candidate of every lane that has any left per step
-    for (;;) {
-        const uint64_t m = __builtin_amdgcn_ballot_w64(mk != 0u);
-        if (!m) return;
+    // A step stages one candidate of every lane that has any left, at the count
+    // of such lanes below it. Where some lane has many (chunks of a query's own
+    // cluster: most points of a column), all of a lane's go to consecutive slots
+    // instead, at the prefix sum of the lanes' counts: fewer instructions per
+    // step, but the sum before the first.
+    uint64_t m = __builtin_amdgcn_ballot_w64(mk != 0u);
+    if (!m) return;
+    const int own = __popc(mk);
+    if (__builtin_amdgcn_ballot_w64(own > 3)) {
+        const int upto = wave_inclusive_scan(own);
+        const uint32_t nh = (uint32_t)__builtin_amdgcn_readlane(upto, 63);
+        if (wn + nh > (uint32_t)S::STG && wn > 0u) scan_flush(a, ss, wave, lane, wn, qw0, nqw);
+        if (wn + nh <= (uint32_t)S::STG) {   // else (a group can hold 1,024) the steps below
+            uint32_t at = wn + (uint32_t)(upto - own);
+            while (mk) {
+                const uint32_t b = (uint32_t)__builtin_ctz(mk);
+                mk &= mk - 1u;
+                ss.pos[wave][at] = prow + ((b >> 2) << 4) + (b & 3u);
+                ss.qid[wave][at] = (uint8_t)q;
+                ++at;
+            }
+            wn += nh;
+            return;
+        }
+    }
+    do {
         const uint32_t nh = (uint32_t)__popcll(m);
         const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
             (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -1915,7 +1948,8 @@ __device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<S>& ss, i
             mk &= mk - 1u;
         }
         wn += nh;
-    }
+        m = __builtin_amdgcn_ballot_w64(mk != 0u);
+    } while (m);
 }
 
 template <class S>
