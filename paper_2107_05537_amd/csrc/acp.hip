@@ -358,18 +358,20 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_kernel(
 // ---------------------------------------------------------------- wave scan
 // Leaves of at most 64 points: one wave per leaf computes the parent
 // distances PD of its points (as acp_pd_kernel) and sorts them ascending
-// (ties by position) across its lanes: spd holds the sorted values (+inf
-// past the leaf's count), sidx the position of each in the leaf.
+// (ties by position) across its lanes: skey holds, in that order, the PD (+inf
+// past the leaf's count), the first two hi coordinates and the position of each
+// point in the leaf, lcen the leaf's centre in one line.
 __global__ __launch_bounds__(WG) void acp_pd_sorted_kernel(
     const float* __restrict__ phi, const float* __restrict__ plo, NodeView v, int64_t leaf_base,
-    int64_t n, int L, int64_t n_leaves, float* __restrict__ ppd, float* __restrict__ spd,
-    uint8_t* __restrict__ sidx) {
+    int64_t n, int L, int64_t n_leaves, float* __restrict__ ppd, float4* __restrict__ skey,
+    float* __restrict__ lcen) {
     const int64_t leaf = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
     if (leaf >= n_leaves) return;          // the whole wave leaves together
     const int lane = lane_id();
     const int64_t p0 = leaf * L;
     const int cnt = (int)(n - p0 < L ? n - p0 : L);
     float val = INFINITY;
+    if (lane < MP) lcen[leaf * MP + lane] = v.cen[(int64_t)lane * v.n_nodes + leaf_base + leaf];
     if (lane < cnt) {
         const int64_t node = leaf_base + leaf;
         float acc = 0.f;
@@ -397,22 +399,31 @@ __global__ __launch_bounds__(WG) void acp_pd_sorted_kernel(
             }
         }
     }
-    spd[leaf * 64 + lane] = val;
-    sidx[leaf * 64 + lane] = (uint8_t)idx;
+    float4 key = make_float4(val, 0.f, 0.f, __int_as_float(idx));
+    if (idx < cnt) {
+        key.y = phi[(p0 + idx) * MP];
+        key.z = phi[(p0 + idx) * MP + 1];
+    }
+    skey[leaf * 64 + lane] = key;
 }
 
-// Number of the 64 ascending values y (one per lane) below v (strict) or at
-// most v; every lane of the wave must call it.
-__device__ __forceinline__ int count_sorted(float y, float v, bool strict) {
-    int pos = 0;
+// Numbers of the 64 ascending values y (one per lane) below v and at most w;
+// every lane of the wave must call it. The two searches share their steps, whose
+// shuffles then overlap.
+__device__ __forceinline__ void count_sorted2(float y, float v, float w, int& below, int& upto) {
+    // positions in bytes, the unit of the lane addresses
+    int p = 0, q = 0;
+    const int yi = __float_as_int(y);
+    auto at = [&](int byte) { return __int_as_float(__builtin_amdgcn_ds_bpermute(byte, yi)); };
 #pragma unroll
     for (int step = 32; step > 0; step >>= 1) {
-        const float yy = __shfl(y, pos + step - 1);
-        if (strict ? yy < v : yy <= v) pos += step;
+        const float a = at(p + 4 * (step - 1)), b = at(q + 4 * (step - 1));
+        p += a < v ? 4 * step : 0;
+        q += b <= w ? 4 * step : 0;
     }
-    const float yy = __shfl(y, pos);
-    if (strict ? yy < v : yy <= v) ++pos;
-    return pos;
+    const float a = at(p), b = at(q);
+    below = (p >> 2) + (a < v ? 1 : 0);
+    upto = (q >> 2) + (b <= w ? 1 : 0);
 }
 
 __device__ __forceinline__ float readlane_f(float x, int l) {
@@ -422,12 +433,6 @@ __device__ __forceinline__ float readlane_f(float x, int l) {
 __device__ __forceinline__ int wave_sum(int x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
-__device__ __forceinline__ int wave_max(int x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o));
     return x;
 }
 
@@ -447,12 +452,11 @@ constexpr int kSparseMax = 40;
 //   2. each b of the interval gets the same per-pair PD test and, when it
 //      passes, the projected distance from the hi/lo coordinates; pairs
 //      with pd^2 < R2 are emitted. When some lane's interval is wide, the
-//      whole tile is scanned instead: lanes take b, the loop takes a.
+//      whole tile is scanned instead, one b at a time.
 // The emitted set is the set acp_tile_scan_kernel emits for the same tiles.
 __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
     const float* __restrict__ phi, const float* __restrict__ plo, const float* __restrict__ ppd,
-    const float* __restrict__ spd, const uint8_t* __restrict__ sidx, NodeView v,
-    int64_t leaf_base, const int32_t* __restrict__ perm, int64_t n, int L,
+    const float4* __restrict__ skey, const float* __restrict__ lcen, const int32_t* __restrict__ perm, int64_t n, int L,
     const int2* __restrict__ tiles, int64_t n_tiles, float R2, float Rlim,
     uint32_t* __restrict__ ck0, uint32_t* __restrict__ cii, uint32_t* __restrict__ cjj,
     int64_t cap, unsigned long long* __restrict__ counter,
@@ -479,15 +483,18 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
     // read it again), so the compiler waits for the oldest ones only.
     const int64_t t_last = t_end - 1;
     int2 nt = t_beg < t_end ? tiles[t_beg] : make_int2(0, 0);
-    float ncen[MP], ny = 0.f;
-    int nsb = 0;
+    float ncen[MP];
+    float4 nkey = make_float4(0.f, 0.f, 0.f, 0.f);
     auto fetch = [&](int e) {
-        const int64_t node = leaf_base + e;
 #pragma unroll
-        for (int j = 0; j < MP; ++j) ncen[j] = v.cen[(int64_t)j * v.n_nodes + node];
-        ny = spd[(int64_t)e * 64 + lane];
-        nsb = sidx[(int64_t)e * 64 + lane];
+        for (int j = 0; j < MP; ++j) ncen[j] = lcen[(int64_t)e * MP + j];   // one scalar load
+        nkey = skey[(int64_t)e * 64 + lane];
     };
+    // A pair whose first (or second) hi coordinates differ by rc or more cannot
+    // pass pd^2 < R2: the hi/lo difference is within 2^-22 of the largest
+    // coordinate of theirs, which Rlim's slack of 2e-5 times it covers, and the
+    // relative part covers the rounding of the squares.
+    const float rc = Rlim * (1.f + 1e-6f);
     int2 nt2 = nt;
     if (t_beg < t_end) {
         fetch(__builtin_amdgcn_readfirstlane(nt.y));
@@ -499,8 +506,8 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
         float cen[MP];
 #pragma unroll
         for (int j = 0; j < MP; ++j) cen[j] = ncen[j];
-        const float y = ny;
-        const int sb = nsb;
+        const float y = nkey.x, c0 = nkey.y, c1 = nkey.z;
+        const int sb = __float_as_int(nkey.w);
         nt = nt2;                                          // tile t + 1 (or t_last)
         fetch(__builtin_amdgcn_readfirstlane(nt.y));
         nt2 = tiles[t + 2 <= t_last ? t + 2 : t_last];     // tile t + 2 (or t_last)
@@ -521,42 +528,52 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
         }
         const int cb = (int)(n - b0 < L ? n - b0 : L);
         const bool diag = e1 == e2;
-        // 1. distance to the centre of e2, interval of PD(b)
+        // 1. distance to the centre of e2, interval of PD(b). The hi coordinates
+        // are enough: they are within 2^-24 of the largest coordinate of the
+        // point, which Rlim's slack covers. |x - y| - 32u (x + y) < Rlim
+        // implies y in (lov, hiv) in exact arithmetic; the bounds are widened
+        // by 1e-5 (x + Rlim), which also covers the FP32 rounding of that test,
+        // of the bounds and of the hardware square root.
         float acc = 0.f;
 #pragma unroll
         for (int j = 0; j < MP; ++j) {
-            const float dt = __fadd_rn(__fsub_rn(h1[j], cen[j]), l1[j]);
-            acc = __fmaf_rn(dt, dt, acc);
+            const float dt = h1[j] - cen[j];
+            acc = fmaf(dt, dt, acc);
         }
-        const float x = sqrtf(acc);
-        // |x - y| - 32u (x + y) < Rlim implies y in (lov, hiv) in exact
-        // arithmetic; the bounds are widened by 1e-6 (x + Rlim), far more than
-        // the FP32 rounding of that test and of the bounds themselves
-        float lov = (x * (1.f - 32.f * u) - Rlim) / (1.f + 32.f * u);
-        float hiv = (x * (1.f + 32.f * u) + Rlim) / (1.f - 32.f * u);
-        const float wid = (x + (Rlim < INFINITY ? Rlim : 0.f)) * 1e-6f + 1e-30f;
-        lov -= wid;
-        hiv += wid;
+        const float x = __builtin_amdgcn_sqrtf(acc);
+        const float wid = (x + Rlim) * 1e-5f + 1e-30f;
+        float lov = x - Rlim - wid;
+        float hiv = x + Rlim + wid;
         if (lane >= ca) {
             lov = INFINITY;
             hiv = -INFINITY;
         }
-        const int lo = count_sorted(y, lov, true);
-        int hi = count_sorted(y, hiv, false);
+        // most tiles that pass Mindist hold no such pair: every interval lies
+        // beyond e2's smallest or largest PD
+        if (!__ballot(lov <= readlane_f(y, cb - 1) && hiv >= readlane_f(y, 0))) continue;
+        int lo, hi;
+        count_sorted2(y, lov, hiv, lo, hi);
         hi = hi < cb ? hi : cb;
         const int mine = hi > lo ? hi - lo : 0;
-        const int widest = wave_max(mine);
-        if (widest == 0) continue;
-        if (widest <= kSparseMax) {
+        if (!__ballot(mine > 0)) continue;
+        if (!__ballot(mine > kSparseMax)) {
             // 2a. lane by lane
-            for (int it = 0; it < widest; ++it) {
+            for (int it = 0; __ballot(it < mine); ++it) {
+                // most of the interval's pairs are apart in one of the first two
+                // coordinates
                 const int pos = lo + (it < mine ? it : 0);
+                const float b0c = __shfl(c0, pos);   // (shuffles read every lane)
+                bool near = it < mine && fabsf(h1[0] - b0c) < rc;
+                if (!__ballot(near)) continue;
+                const float b1c = __shfl(c1, pos);
+                near = near && fabsf(h1[1] - b1c) < rc;
+                if (!__ballot(near)) continue;
                 const float yb = __shfl(y, pos);
                 const int b = __shfl(sb, pos);
                 bool hit = false;
                 float pd2 = 0.f;
                 uint32_t id2 = 0;
-                if (it < mine && (!diag || b > lane) &&
+                if (near && (!diag || b > lane) &&
                     fabsf(x - yb) - 32.f * u * (x + yb) < Rlim) {
                     const float4* hp = reinterpret_cast<const float4*>(phi + (b0 + b) * MP);
                     const float4* lp = reinterpret_cast<const float4*>(plo + (b0 + b) * MP);
@@ -584,39 +601,27 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
                 }
             }
         } else {
-            // 2b. the whole tile: lane b holds point b of e2, the loop takes a
-            const int b = lane < cb ? lane : 0;
-            float h2[MP], l2[MP];
-            const float4* hp = reinterpret_cast<const float4*>(phi + (b0 + b) * MP);
-            const float4* lp = reinterpret_cast<const float4*>(plo + (b0 + b) * MP);
-#pragma unroll
-            for (int q = 0; q < MP / 4; ++q) {
-                const float4 hv = hp[q], lv = lp[q];
-                h2[4 * q] = hv.x; h2[4 * q + 1] = hv.y; h2[4 * q + 2] = hv.z; h2[4 * q + 3] = hv.w;
-                l2[4 * q] = lv.x; l2[4 * q + 1] = lv.y; l2[4 * q + 2] = lv.z; l2[4 * q + 3] = lv.w;
-            }
-            const float yb = ppd[b0 + b];
-            const uint32_t id2 = (uint32_t)perm[b0 + b];
-            for (int a = 0; a < ca; ++a) {
-                const float xa = readlane_f(x, a);
-                bool hit = false;
+            // 2b. the whole tile: the loop takes b, whose row every lane reads
+            for (int b = 0; b < cb; ++b) {
+                const float yb = ppd[b0 + b];
+                const bool near = lane < ca && (!diag || b > lane) &&
+                                  fabsf(x - yb) - 32.f * u * (x + yb) < Rlim;
+                if (!__ballot(near)) continue;
+                const float* hb = phi + (b0 + b) * MP;
+                const float* lb = plo + (b0 + b) * MP;
                 float pd2 = 0.f;
-                if (lane < cb && (!diag || lane > a) &&
-                    fabsf(xa - yb) - 32.f * u * (xa + yb) < Rlim) {
 #pragma unroll
-                    for (int j = 0; j < MP; ++j) {
-                        const float dt = __fadd_rn(__fsub_rn(readlane_f(h1[j], a), h2[j]),
-                                                   __fsub_rn(readlane_f(l1[j], a), l2[j]));
-                        pd2 = __fmaf_rn(dt, dt, pd2);
-                    }
-                    hit = pd2 < R2;
+                for (int j = 0; j < MP; ++j) {
+                    const float dt = __fadd_rn(__fsub_rn(h1[j], hb[j]), __fsub_rn(l1[j], lb[j]));
+                    pd2 = __fmaf_rn(dt, dt, pd2);
                 }
-                const uint32_t ia = (uint32_t)__builtin_amdgcn_readlane((int)id1, a);
+                const bool hit = near && pd2 < R2;
+                const uint32_t id2 = (uint32_t)perm[b0 + b];
                 const int64_t slot = wave_append_global(hit, counter);
                 if (hit && slot < cap) {
                     ck0[slot] = __float_as_uint(pd2);
-                    cii[slot] = ia < id2 ? ia : id2;
-                    cjj[slot] = ia < id2 ? id2 : ia;
+                    cii[slot] = id1 < id2 ? id1 : id2;
+                    cjj[slot] = id1 < id2 ? id2 : id1;
                 }
             }
         }
@@ -1679,7 +1684,7 @@ __global__ __launch_bounds__(WG) void acp_band_gather_kernel(
 // (freed and allocated anew) only when a call needs more than it holds.
 enum Slot {
     S_HIST, S_COUNT, S_DOFF, S_TILES, S_PPD, S_SEEDS, S_CAND = S_SEEDS + 3, S_KEPT = S_CAND + 3,
-    S_POOL = S_KEPT + 3, S_TOP = S_POOL + 3, S_SPD = S_TOP + 3, S_SIDX, S_STATE, S_GHIST,
+    S_POOL = S_KEPT + 3, S_TOP = S_POOL + 3, S_SKEY = S_TOP + 3, S_LCEN, S_STATE, S_GHIST,
     S_SLO, S_STATE2, S_COUNTS, S_RADIUS, S_BAND, S_COUNT_ALL = S_BAND + 3
 };
 
@@ -1871,7 +1876,7 @@ struct TileScan {
     hipStream_t st;
     NodeView v;
     int64_t leaf_base;
-    DevBuf ppd, spd, sidx;
+    DevBuf ppd, skey, lcen;
     bool wave = false;
     size_t lds = 0;
 
@@ -1879,8 +1884,8 @@ struct TileScan {
         : x(idx), st(s),
           v{idx->tree.centre, idx->tree.radius, idx->tree.hr_min, idx->tree.hr_max, idx->n_nodes,
             idx->num_pivots},
-          leaf_base(idx->level_begin[idx->levels - 1]), ppd(idx, S_PPD), spd(idx, S_SPD),
-          sidx(idx, S_SIDX) {}
+          leaf_base(idx->level_begin[idx->levels - 1]), ppd(idx, S_PPD), skey(idx, S_SKEY),
+          lcen(idx, S_LCEN) {}
 
     // parent distances (and their per-leaf sorted copies) of every point
     void prepare() {
@@ -1889,11 +1894,11 @@ struct TileScan {
         ppd.alloc((size_t)n * sizeof(float));
         wave = L <= 64;
         if (wave) {
-            spd.alloc((size_t)NL * 64 * sizeof(float));
-            sidx.alloc((size_t)NL * 64);
+            skey.alloc((size_t)NL * 64 * sizeof(float4));
+            lcen.alloc((size_t)NL * MP * sizeof(float));
             hipLaunchKernelGGL(acp_pd_sorted_kernel, dim3((unsigned)((NL + 3) / 4)), dim3(WG), 0,
                                st, x->proj_hi, x->proj_lo, v, leaf_base, n, L, NL,
-                               ppd.as<float>(), spd.as<float>(), sidx.as<uint8_t>());
+                               ppd.as<float>(), skey.as<float4>(), lcen.as<float>());
             PMLSH_HIP(hipGetLastError());
             return;
         }
@@ -1917,7 +1922,7 @@ struct TileScan {
             const int64_t waves = std::min<int64_t>(n_tiles, 16384);
             hipLaunchKernelGGL(acp_tile_scan_wave_kernel, dim3((unsigned)((waves + 3) / 4)),
                                dim3(WG), 0, st, x->proj_hi, x->proj_lo, ppd.as<float>(),
-                               spd.as<float>(), sidx.as<uint8_t>(), v, leaf_base, x->perm, x->n,
+                               skey.as<float4>(), lcen.as<float>(), x->perm, x->n,
                                x->leaf_size, tiles, n_tiles, R2, Rlim, k0, ii, jj, cap, counter,
                                dn_tiles, rad);
         } else {
