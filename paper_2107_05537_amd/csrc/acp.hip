@@ -56,16 +56,21 @@ __device__ __forceinline__ int64_t wave_append_global(bool take, unsigned long l
 }
 
 // ---------------------------------------------------------------- seeds
+// Where the pairs of a leaf begin among all seeds: every leaf but the last
+// holds L points.
+__device__ __forceinline__ int64_t seed_base(int64_t leaf, int L) {
+    return leaf * ((int64_t)L * (L - 1) / 2);
+}
+
 __global__ __launch_bounds__(WG) void acp_self_join_kernel(
     const float* __restrict__ data, int d_pad, const int32_t* __restrict__ perm, int64_t n,
-    int L, const int64_t* __restrict__ seed_off, uint32_t* __restrict__ k0,
-    uint32_t* __restrict__ ii, uint32_t* __restrict__ jj) {
+    int L, uint32_t* __restrict__ k0, uint32_t* __restrict__ ii, uint32_t* __restrict__ jj) {
     __shared__ float xs[256][SJ_KC + 1];
     const int64_t leaf = blockIdx.x;
     const int64_t p0 = leaf * L;
     const int cnt = (int)(n - p0 < L ? n - p0 : L);
     const int P = cnt * (cnt - 1) / 2;
-    const int64_t out0 = seed_off[leaf];
+    const int64_t out0 = seed_base(leaf, L);
     for (int base = 0; base < P; base += WG * SJ_PER) {
         int ra[SJ_PER], rb[SJ_PER];
         float acc[SJ_PER];
@@ -781,7 +786,7 @@ __global__ __launch_bounds__(WG) void acp_kth_small_kernel(const uint32_t* __res
 // two interleaved accumulators each, so every FP32 sum is a chain of
 // d_pad / 4 terms and the squared distance carries a relative error of at
 // most (d_pad / 4 + 4) u (two chains per half, two halves). Writes the
-// distance bits of pair (a, b) at seed_off[leaf] + a (2 cnt - a - 1) / 2 +
+// distance bits of pair (a, b) at seed_base(leaf) + a (2 cnt - a - 1) / 2 +
 // b - a - 1 (and, with ii/jj, the ids i < j), and adds the top 11 bits of
 // every distance to the device-wide histogram ghist (first radix pass of the
 // k-th smallest seed).
@@ -790,8 +795,8 @@ constexpr int SJ_TASKS = 272;
 constexpr int SJ_CK = 64;
 __global__ __launch_bounds__(SJ_THREADS) void acp_seed_join_kernel(
     const float* __restrict__ data, int d_pad, const int32_t* __restrict__ perm, int64_t n,
-    int L, const int64_t* __restrict__ seed_off, uint32_t* __restrict__ k0,
-    uint32_t* __restrict__ ii, uint32_t* __restrict__ jj, uint32_t* __restrict__ ghist) {
+    int L, uint32_t* __restrict__ k0, uint32_t* __restrict__ ii, uint32_t* __restrict__ jj,
+    uint32_t* __restrict__ ghist) {
     __shared__ float xs[64][SJ_CK + 1];
     __shared__ float part[SJ_TASKS / 2][16];
     __shared__ uint32_t hist[NB];
@@ -857,7 +862,7 @@ __global__ __launch_bounds__(SJ_THREADS) void acp_seed_join_kernel(
     }
     __syncthreads();
     if (task && half == 0) {
-        const int64_t out0 = seed_off[leaf];
+        const int64_t out0 = seed_base(leaf, L);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -1236,15 +1241,15 @@ __global__ __launch_bounds__(WG) void acp_sel_hist_kernel(
 // Within-leaf pairs whose distance bits are at most lim (the band of the
 // top-k, or every seed when lim is +inf): (bits, i, j) appended to the pool.
 __global__ __launch_bounds__(WG) void acp_seed_band_kernel(
-    const uint32_t* __restrict__ k0, const int64_t* __restrict__ seed_off,
-    const int32_t* __restrict__ perm, int64_t n, int L, uint32_t lim,
+    const uint32_t* __restrict__ k0, const int32_t* __restrict__ perm, int64_t n, int L,
+    uint32_t lim,
     uint32_t* __restrict__ ok0, uint32_t* __restrict__ oii, uint32_t* __restrict__ ojj,
     int64_t cap, unsigned long long* __restrict__ counter) {
     const int64_t leaf = blockIdx.x;
     const int64_t p0 = leaf * L;
     const int cnt = (int)(n - p0 < L ? n - p0 : L);
     const int P = cnt * (cnt - 1) / 2;
-    const int64_t off = seed_off[leaf];
+    const int64_t off = seed_base(leaf, L);
     for (int base = 0; base < P; base += WG) {
         const int p = base + threadIdx.x;
         uint32_t key = 0;
@@ -1486,11 +1491,19 @@ __device__ __forceinline__ double row_dist2_f64(const float4* __restrict__ r1,
 // pairs are every pair whose FP32 distance lies within the verify error band
 // of the FP32 k-th one, so the exact top-k is among them; each gets its squared
 // distance in FP64 from the FP32 rows and the k smallest by (d^2, i, j) are
-// written (16 lanes per pair, as in the FP32 verify).
-__global__ __launch_bounds__(WG) void acp_final64_kernel(
+// written (16 lanes per pair, as in the FP32 verify). The count is read on the
+// device; above kTopBand (mass ties) or below k nothing is written and the
+// caller, which reads the count too, takes another way. One workgroup: a
+// chain of row reads, 64 pairs at a time in sixteen waves.
+constexpr int F64_WG = 1024;
+__global__ __launch_bounds__(F64_WG) void acp_final64_kernel(
     const float* __restrict__ data, int d_pad, const int32_t* __restrict__ inv_perm,
-    const uint32_t* __restrict__ ii, const uint32_t* __restrict__ jj, int count, int k,
-    int64_t* __restrict__ out_pairs, float* __restrict__ out_dist) {
+    const uint32_t* __restrict__ ii, const uint32_t* __restrict__ jj,
+    const unsigned long long* __restrict__ dev_count, int k, int64_t* __restrict__ out_pairs,
+    float* __restrict__ out_dist) {
+    constexpr int WG = F64_WG;
+    if (*dev_count > (unsigned long long)kTopBand || (int64_t)*dev_count < k) return;
+    const int count = (int)*dev_count;
     __shared__ double dk[kTopBand];
     __shared__ uint64_t pk[kTopBand];
     const int g = threadIdx.x >> 4, l16 = threadIdx.x & 15;
@@ -1683,7 +1696,7 @@ __global__ __launch_bounds__(WG) void acp_band_gather_kernel(
 // Workspace buffer of one role, kept in the index between calls and grown
 // (freed and allocated anew) only when a call needs more than it holds.
 enum Slot {
-    S_HIST, S_COUNT, S_DOFF, S_TILES, S_PPD, S_SEEDS, S_CAND = S_SEEDS + 3, S_KEPT = S_CAND + 3,
+    S_HIST, S_COUNT, S_TILES, S_PPD, S_SEEDS, S_CAND = S_SEEDS + 3, S_KEPT = S_CAND + 3,
     S_POOL = S_KEPT + 3, S_TOP = S_POOL + 3, S_SKEY = S_TOP + 3, S_LCEN, S_STATE, S_GHIST,
     S_SLO, S_STATE2, S_COUNTS, S_RADIUS, S_BAND, S_COUNT_ALL = S_BAND + 3
 };
@@ -1715,10 +1728,12 @@ struct DevBuf {
 // finishes before the next operation is issued, while copies into pinned
 // memory queue like kernels, so the reads of one step cost one
 // synchronisation. Calls on one index serialise on its mutex and every
-// HostReads waits before the next is made, so one buffer serves them all.
+// HostReads waits before the next is made, so one buffer serves them all
+// (grown, while none is waited for, when a read of the tree needs more).
 constexpr size_t kHostReadBytes = 16384;
 struct HostReads {
     unsigned char* base;
+    size_t cap;
     hipStream_t st;
     size_t used = 0;
     int n = 0;
@@ -1726,13 +1741,22 @@ struct HostReads {
         void* dst;
         size_t off, bytes;
     } items[8];
-    HostReads(const pmlsh_index* x, hipStream_t s) : st(s) {
-        if (!x->acp_host) PMLSH_HIP(hipHostMalloc(&x->acp_host, kHostReadBytes, hipHostMallocDefault));
+    HostReads(const pmlsh_index* x, hipStream_t s, size_t need = kHostReadBytes) : st(s) {
+        if (x->acp_host_bytes < need) {
+            if (x->acp_host) {
+                (void)hipHostFree(x->acp_host);
+                x->acp_host = nullptr;
+                x->acp_host_bytes = 0;
+            }
+            PMLSH_HIP(hipHostMalloc(&x->acp_host, need, hipHostMallocDefault));
+            x->acp_host_bytes = need;
+        }
+        cap = x->acp_host_bytes;
         base = static_cast<unsigned char*>(x->acp_host);
     }
     void add(void* dst, const void* src, size_t bytes) {
         const size_t off = (used + 15) & ~size_t(15);
-        if (n == 8 || off + bytes > kHostReadBytes) fail(PMLSH_EDEVICE, "host read staging overflow");
+        if (n == 8 || off + bytes > cap) fail(PMLSH_EDEVICE, "host read staging overflow");
         PMLSH_HIP(hipMemcpyAsync(base + off, src, bytes, hipMemcpyDeviceToHost, st));
         items[n++] = {dst, off, bytes};
         used = off + bytes;
@@ -1847,21 +1871,27 @@ double pool_gamma(const pmlsh_index* x, bool has_seeds) {
     return 2.0 * u * g;
 }
 
+// Pairs inside leaves.
+int64_t seed_count(int64_t n, int64_t L, int64_t NL) {
+    if (NL <= 0) return 0;
+    const int64_t last = n - (NL - 1) * L;
+    return (NL - 1) * (L * (L - 1) / 2) + last * (last - 1) / 2;
+}
+
 // Self-join of every leaf: distance bits to k0 (and ids to ii/jj when given),
-// in the triangular layout of seed_off. For leaves of at most 64 points the
+// leaf after leaf from seed_base. For leaves of at most 64 points the
 // first radix pass of the k-th seed is added to ghist (returns true).
-bool launch_self_join(const pmlsh_index* x, const int64_t* doff, uint32_t* k0, uint32_t* ii,
-                      uint32_t* jj, uint32_t* ghist, hipStream_t st) {
+bool launch_self_join(const pmlsh_index* x, uint32_t* k0, uint32_t* ii, uint32_t* jj,
+                      uint32_t* ghist, hipStream_t st) {
     if (x->leaf_size <= 64) {
         hipLaunchKernelGGL(acp_seed_join_kernel, dim3((unsigned)x->n_leaves), dim3(SJ_THREADS), 0,
-                           st, x->data, x->d_pad, x->perm, x->n, x->leaf_size, doff, k0, ii, jj,
-                           ghist);
+                           st, x->data, x->d_pad, x->perm, x->n, x->leaf_size, k0, ii, jj, ghist);
         PMLSH_HIP(hipGetLastError());
         return true;
     }
     if (!ii || !jj) fail(PMLSH_EDEVICE, "self-join of large leaves needs id buffers");
     hipLaunchKernelGGL(acp_self_join_kernel, dim3((unsigned)x->n_leaves), dim3(WG), 0, st,
-                       x->data, x->d_pad, x->perm, x->n, x->leaf_size, doff, k0, ii, jj);
+                       x->data, x->d_pad, x->perm, x->n, x->leaf_size, k0, ii, jj);
     PMLSH_HIP(hipGetLastError());
     return false;
 }
@@ -1947,11 +1977,12 @@ struct TileScan {
 // keeps the FP32 order.
 // With dn_add the pool holds n_pool + *dn_add pairs (counted on the device),
 // at most n_max; the count is read back only when the one-workgroup kernel
-// cannot finish alone.
+// cannot finish alone. With `selected` the pool's k-th key is in the state
+// buffer already.
 void pool_topk(const pmlsh_index* x, Triplets& pool, int64_t n_pool, int k, double gamma,
                Triplets& top, DevBuf& dhist, DevBuf& dcount, int64_t* out_pairs,
                float* out_dist, hipStream_t st, const unsigned long long* dn_add = nullptr,
-               int64_t n_max = 0) {
+               int64_t n_max = 0, bool selected = false) {
     DevBuf dstate(x, S_STATE), ghist(x, S_GHIST);
     dstate.alloc(sizeof(SelState));
     ghist.alloc(NB * sizeof(uint32_t));
@@ -1989,9 +2020,11 @@ void pool_topk(const pmlsh_index* x, Triplets& pool, int64_t n_pool, int k, doub
         if (m <= kTopBand) return;
         if (dn_add) exact_count();
     }
-    PMLSH_HIP(hipMemsetAsync(ghist.p, 0, NB * sizeof(uint32_t), st));
-    device_select(pool.k0.as<uint32_t>(), n_pool, k, dstate.as<SelState>(),
-                  ghist.as<uint32_t>(), false, st);
+    if (!selected) {
+        PMLSH_HIP(hipMemsetAsync(ghist.p, 0, NB * sizeof(uint32_t), st));
+        device_select(pool.k0.as<uint32_t>(), n_pool, k, dstate.as<SelState>(),
+                      ghist.as<uint32_t>(), false, st);
+    }
     top.alloc(kTopBand);
     PMLSH_HIP(hipMemsetAsync(dcount.p, 0, sizeof(unsigned long long), st));
     hipLaunchKernelGGL(acp_band_gather_kernel, dim3(grid_for(n_pool, WG)), dim3(WG), 0, st,
@@ -2000,6 +2033,10 @@ void pool_topk(const pmlsh_index* x, Triplets& pool, int64_t n_pool, int k, doub
                        top.ii.as<uint32_t>(), top.jj.as<uint32_t>(), (int64_t)kTopBand,
                        static_cast<unsigned long long*>(dcount.p));
     PMLSH_HIP(hipGetLastError());
+    hipLaunchKernelGGL(acp_final64_kernel, dim3(1), dim3(F64_WG), 0, st, x->data, x->d_pad,
+                       x->inv_perm, top.ii.as<uint32_t>(), top.jj.as<uint32_t>(),
+                       static_cast<const unsigned long long*>(dcount.p), k, out_pairs, out_dist);
+    PMLSH_HIP(hipGetLastError());
     unsigned long long m = 0;
     {
         HostReads rd(x, st);
@@ -2007,11 +2044,7 @@ void pool_topk(const pmlsh_index* x, Triplets& pool, int64_t n_pool, int k, doub
         rd.wait();
     }
     if ((int64_t)m < k) fail(PMLSH_EDEVICE, "top-k selection lost pairs");
-    if ((int64_t)m <= kTopBand) {
-        hipLaunchKernelGGL(acp_final64_kernel, dim3(1), dim3(WG), 0, st, x->data, x->d_pad,
-                           x->inv_perm, top.ii.as<uint32_t>(), top.jj.as<uint32_t>(), (int)m,
-                           k, out_pairs, out_dist);
-    } else {
+    if ((int64_t)m > kTopBand) {
         // mass ties: the k smallest full keys (distance bits, i, j) in FP32
         const SelKey K = select_kth(x, pool.k0.as<uint32_t>(), pool.ii.as<uint32_t>(),
                                     pool.jj.as<uint32_t>(), n_pool, k, false,
@@ -2033,9 +2066,9 @@ void pool_topk(const pmlsh_index* x, Triplets& pool, int64_t n_pool, int k, doub
         hipLaunchKernelGGL(acp_final_kernel, dim3(1), dim3(WG), 0, st, top.k0.as<uint32_t>(),
                            top.ii.as<uint32_t>(), top.jj.as<uint32_t>(), k, out_pairs,
                            out_dist);
+        PMLSH_HIP(hipGetLastError());
+        PMLSH_HIP(hipStreamSynchronize(st));
     }
-    PMLSH_HIP(hipGetLastError());
-    PMLSH_HIP(hipStreamSynchronize(st));
 }
 
 void run_acp(const pmlsh_index* x, int k, double c, double confidence, double beta,
@@ -2067,14 +2100,9 @@ void run_acp(const pmlsh_index* x, int k, double c, double confidence, double be
         return (int64_t)v;
     };
     // ---- seeds: every within-leaf pair
-    std::vector<int64_t> seed_off(NL + 1, 0);
-    for (int64_t b = 0; b < NL; ++b) {
-        const int64_t cnt = std::min<int64_t>(L, n - b * L);
-        seed_off[b + 1] = seed_off[b] + cnt * (cnt - 1) / 2;
-    }
-    const int64_t n_seed = seed_off[NL];
+    const int64_t n_seed = seed_count(n, L, NL);
     Triplets seeds(x, S_SEEDS), band(x, S_BAND);
-    DevBuf doff(x, S_DOFF), slo(x, S_SLO);
+    DevBuf slo(x, S_SLO);
     double ub = HUGE_VAL;
     uint32_t ub2_bits = 0x7f800000u;
     PMLSH_HIP(hipMemsetAsync(ghist.p, 0, NB * sizeof(uint32_t), st));
@@ -2160,9 +2188,6 @@ void run_acp(const pmlsh_index* x, int k, double c, double confidence, double be
     // few seeds the top-k can use are recovered from their position)
     auto direct_seeds = [&] {
         gram = false;
-        doff.alloc((NL + 1) * sizeof(int64_t));
-        PMLSH_HIP(hipMemcpyAsync(doff.p, seed_off.data(), (NL + 1) * sizeof(int64_t),
-                                 hipMemcpyHostToDevice, st));
         seeds.k0.alloc((size_t)n_seed * 4);
         if (L > 64) {
             seeds.ii.alloc((size_t)n_seed * 4);
@@ -2171,7 +2196,7 @@ void run_acp(const pmlsh_index* x, int k, double c, double confidence, double be
         bool first_done;
         {
             StageTimer tm(PMLSH_STAGE_ACP_SELFJOIN, st);
-            first_done = launch_self_join(x, doff.as<int64_t>(), seeds.k0.as<uint32_t>(),
+            first_done = launch_self_join(x, seeds.k0.as<uint32_t>(),
                                           L > 64 ? seeds.ii.as<uint32_t>() : nullptr,
                                           L > 64 ? seeds.jj.as<uint32_t>() : nullptr,
                                           ghist.as<uint32_t>(), st);
@@ -2425,8 +2450,7 @@ void run_acp(const pmlsh_index* x, int k, double c, double confidence, double be
                                    static_cast<unsigned long long*>(dcount.p));
             } else {
                 hipLaunchKernelGGL(acp_seed_band_kernel, dim3((unsigned)NL), dim3(WG), 0, st,
-                                   seeds.k0.as<uint32_t>(), doff.as<int64_t>(), x->perm, n, L,
-                                   seed_lim, pool.k0.as<uint32_t>(), pool.ii.as<uint32_t>(),
+                                   seeds.k0.as<uint32_t>(), x->perm, n, L, seed_lim, pool.k0.as<uint32_t>(), pool.ii.as<uint32_t>(),
                                    pool.jj.as<uint32_t>(), seed_cap,
                                    static_cast<unsigned long long*>(dcount.p));
             }
@@ -2643,18 +2667,16 @@ struct NodeInfo {
     std::vector<float> rad;
 };
 
-NodeInfo fetch_nodes(const pmlsh_index* x) {
+// Its arrays from the children's ranges cb, ce and the radii.
+NodeInfo node_info(const pmlsh_index* x, const int32_t* cb, const int32_t* ce,
+                   const float* rad) {
     const int64_t N = x->n_nodes;
     NodeInfo I;
     I.level.assign(N, 0);
     I.lf.assign(N, 0);
     I.le.assign(N, 0);
     I.parent.assign(N, -1);
-    I.rad.assign(N, 0.f);
-    std::vector<int32_t> cb(N), ce(N);
-    PMLSH_HIP(hipMemcpy(cb.data(), x->tree.child_begin, N * 4, hipMemcpyDeviceToHost));
-    PMLSH_HIP(hipMemcpy(ce.data(), x->tree.child_end, N * 4, hipMemcpyDeviceToHost));
-    PMLSH_HIP(hipMemcpy(I.rad.data(), x->tree.radius, N * 4, hipMemcpyDeviceToHost));
+    I.rad.assign(rad, rad + N);
     const int levels = x->levels;
     const int64_t leaf_base = x->level_begin[levels - 1];
     for (int l = levels - 1; l >= 0; --l) {
@@ -2760,12 +2782,13 @@ void run_acp_lca(const pmlsh_index* x, int k, double c, double confidence, doubl
 
     std::lock_guard<std::mutex> lock(x->acp_mu);
     if ((int)x->acp_bufs.size() < S_COUNT_ALL) x->acp_bufs.resize(S_COUNT_ALL, {nullptr, 0});
-    DevBuf dhist(x, S_HIST), dcount(x, S_COUNT), tiles(x, S_TILES), ghist(x, S_GHIST);
-    Triplets seeds(x, S_SEEDS), cand(x, S_CAND), pool(x, S_POOL), kept(x, S_KEPT),
-        top(x, S_TOP);
+    DevBuf dhist(x, S_HIST), dcount(x, S_COUNT), tiles(x, S_TILES), ghist(x, S_GHIST),
+        dstate(x, S_STATE);
+    Triplets cand(x, S_CAND), pool(x, S_POOL), kept(x, S_KEPT), top(x, S_TOP);
     dhist.alloc(NB * sizeof(uint32_t));
     dcount.alloc(sizeof(unsigned long long));
     ghist.alloc(NB * sizeof(uint32_t));
+    dstate.alloc(sizeof(SelState));
     auto reset_counter = [&] {
         PMLSH_HIP(hipMemsetAsync(dcount.p, 0, sizeof(unsigned long long), st));
     };
@@ -2780,39 +2803,53 @@ void run_acp_lca(const pmlsh_index* x, int k, double c, double confidence, doubl
     };
 
     // 1. seeds
-    std::vector<int64_t> seed_off(NL + 1, 0);
-    for (int64_t b = 0; b < NL; ++b) {
-        const int64_t cnt = std::min<int64_t>(L, n - b * L);
-        seed_off[b + 1] = seed_off[b] + cnt * (cnt - 1) / 2;
-    }
-    const int64_t n_seed = seed_off[NL];
+    const int64_t n_seed = seed_count(n, L, NL);
     // the pool of verified pairs: seeds first, candidates appended
     int64_t pool_cap = std::max<int64_t>(n_seed + (int64_t(1) << 20), k);
     pool.alloc(pool_cap);
-    if (n_seed > 0) {
-        DevBuf doff(x, S_DOFF);
-        doff.alloc((NL + 1) * sizeof(int64_t));
-        PMLSH_HIP(hipMemcpyAsync(doff.p, seed_off.data(), (NL + 1) * sizeof(int64_t),
-                                 hipMemcpyHostToDevice, st));
-        PMLSH_HIP(hipMemsetAsync(ghist.p, 0, NB * sizeof(uint32_t), st));
-        launch_self_join(x, doff.as<int64_t>(), pool.k0.as<uint32_t>(), pool.ii.as<uint32_t>(),
-                         pool.jj.as<uint32_t>(), ghist.as<uint32_t>(), st);
-        PMLSH_HIP(hipStreamSynchronize(st));
-    }
+    // The k-th smallest verified distance is selected on the device; it stays
+    // in dstate, where the top-k at the end takes it from. It comes back with
+    // the tree's node ranges and radii, which need nothing from the join: one
+    // wait for the whole start of the call (the three histograms read back one
+    // by one and three copies of their own took 150 us of a 300 us call at
+    // 50,021 x 130).
     int64_t n_pool = n_seed;
-    auto kth_dist = [&]() -> double {
-        if (n_pool < k) return HUGE_VAL;
-        SelKey K = select_kth(x, pool.k0.as<uint32_t>(), pool.ii.as<uint32_t>(),
-                              pool.jj.as<uint32_t>(), n_pool, k, true, dhist.as<uint32_t>(), st);
-        float v2;
-        std::memcpy(&v2, &K.v0, 4);
-        return std::sqrt((double)v2);
+    auto launch_kth = [&](bool first_done) {
+        device_select(pool.k0.as<uint32_t>(), n_pool, k, dstate.as<SelState>(),
+                      ghist.as<uint32_t>(), first_done, st);
     };
-    double ub = kth_dist();
+    double ub = HUGE_VAL;
+    auto take_ub = [&](const SelState& s) {
+        float v2;
+        std::memcpy(&v2, &s.prefix, 4);
+        ub = std::sqrt((double)v2);
+    };
+    PMLSH_HIP(hipMemsetAsync(ghist.p, 0, NB * sizeof(uint32_t), st));
+    bool first_done = false;
+    if (n_seed > 0)
+        first_done = launch_self_join(x, pool.k0.as<uint32_t>(), pool.ii.as<uint32_t>(),
+                                      pool.jj.as<uint32_t>(), ghist.as<uint32_t>(), st);
+    if (n_seed >= k)
+        launch_kth(first_done);
+    else if (first_done)
+        PMLSH_HIP(hipMemsetAsync(ghist.p, 0, NB * sizeof(uint32_t), st));
+    const int64_t NN = x->n_nodes;
+    std::vector<int32_t> cb(NN), ce(NN);
+    std::vector<float> rad(NN);
+    {
+        SelState hs{};
+        HostReads rd(x, st, 3 * ((size_t)NN * 4 + 16) + kHostReadBytes);
+        rd.add(cb.data(), x->tree.child_begin, (size_t)NN * 4);
+        rd.add(ce.data(), x->tree.child_end, (size_t)NN * 4);
+        rd.add(rad.data(), x->tree.radius, (size_t)NN * 4);
+        rd.add(&hs, dstate.p, sizeof(hs));
+        rd.wait();
+        if (n_seed >= k) take_ub(hs);
+    }
     int64_t count = n_seed;
 
     // 2. FindLCA with R = gamma t ub
-    NodeInfo I = fetch_nodes(x);
+    NodeInfo I = node_info(x, cb.data(), ce.data(), rad.data());
     if (!(gamma > 0.0)) {
         // the estimate depends on the index alone (a fixed sample of pairs)
         if (!(x->acp_gamma085 > 0.0)) x->acp_gamma085 = estimate_gamma(x, I, 0.85);
@@ -2843,7 +2880,7 @@ void run_acp_lca(const pmlsh_index* x, int k, double c, double confidence, doubl
 
     // 3. the found nodes, ascending radius
     TileScan tscan(x, st);
-    tscan.prepare();
+    bool prepared = false;
     int64_t tiles_total = 0, tiles_scanned = 0, n_cand_total = 0;
     for (int64_t e : found) tiles_total += (int64_t)(I.le[e] - I.lf[e]) * (I.le[e] - I.lf[e] - 1) / 2;
     std::vector<int2> tl;
@@ -2854,6 +2891,8 @@ void run_acp_lca(const pmlsh_index* x, int k, double c, double confidence, doubl
         for (int32_t a = I.lf[e]; a < I.le[e]; ++a)
             for (int32_t b = a + 1; b < I.le[e]; ++b) tl.push_back(make_int2(a, b));
         if (tl.empty()) continue;
+        if (!prepared) tscan.prepare();
+        prepared = true;
         tiles.alloc(tl.size() * sizeof(int2));
         PMLSH_HIP(hipMemcpyAsync(tiles.p, tl.data(), tl.size() * sizeof(int2),
                                  hipMemcpyHostToDevice, st));
@@ -2907,13 +2946,20 @@ void run_acp_lca(const pmlsh_index* x, int k, double c, double confidence, doubl
         n_pool += nc;
         count += nc;
         n_cand_total += nc;
-        ub = kth_dist();
+        if (n_pool >= k) {
+            launch_kth(false);
+            SelState hs{};
+            HostReads rd(x, st);
+            rd.add(&hs, dstate.p, sizeof(hs));
+            rd.wait();
+            take_ub(hs);
+        }
     }
 
     // 4. the k nearest verified pairs
     if (n_pool < k) fail(PMLSH_EDEVICE, "fewer verified pairs than k");
     pool_topk(x, pool, n_pool, k, pool_gamma(x, true), top, dhist, dcount, out_pairs, out_dist,
-              st);
+              st, nullptr, 0, true);
     if (stats) {
         stats->t = plan.t;
         stats->ub = ub;
@@ -2928,7 +2974,13 @@ void run_acp_lca(const pmlsh_index* x, int k, double c, double confidence, doubl
 
 void export_nodes(const pmlsh_index* x, int32_t* level, int32_t* first_leaf, int32_t* end_leaf,
                   float* radius) {
-    NodeInfo I = fetch_nodes(x);
+    const int64_t N = x->n_nodes;
+    std::vector<int32_t> cb(N), ce(N);
+    std::vector<float> rad(N);
+    PMLSH_HIP(hipMemcpy(cb.data(), x->tree.child_begin, N * 4, hipMemcpyDeviceToHost));
+    PMLSH_HIP(hipMemcpy(ce.data(), x->tree.child_end, N * 4, hipMemcpyDeviceToHost));
+    PMLSH_HIP(hipMemcpy(rad.data(), x->tree.radius, N * 4, hipMemcpyDeviceToHost));
+    NodeInfo I = node_info(x, cb.data(), ce.data(), rad.data());
     std::copy(I.level.begin(), I.level.end(), level);
     std::copy(I.lf.begin(), I.lf.end(), first_leaf);
     std::copy(I.le.begin(), I.le.end(), end_leaf);
