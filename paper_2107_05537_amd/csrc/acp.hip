@@ -790,20 +790,43 @@ __global__ __launch_bounds__(WG) void acp_kth_small_kernel(const uint32_t* __res
 // b - a - 1 (and, with ii/jj, the ids i < j), and adds the top 11 bits of
 // every distance to the device-wide histogram ghist (first radix pass of the
 // k-th smallest seed).
+//
+// Bounded by the FP32 vector units (66 steps of 32 operations per lane at 130
+// dimensions) once what was beside them is gone: columns past the last are
+// not summed, the next 64 columns are in flight during a step, the LDS rows
+// are SJ_ROW apart with the upper half of a row two columns on (no two of a
+// wave's 32 addresses in one bank), and the distances leave through LDS row
+// by row, so that a store covers consecutive pairs.
 constexpr int SJ_THREADS = 320;
 constexpr int SJ_TASKS = 272;
 constexpr int SJ_CK = 64;
-__global__ __launch_bounds__(SJ_THREADS) void acp_seed_join_kernel(
+constexpr int SJ_ROW = 67;
+constexpr int SJ_PRE = (64 * (SJ_CK / 4) + SJ_THREADS - 1) / SJ_THREADS;
+__device__ __forceinline__ int sj_col(int c) { return c + (c >= SJ_CK / 2 ? 2 : 0); }
+__global__ __launch_bounds__(SJ_THREADS, 5) void acp_seed_join_kernel(
     const float* __restrict__ data, int d_pad, const int32_t* __restrict__ perm, int64_t n,
     int L, uint32_t* __restrict__ k0, uint32_t* __restrict__ ii, uint32_t* __restrict__ jj,
     uint32_t* __restrict__ ghist) {
-    __shared__ float xs[64][SJ_CK + 1];
+    __shared__ float xs[64 * SJ_ROW];
     __shared__ float part[SJ_TASKS / 2][16];
     __shared__ uint32_t hist[NB];
     const int64_t leaf = blockIdx.x;
     const int64_t p0 = leaf * L;
     const int cnt = (int)(n - p0 < L ? n - p0 : L);
     const int t = threadIdx.x;
+    float4 pre[SJ_PRE];
+    auto fetch = [&](int c0) {
+        const int w = d_pad - c0 < SJ_CK ? d_pad - c0 : SJ_CK;
+#pragma unroll
+        for (int u = 0; u < SJ_PRE; ++u) {
+            const int e = t + u * SJ_THREADS;
+            const int r = e / (SJ_CK / 4), q = e % (SJ_CK / 4);
+            pre[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (r < cnt && 4 * q < w)
+                pre[u] = *reinterpret_cast<const float4*>(data + (p0 + r) * d_pad + c0 + 4 * q);
+        }
+    };
+    fetch(0);
     for (int i = t; i < NB; i += SJ_THREADS) hist[i] = 0;
     const bool task = t < SJ_TASKS;
     const int bl = t >> 1, half = t & 1;
@@ -813,29 +836,36 @@ __global__ __launch_bounds__(SJ_THREADS) void acp_seed_join_kernel(
         ++bi;
     }
     const int bj = bi + rem;
+    const float* pa = xs + 4 * bi * SJ_ROW + sj_col(half * (SJ_CK / 2));
+    const float* pb = xs + 4 * bj * SJ_ROW + sj_col(half * (SJ_CK / 2));
     float acc0[16], acc1[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) { acc0[q] = 0.f; acc1[q] = 0.f; }
     for (int c0 = 0; c0 < d_pad; c0 += SJ_CK) {
-        const int w = d_pad - c0 < SJ_CK ? d_pad - c0 : SJ_CK;
         __syncthreads();
-        for (int e = t; e < 64 * (SJ_CK / 4); e += SJ_THREADS) {
+#pragma unroll
+        for (int u = 0; u < SJ_PRE; ++u) {
+            const int e = t + u * SJ_THREADS;
             const int r = e / (SJ_CK / 4), q = e % (SJ_CK / 4);
-            float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (r < cnt && 4 * q < w)
-                val = *reinterpret_cast<const float4*>(data + (p0 + r) * d_pad + c0 + 4 * q);
-            xs[r][4 * q] = val.x;
-            xs[r][4 * q + 1] = val.y;
-            xs[r][4 * q + 2] = val.z;
-            xs[r][4 * q + 3] = val.w;
+            if (r < 64) {
+                float* to = xs + r * SJ_ROW + sj_col(4 * q);
+                to[0] = pre[u].x;
+                to[1] = pre[u].y;
+                to[2] = pre[u].z;
+                to[3] = pre[u].w;
+            }
         }
         __syncthreads();
+        if (c0 + SJ_CK < d_pad) fetch(c0 + SJ_CK);
         if (task) {
-            for (int i = 0; i < SJ_CK / 2; i += 2) {
-                const int dd = half * (SJ_CK / 2) + i;
+            // the half's columns below d_pad (a multiple of 4): the others
+            // hold zeros, which would leave every sum as it is
+            int lim = d_pad - c0 - half * (SJ_CK / 2);
+            lim = lim < SJ_CK / 2 ? lim : SJ_CK / 2;
+            for (int i = 0; i < lim; i += 2) {
                 float xa[4], xb[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) { xa[r] = xs[4 * bi + r][dd]; xb[r] = xs[4 * bj + r][dd]; }
+                for (int r = 0; r < 4; ++r) { xa[r] = pa[r * SJ_ROW + i]; xb[r] = pb[r * SJ_ROW + i]; }
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -844,7 +874,7 @@ __global__ __launch_bounds__(SJ_THREADS) void acp_seed_join_kernel(
                         acc0[4 * r + s] = __fmaf_rn(df, df, acc0[4 * r + s]);
                     }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) { xa[r] = xs[4 * bi + r][dd + 1]; xb[r] = xs[4 * bj + r][dd + 1]; }
+                for (int r = 0; r < 4; ++r) { xa[r] = pa[r * SJ_ROW + i + 1]; xb[r] = pb[r * SJ_ROW + i + 1]; }
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -861,27 +891,32 @@ __global__ __launch_bounds__(SJ_THREADS) void acp_seed_join_kernel(
         for (int q = 0; q < 16; ++q) part[bl][q] = __fadd_rn(acc0[q], acc1[q]);
     }
     __syncthreads();
+    // the squared distances as a 64 x 64 matrix in the rows' place (every
+    // wave is past its last read of them)
     if (task && half == 0) {
-        const int64_t out0 = seed_base(leaf, L);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int a = 4 * bi + r, b = 4 * bj + s;
-                if (a < b && b < cnt) {
-                    const float d2 = __fadd_rn(__fadd_rn(acc0[4 * r + s], acc1[4 * r + s]),
-                                               part[bl][4 * r + s]);
-                    const uint32_t bits = __float_as_uint(d2);
-                    const int64_t p = out0 + (int64_t)a * (2 * cnt - a - 1) / 2 + (b - a - 1);
-                    k0[p] = bits;
-                    if (ii) {
-                        const uint32_t ia = (uint32_t)perm[p0 + a], ib = (uint32_t)perm[p0 + b];
-                        ii[p] = ia < ib ? ia : ib;
-                        jj[p] = ia < ib ? ib : ia;
-                    }
-                    atomicAdd(&hist[bits >> 21], 1u);
-                }
+            for (int s = 0; s < 4; ++s)
+                xs[(4 * bi + r) * SJ_ROW + 4 * bj + s] =
+                    __fadd_rn(__fadd_rn(acc0[4 * r + s], acc1[4 * r + s]), part[bl][4 * r + s]);
+    }
+    __syncthreads();
+    const int lane = lane_id();
+    const uint32_t ib = ii && lane < cnt ? (uint32_t)perm[p0 + lane] : 0u;
+    const int64_t out0 = seed_base(leaf, L);
+    for (int a = t >> 6; a + 1 < cnt; a += SJ_THREADS / 64) {
+        const uint32_t ia = __shfl(ib, a);
+        if (lane > a && lane < cnt) {
+            const uint32_t bits = __float_as_uint(xs[a * SJ_ROW + lane]);
+            const int64_t p = out0 + (int64_t)a * (2 * cnt - a - 1) / 2 + (lane - a - 1);
+            k0[p] = bits;
+            if (ii) {
+                ii[p] = ia < ib ? ia : ib;
+                jj[p] = ia < ib ? ib : ia;
             }
+            atomicAdd(&hist[bits >> 21], 1u);
+        }
     }
     __syncthreads();
     for (int i = t; i < NB; i += SJ_THREADS)
