@@ -208,6 +208,22 @@ __device__ __forceinline__ int block_sum(int v, Smem& sh) {
     return s;
 }
 
+// Sum over each 16 lanes in all of them, by rotations of the lanes within the
+// vector unit rather than exchanges through the LDS: the value that adding the
+// lane 8, 4, 2 and 1 apart gives (a rotation by r reaches that lane or one
+// that holds the same partial sum).
+__device__ __forceinline__ float sum16(float x) {
+    auto turned = [](float v, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+            0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    x += turned(x, std::integral_constant<int, 0x128>{});   // row_ror:8
+    x += turned(x, std::integral_constant<int, 0x124>{});   // row_ror:4
+    x += turned(x, std::integral_constant<int, 0x122>{});   // row_ror:2
+    x += turned(x, std::integral_constant<int, 0x121>{});   // row_ror:1
+    return x;
+}
+
 // Inclusive prefix sum over the wave (row shifts, then the row totals).
 __device__ __forceinline__ int wave_inclusive_scan(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
@@ -634,11 +650,7 @@ __device__ void verify(const AnnArgs& a, const float* qs, const int32_t* cpos, f
         }
 #pragma unroll
         for (int r = 0; r < VR; ++r) {
-            float v = acc[r];
-            v += __shfl_xor(v, 8, 16);
-            v += __shfl_xor(v, 4, 16);
-            v += __shfl_xor(v, 2, 16);
-            v += __shfl_xor(v, 1, 16);
+            const float v = sum16(acc[r]);
             if (ok[r] && l16 == 0) cdist[base + g + GROUPS * r] = v;
         }
     }
@@ -692,11 +704,7 @@ __device__ void verify_list(const AnnArgs& a, const float* qs, const int32_t* cp
         }
 #pragma unroll
         for (int r = 0; r < VR; ++r) {
-            float v = acc[r];
-            v += __shfl_xor(v, 8, 16);
-            v += __shfl_xor(v, 4, 16);
-            v += __shfl_xor(v, 2, 16);
-            v += __shfl_xor(v, 1, 16);
+            const float v = sum16(acc[r]);
             if (ok[r] && l16 == 0) {
                 lo2[mi[r]] = v;
                 hi2[mi[r]] = v;
@@ -772,20 +780,26 @@ __device__ void verify16(const AnnArgs& a, const float* qs, const int32_t* cpos,
         }
 #pragma unroll
         for (int r = 0; r < VR; ++r) {
-            float v = acc[r];
-            v += __shfl_xor(v, 8, 16);
-            v += __shfl_xor(v, 4, 16);
-            v += __shfl_xor(v, 2, 16);
-            v += __shfl_xor(v, 1, 16);
-            if (ok[r] && l16 == 0) {
-                const float eps = se[r].y;
-                const float dlo = sqrtf(v * (1.f - gam)) * (1.f - 4.f * u);
-                const float dhi = sqrtf(v * (1.f + 2.f * gam)) * (1.f + 4.f * u);
-                const float tlo = fmaxf((dlo - eps) * (1.f - 2.f * u), 0.f);
-                const float thi = (dhi + eps) * (1.f + 2.f * u);
-                lo2[base + g + GROUPS * r] = tlo * tlo * (1.f - gam) * (1.f - 4.f * u);
-                hi2[base + g + GROUPS * r] = thi * thi * (1.f + gam) * (1.f + 4.f * u);
-            }
+            acc[r] = sum16(acc[r]);
+        }
+        // lane r of a group takes row r's bounds: one pass of this arithmetic
+        // for the VR rows
+        float v = acc[0], eps = se[0].y;
+        bool mine = ok[0] && l16 == 0;
+#pragma unroll
+        for (int r = 1; r < VR; ++r) {
+            v = l16 == r ? acc[r] : v;
+            eps = l16 == r ? se[r].y : eps;
+            mine = mine || (ok[r] && l16 == r);
+        }
+        if (mine) {
+            const float dlo = sqrtf(v * (1.f - gam)) * (1.f - 4.f * u);
+            const float dhi = sqrtf(v * (1.f + 2.f * gam)) * (1.f + 4.f * u);
+            const float tlo = fmaxf((dlo - eps) * (1.f - 2.f * u), 0.f);
+            const float thi = (dhi + eps) * (1.f + 2.f * u);
+            const int i = base + g + GROUPS * l16;
+            lo2[i] = tlo * tlo * (1.f - gam) * (1.f - 4.f * u);
+            hi2[i] = thi * thi * (1.f + gam) * (1.f + 4.f * u);
         }
     }
 }
