@@ -127,6 +127,7 @@ struct AnnArgs {
     uint16_t* cgmin;
     int64_t cgroups, gld;
     int glds;                   // bound kernel: group minima copied to LDS
+    int ordered;                // the pool kernels take the queries in mask_kernel's order
     int grp_cap;                // bound kernel: most groups or blocks listed (<= kGrpCap)
     // bounded verification: FP16 rows (stride d16), their scales and error
     // bounds, and per C member a lower bound of its squared distance (the
@@ -161,7 +162,8 @@ struct Smem {
     int32_t red[kMaxWaves * 2];
     int32_t cnt0, cnt1, cnt2;
     int32_t thr_bin, thr_below, thr_in;
-    int32_t pad_[2];
+    uint32_t near;
+    int32_t pad_;
     uint64_t skey[CAP];
     int32_t spos[CAP];
 };
@@ -1490,12 +1492,20 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     // passes visit only the ngl groups listed (the whole row when more than
     // a.grp_cap groups qualify).
     clear_hist(sh);
-    for (int j = threadIdx.x; j < ngr; j += WG) atomicAdd(&sh.hist[cbin(gmin[j])], 1u);
+    // the nearest group besides, for the order that the queries finish in
+    uint32_t near = 0xffffffffu;
+    for (int j = threadIdx.x; j < ngr; j += WG) {
+        const uint32_t h = gmin[j];
+        atomicAdd(&sh.hist[cbin(h)], 1u);
+        near = min(near, (h << 16) | (uint32_t)min(j, 0xffff));
+    }
     if (threadIdx.x == 0) {
         sh.thr_bin = NB - 1;
         sh.cnt0 = 0;
+        sh.near = 0xffffffffu;
     }
     __syncthreads();
+    if (a.ordered) atomicMin(&sh.near, near);
     uint32_t b0 = NB - 1;
     if (ngr >= wc) {
         find_threshold(wc, sh);
@@ -1664,7 +1674,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     if (threadIdx.x == 0) {
         a.l_count[qi * a.l_stride] = 0u;
         a.q_scanned[qi] = 0u;   // mask_kernel adds 64 per passing chunk
-        a.q_flag[qi] = 0;
+        a.q_flag[qi] = a.ordered ? (int32_t)(sh.near & 0xffffu) : 0;
         if (qi == 0) a.pq_list[0] = 0u;   // the flagged list of the batch starts empty
         // The query's FP16 row of the matrix-core scan, q' taken relative to
         // the centre of the rows. thr = tau^2 - |q'|^2 plus 96 u (|q'| + S)^2
@@ -1719,6 +1729,59 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) dst[i] = src[i];
     }
+}
+
+// ---- The order that the three finishing kernels of pools take the queries in ----
+//
+// Queries near one another in the leaf order gather many of the same rows, and
+// each XCD has an L2 of its own. Within a window of kOrderWindow queries they
+// are ranked by the nearest group of 64 chunks (ties by index; the group is
+// about 2 MB of FP16 rows at 256 dimensions, half an L2), and the workgroups
+// of an XCD (every eighth one) take a run of consecutive ranks. Each answer
+// stays where it belongs; only the time of the gathers changes. The bound
+// kernel leaves the group's number in the query's flag, which the finishing
+// kernels write later, and the query of a rank goes to the front of the row of
+// group minima with that rank, which nobody reads after the bound kernel.
+// us per call in order of index / of rank, 1,024 queries: 1M x 256 at B =
+// 4,800 842 / 800; 1M x 960 without contrast, B = 1,010, 764 / 757; 256
+// queries, 200,000 x 128 at B = 20,001, 423 / 415. Below kLeanBudget the rows
+// are too few to pay for the detour (1M x 256, B = 875, 207 / 210; 10M x 128,
+// B = 750, 466 / 498), and fewer than 64 queries share too little.
+constexpr int kOrderWindow = 1024;
+
+// The ranks of queries q0 + first, q0 + first + step, ... below q0 + nqb in
+// their window, by one wave (nqb <= 64 and q0 a multiple of 64: one window).
+__device__ void order_queries(const AnnArgs& a, int q0, int nqb, int first, int step) {
+    if (first >= nqb) return;
+    const int w0 = q0 / kOrderWindow * kOrderWindow;
+    const int nw = min(kOrderWindow, a.nq - w0);
+    const int lane = lane_id();
+    int32_t key[kOrderWindow / 64];
+#pragma unroll
+    for (int u = 0; u < kOrderWindow / 64; ++u)
+        key[u] = lane + 64 * u < nw ? a.q_flag[w0 + lane + 64 * u] : 0x7fffffff;
+    for (int i = first; i < nqb; i += step) {
+        const int me = q0 - w0 + i;
+        const int32_t mine = a.q_flag[w0 + me];
+        int rank = 0;
+#pragma unroll
+        for (int u = 0; u < kOrderWindow / 64; ++u)
+            rank += __popcll(__ballot(key[u] < mine || (key[u] == mine && lane + 64 * u < me)));
+        if (lane == 0)
+            *reinterpret_cast<int32_t*>(a.cgmin + (int64_t)(w0 + rank) * a.gld) = w0 + me;
+    }
+}
+
+// Place `b` of `n` workgroups in an order whose runs of consecutive places go
+// to one XCD each (workgroup b runs on XCD b % 8).
+__device__ __forceinline__ uint32_t xcd_place(uint32_t b, uint32_t n) {
+    const uint32_t x = b & 7u, rem = n & 7u;
+    return x * (n >> 3) + min(x, rem) + (b >> 3);
+}
+
+// The query of a finishing kernel's place.
+__device__ __forceinline__ int64_t query_of(const AnnArgs& a, uint32_t place) {
+    return *reinterpret_cast<const int32_t*>(a.cgmin + (int64_t)place * a.gld);
 }
 
 // The chunk-ball test of Eq. 5 for every (query, chunk) pair of the batch,
@@ -1799,6 +1862,8 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
     }
     if (a.out_stats && (int)threadIdx.x < nqb && cnt[threadIdx.x])
         atomicAdd(&a.q_scanned[q0 + threadIdx.x], 64u * cnt[threadIdx.x]);
+    if (a.ordered)
+        order_queries(a, q0, nqb, blockIdx.x * NWAVE + (threadIdx.x >> 6), gridDim.x * NWAVE);
 }
 
 // ---- Matrix-core scan (the range filter of the batched path) ----
@@ -2547,7 +2612,7 @@ template <int T>
 __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
-    const int64_t qi = blockIdx.x;
+    const int64_t qi = a.ordered ? query_of(a, xcd_place(blockIdx.x, gridDim.x)) : blockIdx.x;
     const AnnQueryParams qpar = query_params(a, qi);
     const int B = qpar.budget;
     const uint32_t cnt = a.l_count[qi * a.l_stride];
@@ -2715,14 +2780,17 @@ __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
     if (threadIdx.x == 0) a.q_flag[qi] = sh.cnt0;
 }
 
-// Distance bounds of the members in the first ball: blockIdx.y the query,
-// blockIdx.x the slice of a.vslice members.
+// Distance bounds of the members in the first ball: slices of a.vslice members
+// of each query (blockIdx.x and .y, placed like the other kernels' queries, so
+// that all slices of a run of queries are one XCD's).
 __global__ __launch_bounds__(WG) void pool_verify_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     float* qs = reinterpret_cast<float*>(smem_raw);
-    const int64_t qi = blockIdx.y;
+    uint32_t at = blockIdx.y * gridDim.x + blockIdx.x;
+    if (a.ordered) at = xcd_place(at, gridDim.x * gridDim.y);
+    const int64_t qi = a.ordered ? query_of(a, at / gridDim.x) : at / gridDim.x;
     const int n1 = a.q_flag[qi];
-    const int v0 = (int)blockIdx.x * a.vslice;
+    const int v0 = (int)(at % gridDim.x) * a.vslice;
     if (v0 >= n1) return;
     const float* qrow = a.q + qi * a.d;
     for (int j = threadIdx.x; j < a.d16; j += WG) qs[j] = j < a.d ? qrow[j] : 0.f;
@@ -2736,7 +2804,7 @@ __global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
     float* qs = reinterpret_cast<float*>(smem_raw + ((sizeof(Smem) + 15) & ~size_t(15)));
-    const int64_t qi = blockIdx.x;
+    const int64_t qi = a.ordered ? query_of(a, xcd_place(blockIdx.x, gridDim.x)) : blockIdx.x;
     const int n1 = a.q_flag[qi];
     if (n1 < 0) return;   // the per-query kernel's
     const AnnQueryParams qpar = query_params(a, qi);
@@ -3005,6 +3073,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             StageTimer tm(PMLSH_STAGE_TAU, stream);
             const int64_t ngr = (nchunk + 63) / 64;
             a.sample = ann_bound_sample(x);
+            a.ordered = L.nq >= 64 && (L.budget > kLeanBudget || x.low_contrast);
             a.sel_cap = (int)std::min<int64_t>(kSelMax, std::max<int64_t>(kSelCap, (a.sample * L.budget + 63) / 64 + 1));
             a.grp_cap = (int)std::min<int64_t>(kGrpCap, std::max<int64_t>(0, tune_get(PMLSH_TUNE_GROUP_LIST)));
             const size_t min_bytes = 2 * (size_t)((ngr + 7) & ~7);
