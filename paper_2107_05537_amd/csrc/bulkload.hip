@@ -69,46 +69,102 @@ __global__ __launch_bounds__(256) void bl_sum_kernel(const float* __restrict__ p
     }
 }
 
+// The value that lane (l + N) & 15 of the lane's row of 16 holds.
+template <int N>
+__device__ __forceinline__ double lane_ahead(double v) {
+    if constexpr (N == 0) return v;
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x120 + 16 - N,
+                                                              0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32),
+                                                              0x120 + 16 - N, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 // Centred second moments (upper triangle) of every piece about its node's
-// mean: 64 points at a time through LDS, one thread per matrix entry.
-__global__ __launch_bounds__(256) void bl_cov_kernel(const float* __restrict__ proj,
+// mean, on the FP64 matrix cores. v_mfma_f64_4x4x4 adds four points to four
+// 4 x 4 blocks of the matrix, each entry as four fused multiply-adds in the
+// order of the points, so an entry is the same chain of roundings over its
+// piece as a loop of fma would give. Lane 16 k + 4 b + i holds coordinate
+// 4 b + i of point k: as it stands that is block row b of the left operand,
+// and turned by 4 w lanes within each 16 the block column (b + w) & 3 of the
+// right one, so wave w = 0, 1, 2 of a workgroup forms the blocks w off the
+// diagonal (of the last two pairs each comes twice) from one load per lane.
+//
+// What it was bound by: two LDS reads per multiply-add and point, 64 dependent
+// steps between loads that nothing overlapped. Now the gathers of the rows
+// (64 bytes each) bound it, kCovAhead x 64 of them in flight per wave; the
+// chain takes 22 clocks per four points. A level of 1M points: 206 to 278 us
+// before, 81 to 119 now (3.8 and 1.7 ms a build).
+constexpr int kCovAhead = 4;     // chunks of 64 points in flight
+static_assert(MP == 16, "a row is a lane's row of 16");
+template <int W>
+__device__ void cov_wave(const float* __restrict__ proj, const int32_t* __restrict__ perm,
+                         const Piece& pc, const double* __restrict__ mean,
+                         double* __restrict__ part) {
+    const int lane = threadIdx.x & 63, k = lane >> 4, c = lane & 15;
+    const double mu = mean[(int64_t)pc.seg * MP + c];
+    double acc = 0.0;
+    float v[kCovAhead][16];
+    auto ids = [&](int base) { return perm[min(base + lane, pc.e - 1)]; };
+    // step u of a chunk takes its points 4 u .. 4 u + 3
+    auto fetch = [&](float (&to)[16], int32_t id) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            to[u] = proj[(int64_t)__shfl(id, 4 * u + k) * MP + c];
+    };
+    auto add = [&](const float (&from)[16], int base) {
+        if (base + 64 <= pc.e) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const double x = (double)from[u] - mu;
+                acc = __builtin_amdgcn_mfma_f64_4x4x4f64(x, lane_ahead<4 * W>(x), acc, 0, 0, 0);
+            }
+        } else {
+            // points past the piece add a product of zeros
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const double x = base + 4 * u + k < pc.e ? (double)from[u] - mu : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_4x4x4f64(x, lane_ahead<4 * W>(x), acc, 0, 0, 0);
+            }
+        }
+    };
+    int32_t next[kCovAhead];
+#pragma unroll
+    for (int s = 0; s < kCovAhead; ++s) next[s] = ids(pc.b + 64 * s);
+#pragma unroll
+    for (int s = 0; s < kCovAhead; ++s) {
+        fetch(v[s], next[s]);
+        next[s] = ids(pc.b + 64 * (s + kCovAhead));
+    }
+    for (int base = pc.b; base < pc.e; base += 64 * kCovAhead) {
+#pragma unroll
+        for (int s = 0; s < kCovAhead; ++s) {
+            const int at = base + 64 * s;
+            if (at < pc.e) add(v[s], at);
+            fetch(v[s], next[s]);
+            next[s] = ids(at + 64 * 2 * kCovAhead);
+        }
+    }
+    // lane 16 i + 4 b + j: entry (i, j) of block (b, (b + W) & 3)
+    const int b = (lane >> 2) & 3;
+    const int r0 = 4 * b + k, c0 = 4 * ((b + W) & 3) + (lane & 3);
+    const int r = min(r0, c0), q = max(r0, c0);
+    const bool mine = W == 0 ? r0 <= c0 : W == 1 || b < 2;
+    if (mine) part[(int64_t)blockIdx.x * kCov + r * MP - r * (r - 1) / 2 + (q - r)] = acc;
+}
+
+__global__ __launch_bounds__(192) void bl_cov_kernel(const float* __restrict__ proj,
                                                       const int32_t* __restrict__ perm,
                                                       const Piece* __restrict__ pieces,
                                                       const double* __restrict__ mean,
                                                       double* __restrict__ part) {
     const Piece pc = pieces[blockIdx.x];
-    __shared__ double tile[64][MP + 1];
-    __shared__ double mu[MP];
-    if (threadIdx.x < MP) mu[threadIdx.x] = mean[(int64_t)pc.seg * MP + threadIdx.x];
-    // entry t of the upper triangle: row j, column k >= j
-    int ej = 0, ek = 0;
-    if (threadIdx.x < kCov) {
-        int t = threadIdx.x, j = 0;
-        while (t >= MP - j) { t -= MP - j; ++j; }
-        ej = j;
-        ek = j + t;
+    switch (threadIdx.x >> 6) {
+        case 0: cov_wave<0>(proj, perm, pc, mean, part); break;
+        case 1: cov_wave<1>(proj, perm, pc, mean, part); break;
+        default: cov_wave<2>(proj, perm, pc, mean, part); break;
     }
-    double acc = 0.0;
-    __syncthreads();
-    for (int base = pc.b; base < pc.e; base += 64) {
-        const int cnt = min(64, pc.e - base);
-        {
-            const int q = threadIdx.x >> 2, c0 = (threadIdx.x & 3) * 4;
-            if (q < cnt) {
-                const float4 v = *reinterpret_cast<const float4*>(
-                    proj + (int64_t)perm[base + q] * MP + c0);
-                tile[q][c0] = (double)v.x - mu[c0];
-                tile[q][c0 + 1] = (double)v.y - mu[c0 + 1];
-                tile[q][c0 + 2] = (double)v.z - mu[c0 + 2];
-                tile[q][c0 + 3] = (double)v.w - mu[c0 + 3];
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < kCov)
-            for (int q = 0; q < cnt; ++q) acc = fma(tile[q][ej], tile[q][ek], acc);
-        __syncthreads();
-    }
-    if (threadIdx.x < kCov) part[(int64_t)blockIdx.x * kCov + threadIdx.x] = acc;
 }
 
 // Per node and entry, the sum of its pieces' partial values in piece order,
@@ -855,7 +911,7 @@ void device_split(const float* proj, int64_t n, int leaf, hipStream_t st,
                            dpart);
         hipLaunchKernelGGL(bl_reduce_kernel, dim3((unsigned)(((int64_t)m * MP + 255) / 256)),
                            dim3(256), 0, st, dpart, MP, dpb, m, dcnt, dmean);
-        hipLaunchKernelGGL(bl_cov_kernel, dim3((unsigned)np), dim3(256), 0, st, proj, perm, dp,
+        hipLaunchKernelGGL(bl_cov_kernel, dim3((unsigned)np), dim3(192), 0, st, proj, perm, dp,
                            dmean, dpart);
         hipLaunchKernelGGL(bl_reduce_kernel, dim3((unsigned)(((int64_t)m * kCov + 255) / 256)),
                            dim3(256), 0, st, dpart, kCov, dpb, m, nullptr, dcov);
