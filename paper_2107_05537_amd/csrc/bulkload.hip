@@ -31,37 +31,65 @@ struct Piece {
 };
 
 // Coordinate sums of every piece (four waves, shuffle then LDS, fixed order);
-// positions are ids when perm is null.
+// positions are ids when perm is null. The pieces of leaves fill one wave: the
+// others skip the sums, which took longer than the rows (15,625 leaves: 140 us
+// before, 80 now); of the large pieces the gathers are the bound (32 us
+// a level of 1M points before, 28 now).
+constexpr int kSumAhead = 4;
 __global__ __launch_bounds__(256) void bl_sum_kernel(const float* __restrict__ proj,
                                                       const int32_t* perm,
                                                       const Piece* __restrict__ pieces,
                                                       double* __restrict__ part) {
     const Piece pc = pieces[blockIdx.x];
-    double acc[MP];
-#pragma unroll
-    for (int j = 0; j < MP; ++j) acc[j] = 0.0;
-    for (int i = pc.b + (int)threadIdx.x; i < pc.e; i += 256) {
-        const int64_t row = perm ? (int64_t)perm[i] : (int64_t)i;
-        const float4* p = reinterpret_cast<const float4*>(proj + row * MP);
-#pragma unroll
-        for (int q = 0; q < MP / 4; ++q) {
-            const float4 v = p[q];
-            acc[4 * q] += v.x;
-            acc[4 * q + 1] += v.y;
-            acc[4 * q + 2] += v.z;
-            acc[4 * q + 3] += v.w;
-        }
-    }
     __shared__ double red[4][MP];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (pc.b + 64 * w < pc.e) {
+        double acc[MP];
 #pragma unroll
-    for (int j = 0; j < MP; ++j) {
-        double v = acc[j];
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        acc[j] = v;
+        for (int j = 0; j < MP; ++j) acc[j] = 0.0;
+        // kSumAhead rows in flight per thread, added in their order
+        for (int i = pc.b + (int)threadIdx.x; i < pc.e; i += 256 * kSumAhead) {
+            float4 v[kSumAhead][MP / 4];
+#pragma unroll
+            for (int u = 0; u < kSumAhead; ++u) {
+                const int at = min(i + 256 * u, pc.e - 1);
+                const int64_t row = perm ? (int64_t)perm[at] : (int64_t)at;
+                const float4* p = reinterpret_cast<const float4*>(proj + row * MP);
+#pragma unroll
+                for (int q = 0; q < MP / 4; ++q) v[u][q] = p[q];
+            }
+#pragma unroll
+            for (int u = 0; u < kSumAhead; ++u) {
+                if (i + 256 * u >= pc.e) break;
+#pragma unroll
+                for (int q = 0; q < MP / 4; ++q) {
+                    acc[4 * q] += v[u][q].x;
+                    acc[4 * q + 1] += v[u][q].y;
+                    acc[4 * q + 2] += v[u][q].z;
+                    acc[4 * q + 3] += v[u][q].w;
+                }
+            }
+        }
+        // the sums over the wave, lanes 32, 16, 8, 4, 2 and 1 apart in turn;
+        // while more than one coordinate is left each lane keeps half of them
+        // and hands the other half over
+#pragma unroll
+        for (int h = MP / 2; h > 0; h >>= 1) {
+            const int off = 4 * h;
+            const bool up = (lane & off) != 0;
+#pragma unroll
+            for (int j = 0; j < h; ++j) {
+                const double give = up ? acc[j] : acc[j + h];
+                const double keep = up ? acc[j + h] : acc[j];
+                acc[j] = keep + __shfl_xor(give, off);
+            }
+        }
+        acc[0] += __shfl_xor(acc[0], 2);
+        acc[0] += __shfl_xor(acc[0], 1);
+        if ((lane & 3) == 0) red[w][lane >> 2] = acc[0];
+    } else if (lane < MP) {
+        red[w][lane] = 0.0;
     }
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int j = 0; j < MP; ++j) red[threadIdx.x >> 6][j] = acc[j];
     __syncthreads();
     if (threadIdx.x < MP) {
         const int j = threadIdx.x;
@@ -531,10 +559,22 @@ __global__ void bl_centre_kernel(const double* __restrict__ mean, int64_t count,
     if (t < count) cf[t] = (float)mean[t];
 }
 
+// The reduction of v over the wave by f (its order does not matter): rotations
+// within each row of 16 lanes, then the other rows.
+template <class F>
+__device__ __forceinline__ double wave_of(double v, F f) {
+    v = f(v, lane_ahead<8>(v));
+    v = f(v, lane_ahead<4>(v));
+    v = f(v, lane_ahead<2>(v));
+    v = f(v, lane_ahead<1>(v));
+    v = f(v, __shfl_xor(v, 16));
+    return f(v, __shfl_xor(v, 32));
+}
+
 // Per piece: the largest FP64 distance of its points to their node's FP32
 // centre, and for every pivot the smallest and largest distance to it
 // (width 1 + 2 s per piece; min and max do not depend on the order).
-__global__ __launch_bounds__(256) void bl_ring_kernel(const float* __restrict__ proj,
+__global__ __launch_bounds__(256, 4) void bl_ring_kernel(const float* __restrict__ proj,
                                                        const int32_t* __restrict__ perm,
                                                        const Piece* __restrict__ pieces,
                                                        const float* __restrict__ cf,
@@ -567,6 +607,9 @@ __global__ __launch_bounds__(256) void bl_ring_kernel(const float* __restrict__ 
         rad = fmax(rad, dist64(p, c));
 #pragma unroll
         for (int t = 0; t < PMLSH_MAX_PIVOTS; ++t) {
+            // the pivots are read again for every point: kept in registers
+            // over the loop they leave room for one wave per SIMD
+            asm volatile("" ::: "memory");
             if (t < s) {
                 const double dd = dist64(p, pv[t]);
                 lo[t] = fmin(lo[t], dd);
@@ -574,15 +617,18 @@ __global__ __launch_bounds__(256) void bl_ring_kernel(const float* __restrict__ 
             }
         }
     }
-    for (int off = 32; off > 0; off >>= 1) rad = fmax(rad, __shfl_xor(rad, off));
+    // (a wave without points holds the neutral values already)
+    const int w = threadIdx.x >> 6;
+    if (pc.b + 64 * w < pc.e) {
+        rad = wave_of(rad, [](double a, double b) { return fmax(a, b); });
 #pragma unroll
-    for (int t = 0; t < PMLSH_MAX_PIVOTS; ++t) {
-        for (int off = 32; off > 0; off >>= 1) {
-            lo[t] = fmin(lo[t], __shfl_xor(lo[t], off));
-            hi[t] = fmax(hi[t], __shfl_xor(hi[t], off));
+        for (int t = 0; t < PMLSH_MAX_PIVOTS; ++t) {
+            if (t < s) {
+                lo[t] = wave_of(lo[t], [](double a, double b) { return fmin(a, b); });
+                hi[t] = wave_of(hi[t], [](double a, double b) { return fmax(a, b); });
+            }
         }
     }
-    const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         red[w][0] = rad;
         for (int t = 0; t < s; ++t) {
