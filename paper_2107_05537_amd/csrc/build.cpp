@@ -97,6 +97,8 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
     const int64_t n = a->n;
     const int d = a->d;
 
+    BuildScratch scratch(n);
+
     // ---- inputs on the device
     TmpBuf dsrc, hsrc;
     const float* D = a->data;
