@@ -127,7 +127,8 @@ struct AnnArgs {
     uint16_t* cgmin;
     int64_t cgroups, gld;
     int glds;                   // bound kernel: group minima copied to LDS
-    int ordered;                // the pool kernels take the queries in mask_kernel's order
+    int ordered;                // the pool kernels take the queries in the order q_order,
+    int32_t* q_order;           // which mask_kernel writes
     int grp_cap;                // bound kernel: most groups or blocks listed (<= kGrpCap)
     // bounded verification: FP16 rows (stride d16), their scales and error
     // bounds, and per C member a lower bound of its squared distance (the
@@ -1740,8 +1741,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
 // of an XCD (every eighth one) take a run of consecutive ranks. Each answer
 // stays where it belongs; only the time of the gathers changes. The bound
 // kernel leaves the group's number in the query's flag, which the finishing
-// kernels write later, and the query of a rank goes to the front of the row of
-// group minima with that rank, which nobody reads after the bound kernel.
+// kernels write later.
 // us per call in order of index / of rank, 1,024 queries: 1M x 256 at B =
 // 4,800 842 / 800; 1M x 960 without contrast, B = 1,010, 764 / 757; 256
 // queries, 200,000 x 128 at B = 20,001, 423 / 415. Below kLeanBudget the rows
@@ -1767,8 +1767,7 @@ __device__ void order_queries(const AnnArgs& a, int q0, int nqb, int first, int 
 #pragma unroll
         for (int u = 0; u < kOrderWindow / 64; ++u)
             rank += __popcll(__ballot(key[u] < mine || (key[u] == mine && lane + 64 * u < me)));
-        if (lane == 0)
-            *reinterpret_cast<int32_t*>(a.cgmin + (int64_t)(w0 + rank) * a.gld) = w0 + me;
+        if (lane == 0) a.q_order[w0 + rank] = w0 + me;
     }
 }
 
@@ -1781,7 +1780,7 @@ __device__ __forceinline__ uint32_t xcd_place(uint32_t b, uint32_t n) {
 
 // The query of a finishing kernel's place.
 __device__ __forceinline__ int64_t query_of(const AnnArgs& a, uint32_t place) {
-    return *reinterpret_cast<const int32_t*>(a.cgmin + (int64_t)place * a.gld);
+    return a.q_order[place];
 }
 
 // The chunk-ball test of Eq. 5 for every (query, chunk) pair of the batch,
@@ -1886,7 +1885,8 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
 // compare all pairs of a batch at 16 x 16 x 32 per instruction.
 //
 // Grid: x strides over 64-point chunks, y over blocks of 512 or 1,024 queries;
-// each wave of a workgroup owns up to two of the block's mask words (128 queries).
+// each wave of a workgroup owns two or four of the block's mask words (128 or 256
+// queries).
 // For each chunk a wave packs the queries whose chunk-ball test passed (the
 // set bits of its mask words) into a list and runs the MFMA on groups of 16
 // listed queries, so a group's 16 columns are all queries that may hold
@@ -1899,11 +1899,12 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
 // result register r of lane l holds point 4 (l / 16) + r of the tile and
 // listed query l % 16.
 
-// Two block shapes of the scan, 128 queries per wave in both: 512 queries in
-// four waves (four workgroups per compute unit) for indexes of fewer than
-// kScanLargeChunks chunks, 1,024 in eight waves (two per compute unit) above:
-// staging a block's query rows is a fixed cost per workgroup, paid back only
-// when a workgroup has many chunks to scan. Four waves per SIMD in either
+// Two block shapes of the scan: 512 queries in four waves of 128 (four
+// workgroups per compute unit) for indexes of fewer than kScanLargeChunks
+// chunks, 1,024 in sixteen waves of 256 (one per compute unit) above: staging a
+// block's query rows is a fixed cost per workgroup, and with 128 queries per
+// wave a chunk's rows are read by twice as many waves (10M x 128, 1,024
+// queries: 296 us against 187 with 256). Four waves per SIMD in either
 // (128 VGPRs, two chunk slots in flight): the loop's query lists, matrix products
 // and ballots wait on one another, and more waves hide more of that than deeper
 // slots did. 1M x 256, 1,024 queries, us, three waves with four slots / four
@@ -2960,7 +2961,8 @@ void launch_finish(const AnnArgs& a, const AnnLaunch& L, int lds, hipStream_t st
 // over many workgroups, at the cost of two launches: for a few queries, for
 // budgets whose lists (1.0 to 1.3 B) outgrow the LDS keys, and without contrast,
 // where the lists are longer still. us per call at 1M x 256, threads 256 / 512 /
-// 1,024 / three kernels:
+// 1,024 / three kernels (taken when a row's bounds still cost 5 to 8 % more of
+// the call, in all four alike):
 //   1 query      B = 160  67 /  68 /  72 /  73    900 110 /  98 /  90 /  86
 //   256 queries  B = 160  91 /  89 /  91 / 103    900 134 / 119 / 113 / 125
 //   512          B = 160 106 / 106 / 131 / 120    900 175 / 159 / 180 / 174
@@ -3052,6 +3054,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         a.ws_clo = L.ws_clo;
         a.l_val = L.l_val;
         a.q_flag = L.q_flag;
+        a.q_order = L.q_order;
         a.pq_list = L.pq_list;
         // A query's candidate count sits where its members go later, so that
         // the counts of different queries are on lines of their own: the

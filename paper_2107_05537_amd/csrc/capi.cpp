@@ -188,8 +188,8 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
     int32_t* topk = reinterpret_cast<int32_t*>(cdist + batch * B);
     float* clo = reinterpret_cast<float*>(topk + batch * 3 * (int64_t)k);
     int32_t* q_flag = reinterpret_cast<int32_t*>(clo + (fast ? batch * B : 0));
-    uint32_t* l_count = reinterpret_cast<uint32_t*>(q_flag + batch);
-    uint32_t* q_scanned = l_count + batch;
+    int32_t* q_order = q_flag + batch;
+    uint32_t* q_scanned = reinterpret_cast<uint32_t*>(q_order + batch);
     // count, then the queries the batched path hands to the per-query kernel
     uint32_t* pq_list = q_scanned + batch;
     // low-precision query projections and their bounds (filter_gemm)
@@ -232,7 +232,7 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
             L.ws_cdist2 = cdist2;
             L.ws_cgmin = cgmin;
             L.q_flag = q_flag;
-            L.l_count = l_count;
+            L.q_order = q_order;
             L.q_scanned = q_scanned;
             L.pq_list = pq_list;
             L.ws_qlp = lp ? qlp : nullptr;

@@ -389,7 +389,7 @@ struct AnnLaunch {
     int32_t* ws_topk;       // nq x 3 x k
     // leaf-major fast path, per query
     int32_t* q_flag;
-    uint32_t* l_count;
+    int32_t* q_order;       // nq: the order that pools are finished in
     uint32_t* q_scanned;
     uint32_t* pq_list;      // count, then the queries flagged for the per-query kernel
     uint32_t* l_list;       // nq x pool_cap leaf positions (candidate pool)
