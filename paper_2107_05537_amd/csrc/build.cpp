@@ -134,8 +134,25 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
         std::vector<SplitNode> split;
         x->perm = dev_alloc<int32_t>(x, n);
         device_split(static_cast<const float*>(phi.p), n, x->leaf_size, st, x->perm, &split);
+        // the leaf-order copies need the permutation alone: they run while the
+        // host rounds the node summaries
+        auto leaf_order_copies = [&] {
+            x->inv_perm = dev_alloc<int32_t>(x, n);
+            device_invert(x->perm, n, x->inv_perm, st);
+            x->data = dev_alloc<float>(x, n * x->d_pad);
+            x->proj_hi = dev_alloc<float>(x, n * MP);
+            x->proj_lo = dev_alloc<float>(x, n * MP);
+            launch_gather_rows(D, d, d, x->perm, n, x->data, x->d_pad, st);
+            launch_gather_proj(static_cast<const float*>(phi.p), x->perm, n, x->proj_hi, st);
+            launch_gather_proj(static_cast<const float*>(plo.p), x->perm, n, x->proj_lo, st);
+            // FP16 copy for the bounded verification
+            x->d16 = (x->d + 7) / 8 * 8;
+            x->data16 = dev_alloc<uint16_t>(x, n * x->d16);
+            x->data16_se = dev_alloc<float2>(x, n);
+            launch_half_rows(x->data, n, x->d_pad, x->d16, x->data16, x->data16_se, st);
+        };
         build_tree(static_cast<const float*>(phi.p), n, x->leaf_size, x->fanout, x->num_pivots,
-                   x->perm, split, st, &T);
+                   x->perm, split, st, leaf_order_copies, &T);
     }
     x->levels = T.levels;
     x->n_nodes = T.n_nodes;
@@ -149,8 +166,6 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
         PMLSH_HIP(hipMemcpyAsync(*dst, vec.data(), vec.size() * sizeof(E),
                                  hipMemcpyHostToDevice, st));
     };
-    x->inv_perm = dev_alloc<int32_t>(x, n);
-    device_invert(x->perm, n, x->inv_perm, st);
     upload(T.centre, &x->tree.centre);
     upload(T.radius, &x->tree.radius);
     upload(T.hr_min, &x->tree.hr_min);
@@ -161,19 +176,6 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
     std::vector<float> piv = T.pivots;
     if (piv.empty()) piv.assign(MP, 0.f);
     upload(piv, &x->tree.pivots);
-
-    // ---- leaf-order copies
-    x->data = dev_alloc<float>(x, n * x->d_pad);
-    x->proj_hi = dev_alloc<float>(x, n * MP);
-    x->proj_lo = dev_alloc<float>(x, n * MP);
-    launch_gather_rows(D, d, d, x->perm, n, x->data, x->d_pad, st);
-    launch_gather_proj(static_cast<const float*>(phi.p), x->perm, n, x->proj_hi, st);
-    launch_gather_proj(static_cast<const float*>(plo.p), x->perm, n, x->proj_lo, st);
-    // FP16 copy for the bounded verification
-    x->d16 = (x->d + 7) / 8 * 8;
-    x->data16 = dev_alloc<uint16_t>(x, n * x->d16);
-    x->data16_se = dev_alloc<float2>(x, n);
-    launch_half_rows(x->data, n, x->d_pad, x->d16, x->data16, x->data16_se, st);
 
     // ---- chunk balls, then the FP16 rows of the matrix-core scan
     {

@@ -238,10 +238,11 @@ void device_ball_summaries(const float* proj, const int32_t* perm, const std::ve
 
 // Bulk-loads the tree over the device projection proj (n x MP, original
 // order) from the leaf order (perm_dev, on the device) and the split tree of
-// device_split.
+// device_split. `meanwhile` is called once, where the device's work on the tree
+// is done and the host's is not.
 void build_tree(const float* proj, int64_t n, int leaf_size, int fanout, int num_pivots,
                 const int32_t* perm_dev, const std::vector<SplitNode>& split, hipStream_t st,
-                HostTree* out);
+                const std::function<void()>& meanwhile, HostTree* out);
 
 // ---------------------------------------------------------------- index
 struct DeviceTree {

@@ -42,7 +42,7 @@ float round_down(double v) {
 
 void build_tree(const float* proj, int64_t n, int leaf_size, int fanout, int num_pivots,
                 const int32_t* perm_dev, const std::vector<SplitNode>& bt, hipStream_t st,
-                HostTree* out) {
+                const std::function<void()>& meanwhile, HostTree* out) {
     HostTree& T = *out;
     const int s = num_pivots;
 
@@ -123,6 +123,7 @@ void build_tree(const float* proj, int64_t n, int leaf_size, int fanout, int num
     std::vector<float> cen;
     std::vector<double> rad, ring;
     device_ball_summaries(proj, perm_dev, p0, p1, T.pivots.data(), s, st, &cen, &rad, &ring);
+    meanwhile();   // the device is idle, the rounding below is the host's
     for (int64_t i = 0; i < N; ++i) {
         for (int j = 0; j < MP; ++j) T.centre[(size_t)j * N + i] = cen[(size_t)i * MP + j];
         T.radius[i] = round_up(rad[(size_t)i]);
