@@ -444,6 +444,7 @@ __device__ __forceinline__ int wave_sum(int x) {
 // Lanes with a PD candidate range of at most this many pairs each take them
 // one by one; a wider tile is scanned whole.
 constexpr int kSparseMax = 40;
+constexpr int kScanStage = 256;   // pairs staged per wave
 
 // The pairs of the surviving tiles (leaves of at most 64 points), one wave
 // per contiguous run of the tile list; lane a holds point a of the first
@@ -464,9 +465,10 @@ constexpr int kSparseMax = 40;
 // exchanges, the rows of the second leaf), little of which most tiles need: a
 // tile none of whose lanes can hold a pair is left after x and the two ends of
 // the sorted PDs, and a pair is ruled out before its row is read. 200,000 x 512:
-// 229 us when every tile searched, 96 now.
+// 229 us when every tile searched, 96 now. Where millions of pairs are found
+// (branch and bound) the one counter's atomics bound it, hence the stage.
 __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
-    const float* __restrict__ phi, const float* __restrict__ plo, const float* __restrict__ ppd,
+    const float* __restrict__ phi, const float* __restrict__ plo,
     const float4* __restrict__ skey, const float* __restrict__ lcen, const int32_t* __restrict__ perm, int64_t n, int L,
     const int2* __restrict__ tiles, int64_t n_tiles, float R2, float Rlim,
     uint32_t* __restrict__ ck0, uint32_t* __restrict__ cii, uint32_t* __restrict__ cjj,
@@ -487,6 +489,41 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
     float h1[MP], l1[MP];
     int held = -1, ca = 0;
     uint32_t id1 = 0;
+    // Pairs found, staged per wave: one reservation on the one counter for up
+    // to kScanStage of them.
+    __shared__ uint32_t stage[WG / 64][3][kScanStage];
+    uint32_t(&mine_st)[3][kScanStage] = stage[threadIdx.x >> 6];
+    int staged = 0;
+    auto flush = [&] {
+        if (staged == 0) return;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(counter, (unsigned long long)staged);
+        base = __shfl(base, 0);
+        for (int e = lane; e < staged; e += 64) {
+            const int64_t slot = (int64_t)base + e;
+            if (slot < cap) {
+                ck0[slot] = mine_st[0][e];
+                cii[slot] = mine_st[1][e];
+                cjj[slot] = mine_st[2][e];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        staged = 0;
+    };
+    auto emit = [&](bool hit, float pd2, uint32_t id2) {
+        const uint64_t m = __ballot(hit);
+        if (!m) return;
+        if (staged + 64 > kScanStage) flush();
+        if (hit) {
+            const int e = staged + __popcll(m & ((1ull << lane) - 1ull));
+            mine_st[0][e] = __float_as_uint(pd2);
+            mine_st[1][e] = id1 < id2 ? id1 : id2;
+            mine_st[2][e] = id1 < id2 ? id2 : id1;
+        }
+        staged += __popcll(m);
+    };
     // Two tiles ahead the tile's index is loaded, one tile ahead its second
     // leaf's centre and sorted PDs (which need that index): a tile then waits
     // for one memory round trip begun a whole tile earlier instead of two in
@@ -604,19 +641,18 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
                     hit = pd2 < R2;
                     id2 = (uint32_t)perm[b0 + b];
                 }
-                const int64_t slot = wave_append_global(hit, counter);
-                if (hit && slot < cap) {
-                    ck0[slot] = __float_as_uint(pd2);
-                    cii[slot] = id1 < id2 ? id1 : id2;
-                    cjj[slot] = id1 < id2 ? id2 : id1;
-                }
+                emit(hit, pd2, id2);
             }
         } else {
-            // 2b. the whole tile: the loop takes b, whose row every lane reads
-            for (int b = 0; b < cb; ++b) {
-                const float yb = ppd[b0 + b];
+            // 2b. the whole tile: the loop takes the points of e2 in the order of
+            // their PDs, whose row every lane reads when some lane needs it
+            for (int pos = 0; pos < cb; ++pos) {
+                const float yb = readlane_f(y, pos);
+                const int b = __builtin_amdgcn_readlane(sb, pos);
                 const bool near = lane < ca && (!diag || b > lane) &&
-                                  fabsf(x - yb) - 32.f * u * (x + yb) < Rlim;
+                                  fabsf(x - yb) - 32.f * u * (x + yb) < Rlim &&
+                                  fabsf(h1[0] - readlane_f(c0, pos)) < rc &&
+                                  fabsf(h1[1] - readlane_f(c1, pos)) < rc;
                 if (!__ballot(near)) continue;
                 const float* hb = phi + (b0 + b) * MP;
                 const float* lb = plo + (b0 + b) * MP;
@@ -627,16 +663,13 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
                     pd2 = __fmaf_rn(dt, dt, pd2);
                 }
                 const bool hit = near && pd2 < R2;
+                if (!__ballot(hit)) continue;
                 const uint32_t id2 = (uint32_t)perm[b0 + b];
-                const int64_t slot = wave_append_global(hit, counter);
-                if (hit && slot < cap) {
-                    ck0[slot] = __float_as_uint(pd2);
-                    cii[slot] = id1 < id2 ? id1 : id2;
-                    cjj[slot] = id1 < id2 ? id2 : id1;
-                }
+                emit(hit, pd2, id2);
             }
         }
     }
+    flush();
 }
 
 // ---------------------------------------------------------------- seeds
@@ -1993,7 +2026,7 @@ struct TileScan {
         if (wave) {
             const int64_t waves = std::min<int64_t>(n_tiles, 16384);
             hipLaunchKernelGGL(acp_tile_scan_wave_kernel, dim3((unsigned)((waves + 3) / 4)),
-                               dim3(WG), 0, st, x->proj_hi, x->proj_lo, ppd.as<float>(),
+                               dim3(WG), 0, st, x->proj_hi, x->proj_lo,
                                skey.as<float4>(), lcen.as<float>(), x->perm, x->n,
                                x->leaf_size, tiles, n_tiles, R2, Rlim, k0, ii, jj, cap, counter,
                                dn_tiles, rad);
