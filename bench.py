@@ -250,7 +250,7 @@ def config3_bench(pm, torch, dev, cs=(1.2, 1.5, 2.0),
             rat = overall_ratio(torch, D, Q, ids, truth_dist)
             stn = st.cpu().numpy().astype(np.int64)
             row = {"c": c, "beta": beta, "budget_B": int(plan["budget"]),
-                   "path": "batched" if plan["budget"] <= 2048 else "per-query",
+                   "path": "batched" if plan["budget"] <= 196608 else "per-query",
                    "recall@10": round(rec, 4), "overall_ratio": round(rat, 6),
                    "queries_per_s": round(Q.shape[0] / el, 1),
                    "mean_C": round(float(stn[:, 1].mean()), 1),

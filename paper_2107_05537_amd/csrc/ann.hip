@@ -1743,8 +1743,8 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
 // kernel leaves the group's number in the query's flag, which the finishing
 // kernels write later.
 // us per call in order of index / of rank, 1,024 queries: 1M x 256 at B =
-// 4,800 842 / 800; 1M x 960 without contrast, B = 1,010, 764 / 757; 256
-// queries, 200,000 x 128 at B = 20,001, 423 / 415. Below kLeanBudget the rows
+// 4,899 842 / 800; 1M x 960 without contrast, B = 1,010, 764 / 757; 256
+// queries, 200,000 x 128 at B = 19,349, 423 / 415. Below kLeanBudget the rows
 // are too few to pay for the detour (1M x 256, B = 875, 207 / 210; 10M x 128,
 // B = 750, 466 / 498), and fewer than 64 queries share too little.
 constexpr int kOrderWindow = 1024;
@@ -1909,7 +1909,7 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
 // and ballots wait on one another, and more waves hide more of that than deeper
 // slots did. 1M x 256, 1,024 queries, us, three waves with four slots / four
 // with three / four with two / four with one: B = 885 54 / 70 / 48 / 52;
-// B = 4,810 139 / 145 / 127 / 132; 1M x 960 without contrast 284 / 239 / 226 / 230
+// B = 4,899 139 / 145 / 127 / 132; 1M x 960 without contrast 284 / 239 / 226 / 230
 // (with empty chunks skipped and the denser staging 43, 118 and 183 now).
 struct ScanSmall { static constexpr int QB = 512, QW = 128, NW = 4, WGS = 4, STG = 512; };
 struct ScanLarge { static constexpr int QB = 1024, QW = 256, NW = 16, WGS = 1, STG = 512; };
@@ -2598,8 +2598,8 @@ __global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
 // No step holds a whole list in LDS, so they take any budget up to
 // kWideBudget. Budgets above kLeanBudget used to go to the per-query kernel,
 // whose tree walk and leaf scans run query by query: 1M x 256, 1,024 queries
-// of B = 4,810 26.6 ms (now cut 118 us, verify 348 us, answer 79 us, 0.80 ms
-// in all); 200,000 x 128, 256 queries of B = 19,200 4.7 ms (66, 144, 44 us,
+// of B = 4,899 26.6 ms (now cut 118 us, verify 348 us, answer 79 us, 0.80 ms
+// in all); 200,000 x 128, 256 queries of B = 19,349 4.7 ms (66, 144, 44 us,
 // 0.41 ms). The cut is bound by the 64-byte projection rows of the pool
 // (gathered through 128-byte lines), the verification by HBM (the FP16 rows of
 // all members), the answer by the latency of its passes.
