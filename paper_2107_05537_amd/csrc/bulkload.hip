@@ -802,9 +802,11 @@ struct DevVec {
 }  // namespace
 
 // The build's largest buffers come to 46 bytes per point and its level lists
-// to some 20 more; what does not fit is allocated on its own.
+// to some 20 more; what does not fit is allocated on its own. Beyond 2 GB (22
+// million points) the allocations are short beside the build, and memory that
+// stays idle between its stages could be missed.
 BuildScratch::BuildScratch(int64_t n) {
-    const size_t want = (size_t)n * 96 + (size_t(1) << 20);
+    const size_t want = std::min<size_t>((size_t)n * 96 + (size_t(1) << 20), size_t(2) << 30);
     if (hipMalloc(&base_, want) != hipSuccess) {
         (void)hipGetLastError();
         base_ = nullptr;
