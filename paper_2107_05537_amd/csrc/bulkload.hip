@@ -282,11 +282,11 @@ __global__ __launch_bounds__(256) void bl_keys_kernel(const float* __restrict__ 
 // result does not depend on the scatter's order, equal keys keep theirs and
 // never gather in one bucket. One workgroup per node, as a segmented sort has
 // it, leaves the chip idle at the top of the tree: at 1M points it took 5.4 ms
-// per level on average (146 of the build's 195 ms); this takes 0.15 ms (sorting
-// 0.09, samples 0.025, buckets and scatter 0.03), bound by the LDS passes of the
-// bitonic network (256 / 512 / 1,024 threads: 91 / 66 / 64 us per launch;
-// ranges of 2,048 cost more bucket passes than they save). 10M points: 1.74 s
-// of sorts per build before.
+// per level on average (146 of the build's 195 ms); this takes 0.1 ms (sorting
+// 0.05, samples 0.016, buckets and scatter 0.03), bound by the LDS passes of the
+// bitonic network (256 / 512 / 1,024 threads with one step per pass: 91 / 66 /
+// 64 us per launch; ranges of 2,048 cost more bucket passes than they save).
+// 10M points: 1.74 s of sorts per build before.
 constexpr int kSortCap = 4096;
 constexpr int kBucket = 1536;
 constexpr int kOver = 16;
@@ -334,33 +334,71 @@ __device__ __forceinline__ SortKey load_key(const double* key, const uint64_t* s
     return r;
 }
 
-// Bitonic sort of the n <= capacity keys in LDS (padded to a power of two).
+// Element i of a list sorted in LDS: one free place after every 16, so that
+// lanes eight elements apart do not meet in one bank.
+__device__ __forceinline__ int lds_at(int i) { return i + (i >> 4); }
+constexpr int lds_places(int n) { return n + n / 16; }
+
+// The steps of distances h 2^(S-1), ..., 2 h, h of a bitonic merge of runs of k,
+// 2^S elements in registers per thread and pass.
+template <int T, int S>
+__device__ __forceinline__ void merge_steps(uint64_t* sk, uint32_t* sp, int P, int k, int h) {
+    constexpr int E = 1 << S;
+    for (int t = threadIdx.x; t < P >> S; t += T) {
+        const int base = ((t & ~(h - 1)) << S) | (t & (h - 1));
+        const bool up = (base & k) == 0;
+        uint64_t a[E];
+        uint32_t b[E];
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            a[m] = sk[lds_at(base + m * h)];
+            b[m] = sp[lds_at(base + m * h)];
+        }
+#pragma unroll
+        for (int q = S - 1; q >= 0; --q) {
+#pragma unroll
+            for (int m = 0; m < E; ++m) {
+                const int x = m | (1 << q);
+                if (x == m) continue;
+                const bool swap = key_less(a[x], b[x], a[m], b[m]) == up;
+                const uint64_t ta = a[m];
+                const uint32_t tb = b[m];
+                a[m] = swap ? a[x] : ta;
+                b[m] = swap ? b[x] : tb;
+                a[x] = swap ? ta : a[x];
+                b[x] = swap ? tb : b[x];
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            sk[lds_at(base + m * h)] = a[m];
+            sp[lds_at(base + m * h)] = b[m];
+        }
+    }
+    __syncthreads();
+}
+
+// Sorts n elements (at lds_at(0) .. lds_at(n - 1), lds_places of the next power
+// of two reserved) by (key, position). Three steps of the bitonic network per
+// pass over the LDS: 26 passes and barriers for 2,048 elements instead of 66,
+// which is what it is bound by (1M points: 66 us per launch of the ranges' sorts
+// with one step per pass, 38 now; the largest samples 118, 60).
 template <int T>
 __device__ void sort_lds(uint64_t* sk, uint32_t* sp, int n) {
     int P = 2;
     while (P < n) P <<= 1;
     for (int i = n + (int)threadIdx.x; i < P; i += T) {
-        sk[i] = ~0ull;
-        sp[i] = ~0u;
+        sk[lds_at(i)] = ~0ull;
+        sp[lds_at(i)] = ~0u;
     }
     __syncthreads();
     for (int k = 2; k <= P; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = threadIdx.x; t < P / 2; t += T) {
-                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-                const int x = i | j;
-                const bool up = (i & k) == 0;
-                const uint64_t a = sk[i], b = sk[x];
-                const uint32_t pa = sp[i], pb = sp[x];
-                if (key_less(b, pb, a, pa) == up) {
-                    sk[i] = b;
-                    sk[x] = a;
-                    sp[i] = pb;
-                    sp[x] = pa;
-                }
-            }
-            __syncthreads();
-        }
+        int j = k >> 1;
+        for (; j >= 4; j >>= 3) merge_steps<T, 3>(sk, sp, P, k, j >> 2);
+        if (j == 2)
+            merge_steps<T, 2>(sk, sp, P, k, 1);
+        else if (j == 1)
+            merge_steps<T, 1>(sk, sp, P, k, 1);
     }
 }
 
@@ -373,19 +411,19 @@ __global__ __launch_bounds__(kSampleWg) void bl_sample_kernel(
     const CutRange r = ranges[blockIdx.x];
     const int ns = r.k * kOver;
     uint64_t* sk = reinterpret_cast<uint64_t*>(smem);
-    uint32_t* sp = reinterpret_cast<uint32_t*>(sk + kMaxBuckets * kOver);
+    uint32_t* sp = reinterpret_cast<uint32_t*>(sk + lds_places(kMaxBuckets * kOver));
     const int64_t len = r.e - r.b;
     for (int i = threadIdx.x; i < ns; i += kSampleWg) {
         const SortKey v = load_key(key, skey, spos, r.scattered, r.b + (int32_t)(i * len / ns));
-        sk[i] = v.k;
-        sp[i] = v.p;
+        sk[lds_at(i)] = v.k;
+        sp[lds_at(i)] = v.p;
     }
     __syncthreads();
     sort_lds<kSampleWg>(sk, sp, ns);
     for (int i = threadIdx.x; i < r.k; i += kSampleWg) {
         const int at = min((i + 1) * kOver, ns - 1);
-        split_k[r.first + i] = sk[at];
-        split_p[r.first + i] = sp[at];
+        split_k[r.first + i] = sk[lds_at(at)];
+        split_p[r.first + i] = sp[lds_at(at)];
         count[r.first + i] = 0;
     }
 }
@@ -486,20 +524,20 @@ __global__ __launch_bounds__(kSortWg) void bl_sort_kernel(
     const uint64_t* __restrict__ skey, const uint32_t* __restrict__ spos,
     const int32_t* __restrict__ perm, double* __restrict__ key_out,
     int32_t* __restrict__ perm_out) {
-    __shared__ uint64_t sk[kSortCap];
-    __shared__ uint32_t sp[kSortCap];
+    __shared__ uint64_t sk[lds_places(kSortCap)];
+    __shared__ uint32_t sp[lds_places(kSortCap)];
     const SortRange r = ranges[blockIdx.x];
     const int n = r.e - r.b;
     for (int i = threadIdx.x; i < n; i += kSortWg) {
         const SortKey v = load_key(key, skey, spos, r.scattered, r.b + i);
-        sk[i] = v.k;
-        sp[i] = v.p;
+        sk[lds_at(i)] = v.k;
+        sp[lds_at(i)] = v.p;
     }
     __syncthreads();
     sort_lds<kSortWg>(sk, sp, n);
     for (int i = threadIdx.x; i < n; i += kSortWg) {
-        key_out[r.b + i] = from_ordered_bits(sk[i]);
-        if (perm) perm_out[r.b + i] = perm[sp[i]];
+        key_out[r.b + i] = from_ordered_bits(sk[lds_at(i)]);
+        if (perm) perm_out[r.b + i] = perm[sp[lds_at(i)]];
     }
 }
 
@@ -914,7 +952,8 @@ struct LevelSort {
                                      hipMemcpyHostToDevice, st));
             PMLSH_HIP(hipMemcpyAsync(dp, pieces.data(), pieces.size() * sizeof(Piece),
                                      hipMemcpyHostToDevice, st));
-            constexpr int lds = kMaxBuckets * kOver * (int)(sizeof(uint64_t) + sizeof(uint32_t));
+            constexpr int lds = lds_places(kMaxBuckets * kOver) *
+                                (int)(sizeof(uint64_t) + sizeof(uint32_t));
             PMLSH_HIP(hipFuncSetAttribute((const void*)bl_sample_kernel,
                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds));
             const dim3 gr((unsigned)cut.size()), gp((unsigned)pieces.size());
