@@ -2356,6 +2356,142 @@ __device__ uint32_t select_u32(int n, int need, uint32_t lo, uint32_t hi, Get&& 
     }
 }
 
+// L from a list of any length, which stays in memory: emit(take, position, pd^2
+// bits), called by whole waves, gets the B of its n >= B entries, sh.cnt0 and
+// sh.cnt1 being zero before the first. The B-th smallest pd^2 by radix passes;
+// the FP64 order decides around it as in cut_fp64, so L is the same whichever
+// kernel finishes a query and whatever queries it came with; the FP32 order with
+// ties by id when more than kBandCap entries lie there.
+template <int T, class Emit>
+__device__ void pool_cut(const AnnArgs& a, int64_t qi, const QueryCtx& qc, const uint32_t* list,
+                         int n, int B, Emit&& emit, Smem& sh) {
+    // the pd^2 bits are computed once into l_val (or again in every pass, where
+    // the workspace has no room for them)
+    uint32_t* val = a.l_val ? a.l_val + qi * a.q_cap : nullptr;
+    auto compute = [&](int i) {
+        return __float_as_uint(proj_dist2(a.proj + (int64_t)(int32_t)list[i] * MP, qc.qp));
+    };
+    auto get = [&](int i) { return val ? val[i] : compute(i); };
+    // f(valid, entry, bits) for every entry, wave-uniform, four loads in flight
+    auto for_pool = [&](auto&& f) {
+        for (int b0 = 0; b0 < n; b0 += 4 * T) {
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = get(min(b0 + u * T + (int)threadIdx.x, n - 1));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = b0 + u * T + threadIdx.x;
+                f(i < n, min(i, n - 1), v[u]);
+            }
+        }
+    };
+    // the bin of the B-th: 256 bins per octave up to the test radius, which at
+    // least B entries do not exceed
+    const float tq = a.qtest[qi].x;
+    const uint32_t hb = __float_as_uint(tq * tq) >> 15;
+    const uint32_t base = hb > (uint32_t)(NB - 1) ? hb - (uint32_t)(NB - 1) : 0u;
+    clear_hist<T>(sh);
+    if (threadIdx.x == 0) {
+        sh.thr_bin = NB - 1;
+        sh.thr_below = 0;
+    }
+    for (int b0 = 0; b0 < n; b0 += 4 * T) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = compute(min(b0 + u * T + (int)threadIdx.x, n - 1));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = b0 + u * T + threadIdx.x;
+            if (i >= n) break;
+            if (val) val[i] = v[u];
+            atomicAdd(&sh.hist[min(radius_bin(__uint_as_float(v[u]), base), NB - 1)], 1u);
+        }
+    }
+    __syncthreads();
+    find_threshold<T>(B, sh);
+    const uint32_t tb = (uint32_t)sh.thr_bin;
+    const int before = sh.thr_below;
+    __syncthreads();
+    const uint32_t k2 = select_u32<T>(
+        n, B - before, tb == 0u ? 0u : (base + tb) << 15,
+        tb == (uint32_t)(NB - 1) ? 0xffffffffu : ((base + tb + 1u) << 15) - 1u, get, sh);
+    // the FP64 order decides inside the band of cut_fp64
+    constexpr int kBandCap = 512;
+    int32_t* band = reinterpret_cast<int32_t*>(sh.hist);              // entry
+    uint32_t* bid = reinterpret_cast<uint32_t*>(sh.hist + kBandCap);  // its id
+    double* b64 = reinterpret_cast<double*>(sh.hist + 2 * kBandCap);  // its FP64 pd^2
+    const float kf = __uint_as_float(k2);
+    const float big = sqrtf(qc.qn2) + a.coord_scale;
+    const float e = 2.f * (2.384185791015625e-07f * sqrtf(kf) * big + 1.9073486328125e-06f * kf);
+    const float blo = kf - 2.f * e, bhi = kf + 2.f * e;
+    if (threadIdx.x == 0) sh.cnt2 = 0;
+    __syncthreads();
+    int below = 0, less = 0, equal = 0;
+    for_pool([&](bool ok, int i, uint32_t b) {
+        const float v = __uint_as_float(b);
+        below += ok && v < blo;
+        less += ok && b < k2;
+        equal += ok && b == k2;
+        const bool inb = ok && v >= blo && v <= bhi;
+        const int slot = wave_append(inb, &sh.cnt2);
+        if (inb && slot < kBandCap) {
+            band[slot] = i;
+            bid[slot] = (uint32_t)a.perm[list[i]];
+        }
+    });
+    below = block_sum<T>(below, sh);
+    less = block_sum<T>(less, sh);
+    equal = block_sum<T>(equal, sh);
+    const int nb = sh.cnt2;
+    const bool by64 = nb <= kBandCap && below < B && below + nb >= B;
+    float flim = bhi;          // by64: everything below blo, and the band or part of it
+    uint32_t idlim = 0xffffffffu;
+    if (by64 && below + nb > B) {
+        for (int j = threadIdx.x; j < nb; j += T) {
+            const int64_t pos = list[band[j]];
+            double acc = 0.0;
+#pragma unroll
+            for (int t = 0; t < MP; ++t) {
+                const double o = (double)a.proj[pos * MP + t] + (double)a.proj_lo[pos * MP + t];
+                const double q = (double)a.qp[qi * MP + t] + (double)a.qp_lo[qi * MP + t];
+                const double dd = q - o;
+                acc = fma(dd, dd, acc);
+            }
+            b64[j] = acc;
+        }
+        flim = -1.f;   // the band's members are emitted from the list below
+    } else if (!by64 && less + equal > B) {
+        // more entries than wanted at the B-th value: the smallest ids of them
+        idlim = select_u32<T>(
+            n, B - less, 0u, 0x7fffffffu,
+            [&](int i) { return get(i) == k2 ? (uint32_t)a.perm[list[i]] : 0xffffffffu; }, sh);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
+    __syncthreads();
+    for_pool([&](bool ok, int i, uint32_t b) {
+        const float v = __uint_as_float(b);
+        bool take = ok && (by64 ? v < blo || v <= flim : b <= k2);
+        if (idlim != 0xffffffffu && take && b == k2) take = (uint32_t)a.perm[list[i]] <= idlim;
+        emit(take, take ? (int32_t)list[i] : 0, b);
+    });
+    if (by64 && flim < 0.f) {
+        const int want = B - below;
+        for (int b0 = 0; b0 < nb; b0 += T) {
+            const int j = b0 + threadIdx.x;
+            int rank = want;
+            if (j < nb) {
+                const double v = b64[j];
+                const uint32_t id = bid[j];
+                rank = 0;
+                for (int y = 0; y < nb; ++y) rank += b64[y] < v || (b64[y] == v && bid[y] < id);
+            }
+            const bool take = rank < want;
+            emit(take, take ? (int32_t)list[band[j]] : 0, take ? get(band[j]) : 0u);
+        }
+    }
+}
+
 // The answer from the bounds lo2 <= exact <= hi2 of the n_ver members i < lim of
 // C with member(i): the top-k and the statistics.
 template <int T, class Member>
@@ -2470,11 +2606,10 @@ __global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
     int32_t* cpos = a.ws_cpos + qi * (int64_t)a.budget;
     float* cdist = a.ws_cdist + qi * (int64_t)a.budget;
     const uint32_t* list = a.l_list + qi * a.q_cap;
-    const int32_t* perm = a.perm;
     const int n = (int)cnt;
 
-    // L: the B smallest (pd^2 bits, id) of the list, kept in LDS as keys and
-    // leaf positions (entries outside L get the key ~0). Every ball of the
+    // L: the B smallest (pd^2, id) of the list, kept in LDS as keys (pd^2 bits,
+    // the entry's number) and leaf positions (entries outside L get the key ~0). Every ball of the
     // rounds below holds the members of L with pd^2 bits <= its radius bits,
     // which is the prefix of L in (pd^2, id) order, so L needs no sorting.
     int nl;
@@ -2483,27 +2618,18 @@ __global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
         lds_cut<T>(a, qi, qc, list, n, B, sh);
         nl = n;
     } else {
-        auto list_src = [&](auto&& v) {
-            for (int base = 0; base < n; base += T) {
-                const int i = base + threadIdx.x;
-                const bool valid = i < n;
-                uint64_t key = 0;
-                int32_t pos = 0;
-                if (valid) {
-                    pos = (int32_t)list[i];
-                    const float pd2 = proj_dist2(a.proj + (int64_t)pos * MP, qc.qp);
-                    key = ((uint64_t)__float_as_uint(pd2) << 32) | (uint32_t)perm[pos];
-                }
-                v(valid, key, pos);
-            }
-        };
-        block_select<T>(list_src, [&](int32_t pos, int slot) { if (slot < B) cpos[slot] = pos; },
-                     0ull, ~0ull, B, false, 0, sh);
+        pool_cut<T>(
+            a, qi, qc, list, n, B,
+            [&](bool take, int32_t pos, uint32_t) {
+                const int slot = wave_append(take, &sh.cnt0);
+                if (take && slot < B) cpos[slot] = pos;
+            },
+            sh);
         __syncthreads();
         for (int j = threadIdx.x; j < B; j += T) {
             const int32_t pos = cpos[j];
             sh.skey[j] = ((uint64_t)__float_as_uint(proj_dist2(a.proj + (int64_t)pos * MP, qc.qp)) << 32) |
-                         (uint32_t)perm[pos];
+                         (uint32_t)j;
             sh.spos[j] = pos;
         }
         __syncthreads();
@@ -2653,131 +2779,7 @@ __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
         if (threadIdx.x == 0) a.q_flag[qi] = sh.cnt0;
         return;
     }
-    // A longer list stays in memory: its pd^2 bits are computed once into
-    // l_val (or again in every pass, where the workspace has no room for them).
-    uint32_t* val = a.l_val ? a.l_val + qi * a.q_cap : nullptr;
-    auto compute = [&](int i) {
-        return __float_as_uint(proj_dist2(a.proj + (int64_t)(int32_t)list[i] * MP, qc.qp));
-    };
-    auto get = [&](int i) { return val ? val[i] : compute(i); };
-    // f(valid, entry, bits) for every entry, wave-uniform, four loads in flight
-    auto for_pool = [&](auto&& f) {
-        for (int b0 = 0; b0 < n; b0 += 4 * T) {
-            uint32_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = get(min(b0 + u * T + (int)threadIdx.x, n - 1));
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = b0 + u * T + threadIdx.x;
-                f(i < n, min(i, n - 1), v[u]);
-            }
-        }
-    };
-    // the bin of the B-th: 256 bins per octave up to the test radius, which at
-    // least B entries do not exceed
-    const float tq = a.qtest[qi].x;
-    const uint32_t hb = __float_as_uint(tq * tq) >> 15;
-    const uint32_t base = hb > (uint32_t)(NB - 1) ? hb - (uint32_t)(NB - 1) : 0u;
-    clear_hist<T>(sh);
-    if (threadIdx.x == 0) {
-        sh.thr_bin = NB - 1;
-        sh.thr_below = 0;
-    }
-    for (int b0 = 0; b0 < n; b0 += 4 * T) {
-        uint32_t v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = compute(min(b0 + u * T + (int)threadIdx.x, n - 1));
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = b0 + u * T + threadIdx.x;
-            if (i >= n) break;
-            if (val) val[i] = v[u];
-            atomicAdd(&sh.hist[min(radius_bin(__uint_as_float(v[u]), base), NB - 1)], 1u);
-        }
-    }
-    __syncthreads();
-    find_threshold<T>(B, sh);
-    const uint32_t tb = (uint32_t)sh.thr_bin;
-    const int before = sh.thr_below;
-    __syncthreads();
-    const uint32_t k2 = select_u32<T>(
-        n, B - before, tb == 0u ? 0u : (base + tb) << 15,
-        tb == (uint32_t)(NB - 1) ? 0xffffffffu : ((base + tb + 1u) << 15) - 1u, get, sh);
-    // the FP64 order decides inside the band of cut_fp64
-    constexpr int kBandCap = 512;
-    int32_t* band = reinterpret_cast<int32_t*>(sh.hist);              // entry
-    uint32_t* bid = reinterpret_cast<uint32_t*>(sh.hist + kBandCap);  // its id
-    double* b64 = reinterpret_cast<double*>(sh.hist + 2 * kBandCap);  // its FP64 pd^2
-    const float kf = __uint_as_float(k2);
-    const float big = sqrtf(qc.qn2) + a.coord_scale;
-    const float e = 2.f * (2.384185791015625e-07f * sqrtf(kf) * big + 1.9073486328125e-06f * kf);
-    const float blo = kf - 2.f * e, bhi = kf + 2.f * e;
-    if (threadIdx.x == 0) sh.cnt2 = 0;
-    __syncthreads();
-    int below = 0, less = 0, equal = 0;
-    for_pool([&](bool ok, int i, uint32_t b) {
-        const float v = __uint_as_float(b);
-        below += ok && v < blo;
-        less += ok && b < k2;
-        equal += ok && b == k2;
-        const bool inb = ok && v >= blo && v <= bhi;
-        const int slot = wave_append(inb, &sh.cnt2);
-        if (inb && slot < kBandCap) {
-            band[slot] = i;
-            bid[slot] = (uint32_t)a.perm[list[i]];
-        }
-    });
-    below = block_sum<T>(below, sh);
-    less = block_sum<T>(less, sh);
-    equal = block_sum<T>(equal, sh);
-    const int nb = sh.cnt2;
-    const bool by64 = nb <= kBandCap && below < B && below + nb >= B;
-    float flim = bhi;          // by64: everything below blo, and the band or part of it
-    uint32_t idlim = 0xffffffffu;
-    if (by64 && below + nb > B) {
-        for (int j = threadIdx.x; j < nb; j += T) {
-            const int64_t pos = list[band[j]];
-            double acc = 0.0;
-#pragma unroll
-            for (int t = 0; t < MP; ++t) {
-                const double o = (double)a.proj[pos * MP + t] + (double)a.proj_lo[pos * MP + t];
-                const double q = (double)a.qp[qi * MP + t] + (double)a.qp_lo[qi * MP + t];
-                const double dd = q - o;
-                acc = fma(dd, dd, acc);
-            }
-            b64[j] = acc;
-        }
-        flim = -1.f;   // the band's members are emitted from the list below
-    } else if (!by64 && less + equal > B) {
-        // more entries than wanted at the B-th value: the smallest ids of them
-        idlim = select_u32<T>(
-            n, B - less, 0u, 0x7fffffffu,
-            [&](int i) { return get(i) == k2 ? (uint32_t)a.perm[list[i]] : 0xffffffffu; }, sh);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
-    __syncthreads();
-    for_pool([&](bool ok, int i, uint32_t b) {
-        const float v = __uint_as_float(b);
-        bool take = ok && (by64 ? v < blo || v <= flim : b <= k2);
-        if (idlim != 0xffffffffu && take && b == k2) take = (uint32_t)a.perm[list[i]] <= idlim;
-        emit(take, take ? (int32_t)list[i] : 0, b);
-    });
-    if (by64 && flim < 0.f) {
-        const int want = B - below;
-        for (int b0 = 0; b0 < nb; b0 += T) {
-            const int j = b0 + threadIdx.x;
-            int rank = want;
-            if (j < nb) {
-                const double v = b64[j];
-                const uint32_t id = bid[j];
-                rank = 0;
-                for (int y = 0; y < nb; ++y) rank += b64[y] < v || (b64[y] == v && bid[y] < id);
-            }
-            const bool take = rank < want;
-            emit(take, take ? (int32_t)list[band[j]] : 0, take ? get(band[j]) : 0u);
-        }
-    }
+    pool_cut<T>(a, qi, qc, list, n, B, emit, sh);
     __syncthreads();
     if (threadIdx.x == 0) a.q_flag[qi] = sh.cnt0;
 }
