@@ -1742,11 +1742,11 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
 // stays where it belongs; only the time of the gathers changes. The bound
 // kernel leaves the group's number in the query's flag, which the finishing
 // kernels write later.
-// us per call in order of index / of rank, 1,024 queries: 1M x 256 at B =
-// 4,899 842 / 800; 1M x 960 without contrast, B = 1,010, 764 / 757; 256
-// queries, 200,000 x 128 at B = 19,349, 423 / 415. Below kLeanBudget the rows
-// are too few to pay for the detour (1M x 256, B = 875, 207 / 210; 10M x 128,
-// B = 750, 466 / 498), and fewer than 64 queries share too little.
+// us per call in order of index / of rank: 1,024 queries, 1M x 256 at B = 4,899
+// 842 / 800; 256 queries, 200,000 x 128 at B = 19,349, 423 / 415. Up to
+// kLeanBudget the rows are too few to pay for the detour (1M x 256, B = 875,
+// 207 / 210; 10M x 128, B = 750, 466 / 498; 20,000 x 32 without contrast, B =
+// 300, 107 / 113), and fewer than 64 queries share too little.
 constexpr int kOrderWindow = 1024;
 
 // The ranks of queries q0 + first, q0 + first + step, ... below q0 + nqb in
@@ -2932,10 +2932,10 @@ int ann_lds_bytes(int d_pad) {
 
 namespace {
 
-// Members of L per verify workgroup: enough workgroups to fill the chip a few
-// times over, at least the 64 rows that one has in flight.
 template <int T>
 void launch_pool(AnnArgs& a, const AnnLaunch& L, int lds_cut, int lds_answer, hipStream_t stream) {
+    // members of L per verify workgroup: enough workgroups to fill the chip a few
+    // times over, at least the 64 rows that one has in flight
     const int64_t per = (L.budget * L.nq + 4095) / 4096;
     a.vslice = (int)std::min<int64_t>(512, std::max<int64_t>(64, (per + 63) / 64 * 64));
     PMLSH_HIP(hipFuncSetAttribute((const void*)pool_cut_kernel<T>,
@@ -2955,23 +2955,6 @@ void launch_finish(const AnnArgs& a, const AnnLaunch& L, int lds, hipStream_t st
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     hipLaunchKernelGGL(finish_kernel<T>, dim3((unsigned)L.nq), dim3(T), (unsigned)lds, stream, a);
 }
-
-// Which kernels finish a budget of at most kLeanBudget. One workgroup of 256
-// threads per query suits more than 512 queries: four are resident per compute
-// unit. With fewer queries the chip has room, and a query's chain of row gathers
-// (64 rows in flight per 256 threads) sets the time: 512 threads up to 512
-// queries, 1,024 up to 256 queries. The three kernels spread one query's rows
-// over many workgroups, at the cost of two launches: for a few queries, for
-// budgets whose lists (1.0 to 1.3 B) outgrow the LDS keys, and without contrast,
-// where the lists are longer still. us per call at 1M x 256, threads 256 / 512 /
-// 1,024 / three kernels (taken when a row's bounds still cost 5 to 8 % more of
-// the call, in all four alike):
-//   1 query      B = 160  67 /  68 /  72 /  73    900 110 /  98 /  90 /  86
-//   256 queries  B = 160  91 /  89 /  91 / 103    900 134 / 119 / 113 / 125
-//   512          B = 160 106 / 106 / 131 / 120    900 175 / 159 / 180 / 174
-//   1,024        B = 900 241 / 269 / 307 / 262   1,900 492 / 526 / 609 / 433
-// and at 1M x 960 without contrast, 1,024 queries of B = 1,010: 1,085 with 256
-// threads, 873 with three kernels.
 
 // Points sampled per budget point by the bound kernel. Where the chunks are
 // wider than the spread of their centres, points of every chunk lie inside the
@@ -3079,7 +3062,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             StageTimer tm(PMLSH_STAGE_TAU, stream);
             const int64_t ngr = (nchunk + 63) / 64;
             a.sample = ann_bound_sample(x);
-            a.ordered = L.nq >= 64 && (L.budget > kLeanBudget || x.low_contrast);
+            a.ordered = L.nq >= 64 && L.budget > kLeanBudget;
             a.sel_cap = (int)std::min<int64_t>(kSelMax, std::max<int64_t>(kSelCap, (a.sample * L.budget + 63) / 64 + 1));
             a.grp_cap = (int)std::min<int64_t>(kGrpCap, std::max<int64_t>(0, tune_get(PMLSH_TUNE_GROUP_LIST)));
             const size_t min_bytes = 2 * (size_t)((ngr + 7) & ~7);
@@ -3121,12 +3104,34 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             PMLSH_HIP(hipGetLastError());
         }
         StageTimer tm(PMLSH_STAGE_FINISH, stream);
+        // Which kernels finish a budget of at most kLeanBudget. One workgroup of
+        // 256 threads per query suits more than 512 queries: four are resident
+        // per compute unit. With fewer queries the chip has room, and a query's
+        // chain of row gathers (64 rows in flight per 256 threads) sets the time:
+        // 512 threads up to 512 queries, 1,024 up to 256, but 256 where there are
+        // so few rows that the barriers of a larger workgroup cost more. The three
+        // kernels spread one query's rows over many workgroups for two launches
+        // more: that pays for a few queries of many wide rows only. us per call,
+        // threads 256 / 512 / 1,024 / three kernels:
+        //   5,000 x 64          100 queries, B = 150    58 /  59 /  62 /  68
+        //   20,000 x 32 (*)     256 queries, B = 20     58 /  59 /  62 /  67
+        //   1M x 128              1 query,   B = 20     56 /  58 /  61 /  62
+        //                       256 queries, B = 520    85 /  83 /  84 /  90
+        //   1M x 256             32 queries, B = 900    89 /  82 /  80 /  80
+        //                       256 queries, B = 1,900 211 / 181 / 170 / 198
+        //                       512 queries, B = 1,900 266 / 243 / 262 / 271
+        //                     1,024 queries, B = 900   212 / 229 / 269 / 227
+        //                     1,024 queries, B = 2,040 418 / 427 / 471 / 424
+        //   1M x 960 (*)          1 query,   B = 1,020 179 / 152 / 144 / 138
+        //                     1,024 queries, B = 1,020 747 / 769 / 819 / 758
+        //   20,000 x 900         32 queries, B = 900   126 / 106 / 105 /  93
+        // (*) data without contrast.
         const int64_t B = L.budget, nq = L.nq;
         if (B > kLeanBudget)
             launch_pool<1024>(a, L, lds0, lds, stream);
-        else if (B >= 1536 || x.low_contrast || (nq <= 32 && B >= 768))
+        else if (nq <= 32 && B >= 768 && x.d16 > 256)
             launch_pool<WG>(a, L, lds0, lds, stream);
-        else if (nq > 512)
+        else if (nq > 512 || B < 128)
             launch_finish<WG>(a, L, lds, stream);
         else if (nq > 256 || B < 512)
             launch_finish<512>(a, L, lds, stream);
