@@ -516,8 +516,9 @@ int pmlsh_ann_timing_read(pmlsh_ann_timing* out, int reset);
  *   PMLSH_TUNE_SCAN_SHAPE         0 (default): the range filter's query block
  *                                 follows the index's size (512 queries per
  *                                 workgroup below 32,768 chunks of 64 points,
- *                                 1,024 from there on); 1: always 512; 2:
- *                                 always 1,024
+ *                                 1,024 from there on, 256 where chunks and
+ *                                 queries are too few to fill the chip); 1:
+ *                                 always 512; 2: always 1,024
  * value -1 restores the default; a key or value out of range: PMLSH_EINVAL.
  * A call running while a switch changes may see either setting.
  */

@@ -1914,6 +1914,12 @@ __global__ __launch_bounds__(WG) void mask_kernel(AnnArgs a) {
 struct ScanSmall { static constexpr int QB = 512, QW = 128, NW = 4, WGS = 4, STG = 512; };
 struct ScanLarge { static constexpr int QB = 1024, QW = 256, NW = 16, WGS = 1, STG = 512; };
 constexpr int64_t kScanLargeChunks = 32768;   // 2,097,152 points
+// An index so small that waves of 128 queries would leave SIMDs idle is bound by
+// one wave's chain of candidates and flushes (every point of its chunk may be a
+// candidate of every query): waves of 64 queries with a longer stage. 1,000
+// queries, whole calls, with ScanSmall / ScanFew: 200 x 16, B = 100 97 / 72 us;
+// 1,000 x 32, B = 300 94 / 78; 5,000 x 64, B = 300 78 / 72.
+struct ScanFew { static constexpr int QB = 256, QW = 64, NW = 4, WGS = 2, STG = 1024; };
 
 // Query rows, then per-wave candidate stages: every wave packs, stages,
 // counts and flushes its own candidates, so after the rows are loaded the
@@ -1935,7 +1941,7 @@ constexpr bool scan_shape_ok() {
            (S::QB / S::QW & (S::QB / S::QW - 1)) == 0 && S::NW % (S::QB / S::QW) == 0 &&
            sizeof(ScanShared<S>) * S::WGS <= 160 * 1024;
 }
-static_assert(scan_shape_ok<ScanSmall>() && scan_shape_ok<ScanLarge>(),
+static_assert(scan_shape_ok<ScanSmall>() && scan_shape_ok<ScanLarge>() && scan_shape_ok<ScanFew>(),
               "a wave's queries are whole mask words (ids below 256), every query has the same "
               "number of waves, and the scan workgroups of a compute unit fit its LDS");
 
@@ -3083,11 +3089,12 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         // block shape that suits the index's size
         const int64_t shape = tune_get(PMLSH_TUNE_SCAN_SHAPE);
         const bool large = shape == 0 ? nchunk >= kScanLargeChunks : shape == 2;
-        auto* scan_fn = large ? scan_kernel<ScanLarge> : scan_kernel<ScanSmall>;
-        const int sqb = large ? ScanLarge::QB : ScanSmall::QB;
-        const int swg = 64 * (large ? ScanLarge::NW : ScanSmall::NW);
-        static thread_local int scan_slots[64][2] = {};
-        int& slots = scan_slots[x.device & 63][large ? 1 : 0];
+        const bool few = shape == 0 && nchunk * ((L.nq + ScanSmall::QW - 1) / ScanSmall::QW) < 1024;
+        auto* scan_fn = large ? scan_kernel<ScanLarge> : few ? scan_kernel<ScanFew> : scan_kernel<ScanSmall>;
+        const int sqb = large ? ScanLarge::QB : few ? ScanFew::QB : ScanSmall::QB;
+        const int swg = 64 * (large ? ScanLarge::NW : few ? ScanFew::NW : ScanSmall::NW);
+        static thread_local int scan_slots[64][3] = {};
+        int& slots = scan_slots[x.device & 63][large ? 1 : few ? 2 : 0];
         if (slots == 0) {
             int per_cu = 0, cus = 0;
             PMLSH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)scan_fn, swg, 0));
