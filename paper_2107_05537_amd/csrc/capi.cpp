@@ -51,12 +51,18 @@ struct AnnWorkspace {
     bool vals;   // pd^2 bits kept per pool entry
 };
 
-// Workgroups of the per-query kernel, each with its own pair of frontier
-// lists: few on the batched path (only the queries it hands over), more
-// when every query takes the per-query path.
-int64_t front_slots(const pmlsh_index* x, bool fast, int64_t batch) {
+// Most workgroups of the per-query kernel, each with its own pair of frontier
+// lists: few on the batched path, which hands single queries over; more when
+// every query takes the per-query path, and for large budgets, whose queries
+// are handed over all together where the filter's widened radius overflows
+// their pools (1M x 256 without contrast, BF16 filter, 1,024 queries of B =
+// 5,000: 64 ms a call with 2,048 workgroups, 105 with 256).
+int64_t front_slots_most(const AnnWorkspace& w) {
+    return w.fast && w.B <= kLeanBudget ? 256 : 2048;
+}
+int64_t front_slots(const pmlsh_index* x, const AnnWorkspace& w, int64_t batch) {
     const int64_t by_memory = std::max<int64_t>(1, (int64_t(1) << 30) / (8 * x->n_leaves));
-    return std::min<int64_t>({batch, fast ? 256 : 2048, by_memory});
+    return std::min<int64_t>({batch, front_slots_most(w), by_memory});
 }
 
 // Bytes of the workspace layout for batches of `batch` queries and `slots`
@@ -96,7 +102,7 @@ AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B) {
                               : 0);
     w.batch = std::max<int64_t>(1, std::min<int64_t>(nq, kWorkspaceCap / per_query_all));
     w.batch = std::min<int64_t>(w.batch, 65535);
-    w.slots = front_slots(x, w.fast, w.batch);
+    w.slots = front_slots(x, w, w.batch);
     w.bytes = ann_layout_bytes(x, w, w.batch, w.slots);
     // sizes rounded up (to 1 MiB, or 64 MiB above 256 MiB) so that calls of
     // different batch sizes reuse the same pool blocks
@@ -112,7 +118,7 @@ AnnWorkspace ann_workspace_in(const pmlsh_index* x, int64_t nq, int k, int64_t B
                               bool wide = true) {
     AnnWorkspace w = ann_workspace_base(x, k, B, wide);
     const int64_t per_slot = 2 * x->n_leaves * 4;
-    int64_t slots = std::min<int64_t>(w.fast ? 256 : 2048, (cap / 4) / per_slot);
+    int64_t slots = std::min<int64_t>(front_slots_most(w), (cap / 4) / per_slot);
     slots = std::max<int64_t>(slots, 1);
     int64_t lo = 0, hi = std::min<int64_t>(nq, 65535);
     while (lo < hi) {   // largest batch with bytes <= cap
