@@ -85,7 +85,7 @@ AnnWorkspace ann_workspace_base(const pmlsh_index* x, int k, int64_t B, bool wid
     // FP32 path is switched on (read once per call: layout and launch agree)
     w.fast = ann_fast_path(B) && tune_get(PMLSH_TUNE_FP32_PATH) == 0 && (wide || B <= kLeanBudget);
     w.vals = w.fast && wide;
-    w.pool_q = w.fast ? ann_pool_per_query(x->n, B) : 0;
+    w.pool_q = w.fast ? ann_pool_per_query(*x, B) : 0;
     w.per_query = (int64_t)MP * 8 + 64 + B * 8 + 3 * (int64_t)k * 4 +
                   (w.fast ? 4 * 4 + w.pool_q * (w.vals ? 8 : 4) + B * 4 : 0) +
                   (w.fast && x->filter_gemm ? (MP + 1) * 4 : 0);
