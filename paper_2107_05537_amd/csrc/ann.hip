@@ -1176,7 +1176,12 @@ __device__ void ann_one(const AnnArgs& a, int64_t qi, int32_t* fa, int32_t* fb, 
             for (int i = threadIdx.x; i < n_ver; i += WG) loc += cdist[i] <= thr2;
             if (block_sum(loc, sh) >= qpar.k) { exit_kind = PMLSH_EXIT_NEAR; break; }
         }
-        if (rounds >= MAX_ROUNDS) r = __longlong_as_double(0x7ff0000000000000ll);
+        // the round after the cap is the last: every point whose projected
+        // distance is a number lies in its ball, so only a query whose
+        // distances are not (NaN or infinite coordinates) leaves it without
+        // the budget's points
+        const bool last = rounds >= MAX_ROUNDS;
+        if (last) r = __longlong_as_double(0x7ff0000000000000ll);
         const double Rd = qpar.t * r;
         const float R = (float)Rd;
         const float R2 = (float)(Rd * Rd);
@@ -1252,11 +1257,17 @@ __device__ void ann_one(const AnnArgs& a, int64_t qi, int32_t* fa, int32_t* fb, 
         __syncthreads();
         prev_hi = hi_hi;
         first = false;
-        if (rounds >= a.max_rounds) break;
+        if (last || rounds >= a.max_rounds) break;
         r = qpar.c * r;
     }
 
     write_topk(a, qi, qs, cpos, cdist, n_ver, rounds, exit_kind, scanned, sh);
+    // places that no member fills
+    __syncthreads();
+    for (int j = n_ver + (int)threadIdx.x; j < qpar.k; j += WG) {
+        a.out_ids[qi * a.out_stride + j] = -1;
+        a.out_dist[qi * a.out_stride + j] = __int_as_float(0x7f800000);
+    }
 }
 
 // ------------------------------------------------------------------------
