@@ -23,8 +23,7 @@ constexpr int64_t kSamplePairs = 100000;
 template <class T>
 T* dev_alloc(pmlsh_index* idx, int64_t count) {
     if (count <= 0) count = 1;
-    void* p = nullptr;
-    PMLSH_HIP(hipMalloc(&p, (size_t)count * sizeof(T)));
+    void* p = device_malloc((size_t)count * sizeof(T));
     idx->device_bytes += count * (int64_t)sizeof(T);
     return static_cast<T*>(p);
 }
@@ -104,11 +103,11 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
     const float* D = a->data;
     const float* H = a->hash;
     if (!a->data_on_device) {
-        PMLSH_HIP(hipMalloc(&dsrc.p, (size_t)n * d * sizeof(float)));
+        dsrc.p = device_malloc((size_t)n * d * sizeof(float));
         PMLSH_HIP(hipMemcpyAsync(dsrc.p, a->data, (size_t)n * d * sizeof(float),
                                  hipMemcpyHostToDevice, st));
         D = static_cast<const float*>(dsrc.p);
-        PMLSH_HIP(hipMalloc(&hsrc.p, (size_t)a->m * d * sizeof(float)));
+        hsrc.p = device_malloc((size_t)a->m * d * sizeof(float));
         PMLSH_HIP(hipMemcpyAsync(hsrc.p, a->hash, (size_t)a->m * d * sizeof(float),
                                  hipMemcpyHostToDevice, st));
         H = static_cast<const float*>(hsrc.p);
@@ -122,8 +121,8 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
 
     // ---- projection in original order
     TmpBuf phi, plo;
-    PMLSH_HIP(hipMalloc(&phi.p, (size_t)n * MP * sizeof(float)));
-    PMLSH_HIP(hipMalloc(&plo.p, (size_t)n * MP * sizeof(float)));
+    phi.p = device_malloc((size_t)n * MP * sizeof(float));
+    plo.p = device_malloc((size_t)n * MP * sizeof(float));
     launch_project(D, n, d, d, x->hash, static_cast<float*>(phi.p), static_cast<float*>(plo.p), st);
     if (!device_all_finite(static_cast<const float*>(phi.p), n * MP, st))
         fail(PMLSH_EINVAL, "data or hash holds a non-finite value");
@@ -237,8 +236,8 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
         const float* proj_scan = x->proj_hi;
         TmpBuf lp, lpe;
         if (x->filter_gemm) {
-            PMLSH_HIP(hipMalloc(&lp.p, (size_t)n * MP * sizeof(float)));
-            PMLSH_HIP(hipMalloc(&lpe.p, (size_t)n * sizeof(float)));
+            lp.p = device_malloc((size_t)n * MP * sizeof(float));
+            lpe.p = device_malloc((size_t)n * sizeof(float));
             float* lpp = static_cast<float*>(lp.p);
             float* lpep = static_cast<float*>(lpe.p);
             launch_project_lp(x->data, n, d, x->d_pad, x->hash, x->filter_gemm, lpp, lpep, st);
@@ -271,7 +270,7 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
     if (n >= 2) {
         const int64_t S = std::min<int64_t>(n * (n - 1) / 2, kSamplePairs);
         TmpBuf dd;
-        PMLSH_HIP(hipMalloc(&dd.p, (size_t)S * sizeof(double)));
+        dd.p = device_malloc((size_t)S * sizeof(double));
         launch_pair_dist_f64(D, n, d, d, a->sample_seed, S, static_cast<double*>(dd.p), st);
         device_sorted(static_cast<const double*>(dd.p), S, st, &x->sample_sorted);
     }

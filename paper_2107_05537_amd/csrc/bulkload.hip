@@ -810,8 +810,6 @@ dim3 grid_of(int64_t n) {
     return dim3((unsigned)std::min<int64_t>(4096, std::max<int64_t>(1, (n + 255) / 256)));
 }
 
-thread_local BuildScratch* t_scratch = nullptr;   // of the build that this thread runs
-
 // Device buffer that grows to at least twice its size, so that the levels of a
 // build, each a little larger than the one before, do not free and allocate in
 // turn. Its memory is the build's scratch while that has room.
@@ -821,7 +819,7 @@ struct DevVec {
     size_t cap = 0;
     ~DevVec() { release(); }
     void release() {
-        if (p && !(t_scratch && t_scratch->give(p))) (void)hipFree(p);
+        if (p && !BuildScratch::give_back(p)) (void)hipFree(p);
         p = nullptr;
         cap = 0;
     }
@@ -829,74 +827,13 @@ struct DevVec {
         if (count > cap || !p) {
             const size_t want = std::max<size_t>(count, std::max<size_t>(2 * cap, 1));
             release();
-            if (t_scratch) p = static_cast<T*>(t_scratch->take(want * sizeof(T)));
-            if (!p) PMLSH_HIP(hipMalloc(&p, want * sizeof(T)));
+            p = static_cast<T*>(BuildScratch::take_piece(want * sizeof(T)));
+            if (!p) p = static_cast<T*>(device_malloc(want * sizeof(T)));
             cap = want;
         }
         return p;
     }
 };
-
-}  // namespace
-
-// The build's largest buffers come to 46 bytes per point and its level lists
-// to some 20 more; what does not fit is allocated on its own. Beyond 2 GB (22
-// million points) the allocations are short beside the build, and memory that
-// stays idle between its stages could be missed.
-BuildScratch::BuildScratch(int64_t n) {
-    const size_t want = std::min<size_t>((size_t)n * 96 + (size_t(1) << 20), size_t(2) << 30);
-    if (hipMalloc(&base_, want) != hipSuccess) {
-        (void)hipGetLastError();
-        base_ = nullptr;
-        return;
-    }
-    bytes_ = want;
-    free_[0] = want;
-    outer_ = t_scratch;
-    t_scratch = this;
-}
-
-BuildScratch::~BuildScratch() {
-    if (!base_) return;
-    t_scratch = outer_;
-    (void)hipFree(base_);
-}
-
-void* BuildScratch::take(size_t bytes) {
-    bytes = std::max<size_t>((bytes + 255) & ~size_t(255), 256);
-    for (auto it = free_.begin(); it != free_.end(); ++it) {
-        if (it->second < bytes) continue;
-        const size_t at = it->first, left = it->second - bytes;
-        free_.erase(it);
-        if (left) free_[at + bytes] = left;
-        used_[at] = bytes;
-        return static_cast<char*>(base_) + at;
-    }
-    return nullptr;
-}
-
-bool BuildScratch::give(void* p) {
-    const size_t at = (size_t)(static_cast<char*>(p) - static_cast<char*>(base_));
-    auto u = static_cast<char*>(p) < static_cast<char*>(base_) ? used_.end() : used_.find(at);
-    if (u == used_.end()) return false;
-    auto f = free_.emplace(at, u->second).first;
-    used_.erase(u);
-    auto next = std::next(f);
-    if (next != free_.end() && f->first + f->second == next->first) {
-        f->second += next->second;
-        free_.erase(next);
-    }
-    if (f != free_.begin()) {
-        auto prev = std::prev(f);
-        if (prev->first + prev->second == f->first) {
-            prev->second += f->second;
-            free_.erase(f);
-        }
-    }
-    return true;
-}
-
-namespace {
 
 // Device buffers of the level sorts, and their host lists.
 struct LevelSort {

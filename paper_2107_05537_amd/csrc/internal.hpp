@@ -106,6 +106,35 @@ void ws_free(void* p, hipStream_t st);
 void* pinned_alloc(size_t bytes);
 void pinned_free(void* p, hipStream_t st);
 
+// hipMalloc; when the device has no memory left, what the library keeps for reuse
+// (idle workspace blocks, the build's scratch when no piece of it is in use)
+// is given back and the allocation tried once more. Throws.
+void* device_malloc(size_t bytes);
+
+// Device memory of one build's temporaries: one allocation, carved up on the
+// host while the object lives on the thread that made it. A piece given back
+// may be taken again at once, so all work on the pieces has to be on the
+// build's one stream. (A build of 1M points made some hundred allocations, and
+// every release of one waited for the device; now some twenty.)
+class BuildScratch {
+  public:
+    explicit BuildScratch(int64_t n);
+    ~BuildScratch();
+    BuildScratch(const BuildScratch&) = delete;
+    BuildScratch& operator=(const BuildScratch&) = delete;
+    // of the scratch on this thread: null when there is none or the piece does
+    // not fit; false when p is not one of its pieces; false when there is
+    // none, it is in use or has been given up already
+    static void* take_piece(size_t bytes);
+    static bool give_back(void* p);
+    static bool give_up();
+
+  private:
+    void* base_ = nullptr;
+    BuildScratch* outer_ = nullptr;
+    std::map<size_t, size_t> free_, used_;   // offset -> bytes
+};
+
 // Parameters of one query of a launch whose queries differ in k, c,
 // confidence, beta or r_min (device array, one entry per query).
 struct AnnQueryParams {
@@ -187,27 +216,6 @@ struct HostTree {
 struct SplitNode {
     int64_t leaf_begin, leaf_end;
     int32_t left, right;
-};
-
-// Device memory of one build's temporaries: one allocation, carved up on the
-// host while the object lives on the thread that made it. A piece given back
-// may be taken again at once, so all work on the pieces has to be on the
-// build's one stream. (A build of 1M points made some hundred allocations, and
-// every release of one waited for the device: 23.1 ms before, 18.2 now.)
-class BuildScratch {
-  public:
-    explicit BuildScratch(int64_t n);
-    ~BuildScratch();
-    BuildScratch(const BuildScratch&) = delete;
-    BuildScratch& operator=(const BuildScratch&) = delete;
-    void* take(size_t bytes);   // null when it does not fit
-    bool give(void* p);         // false when p is not one of its pieces
-
-  private:
-    void* base_ = nullptr;
-    size_t bytes_ = 0;
-    BuildScratch* outer_ = nullptr;
-    std::map<size_t, size_t> free_, used_;   // offset -> bytes
 };
 
 // Recursive gap-aware splits of the leaf order on the device, level by level

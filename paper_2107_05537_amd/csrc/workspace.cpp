@@ -5,8 +5,9 @@
 // stream once its event has completed. New blocks come from hipMalloc (sizes
 // rounded up to 1 MiB, or 64 MiB above 256 MiB), only when no cached block
 // fits, so repeated calls neither map fresh pages nor synchronise the device.
-// Cached blocks are held until the process ends; the device holds at most
-// the peak workspace of the calls that overlapped.
+// Cached blocks are held until the process ends or an allocation of the library
+// finds no memory; the device holds at most the peak workspace of the calls that
+// overlapped.
 #include <algorithm>
 #include <cstddef>
 #include <map>
@@ -46,6 +47,23 @@ Cache& cache_for_current_device() {
     if (dev < 0 || dev >= kMaxDevices) fail(PMLSH_EDEVICE, "device ordinal out of range");
     return g_cache[dev];
 }
+
+// Frees the cached blocks whose work has ended (c.mu held).
+void trim(Cache& c) {
+    for (auto it = c.free_blocks.begin(); it != c.free_blocks.end();) {
+        Block& b = it->second.second;
+        if (hipEventQuery(b.ready) == hipSuccess) {
+            (void)hipEventDestroy(b.ready);
+            (void)hipFree(it->second.first);
+            it = c.free_blocks.erase(it);
+        } else {
+            ++it;
+        }
+    }
+    (void)hipGetLastError();   // "not ready" of the queries
+}
+
+thread_local BuildScratch* t_scratch = nullptr;   // of the build that this thread runs
 
 // Pinned host blocks of one device: handed out, and idle ones with the event
 // after which their last reader is done. At most kPinnedBlocks idle blocks of at
@@ -138,17 +156,7 @@ void* ws_alloc(size_t bytes, hipStream_t st) {
     hipError_t e = hipMalloc(&p, want);
     if (e == hipErrorOutOfMemory && !c.free_blocks.empty()) {
         // give the cached blocks that are idle back and try once more
-        (void)hipGetLastError();
-        for (auto it = c.free_blocks.begin(); it != c.free_blocks.end();) {
-            Block& b = it->second.second;
-            if (hipEventQuery(b.ready) == hipSuccess) {
-                (void)hipEventDestroy(b.ready);
-                (void)hipFree(it->second.first);
-                it = c.free_blocks.erase(it);
-            } else {
-                ++it;
-            }
-        }
+        trim(c);
         e = hipMalloc(&p, want);
     }
     if (e != hipSuccess) {
@@ -183,6 +191,95 @@ void ws_free(void* p, hipStream_t st) {
         (void)hipEventRecord(b.ready, nullptr);
     }
     c.free_blocks.emplace(b.size, std::make_pair(p, b));
+}
+
+void* device_malloc(size_t bytes) {
+    void* p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        (void)BuildScratch::give_up();
+        {
+            Cache& c = cache_for_current_device();
+            std::lock_guard<std::mutex> g(c.mu);
+            trim(c);
+        }
+        e = hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        fail(e == hipErrorOutOfMemory ? PMLSH_ENOMEM : PMLSH_EDEVICE,
+             "hipMalloc of " + std::to_string(bytes) + " bytes: " + hipGetErrorString(e));
+    }
+    return p;
+}
+
+// The build's largest buffers come to 46 bytes per point and its level lists
+// to some 20 more; what does not fit is allocated on its own. Beyond 2 GB (22
+// million points) the allocations are short beside the build.
+BuildScratch::BuildScratch(int64_t n) {
+    const size_t want = std::min<size_t>((size_t)n * 96 + (size_t(1) << 20), size_t(2) << 30);
+    if (hipMalloc(&base_, want) != hipSuccess) {
+        (void)hipGetLastError();
+        base_ = nullptr;
+    } else {
+        free_[0] = want;
+    }
+    outer_ = t_scratch;
+    t_scratch = this;
+}
+
+BuildScratch::~BuildScratch() {
+    t_scratch = outer_;
+    if (base_) (void)hipFree(base_);
+}
+
+// The index's own arrays may need the memory: they come when the temporaries are
+// done with, as if those had been allocated one by one.
+bool BuildScratch::give_up() {
+    BuildScratch* s = t_scratch;
+    if (!s || !s->base_ || !s->used_.empty()) return false;
+    (void)hipFree(s->base_);   // waits for the work on its pieces
+    s->base_ = nullptr;
+    s->free_.clear();
+    return true;
+}
+
+void* BuildScratch::take_piece(size_t bytes) {
+    BuildScratch* s = t_scratch;
+    if (!s) return nullptr;
+    bytes = std::max<size_t>((bytes + 255) & ~size_t(255), 256);
+    for (auto it = s->free_.begin(); it != s->free_.end(); ++it) {
+        if (it->second < bytes) continue;
+        const size_t at = it->first, left = it->second - bytes;
+        s->free_.erase(it);
+        if (left) s->free_[at + bytes] = left;
+        s->used_[at] = bytes;
+        return static_cast<char*>(s->base_) + at;
+    }
+    return nullptr;
+}
+
+bool BuildScratch::give_back(void* p) {
+    BuildScratch* s = t_scratch;
+    if (!s || !s->base_ || static_cast<char*>(p) < static_cast<char*>(s->base_)) return false;
+    auto u = s->used_.find((size_t)(static_cast<char*>(p) - static_cast<char*>(s->base_)));
+    if (u == s->used_.end()) return false;
+    auto f = s->free_.emplace(u->first, u->second).first;
+    s->used_.erase(u);
+    auto next = std::next(f);
+    if (next != s->free_.end() && f->first + f->second == next->first) {
+        f->second += next->second;
+        s->free_.erase(next);
+    }
+    if (f != s->free_.begin()) {
+        auto prev = std::prev(f);
+        if (prev->first + prev->second == f->first) {
+            prev->second += f->second;
+            s->free_.erase(f);
+        }
+    }
+    return true;
 }
 
 }  // namespace pmlsh
