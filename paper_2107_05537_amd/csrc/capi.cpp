@@ -93,6 +93,17 @@ AnnWorkspace ann_workspace_base(const pmlsh_index* x, int k, int64_t B, bool wid
     return w;
 }
 
+// The batch, the frontier lists and the bytes of a layout.
+void ann_workspace_size(const pmlsh_index* x, int64_t batch, AnnWorkspace* w) {
+    w->batch = std::min<int64_t>(batch, 65535);
+    w->slots = front_slots(x, *w, w->batch);
+    w->bytes = ann_layout_bytes(x, *w, w->batch, w->slots);
+    // sizes rounded up (to 1 MiB, or 64 MiB above 256 MiB) so that calls of
+    // different batch sizes reuse the same pool blocks
+    const int64_t q = w->bytes > (int64_t(256) << 20) ? int64_t(64) << 20 : int64_t(1) << 20;
+    w->bytes = (w->bytes + q - 1) / q * q;
+}
+
 AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B) {
     AnnWorkspace w = ann_workspace_base(x, k, B);
     // per query, with the distance blocks of a 64-query band spread over it
@@ -100,15 +111,35 @@ AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B) {
         w.per_query + (w.fast ? 8 + 2 * (64 * cdist_groups(w.nchunk) + cdist_gmin_len(w.nchunk)) +
                                     (w.nchunk + 7) / 8
                               : 0);
-    w.batch = std::max<int64_t>(1, std::min<int64_t>(nq, kWorkspaceCap / per_query_all));
-    w.batch = std::min<int64_t>(w.batch, 65535);
-    w.slots = front_slots(x, w, w.batch);
-    w.bytes = ann_layout_bytes(x, w, w.batch, w.slots);
-    // sizes rounded up (to 1 MiB, or 64 MiB above 256 MiB) so that calls of
-    // different batch sizes reuse the same pool blocks
-    const int64_t q = w.bytes > (int64_t(256) << 20) ? int64_t(64) << 20 : int64_t(1) << 20;
-    w.bytes = (w.bytes + q - 1) / q * q;
+    ann_workspace_size(x, std::max<int64_t>(1, std::min<int64_t>(nq, kWorkspaceCap / per_query_all)),
+                       &w);
     return w;
+}
+
+// The next smaller layout, for a device that has no memory for w: half the
+// queries per batch, then the one without pools for large budgets. False when
+// there is none.
+bool ann_workspace_smaller(const pmlsh_index* x, int k, AnnWorkspace* w) {
+    if (w->batch > 1) {
+        ann_workspace_size(x, w->batch / 2, w);
+        return true;
+    }
+    if (!w->vals) return false;
+    *w = ann_workspace_base(x, k, w->B, false);
+    ann_workspace_size(x, 1, w);
+    return true;
+}
+
+// The workspace of one call, as large a layout as the device has memory for.
+void* ann_workspace_alloc(const pmlsh_index* x, int64_t nq, int k, int64_t B, hipStream_t st,
+                          AnnWorkspace* w) {
+    *w = ann_workspace(x, nq, k, B);
+    return ws_alloc_least(
+        w->bytes, st, [&](int64_t* bytes) {
+            const bool more = ann_workspace_smaller(x, k, w);
+            *bytes = w->bytes;
+            return more;
+        });
 }
 
 // Layout that fits a fixed region of cap bytes: at most a quarter of it for
@@ -129,6 +160,15 @@ AnnWorkspace ann_workspace_in(const pmlsh_index* x, int64_t nq, int k, int64_t B
     w.batch = lo;
     w.slots = std::min(slots, std::max<int64_t>(lo, 1));
     w.bytes = lo > 0 ? ann_layout_bytes(x, w, w.batch, w.slots) : 0;
+    return w;
+}
+
+// As ann_workspace_in for a region of a launch; the layout without pools where
+// those leave no room for a single query.
+AnnWorkspace ann_workspace_region(const pmlsh_index* x, int64_t nq, int k, int64_t B, int64_t bytes,
+                                  bool wide = true) {
+    AnnWorkspace w = ann_workspace_in(x, nq, k, B, bytes, wide);
+    if (w.batch < 1 && wide) w = ann_workspace_in(x, nq, k, B, bytes, false);
     return w;
 }
 
@@ -297,9 +337,9 @@ void run_ann(const pmlsh_index* x, const float* queries, int64_t nq, int k, doub
     pmlsh_plan plan;
     r_min = ann_plan(x, k, c, confidence, beta, r_min, &plan);
     if (nq == 0) return;
-    const AnnWorkspace w = ann_workspace(x, nq, k, plan.budget);
+    AnnWorkspace w;
     const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, max_rounds};
-    void* ws = ws_alloc((size_t)w.bytes, st);
+    void* ws = ann_workspace_alloc(x, nq, k, plan.budget, st, &w);
     try {
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, ws);
     } catch (...) {
@@ -318,9 +358,8 @@ void run_ann_in(const pmlsh_index* x, const float* queries, int64_t nq, int k, d
     if (nq == 0) return;
     // a small fixed region holds most queries without the lists' pd^2 bits; a
     // large budget whose candidate pool does not fit takes the per-query path
-    AnnWorkspace w = ann_workspace_in(x, nq, k, plan.budget, region_bytes,
-                                      plan.budget > kLeanBudget);
-    if (w.batch < 1) w = ann_workspace_in(x, nq, k, plan.budget, region_bytes, false);
+    const AnnWorkspace w = ann_workspace_region(x, nq, k, plan.budget, region_bytes,
+                                                plan.budget > kLeanBudget);
     if (w.batch < 1) {
         const AnnWorkspace one = ann_workspace_in(x, 1, k, plan.budget, int64_t(1) << 62, false);
         fail(PMLSH_EUNSUPPORTED,
@@ -375,7 +414,7 @@ void run_ann_planned(const pmlsh_index* x, const float* queries, int64_t nq,
                      const AnnQueryParams& p, int64_t* out_ids, float* out_dist, hipStream_t st,
                      void* region, int64_t region_bytes) {
     if (nq == 0) return;
-    const AnnWorkspace w = ann_workspace_in(x, nq, p.k, p.budget, region_bytes);
+    const AnnWorkspace w = ann_workspace_region(x, nq, p.k, p.budget, region_bytes);
     if (w.batch < 1) fail(PMLSH_ENOMEM, "the workspace region holds no query");
     const AnnCall call{p.k, p.budget, p.c, p.t, p.r_min, nullptr, p.k, 0};
     run_ann_region(x, queries, nq, call, out_ids, out_dist, nullptr, st, w, region);
@@ -385,6 +424,12 @@ int64_t ann_workspace_bytes_mixed(const pmlsh_index* x, int64_t nq, int kmax, in
     return nq > 0 ? ann_workspace(x, nq, kmax, bmax).bytes : 0;
 }
 
+int64_t ann_workspace_bytes_least(const pmlsh_index* x, int kmax, int64_t bmax) {
+    AnnWorkspace w = ann_workspace_base(x, kmax, bmax, false);
+    ann_workspace_size(x, 1, &w);
+    return w.bytes;
+}
+
 void run_ann_mixed(const pmlsh_index* x, const float* queries, int64_t nq,
                    const AnnQueryParams* qpar, int kmax, int64_t bmax, int out_stride,
                    int64_t* out_ids, float* out_dist, int32_t* out_stats, hipStream_t st,
@@ -392,13 +437,13 @@ void run_ann_mixed(const pmlsh_index* x, const float* queries, int64_t nq,
     if (nq == 0) return;
     const AnnCall call{kmax, bmax, 0.0, 0.0, 0.0, qpar, out_stride, 0};
     if (region) {
-        const AnnWorkspace w = ann_workspace_in(x, nq, kmax, bmax, region_bytes);
+        const AnnWorkspace w = ann_workspace_region(x, nq, kmax, bmax, region_bytes);
         if (w.batch < 1) fail(PMLSH_ENOMEM, "the workspace region holds no query");
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, region);
         return;
     }
-    const AnnWorkspace w = ann_workspace(x, nq, kmax, bmax);
-    void* ws = ws_alloc((size_t)w.bytes, st);
+    AnnWorkspace w;
+    void* ws = ann_workspace_alloc(x, nq, kmax, bmax, st, &w);
     try {
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, ws);
     } catch (...) {

@@ -100,6 +100,9 @@ int guarded(F&& fn) {
 // never throws.
 void* ws_alloc(size_t bytes, hipStream_t st);
 void ws_free(void* p, hipStream_t st);
+// ws_alloc of `bytes`, or of the next size that smaller(&bytes) names while the
+// device has no memory (it returns false when there is none).
+void* ws_alloc_least(int64_t bytes, hipStream_t st, const std::function<bool(int64_t*)>& smaller);
 // Pinned host memory from a small per-device cache: pinned_free gives a block
 // back once the work queued on st so far (its last reader) has completed; it
 // never throws.
@@ -173,6 +176,8 @@ void plan_queries(const pmlsh_index* x, const pmlsh_query_args* args, int64_t nq
                   std::vector<AnnQueryParams>* out, int* kmax, int64_t* bmax);
 // Workspace bytes of run_ann_mixed on nq queries with these largest k, B.
 int64_t ann_workspace_bytes_mixed(const pmlsh_index* x, int64_t nq, int kmax, int64_t bmax);
+// Bytes that any such launch runs in, a query at a time.
+int64_t ann_workspace_bytes_least(const pmlsh_index* x, int kmax, int64_t bmax);
 // pmlsh_ann over a fixed device region of region_bytes instead of the
 // caching allocator: the queries go through in batches that fit it;
 // EUNSUPPORTED (before any HIP call) when not even one query fits. The

@@ -255,8 +255,10 @@ void slot_release(Slot& sl) {
 }
 
 // Sizes a slot for `rows` queries with answers of up to kcap entries and a
-// workspace of ws_bytes (called with the slot idle).
-void slot_reserve(const pmlsh_server* s, Slot& sl, int64_t rows, int64_t kcap, int64_t ws_bytes) {
+// workspace of ws_bytes, or what the device has memory for down to ws_least
+// (called with the slot idle).
+void slot_reserve(const pmlsh_server* s, Slot& sl, int64_t rows, int64_t kcap, int64_t ws_bytes,
+                  int64_t ws_least) {
     if (rows > sl.rows || kcap > sl.kcap) {
         rows = std::max(rows, sl.rows);
         kcap = std::max(kcap, sl.kcap);
@@ -286,7 +288,15 @@ void slot_reserve(const pmlsh_server* s, Slot& sl, int64_t rows, int64_t kcap, i
         (void)hipFree(sl.ws);
         sl.ws = nullptr;
         sl.ws_bytes = 0;
-        PMLSH_HIP(hipMalloc(&sl.ws, (size_t)ws_bytes));
+        for (;;) {
+            try {
+                sl.ws = device_malloc((size_t)ws_bytes);
+                break;
+            } catch (const Error& e) {
+                if (e.code != PMLSH_ENOMEM || ws_bytes <= ws_least) throw;
+                ws_bytes = std::max(ws_bytes / 2, ws_least);
+            }
+        }
         sl.ws_bytes = ws_bytes;
     }
 }
@@ -310,7 +320,8 @@ void issue(pmlsh_server* s, Launch& L, const Shape& shp) {
     hipStream_t st = s->stream;
     Slot& sl = s->slots[(size_t)L.slot];
     L.status = guarded([&] {
-        slot_reserve(s, sl, shp.nb, shp.kmax, L.bytes);
+        slot_reserve(s, sl, shp.nb, shp.kmax, L.bytes,
+                     ann_workspace_bytes_least(s->idx, shp.kmax, shp.bmax));
         if (L.segs.size() == 1) {
             // one request: its own queries and outputs, its plan as scalars
             const Segment& sg = L.segs.front();
@@ -445,16 +456,17 @@ int pmlsh_server_create(const pmlsh_index* index, const pmlsh_server_args* args,
             (void)hipStreamDestroy(s->stream);
         };
         try {
-            // slots sized for full launches of k up to 100 within the
-            // batched path's budget limit; larger launches grow them
+            // slots sized for full launches of k up to 100 and budgets up to
+            // 2,048; larger launches grow them
             s->slots.resize((size_t)s->max_inflight);
-            const int64_t ws0 =
-                ann_workspace_bytes_mixed(index, s->max_batch, std::min<int64_t>(100, index->n),
-                                          std::min<int64_t>(2048, index->n));
+            const int k0 = (int)std::min<int64_t>(100, index->n);
+            const int64_t b0 = std::min<int64_t>(2048, index->n);
+            const int64_t ws0 = ann_workspace_bytes_mixed(index, s->max_batch, k0, b0);
+            const int64_t ws1 = ann_workspace_bytes_least(index, k0, b0);
             for (int i = 0; i < s->max_inflight; ++i) {
                 Slot& sl = s->slots[(size_t)i];
                 PMLSH_HIP(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
-                slot_reserve(s.get(), sl, s->max_batch, std::min<int64_t>(100, index->n), ws0);
+                slot_reserve(s.get(), sl, s->max_batch, k0, ws0, ws1);
                 s->free_slots.push_back(s->max_inflight - 1 - i);
             }
         } catch (...) {

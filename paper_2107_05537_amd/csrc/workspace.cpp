@@ -174,6 +174,16 @@ void* ws_alloc(size_t bytes, hipStream_t st) {
     return p;
 }
 
+void* ws_alloc_least(int64_t bytes, hipStream_t st, const std::function<bool(int64_t*)>& smaller) {
+    for (;;) {
+        try {
+            return ws_alloc((size_t)bytes, st);
+        } catch (const Error& e) {
+            if (e.code != PMLSH_ENOMEM || !smaller(&bytes)) throw;
+        }
+    }
+}
+
 void ws_free(void* p, hipStream_t st) {
     if (!p) return;
     int dev = 0;

@@ -161,3 +161,17 @@ def test_idle_workspace_is_given_back(tmp_path):
     (void)device_malloc(70 << 20);
     CHECK(model().room == (30 << 20) && model().waits == 0);
     """)
+
+
+def test_workspace_shrinks_to_the_memory_there_is(tmp_path):
+    _run(tmp_path, r"""
+    ihipStream_t st;
+    model().room = (100 << 20);
+    int asked = 0;
+    auto halves = [&](int64_t* b) { ++asked; *b /= 2; return *b >= (16 << 20); };
+    void* a = ws_alloc_least(int64_t(1) << 30, &st, halves);
+    CHECK(a && asked == 4 && model().device.at(a) == (64 << 20));
+    CHECK(code_of([&] { ws_alloc_least(int64_t(1) << 30, &st, [](int64_t* b) {
+        *b /= 2; return *b >= (40 << 20); }); }) == PMLSH_ENOMEM);
+    CHECK(ws_alloc_least(30 << 20, &st, halves) && asked == 4);
+    """)
