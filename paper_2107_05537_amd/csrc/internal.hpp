@@ -103,9 +103,9 @@ void ws_free(void* p, hipStream_t st);
 // ws_alloc of `bytes`, or of the next size that smaller(&bytes) names while the
 // device has no memory (it returns false when there is none).
 void* ws_alloc_least(int64_t bytes, hipStream_t st, const std::function<bool(int64_t*)>& smaller);
-// Pinned host memory from a small per-device cache: pinned_free gives a block
-// back once the work queued on st so far (its last reader) has completed; it
-// never throws.
+// Pinned host memory from a small per-device cache: a block given back is handed
+// out again once the work queued on st so far (its last reader) has completed.
+// pinned_free neither waits for that work nor throws.
 void* pinned_alloc(size_t bytes);
 void pinned_free(void* p, hipStream_t st);
 

@@ -9,7 +9,6 @@
 // finds no memory; the device holds at most the peak workspace of the calls that
 // overlapped.
 #include <algorithm>
-#include <cstddef>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -65,9 +64,10 @@ void trim(Cache& c) {
 
 thread_local BuildScratch* t_scratch = nullptr;   // of the build that this thread runs
 
-// Pinned host blocks of one device: handed out, and idle ones with the event
-// after which their last reader is done. At most kPinnedBlocks idle blocks of at
-// most kPinnedMost bytes are kept; others are freed when they are given back.
+// Pinned host blocks of one device: handed out, and given back with the event
+// after which their last reader is done. Nothing waits for that event: of the
+// blocks whose readers are done, at most kPinnedBlocks of at most kPinnedMost
+// bytes are kept, and the next allocation frees the others.
 constexpr size_t kPinnedBlocks = 16, kPinnedMost = size_t(4) << 20;
 
 struct PinnedBlock {
@@ -78,7 +78,7 @@ struct PinnedBlock {
 struct PinnedCache {
     std::mutex mu;
     std::unordered_map<void*, PinnedBlock> live;
-    std::vector<PinnedBlock> idle;
+    std::vector<PinnedBlock> back;
 };
 PinnedCache g_pinned[kMaxDevices];
 
@@ -95,23 +95,45 @@ void* pinned_alloc(size_t bytes) {
     if (dev < 0 || dev >= kMaxDevices) fail(PMLSH_EDEVICE, "device ordinal out of range");
     PinnedCache& c = g_pinned[dev];
     const size_t want = (std::max<size_t>(bytes, 1) + 65535) / 65536 * 65536;
-    std::lock_guard<std::mutex> g(c.mu);
-    for (size_t i = 0; i < c.idle.size(); ++i) {
-        PinnedBlock b = c.idle[i];
-        if (b.size < want || hipEventQuery(b.done) != hipSuccess) continue;
-        c.idle.erase(c.idle.begin() + (std::ptrdiff_t)i);
-        c.live[b.p] = b;
-        return b.p;
-    }
-    (void)hipGetLastError();   // "not ready" of the queries
     PinnedBlock b;
+    std::vector<PinnedBlock> surplus;
+    {
+        std::lock_guard<std::mutex> g(c.mu);
+        // room for every block that is out to come back
+        std::vector<PinnedBlock> keep;
+        keep.reserve(c.back.size() + c.live.size() + 1);
+        // those still read first, then the idle ones, the smallest in front
+        auto mid = std::stable_partition(c.back.begin(), c.back.end(), [](const PinnedBlock& x) {
+            return hipEventQuery(x.done) != hipSuccess;
+        });
+        (void)hipGetLastError();   // "not ready" of the queries
+        std::sort(mid, c.back.end(),
+                  [](const PinnedBlock& x, const PinnedBlock& y) { return x.size < y.size; });
+        keep.assign(c.back.begin(), mid);
+        for (size_t idle = 0; mid != c.back.end(); ++mid) {
+            if (!b.p && mid->size >= want) {
+                b = *mid;
+            } else if (mid->size <= kPinnedMost && idle < kPinnedBlocks) {
+                keep.push_back(*mid);
+                ++idle;
+            } else {
+                surplus.push_back(*mid);
+            }
+        }
+        if (b.p) c.live[b.p] = b;
+        c.back.swap(keep);
+    }
+    for (PinnedBlock& x : surplus) pinned_release(x);
+    if (b.p) return b.p;
     b.size = want;
     PMLSH_HIP(hipHostMalloc(&b.p, want, hipHostMallocDefault));
     if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
         (void)hipHostFree(b.p);
         fail(PMLSH_EDEVICE, "hipEventCreate for a pinned block failed");
     }
+    std::lock_guard<std::mutex> g(c.mu);
     c.live[b.p] = b;
+    c.back.reserve(c.back.size() + c.live.size());
     return b.p;
 }
 
@@ -126,16 +148,12 @@ void pinned_free(void* p, hipStream_t st) {
     PinnedBlock b = it->second;
     c.live.erase(it);
     if (hipEventRecord(b.done, st) != hipSuccess) {
+        // no event: only a wait tells when the readers are done
         (void)hipStreamSynchronize(st);
         pinned_release(b);
         return;
     }
-    if (b.size <= kPinnedMost && c.idle.size() < kPinnedBlocks) {
-        c.idle.push_back(b);
-        return;
-    }
-    (void)hipEventSynchronize(b.done);
-    pinned_release(b);
+    c.back.push_back(b);
 }
 
 void* ws_alloc(size_t bytes, hipStream_t st) {

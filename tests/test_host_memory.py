@@ -175,3 +175,29 @@ def test_workspace_shrinks_to_the_memory_there_is(tmp_path):
         *b /= 2; return *b >= (40 << 20); }); }) == PMLSH_ENOMEM);
     CHECK(ws_alloc_least(30 << 20, &st, halves) && asked == 4);
     """)
+
+
+def test_pinned_blocks_never_wait(tmp_path):
+    """Any number and size of blocks given back under work that has not ended: no
+    wait, no block handed out twice, and a bounded number kept afterwards."""
+    _run(tmp_path, r"""
+    ihipStream_t st, other;
+    st.busy = true;
+    std::map<void*, int> seen;
+    for (int i = 0; i < 40; ++i) {
+        void* p = pinned_alloc(i % 8 ? 1000 : 8 << 20);
+        CHECK(++seen[p] == 1);
+        pinned_free(p, &st);
+    }
+    CHECK(model().waits == 0 && model().host.size() == 40);
+    // another stream's block is free at once and comes back
+    void* q = pinned_alloc(1000);
+    CHECK(!seen.count(q));
+    pinned_free(q, &other);
+    CHECK(pinned_alloc(1000) == q && model().host.size() == 41);
+    st.busy = false;
+    void* r = pinned_alloc(2000);
+    CHECK(seen.count(r) && model().waits == 0);
+    CHECK(model().host.size() <= 16 + 2);                // kept, and the two in use
+    for (auto& h : model().host) CHECK(h.second <= (4u << 20));
+    """)
