@@ -164,9 +164,11 @@ int pmlsh_default_r_min(const pmlsh_index* index, int64_t budget, double* r_min)
  * FP64 projection and FP64 distances from the FP32 rows), and out_dist is
  * the FP32 rounding of the FP64 distance (more than 512 members within FP32
  * rounding of the k-th keep the FP32 order and distances).
- * Queries have to be finite, with squared distances inside FP32. Of others a
- * NaN finds nothing (ids -1, distances +inf, exit kind 0), an infinity nothing
- * or points at distance +inf; the other queries of the batch are not affected.
+ * Queries have to be finite. Of others a NaN finds nothing (ids -1, distances
+ * +inf, exit kind 0), an infinity nothing or points at distance +inf; the other
+ * queries of the batch are not affected. The order is that of the distances
+ * where their squares, in the data's space and in the projected one, are normal
+ * FP32 numbers; squares that underflow or overflow compare as what they round to.
  * Asynchronous on `stream`. Errors: EINVAL, ENOMEM (workspace), EDEVICE,
  * EUNSUPPORTED (k > PMLSH_MAX_K).
  */

@@ -2008,6 +2008,8 @@ __device__ __forceinline__ void scan_emit(const AnnArgs& a, ScanShared<S>& ss, i
 #pragma unroll
     for (int b = 15; b >= 0; --b)
         mk = __builtin_amdgcn_alignbit(mk, __float_as_uint(cc[b >> 2][b & 3]), 31);
+    // a padding column has no query to write for, whatever its products
+    mk = q < 0 ? 0u : mk;
     const uint32_t prow = (uint32_t)p0 + 4u * (uint32_t)(lane >> 4);
     // A step stages one candidate of every lane that has any left, at the count
     // of such lanes below it. Where some lane has many (chunks of a query's own

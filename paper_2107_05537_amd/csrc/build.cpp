@@ -257,7 +257,9 @@ pmlsh_index* index_build(const pmlsh_build_args* a) {
         int e = 0;
         const float S = x->scan_scale;
         if (S > 0.f && std::isfinite(S)) (void)std::frexp(S, &e);
-        x->scale16 = std::ldexp(1.f, 5 - e);
+        // s^2 and S^2 have to be normal FP32 numbers for the rows to be numbers
+        x->scan_ok = std::isfinite(S) && e >= -57 && e <= 62;
+        x->scale16 = std::ldexp(1.f, 5 - std::min(62, std::max(-57, e)));
         x->proj16 = dev_alloc<uint16_t>(x, x->n_pad16 * kScanRow);
         launch_augment16(proj_scan, n, x->n_pad16, x->scale16, kScanMarginWeight, x->scan_centre,
                          x->proj16, st);

@@ -81,9 +81,11 @@ int64_t ann_layout_bytes(const pmlsh_index* x, const AnnWorkspace& w, int64_t ba
 AnnWorkspace ann_workspace_base(const pmlsh_index* x, int k, int64_t B, bool wide = true) {
     AnnWorkspace w{};
     w.B = B;
-    // the batched path, unless the budget exceeds its limit or the plain
-    // FP32 path is switched on (read once per call: layout and launch agree)
-    w.fast = ann_fast_path(B) && tune_get(PMLSH_TUNE_FP32_PATH) == 0 && (wide || B <= kLeanBudget);
+    // the batched path, unless the budget exceeds its limit, the index's scan rows
+    // cannot be formed or the plain FP32 path is switched on (read once per
+    // call: layout and launch agree)
+    w.fast = ann_fast_path(B) && x->scan_ok && tune_get(PMLSH_TUNE_FP32_PATH) == 0 &&
+             (wide || B <= kLeanBudget);
     w.vals = w.fast && wide;
     w.pool_q = w.fast ? ann_pool_per_query(*x, B) : 0;
     w.per_query = (int64_t)MP * 8 + 64 + B * 8 + 3 * (int64_t)k * 4 +

@@ -284,6 +284,7 @@ struct pmlsh_index {
     uint16_t* proj16 = nullptr;  // n_pad16 x kScanRow FP16 rows of the matrix-core scan
     int64_t n_pad16 = 0;         // n rounded up to 64
     float scale16 = 1.f;         // power-of-two scale s of those rows
+    bool scan_ok = true;         // the projections lie where such rows can be formed
     float* chunk_cen = nullptr;  // n_pad16 / 64 x MP: centre of each 64-point chunk
     float* chunk_rad = nullptr;  // n_pad16 / 64: radius covering the chunk's points
     uint16_t* data16 = nullptr;  // n x d16 FP16 copy of D_leaf, rows scaled by a power of two

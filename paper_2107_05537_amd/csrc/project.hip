@@ -373,6 +373,7 @@ __global__ __launch_bounds__(256) void half_rows_kernel(
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     int e = 0;
     if (mx > 0.f) (void)frexpf(mx, &e);
+    e = max(e, 15 - 126);                         // s stays a normal number
     const float s = ldexpf(1.f, e - 15);          // mx / s < 2^15
     const bool inverse = e - 15 >= -126 && e - 15 <= 126;
     const float is = inverse ? ldexpf(1.f, 15 - e) : 0.f;
