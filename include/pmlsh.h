@@ -191,7 +191,8 @@ int pmlsh_ann(const pmlsh_index* index, const float* queries, int64_t nq,
  *   out_stats   optional nq x 4 int32 device pointer, as for pmlsh_ann.
  * The per-query parameters are copied before the call returns (args may be
  * reused) and taken to the device on `stream`; everything on the stream is
- * asynchronous. Errors: EINVAL (an entry or out_stride invalid, naming the
+ * asynchronous (with 64 such calls in flight on the device, the next one waits
+ * until one of them has taken its parameters). Errors: EINVAL (an entry or out_stride invalid, naming the
  * entry), EUNSUPPORTED (a k above PMLSH_MAX_K), ENOMEM, EDEVICE (also while
  * `stream` is being captured).
  */

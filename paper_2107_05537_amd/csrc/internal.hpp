@@ -105,7 +105,8 @@ void ws_free(void* p, hipStream_t st);
 void* ws_alloc_least(int64_t bytes, hipStream_t st, const std::function<bool(int64_t*)>& smaller);
 // Pinned host memory from a small per-device cache: a block given back is handed
 // out again once the work queued on st so far (its last reader) has completed.
-// pinned_free neither waits for that work nor throws.
+// pinned_alloc waits only where 64 small blocks are out under work that has not
+// ended.
 void* pinned_alloc(size_t bytes);
 void pinned_free(void* p, hipStream_t st);
 

@@ -9,6 +9,7 @@
 // finds no memory; the device holds at most the peak workspace of the calls that
 // overlapped.
 #include <algorithm>
+#include <deque>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -65,10 +66,12 @@ void trim(Cache& c) {
 thread_local BuildScratch* t_scratch = nullptr;   // of the build that this thread runs
 
 // Pinned host blocks of one device: handed out, and given back with the event
-// after which their last reader is done. Nothing waits for that event: of the
-// blocks whose readers are done, at most kPinnedBlocks of at most kPinnedMost
-// bytes are kept, and the next allocation frees the others.
-constexpr size_t kPinnedBlocks = 16, kPinnedMost = size_t(4) << 20;
+// after which their last reader is done. Those of at most kPinnedSmall bytes come
+// kPinnedSlab to an allocation (one of its own took longer than a call's other
+// host work) and are kept, in the order in which they came back; where the
+// readers of kPinnedMost of them are still at work, the next one is waited for.
+// Larger blocks are allocated on their own; of those that are idle one is kept.
+constexpr size_t kPinnedSmall = 65536, kPinnedSlab = 16, kPinnedMost = 64;
 
 struct PinnedBlock {
     void* p = nullptr;
@@ -78,13 +81,17 @@ struct PinnedBlock {
 struct PinnedCache {
     std::mutex mu;
     std::unordered_map<void*, PinnedBlock> live;
-    std::vector<PinnedBlock> back;
+    std::vector<PinnedBlock> fresh;         // small, not yet used
+    std::deque<PinnedBlock> back, large;
+    size_t made = 0;                        // small ones
 };
 PinnedCache g_pinned[kMaxDevices];
 
-void pinned_release(PinnedBlock& b) {
-    if (b.done) (void)hipEventDestroy(b.done);
-    (void)hipHostFree(b.p);
+bool idle(const PinnedBlock& b) { return hipEventQuery(b.done) == hipSuccess; }
+
+void event_of(PinnedBlock& b) {
+    if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess)
+        fail(PMLSH_EDEVICE, "hipEventCreate for a pinned block failed");
 }
 
 }  // namespace
@@ -94,46 +101,71 @@ void* pinned_alloc(size_t bytes) {
     PMLSH_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) fail(PMLSH_EDEVICE, "device ordinal out of range");
     PinnedCache& c = g_pinned[dev];
-    const size_t want = (std::max<size_t>(bytes, 1) + 65535) / 65536 * 65536;
     PinnedBlock b;
+    if (bytes <= kPinnedSmall) {
+        bool wait = false;
+        {
+            std::lock_guard<std::mutex> g(c.mu);
+            auto at = c.back.begin();
+            if (c.fresh.empty() && (at == c.back.end() || !idle(*at)) && c.made >= kPinnedMost) {
+                at = std::find_if(c.back.begin(), c.back.end(), idle);
+                wait = at == c.back.end() && !c.back.empty();
+                if (wait) at = c.back.begin();
+            }
+            if (at != c.back.end() && (wait || idle(*at))) {
+                b = *at;
+                c.back.erase(at);
+            } else {
+                if (c.fresh.empty()) {
+                    char* slab = nullptr;
+                    PMLSH_HIP(hipHostMalloc(&slab, kPinnedSlab * kPinnedSmall, hipHostMallocDefault));
+                    for (size_t i = 0; i < kPinnedSlab; ++i) {
+                        PinnedBlock x;
+                        x.p = slab + i * kPinnedSmall;
+                        x.size = kPinnedSmall;
+                        event_of(x);
+                        c.fresh.push_back(x);
+                        ++c.made;
+                    }
+                }
+                b = c.fresh.back();
+                c.fresh.pop_back();
+            }
+            (void)hipGetLastError();   // "not ready" of the queries
+            c.live[b.p] = b;
+        }
+        if (wait) PMLSH_HIP(hipEventSynchronize(b.done));
+        return b.p;
+    }
     std::vector<PinnedBlock> surplus;
     {
         std::lock_guard<std::mutex> g(c.mu);
-        // room for every block that is out to come back
-        std::vector<PinnedBlock> keep;
-        keep.reserve(c.back.size() + c.live.size() + 1);
-        // those still read first, then the idle ones, the smallest in front
-        auto mid = std::stable_partition(c.back.begin(), c.back.end(), [](const PinnedBlock& x) {
-            return hipEventQuery(x.done) != hipSuccess;
-        });
-        (void)hipGetLastError();   // "not ready" of the queries
-        std::sort(mid, c.back.end(),
-                  [](const PinnedBlock& x, const PinnedBlock& y) { return x.size < y.size; });
-        keep.assign(c.back.begin(), mid);
-        for (size_t idle = 0; mid != c.back.end(); ++mid) {
-            if (!b.p && mid->size >= want) {
-                b = *mid;
-            } else if (mid->size <= kPinnedMost && idle < kPinnedBlocks) {
-                keep.push_back(*mid);
-                ++idle;
-            } else {
-                surplus.push_back(*mid);
+        bool kept = false;
+        for (size_t i = 0; i < c.large.size();) {
+            const PinnedBlock x = c.large[i];
+            const bool take = !b.p && x.size >= bytes && idle(x);
+            if (!take && (!idle(x) || !kept)) {
+                kept = kept || idle(x);
+                ++i;
+                continue;
             }
+            c.large.erase(c.large.begin() + (std::ptrdiff_t)i);
+            if (take) b = x;
+            else surplus.push_back(x);
         }
+        (void)hipGetLastError();
         if (b.p) c.live[b.p] = b;
-        c.back.swap(keep);
     }
-    for (PinnedBlock& x : surplus) pinned_release(x);
+    for (PinnedBlock& x : surplus) {
+        (void)hipEventDestroy(x.done);
+        (void)hipHostFree(x.p);
+    }
     if (b.p) return b.p;
-    b.size = want;
-    PMLSH_HIP(hipHostMalloc(&b.p, want, hipHostMallocDefault));
-    if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
-        (void)hipHostFree(b.p);
-        fail(PMLSH_EDEVICE, "hipEventCreate for a pinned block failed");
-    }
+    b.size = bytes;
+    event_of(b);
+    PMLSH_HIP(hipHostMalloc(&b.p, bytes, hipHostMallocDefault));
     std::lock_guard<std::mutex> g(c.mu);
     c.live[b.p] = b;
-    c.back.reserve(c.back.size() + c.live.size());
     return b.p;
 }
 
@@ -145,15 +177,11 @@ void pinned_free(void* p, hipStream_t st) {
     std::lock_guard<std::mutex> g(c.mu);
     auto it = c.live.find(p);
     if (it == c.live.end()) return;
-    PinnedBlock b = it->second;
+    const PinnedBlock b = it->second;
     c.live.erase(it);
-    if (hipEventRecord(b.done, st) != hipSuccess) {
-        // no event: only a wait tells when the readers are done
-        (void)hipStreamSynchronize(st);
-        pinned_release(b);
-        return;
-    }
-    c.back.push_back(b);
+    // without an event only a wait tells when the readers are done
+    if (hipEventRecord(b.done, st) != hipSuccess) (void)hipStreamSynchronize(st);
+    (b.size == kPinnedSmall ? c.back : c.large).push_back(b);
 }
 
 void* ws_alloc(size_t bytes, hipStream_t st) {

@@ -177,27 +177,39 @@ def test_workspace_shrinks_to_the_memory_there_is(tmp_path):
     """)
 
 
-def test_pinned_blocks_never_wait(tmp_path):
-    """Any number and size of blocks given back under work that has not ended: no
-    wait, no block handed out twice, and a bounded number kept afterwards."""
+def test_pinned_blocks(tmp_path):
+    """Blocks given back under work that has not ended: no wait until 64 small ones
+    are out, no block handed out twice, a bounded number kept afterwards."""
     _run(tmp_path, r"""
     ihipStream_t st, other;
     st.busy = true;
     std::map<void*, int> seen;
-    for (int i = 0; i < 40; ++i) {
-        void* p = pinned_alloc(i % 8 ? 1000 : 8 << 20);
+    for (int i = 0; i < 60; ++i) {
+        const size_t bytes = i % 8 ? 1000 + i : 8 << 20;
+        char* p = (char*)pinned_alloc(bytes);
         CHECK(++seen[p] == 1);
+        p[0] = p[bytes - 1] = 1;
         pinned_free(p, &st);
     }
-    CHECK(model().waits == 0 && model().host.size() == 40);
-    // another stream's block is free at once and comes back
+    CHECK(model().waits == 0);
+    // another stream's block is free at once
     void* q = pinned_alloc(1000);
     CHECK(!seen.count(q));
     pinned_free(q, &other);
-    CHECK(pinned_alloc(1000) == q && model().host.size() == 41);
+    for (int i = 0; i < 11; ++i) {
+        void* p = pinned_alloc(1000);
+        CHECK(model().waits == 0);
+        if (p != q) CHECK(++seen[p] == 1);
+        pinned_free(p, p == q ? &other : &st);
+    }
+    while (pinned_alloc(65536) && model().waits == 0) {}   // all 64 are out
+    CHECK(model().waits == 1);
     st.busy = false;
-    void* r = pinned_alloc(2000);
-    CHECK(seen.count(r) && model().waits == 0);
-    CHECK(model().host.size() <= 16 + 2);                // kept, and the two in use
-    for (auto& h : model().host) CHECK(h.second <= (4u << 20));
+    void* r = pinned_alloc(9 << 20);                       // the large ones go, but one
+    CHECK(r && model().waits == 1);
+    size_t large = 0;
+    for (auto& h : model().host) large += h.second > (4u << 20);
+    CHECK(large == 2);
+    pinned_free(r, &st);
+    CHECK(pinned_alloc(9 << 20) == r);
     """)
