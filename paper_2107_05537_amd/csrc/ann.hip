@@ -3143,7 +3143,8 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         //   20,000 x 32 (*)     256 queries, B = 20     58 /  59 /  62 /  67
         //   1M x 128              1 query,   B = 20     56 /  58 /  61 /  62
         //                       256 queries, B = 520    85 /  83 /  84 /  90
-        //   1M x 256             32 queries, B = 900    89 /  82 /  80 /  80
+        //   1M x 256              1 query,   B = 885     - /   - /  70 /  68
+        //                       32 queries, B = 900    89 /  82 /  80 /  80
         //                       256 queries, B = 1,900 211 / 181 / 170 / 198
         //                       512 queries, B = 1,900 266 / 243 / 262 / 271
         //                     1,024 queries, B = 900   212 / 229 / 269 / 227
@@ -3155,7 +3156,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         const int64_t B = L.budget, nq = L.nq;
         if (B > kLeanBudget)
             launch_pool<1024>(a, L, lds0, lds, stream);
-        else if (nq <= 32 && B >= 768 && x.d16 > 256)
+        else if (nq <= 32 && B >= 768 && x.d16 >= 256)
             launch_pool<WG>(a, L, lds0, lds, stream);
         else if (nq > 512 || B < 128)
             launch_finish<WG>(a, L, lds, stream);
