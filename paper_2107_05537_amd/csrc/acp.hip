@@ -368,8 +368,7 @@ __global__ __launch_bounds__(WG) void acp_tile_scan_kernel(
 // point in the leaf, lcen the leaf's centre in one line.
 __global__ __launch_bounds__(WG) void acp_pd_sorted_kernel(
     const float* __restrict__ phi, const float* __restrict__ plo, NodeView v, int64_t leaf_base,
-    int64_t n, int L, int64_t n_leaves, float* __restrict__ ppd, float4* __restrict__ skey,
-    float* __restrict__ lcen) {
+    int64_t n, int L, int64_t n_leaves, float4* __restrict__ skey, float* __restrict__ lcen) {
     const int64_t leaf = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
     if (leaf >= n_leaves) return;          // the whole wave leaves together
     const int lane = lane_id();
@@ -388,7 +387,6 @@ __global__ __launch_bounds__(WG) void acp_pd_sorted_kernel(
             acc = __fmaf_rn(dt, dt, acc);
         }
         val = sqrtf(acc);
-        ppd[p0 + lane] = val;
     }
     int idx = lane;
     // bitonic network over the 64 lanes on (value, position)
@@ -444,12 +442,6 @@ __device__ __forceinline__ float readlane_f(float x, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
 
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
 // Lanes with a PD candidate range of at most this many pairs each take them
 // one by one; a wider tile is scanned whole.
 constexpr int kSparseMax = 40;
@@ -478,7 +470,8 @@ constexpr int kScanStage = 256;   // pairs staged per wave
 // (branch and bound) the one counter's atomics bound it, hence the stage.
 __global__ __launch_bounds__(WG) void acp_tile_scan_wave_kernel(
     const float* __restrict__ phi, const float* __restrict__ plo,
-    const float4* __restrict__ skey, const float* __restrict__ lcen, const int32_t* __restrict__ perm, int64_t n, int L,
+    const float4* __restrict__ skey, const float* __restrict__ lcen,
+    const int32_t* __restrict__ perm, int64_t n, int L,
     const int2* __restrict__ tiles, int64_t n_tiles, float R2, float Rlim,
     uint32_t* __restrict__ ck0, uint32_t* __restrict__ cii, uint32_t* __restrict__ cjj,
     int64_t cap, unsigned long long* __restrict__ counter,
@@ -1810,7 +1803,7 @@ __global__ __launch_bounds__(WG) void acp_band_gather_kernel(
 // (freed and allocated anew) only when a call needs more than it holds.
 enum Slot {
     S_HIST, S_COUNT, S_TILES, S_PPD, S_SEEDS, S_CAND = S_SEEDS + 3, S_KEPT = S_CAND + 3,
-    S_POOL = S_KEPT + 3, S_TOP = S_POOL + 3, S_SKEY = S_TOP + 3, S_LCEN, S_STATE, S_GHIST,
+    S_POOL = S_KEPT + 3, S_TOP = S_POOL + 3, S_SKEY = S_TOP + 3, S_STATE, S_GHIST,
     S_SLO, S_STATE2, S_COUNTS, S_RADIUS, S_BAND, S_COUNT_ALL = S_BAND + 3
 };
 
@@ -2019,7 +2012,8 @@ struct TileScan {
     hipStream_t st;
     NodeView v;
     int64_t leaf_base;
-    DevBuf ppd, skey, lcen;
+    DevBuf ppd, skey;   // by the kernel: leaves above 64 points, or up to 64
+    float* lcen = nullptr;
     bool wave = false;
     size_t lds = 0;
 
@@ -2027,24 +2021,23 @@ struct TileScan {
         : x(idx), st(s),
           v{idx->tree.centre, idx->tree.radius, idx->tree.hr_min, idx->tree.hr_max, idx->n_nodes,
             idx->num_pivots},
-          leaf_base(idx->level_begin[idx->levels - 1]), ppd(idx, S_PPD), skey(idx, S_SKEY),
-          lcen(idx, S_LCEN) {}
+          leaf_base(idx->level_begin[idx->levels - 1]), ppd(idx, S_PPD), skey(idx, S_SKEY) {}
 
-    // parent distances (and their per-leaf sorted copies) of every point
+    // parent distances of every point, sorted per leaf for the wave scan
     void prepare() {
         const int64_t n = x->n, NL = x->n_leaves;
         const int L = x->leaf_size;
-        ppd.alloc((size_t)n * sizeof(float));
         wave = L <= 64;
         if (wave) {
-            skey.alloc((size_t)NL * 64 * sizeof(float4));
-            lcen.alloc((size_t)NL * MP * sizeof(float));
+            skey.alloc((size_t)NL * (64 * sizeof(float4) + MP * sizeof(float)));
+            lcen = reinterpret_cast<float*>(skey.as<float4>() + NL * 64);
             hipLaunchKernelGGL(acp_pd_sorted_kernel, dim3((unsigned)((NL + 3) / 4)), dim3(WG), 0,
                                st, x->proj_hi, x->proj_lo, v, leaf_base, n, L, NL,
-                               ppd.as<float>(), skey.as<float4>(), lcen.as<float>());
+                               skey.as<float4>(), lcen);
             PMLSH_HIP(hipGetLastError());
             return;
         }
+        ppd.alloc((size_t)n * sizeof(float));
         hipLaunchKernelGGL(acp_pd_kernel, dim3((unsigned)((n + WG - 1) / WG)), dim3(WG), 0, st,
                            x->proj_hi, x->proj_lo, v, leaf_base, n, L, ppd.as<float>());
         PMLSH_HIP(hipGetLastError());
@@ -2065,7 +2058,7 @@ struct TileScan {
             const int64_t waves = std::min<int64_t>(n_tiles, 16384);
             hipLaunchKernelGGL(acp_tile_scan_wave_kernel, dim3((unsigned)((waves + 3) / 4)),
                                dim3(WG), 0, st, x->proj_hi, x->proj_lo,
-                               skey.as<float4>(), lcen.as<float>(), x->perm, x->n,
+                               skey.as<float4>(), lcen, x->perm, x->n,
                                x->leaf_size, tiles, n_tiles, R2, Rlim, k0, ii, jj, cap, counter,
                                dn_tiles, rad);
         } else {
@@ -2619,7 +2612,6 @@ void run_acp_bb(const pmlsh_index* x, int k, double c, double confidence, double
     pmlsh_plan plan;
     plan_params(x->n, x->m, k, c, confidence, beta, &plan);
     const int64_t n = x->n;
-    const int L = x->leaf_size;
     const int64_t NL = x->n_leaves;
     const int64_t n_pairs = n * (n - 1) / 2;
     const int64_t T = std::min<int64_t>(plan.acp_budget, n_pairs);
