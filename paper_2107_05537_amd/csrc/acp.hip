@@ -1820,7 +1820,7 @@ struct DevBuf {
                 (void)hipFree(b.first);
                 b = {nullptr, 0};
             }
-            PMLSH_HIP(hipMalloc(&b.first, bytes));
+            b.first = device_malloc(bytes);
             b.second = bytes;
         }
         p = b.first;
