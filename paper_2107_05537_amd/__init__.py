@@ -257,13 +257,17 @@ def _query_args(params):
         rows["k"][:len(ks)] = ks
     except OverflowError:
         rows["k"][:len(ks)] = [ctypes.c_int32(k).value for k in ks]
+    # of plain dicts a column at once; other mappings decide themselves what is in them
+    plain = set(map(type, params)) <= {dict}
     for name, default in _QUERY_DEFAULTS.items():
-        if not any(map(operator.contains, params, itertools.repeat(name))):
+        if plain and not any(map(operator.contains, params, itertools.repeat(name))):
             rows[name][:len(ks)] = default
             continue
         try:
-            column = list(map(operator.itemgetter(name), params))
+            column = list(map(operator.itemgetter(name), params)) if plain else None
         except KeyError:
+            column = None
+        if column is None:
             column = [p.get(name, default) for p in params]
         rows[name][:len(ks)] = list(map(float, column))
     return rows.ctypes.data_as(ctypes.POINTER(_QueryArgs)), max(ks, default=1)
