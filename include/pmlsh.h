@@ -46,6 +46,7 @@ extern "C" {
 #define PMLSH_MAX_M 16          /* hash functions per index                  */
 #define PMLSH_MAX_PIVOTS 8      /* global pivots of the PM-tree              */
 #define PMLSH_MAX_K 1024        /* results per ANN query / ACP call          */
+#define PMLSH_BATCHED_BUDGET 196608 /* largest budget B of the batched ANN path */
 
 /* exit kinds reported per ANN query (Algorithm 2)                          */
 #define PMLSH_EXIT_NEAR 1      /* k verified points within c*r              */

@@ -27,6 +27,7 @@ library_path = os.path.join(_HERE, "libpmlsh.so")
 OK, EINVAL, ENOMEM, EDEVICE, EUNSUPPORTED = 0, -1, -2, -3, -4
 EXIT_NEAR, EXIT_BUDGET = 1, 2
 MAX_K = 1024
+BATCHED_BUDGET = 196608      # largest budget of the batched ANN path
 
 
 class PmlshError(RuntimeError):

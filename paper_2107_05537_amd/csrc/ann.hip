@@ -38,7 +38,7 @@ constexpr int NWAVE = WG / 64;
 constexpr int kMaxWaves = 16;   // waves of the largest workgroup (1,024 threads)
 constexpr int NB = 2048;    // histogram bins of one radix-select step
 constexpr int CAP = 2048;   // keys sorted in LDS at once (power of two)
-constexpr int64_t kWideBudget = 196608;   // largest budget of the batched path
+constexpr int64_t kWideBudget = PMLSH_BATCHED_BUDGET;
 constexpr int64_t kSelMax = 8192;         // most chunks the bound chooses per query
 static_assert(kSelMax * 64 >= 2 * kWideBudget + 128, "the chosen chunks must hold 2 * budget points");
 constexpr int MAX_LEVELS = 16;
