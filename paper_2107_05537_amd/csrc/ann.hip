@@ -2564,6 +2564,7 @@ __device__ void answer_members(const AnnArgs& a, int64_t qi, const float* qs, in
     }
     __syncthreads();
     const int m = sh.cnt1;
+    __syncthreads();   // the counter is used again below
     if (m <= kRerankCap) {
         // the FP64 re-rank decides their order from their rows (no FP32 value
         // is needed)

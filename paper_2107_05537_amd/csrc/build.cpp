@@ -2,7 +2,8 @@
 //
 //   1. D and A to HBM (if given on the host); A padded to 16 zero-filled rows;
 //   2. O' = D A^T on the FP64 matrix cores (hi/lo FP32 pair per coordinate);
-//   3. the PM-tree is bulk-loaded on the host over the FP32 `hi` coordinates;
+//   3. the PM-tree is bulk-loaded over the FP32 `hi` coordinates (splits and node
+//      summaries on the device, inner levels and rounding on the host);
 //   4. D, O'_hi and O'_lo are permuted to leaf order on the device, so a leaf
 //      is one contiguous run of rows for the scans and the verification;
 //   5. the r_min sample: S = min(n(n-1)/2, 100000) SplitMix64-drawn pairs,
