@@ -2973,9 +2973,10 @@ void run_acp_lca(const pmlsh_index* x, int k, double c, double confidence, doubl
             if ((double)I.rad[e] < Rlca) {
                 found.push_back(e);
             } else {
-                for (int64_t ch = x->level_begin[I.level[e] + 1]; ch < x->level_begin[I.level[e] + 2];
-                     ++ch)
-                    if (I.parent[ch] == e) stack.push_back(ch);
+                // (a search of the whole level below for them took 16 to 20 us
+                // of a 150 us call at 50,021 points, by where the loop lay in
+                // memory, and grows with the square of the nodes)
+                for (int32_t ch = cb[e]; ch < ce[e]; ++ch) stack.push_back(ch);
             }
         }
     }
