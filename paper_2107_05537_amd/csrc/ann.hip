@@ -2914,9 +2914,9 @@ __global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
 // queries that overflow cost milliseconds on the per-query kernel: 1M x 256
 // without contrast, FP16 filter, 1,024 queries of B = 2,500 52 ms a call when all
 // of them went there, 19 with the entries of the exact filter, 1.0 with twice as
-// many.
-int64_t ann_pool_per_query(const pmlsh_index& x, int64_t budget) {
-    const int64_t f = x.filter_gemm ? 2 : 1;
+// many. least: the exact filter's, where memory is short.
+int64_t ann_pool_per_query(const pmlsh_index& x, int64_t budget, bool least) {
+    const int64_t f = x.filter_gemm && !least ? 2 : 1;
     const int64_t want = std::max(std::min<int64_t>(f * 8 * budget, f * 65536), (f + 2) * budget);
     return std::min(x.n, std::max<int64_t>(want, 16384));
 }

@@ -45,8 +45,13 @@ namespace {
 // path, the chunk distances, chosen chunks and the chunk x query mask (a
 // 64-bit word per chunk and 64 queries, both layouts); plus the frontier
 // lists of the per-query kernel's workgroups.
+// All: budgets above kLeanBudget take the batched path too, and long candidate
+// lists keep their pd^2 bits in memory. Short: neither. Least: besides, the pools
+// hold what an exact filter needs.
+enum class Pools { All, Short, Least };
 struct AnnWorkspace {
     int64_t B, pool_q, per_query, nchunk, batch, slots, bytes;
+    Pools pools;
     bool fast;
     bool vals;   // pd^2 bits kept per pool entry
 };
@@ -76,18 +81,18 @@ int64_t ann_layout_bytes(const pmlsh_index* x, const AnnWorkspace& w, int64_t ba
     return batch * w.per_query + mask_bytes + slots * 2 * x->n_leaves * 4;
 }
 
-// wide: budgets above kLeanBudget take the batched path too, and long candidate
-// lists keep their pd^2 bits in memory.
-AnnWorkspace ann_workspace_base(const pmlsh_index* x, int k, int64_t B, bool wide = true) {
+AnnWorkspace ann_workspace_base(const pmlsh_index* x, int k, int64_t B, Pools pools = Pools::All) {
+    const bool wide = pools == Pools::All;
     AnnWorkspace w{};
     w.B = B;
+    w.pools = pools;
     // the batched path, unless the budget exceeds its limit, the index's scan rows
     // cannot be formed or the plain FP32 path is switched on (read once per
     // call: layout and launch agree)
     w.fast = ann_fast_path(B) && x->scan_ok && tune_get(PMLSH_TUNE_FP32_PATH) == 0 &&
              (wide || B <= kLeanBudget);
     w.vals = w.fast && wide;
-    w.pool_q = w.fast ? ann_pool_per_query(*x, B) : 0;
+    w.pool_q = w.fast ? ann_pool_per_query(*x, B, pools == Pools::Least) : 0;
     w.per_query = (int64_t)MP * 8 + 64 + B * 8 + 3 * (int64_t)k * 4 +
                   (w.fast ? 4 * 4 + w.pool_q * (w.vals ? 8 : 4) + B * 4 : 0) +
                   (w.fast && x->filter_gemm ? (MP + 1) * 4 : 0);
@@ -119,15 +124,14 @@ AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B) {
 }
 
 // The next smaller layout, for a device that has no memory for w: half the
-// queries per batch, then the one without pools for large budgets. False when
-// there is none.
+// queries per batch, then shorter pools. False when there is none.
 bool ann_workspace_smaller(const pmlsh_index* x, int k, AnnWorkspace* w) {
     if (w->batch > 1) {
         ann_workspace_size(x, w->batch / 2, w);
         return true;
     }
-    if (!w->vals) return false;
-    *w = ann_workspace_base(x, k, w->B, false);
+    if (!w->fast || w->pools == Pools::Least) return false;
+    *w = ann_workspace_base(x, k, w->B, w->vals ? Pools::Short : Pools::Least);
     ann_workspace_size(x, 1, w);
     return true;
 }
@@ -148,8 +152,8 @@ void* ann_workspace_alloc(const pmlsh_index* x, int64_t nq, int k, int64_t B, hi
 // the frontier lists, the largest batch that fits in the rest. batch = 0
 // when not even one query fits.
 AnnWorkspace ann_workspace_in(const pmlsh_index* x, int64_t nq, int k, int64_t B, int64_t cap,
-                              bool wide = true) {
-    AnnWorkspace w = ann_workspace_base(x, k, B, wide);
+                              Pools pools) {
+    AnnWorkspace w = ann_workspace_base(x, k, B, pools);
     const int64_t per_slot = 2 * x->n_leaves * 4;
     int64_t slots = std::min<int64_t>(front_slots_most(w), (cap / 4) / per_slot);
     slots = std::max<int64_t>(slots, 1);
@@ -165,12 +169,13 @@ AnnWorkspace ann_workspace_in(const pmlsh_index* x, int64_t nq, int k, int64_t B
     return w;
 }
 
-// As ann_workspace_in for a region of a launch; the layout without pools where
-// those leave no room for a single query.
+// As ann_workspace_in for a region of a launch; shorter pools where those leave no
+// room for a single query.
 AnnWorkspace ann_workspace_region(const pmlsh_index* x, int64_t nq, int k, int64_t B, int64_t bytes,
-                                  bool wide = true) {
-    AnnWorkspace w = ann_workspace_in(x, nq, k, B, bytes, wide);
-    if (w.batch < 1 && wide) w = ann_workspace_in(x, nq, k, B, bytes, false);
+                                  Pools pools = Pools::All) {
+    AnnWorkspace w = ann_workspace_in(x, nq, k, B, bytes, pools);
+    if (w.batch < 1 && pools == Pools::All) w = ann_workspace_in(x, nq, k, B, bytes, Pools::Short);
+    if (w.batch < 1) w = ann_workspace_in(x, nq, k, B, bytes, Pools::Least);
     return w;
 }
 
@@ -361,9 +366,9 @@ void run_ann_in(const pmlsh_index* x, const float* queries, int64_t nq, int k, d
     // a small fixed region holds most queries without the lists' pd^2 bits; a
     // large budget whose candidate pool does not fit takes the per-query path
     const AnnWorkspace w = ann_workspace_region(x, nq, k, plan.budget, region_bytes,
-                                                plan.budget > kLeanBudget);
+                                                plan.budget > kLeanBudget ? Pools::All : Pools::Short);
     if (w.batch < 1) {
-        const AnnWorkspace one = ann_workspace_in(x, 1, k, plan.budget, int64_t(1) << 62, false);
+        const AnnWorkspace one = ann_workspace_in(x, 1, k, plan.budget, int64_t(1) << 62, Pools::Least);
         fail(PMLSH_EUNSUPPORTED,
              "one query of this index needs " + std::to_string(one.bytes) +
                  " bytes of workspace; the fixed region holds " + std::to_string(region_bytes));
@@ -427,7 +432,7 @@ int64_t ann_workspace_bytes_mixed(const pmlsh_index* x, int64_t nq, int kmax, in
 }
 
 int64_t ann_workspace_bytes_least(const pmlsh_index* x, int kmax, int64_t bmax) {
-    AnnWorkspace w = ann_workspace_base(x, kmax, bmax, false);
+    AnnWorkspace w = ann_workspace_base(x, kmax, bmax, Pools::Least);
     ann_workspace_size(x, 1, &w);
     return w.bytes;
 }

@@ -428,7 +428,7 @@ struct AnnLaunch {
 };
 void launch_ann(const AnnLaunch& a, hipStream_t stream);
 int ann_lds_bytes(int d_pad);
-int64_t ann_pool_per_query(const pmlsh_index& x, int64_t budget);
+int64_t ann_pool_per_query(const pmlsh_index& x, int64_t budget, bool least);
 bool ann_fast_path(int64_t budget);
 
 }  // namespace pmlsh

@@ -102,6 +102,25 @@ def test_fixed_workspace_too_small_for_the_pools():
     assert e.value.code == pm.EUNSUPPORTED
 
 
+def test_fixed_workspace_with_room_for_an_exact_filters_pools():
+    """29.8 million points: the fixed array holds one query with 16,384 pool entries, not
+    with the 32,768 that a low-precision filter takes at the largest lean budget."""
+    pm = _gpu()
+    say("case: noalloc with the least pools, n=29.765M")
+    n = 29_765_000
+    D, Q, A = _points(n, 4, "clusters", 5, 3)
+    idx = pm.Index(D, A[:4].contiguous(), filter_gemm=pm.FILTER_GEMM_FP16)
+    del D
+    beta = (2_048 - 10) / n
+    assert pm.plan_params(n, 4, 10, 1.5, CONF, beta)["budget"] == 2_048
+    ref = [t.cpu().numpy() for t in idx.ann(Q, 10, beta=beta, stats=True)]
+    ids = torch.empty((3, 10), dtype=torch.int64, device="cuda")
+    dist = torch.empty((3, 10), dtype=torch.float32, device="cuda")
+    st = torch.empty((3, 4), dtype=torch.int32, device="cuda")
+    idx.ann_noalloc(Q, 10, 1.5, CONF, beta, 0.0, ids, dist, st)
+    _same([t.cpu().numpy() for t in (ids, dist, st)], ref)
+
+
 # budgets whose chosen chunks outgrow the usual list (from 32,736 points), at which its
 # cap is reached (without contrast), and on both sides of the batched path's limit
 @pytest.mark.parametrize("n,budget,kind", [
