@@ -253,7 +253,9 @@ def _query_args(params):
     """The parameter sets as an array of pmlsh_query_args (a column at a time:
     a thousand sets in 0.2 ms instead of 1 ms one by one), and the largest k."""
     rows = np.zeros(max(1, len(params)), dtype=_QUERY_DTYPE)
-    ks = list(map(int, map(operator.itemgetter("k"), params)))
+    ks = list(map(operator.itemgetter("k"), params))
+    if not set(map(type, ks)) <= {int}:
+        ks = list(map(int, ks))
     try:
         rows["k"][:len(ks)] = ks
     except OverflowError:
