@@ -1426,6 +1426,12 @@ constexpr uint32_t kCenBinBase = 63u << 4;
 constexpr int kGrpCap = 2048;
 constexpr size_t kTauGroupLds = 64 * 1024;
 
+// Bits of the squared radius of the first range query.
+__device__ __forceinline__ uint32_t first_radius_bits(const AnnQueryParams& p) {
+    const double rd = p.t * p.r_min;
+    return __float_as_uint((float)(rd * rd));
+}
+
 // Upper bound tau on the budget-th smallest projected distance of one query,
 // and the query's row of the chunk mask:
 //   1. the squared distances from q' to every 64-point chunk centre (computed
@@ -1443,12 +1449,10 @@ constexpr size_t kTauGroupLds = 64 * 1024;
 // `budget` points and therefore the budget nearest points by projected
 // distance. The choice of chunks only affects how tight tau is, never its
 // validity.
-__global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
-    const int64_t qi = blockIdx.x;
-    QueryCtx qc;
-    load_query(a, qi, nullptr, qc);
+//
+// Steps 1 to 3 are this function's, which returns tau^2.
+__device__ __forceinline__ float budget_radius2(const AnnArgs& a, int64_t qi, const QueryCtx& qc,
+                                                Smem& sh, unsigned char* smem_raw) {
     const int nch = (int)(a.n_pad16 >> 6);
     const int ng4 = (nch + 3) >> 2;
     const int ngr = (nch + 63) >> 6;
@@ -1671,6 +1675,23 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
         // rounding left fewer than `budget` chosen points inside R: no bound
         R2 = __int_as_float(0x7f800000);
     }
+    return R2;
+}
+
+// BALL: one range query answers ((r,c)-BC) and its ball is expected to hold less than
+// the budget, so that tau is its radius and no bound is needed.
+template <bool BALL>
+__global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
+    const int64_t qi = blockIdx.x;
+    QueryCtx qc;
+    load_query(a, qi, nullptr, qc);
+    float R2;
+    if constexpr (BALL)
+        R2 = __uint_as_float(first_radius_bits(query_params(a, qi)));
+    else
+        R2 = budget_radius2(a, qi, qc, sh, smem_raw);
 
     // 4: the radius of the chunk-ball test, which mask_kernel applies: it
     // covers the FP32 errors of pd^2 and of the test's own distance
@@ -1735,6 +1756,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
             // outside the FP16 range (or no finite bound): every product is
             // +1, no candidate, and the per-query path answers the query
             w[18] = (_Float16)1.f;
+            if constexpr (BALL) a.l_count[qi * a.l_stride] = 0xffffffffu;   // as a list too long
         }
         uint4* dst = reinterpret_cast<uint4*>(a.qaug + qi * 32);
         const uint4* src = reinterpret_cast<const uint4*>(w);
@@ -2750,13 +2772,8 @@ __global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
 // (gathered through 128-byte lines), the verification by HBM (the FP16 rows of
 // all members), the answer by the latency of its passes.
 
-// Bits of the squared radius of the first range query.
-__device__ __forceinline__ uint32_t first_radius_bits(const AnnQueryParams& p) {
-    const double rd = p.t * p.r_min;
-    return __float_as_uint((float)(rd * rd));
-}
-
-template <int T>
+// BALL: after tau_kernel<true>, with lists that hold the whole ball however short.
+template <int T, bool BALL>
 __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
@@ -2764,7 +2781,7 @@ __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
     const AnnQueryParams qpar = query_params(a, qi);
     const int B = qpar.budget;
     const uint32_t cnt = a.l_count[qi * a.l_stride];
-    if (cnt > (uint32_t)a.q_cap || cnt < (uint32_t)B) {
+    if (cnt > (uint32_t)a.q_cap || (!BALL && cnt < (uint32_t)B)) {
         // list overflow, or the bound fell short: the per-query kernel answers
         if (threadIdx.x == 0) {
             a.q_flag[qi] = -1;
@@ -2786,6 +2803,20 @@ __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
         const int slot = in ? s0 : B - 1 - s1;
         if (take && slot >= 0 && slot < B) cpos[slot] = pos;
     };
+    if (BALL && n <= B) {
+        // every entry is in L
+        if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
+        __syncthreads();
+        for (int b0 = 0; b0 < n; b0 += T) {
+            const int i = b0 + threadIdx.x;
+            const int32_t pos = i < n ? (int32_t)list[i] : 0;
+            const float pd2 = i < n ? proj_dist2(a.proj + (int64_t)pos * MP, qc.qp) : 0.f;
+            emit(i < n, pos, __float_as_uint(pd2));
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) a.q_flag[qi] = sh.cnt0;
+        return;
+    }
     if (n <= CAP) {
         lds_cut<T>(a, qi, qc, list, n, B, sh);
         if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
@@ -2965,17 +2996,18 @@ int ann_lds_bytes(int d_pad) {
 
 namespace {
 
-template <int T>
+template <int T, bool BALL = false>
 void launch_pool(AnnArgs& a, const AnnLaunch& L, int lds_cut, int lds_answer, hipStream_t stream) {
     // members of L per verify workgroup: enough workgroups to fill the chip a few
     // times over, at least the 64 rows that one has in flight
     const int64_t per = (L.budget * L.nq + 4095) / 4096;
     a.vslice = (int)std::min<int64_t>(512, std::max<int64_t>(64, (per + 63) / 64 * 64));
-    PMLSH_HIP(hipFuncSetAttribute((const void*)pool_cut_kernel<T>,
+    PMLSH_HIP(hipFuncSetAttribute((const void*)pool_cut_kernel<T, BALL>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_cut));
     PMLSH_HIP(hipFuncSetAttribute((const void*)pool_answer_kernel<T>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_answer));
-    hipLaunchKernelGGL(pool_cut_kernel<T>, dim3((unsigned)L.nq), dim3(T), (unsigned)lds_cut, stream, a);
+    hipLaunchKernelGGL((pool_cut_kernel<T, BALL>), dim3((unsigned)L.nq), dim3(T), (unsigned)lds_cut,
+                       stream, a);
     const dim3 vgrid((unsigned)((L.budget + a.vslice - 1) / a.vslice), (unsigned)L.nq);
     hipLaunchKernelGGL(pool_verify_kernel, vgrid, dim3(WG), (unsigned)(4 * a.d16), stream, a);
     hipLaunchKernelGGL(pool_answer_kernel<T>, dim3((unsigned)L.nq), dim3(T), (unsigned)lds_answer,
@@ -3095,7 +3127,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             StageTimer tm(PMLSH_STAGE_TAU, stream);
             const int64_t ngr = (nchunk + 63) / 64;
             a.sample = ann_bound_sample(x);
-            a.ordered = L.nq >= 64 && L.budget > kLeanBudget;
+            a.ordered = L.nq >= 64 && L.budget > kLeanBudget && !L.ball;
             a.sel_cap = (int)std::min<int64_t>(kSelMax, std::max<int64_t>(kSelCap, (a.sample * L.budget + 63) / 64 + 1));
             a.grp_cap = (int)std::min<int64_t>(kGrpCap, std::max<int64_t>(0, tune_get(PMLSH_TUNE_GROUP_LIST)));
             const size_t min_bytes = 2 * (size_t)((ngr + 7) & ~7);
@@ -3104,9 +3136,10 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             const size_t lds_t = std::max((size_t)lds0, offsetof(Smem, skey) +
                                           (a.glds ? min_bytes : 0) +
                                           4 * (size_t)(kGrpCap + a.sel_cap));
-            PMLSH_HIP(hipFuncSetAttribute((const void*)tau_kernel,
+            auto* tau_fn = L.ball ? tau_kernel<true> : tau_kernel<false>;
+            PMLSH_HIP(hipFuncSetAttribute((const void*)tau_fn,
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_t));
-            hipLaunchKernelGGL(tau_kernel, dim3((unsigned)L.nq), dim3(WG), (unsigned)lds_t, stream, a);
+            hipLaunchKernelGGL(tau_fn, dim3((unsigned)L.nq), dim3(WG), (unsigned)lds_t, stream, a);
             PMLSH_HIP(hipGetLastError());
             dim3 mgrid((unsigned)((nchunk + MCH - 1) / MCH), (unsigned)((L.nq + MQB - 1) / MQB));
             hipLaunchKernelGGL(mask_kernel, mgrid, dim3(WG), 0, stream, a);
@@ -3162,7 +3195,9 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         //   20,000 x 900         32 queries, B = 900   126 / 106 / 105 /  93
         // (*) data without contrast.
         const int64_t B = L.budget, nq = L.nq;
-        if (B > kLeanBudget)
+        if (L.ball)
+            launch_pool<1024, true>(a, L, lds0, lds, stream);
+        else if (B > kLeanBudget)
             launch_pool<1024>(a, L, lds0, lds, stream);
         else if (nq <= 32 && B >= 768 && x.d16 >= 256)
             launch_pool<WG>(a, L, lds0, lds, stream);

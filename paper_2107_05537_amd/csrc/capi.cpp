@@ -212,6 +212,7 @@ struct AnnCall {
     const AnnQueryParams* qpar;
     int out_stride;
     int max_rounds;
+    bool ball = false;
 };
 
 // The batches of one ANN call over the workspace region ws laid out by w.
@@ -272,6 +273,7 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
         L.qpar = call.qpar ? call.qpar + q0 : nullptr;
         L.out_stride = stride;
         L.fast = fast;
+        L.ball = fast && call.ball;
         L.ws_front = front;
         L.front_slots = std::min<int64_t>(w.slots, nb);
         L.ws_cpos = cpos;
@@ -344,8 +346,25 @@ void run_ann(const pmlsh_index* x, const float* queries, int64_t nq, int k, doub
     pmlsh_plan plan;
     r_min = ann_plan(x, k, c, confidence, beta, r_min, &plan);
     if (nq == 0) return;
+    // (r,c)-BC of a large budget whose ball the sampled distances expect to hold fewer
+    // points: the filter looks for the ball's points instead of for the budget's. The
+    // rule leaves room for queries whose balls hold many more than the sample's, since
+    // lists that outgrow the pools are the per-query kernel's after all. us per call of
+    // 1,000 queries, for the budget / for the ball / on the per-query kernel, by r in
+    // units of the radius whose ball is expected to hold the budget:
+    //   30,000 x 32, B = 2,902     r = 0.25   239 /   136 /    126
+    //                              r = 0.5    245 /   145 /    161
+    //   1M x 128, B = 96,695       r = 0.25 3,812 /   224 /  1,073
+    //                              r = 0.5  3,837 /   284 /  2,404
+    //                              r = 0.8  6,467 / 23,324 / 24,972
+    //   1M x 128 without contrast,
+    //             B = 3,001        r = 0.5    643 /   227 / 16,668
+    //                              r = 0.65   700 / 23,720 / 29,888
+    const double share = plan.budget * 100 >= x->n ? 0.7 : 0.6;
+    const bool ball = max_rounds == 1 && plan.budget > kLeanBudget &&
+                      r_min < share * index_default_r_min(x, plan.budget);
     AnnWorkspace w;
-    const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, max_rounds};
+    const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, max_rounds, ball};
     void* ws = ann_workspace_alloc(x, nq, k, plan.budget, st, &w);
     try {
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, ws);
