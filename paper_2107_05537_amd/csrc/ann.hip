@@ -86,6 +86,11 @@ struct AnnArgs {
     const AnnQueryParams* qpar;
     int out_stride;             // row stride of out_ids / out_dist (>= every k)
     int max_rounds;             // range queries per query at most ((r,c)-BC: 1)
+    // Pass::Ball: the largest radius of a round that the lists hold the ball of, the
+    // square of that ball's radius, and whether Pass::Rest follows
+    double ball_r;
+    float ball2;
+    int staged;
     int32_t* ws_front;
     int32_t* ws_cpos;
     float* ws_cdist;
@@ -1426,12 +1431,6 @@ constexpr uint32_t kCenBinBase = 63u << 4;
 constexpr int kGrpCap = 2048;
 constexpr size_t kTauGroupLds = 64 * 1024;
 
-// Bits of the squared radius of the first range query.
-__device__ __forceinline__ uint32_t first_radius_bits(const AnnQueryParams& p) {
-    const double rd = p.t * p.r_min;
-    return __float_as_uint((float)(rd * rd));
-}
-
 // Upper bound tau on the budget-th smallest projected distance of one query,
 // and the query's row of the chunk mask:
 //   1. the squared distances from q' to every 64-point chunk centre (computed
@@ -1678,18 +1677,34 @@ __device__ __forceinline__ float budget_radius2(const AnnArgs& a, int64_t qi, co
     return R2;
 }
 
-// BALL: one range query answers ((r,c)-BC) and its ball is expected to hold less than
-// the budget, so that tau is its radius and no bound is needed.
-template <bool BALL>
+// What a pass over a batch looks for. Budget: every query's budget. Ball: the points of
+// one ball, where those are expected to be fewer than a budget above kLeanBudget: tau
+// is its radius and no bound is needed. The lists answer the one range query of
+// (r,c)-BC, or those rounds of Algorithm 2 whose balls they hold; queries that are
+// undecided after those, or whose lists outgrow their pools, are the Rest, a pass for
+// the budget that leaves the decided queries out.
+enum class Pass { Budget, Ball, Rest };
+constexpr int kDecided = -2, kUndecided = -3;   // in a query's flag, after Pass::Ball
+
+template <Pass PASS>
 __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
     const int64_t qi = blockIdx.x;
+    if constexpr (PASS == Pass::Rest) {
+        if (a.q_flag[qi] != kUndecided) {
+            if (threadIdx.x == 0) {
+                a.qtest[qi] = make_float2(__int_as_float(0x7fc00000), 0.f);   // no chunk passes
+                if (qi == 0) a.pq_list[0] = 0u;
+            }
+            return;
+        }
+    }
     QueryCtx qc;
     load_query(a, qi, nullptr, qc);
     float R2;
-    if constexpr (BALL)
-        R2 = __uint_as_float(first_radius_bits(query_params(a, qi)));
+    if constexpr (PASS == Pass::Ball)
+        R2 = a.ball2;
     else
         R2 = budget_radius2(a, qi, qc, sh, smem_raw);
 
@@ -1756,7 +1771,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
             // outside the FP16 range (or no finite bound): every product is
             // +1, no candidate, and the per-query path answers the query
             w[18] = (_Float16)1.f;
-            if constexpr (BALL) a.l_count[qi * a.l_stride] = 0xffffffffu;   // as a list too long
+            if constexpr (PASS == Pass::Ball) a.l_count[qi * a.l_stride] = 0xffffffffu;   // as a list too long
         }
         uint4* dst = reinterpret_cast<uint4*>(a.qaug + qi * 32);
         const uint4* src = reinterpret_cast<const uint4*>(w);
@@ -2772,18 +2787,29 @@ __global__ __launch_bounds__(T) void finish_kernel(AnnArgs a) {
 // (gathered through 128-byte lines), the verification by HBM (the FP16 rows of
 // all members), the answer by the latency of its passes.
 
-// BALL: after tau_kernel<true>, with lists that hold the whole ball however short.
-template <int T, bool BALL>
+// Bits of the squared radius of the first range query.
+__device__ __forceinline__ uint32_t first_radius_bits(const AnnQueryParams& p) {
+    const double rd = p.t * p.r_min;
+    return __float_as_uint((float)(rd * rd));
+}
+
+template <int T, Pass PASS>
 __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
     const int64_t qi = a.ordered ? query_of(a, xcd_place(blockIdx.x, gridDim.x)) : blockIdx.x;
     const AnnQueryParams qpar = query_params(a, qi);
     const int B = qpar.budget;
+    constexpr bool BALL = PASS == Pass::Ball;
+    if constexpr (PASS == Pass::Rest) {
+        if (a.q_flag[qi] < 0) return;
+    }
     const uint32_t cnt = a.l_count[qi * a.l_stride];
     if (cnt > (uint32_t)a.q_cap || (!BALL && cnt < (uint32_t)B)) {
         // list overflow, or the bound fell short: the per-query kernel answers
-        if (threadIdx.x == 0) {
+        if (BALL && a.staged) {
+            if (threadIdx.x == 0) a.q_flag[qi] = kUndecided;
+        } else if (threadIdx.x == 0) {
             a.q_flag[qi] = -1;
             a.pq_list[1 + atomicAdd(&a.pq_list[0], 1u)] = (uint32_t)qi;
         }
@@ -2794,15 +2820,17 @@ __global__ __launch_bounds__(T) void pool_cut_kernel(AnnArgs a) {
     int32_t* cpos = a.ws_cpos + qi * (int64_t)a.budget;
     const uint32_t* list = a.l_list + qi * a.q_cap;
     const int n = (int)cnt;
+    const int nl = BALL ? min(n, B) : B;   // a ball's list is L however short
     const uint32_t first = first_radius_bits(qpar);
     // members of L: the first ball's from the front, the others from the back
     auto emit = [&](bool take, int32_t pos, uint32_t bits) {
         const bool in = take && bits <= first;
         const int s0 = wave_append(in, &sh.cnt0);
         const int s1 = wave_append(take && !in, &sh.cnt1);
-        const int slot = in ? s0 : B - 1 - s1;
-        if (take && slot >= 0 && slot < B) cpos[slot] = pos;
+        const int slot = in ? s0 : nl - 1 - s1;
+        if (take && slot >= 0 && slot < nl) cpos[slot] = pos;
     };
+    if (BALL && threadIdx.x == 0) a.q_order[qi] = nl;
     if (BALL && n <= B) {
         // every entry is in L
         if (threadIdx.x == 0) sh.cnt0 = sh.cnt1 = 0;
@@ -2854,16 +2882,17 @@ __global__ __launch_bounds__(WG) void pool_verify_kernel(AnnArgs a) {
     verify16(a, qs, a.ws_cpos + row, a.ws_clo + row, a.ws_cdist + row, v0, min(n1, v0 + a.vslice));
 }
 
-template <int T>
+template <int T, Pass PASS>
 __global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Smem& sh = *reinterpret_cast<Smem*>(smem_raw);
     float* qs = reinterpret_cast<float*>(smem_raw + ((sizeof(Smem) + 15) & ~size_t(15)));
     const int64_t qi = a.ordered ? query_of(a, xcd_place(blockIdx.x, gridDim.x)) : blockIdx.x;
     const int n1 = a.q_flag[qi];
-    if (n1 < 0) return;   // the per-query kernel's
+    if (n1 < 0) return;   // the per-query kernel's (or decided already, or the rest's)
     const AnnQueryParams qpar = query_params(a, qi);
     const int B = qpar.budget;
+    const int nl = PASS == Pass::Ball ? a.q_order[qi] : B;   // members of L
     const int k = qpar.k;
     const float* qrow = a.q + qi * a.d;
     for (int j = threadIdx.x; j < a.d16; j += T) qs[j] = j < a.d ? qrow[j] : 0.f;
@@ -2919,22 +2948,27 @@ __global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
             sure = block_sum<T>(loc, sh);
         }
         if (sure >= k) { exit_kind = PMLSH_EXIT_NEAR; break; }
+        if (PASS == Pass::Ball && r > a.ball_r) {
+            if (threadIdx.x == 0) a.q_flag[qi] = kUndecided;
+            return;
+        }
         if (rounds >= MAX_ROUNDS) r = __longlong_as_double(0x7ff0000000000000ll);
         const double rd = qpar.t * r;
         cbits = __float_as_uint((float)(rd * rd));
-        if (lim < B) {
-            verify16<T>(a, qs, cpos, lo2, hi2, lim, B);
-            lim = B;
+        if (lim < nl) {
+            verify16<T>(a, qs, cpos, lo2, hi2, lim, nl);
+            lim = nl;
             __syncthreads();
         }
         int loc = 0;
-        for (int i = threadIdx.x; i < B; i += T) loc += member(i);
+        for (int i = threadIdx.x; i < nl; i += T) loc += member(i);
         n_ver = block_sum<T>(loc, sh);
         ++rounds;
         if (n_ver == B) exit_kind = PMLSH_EXIT_BUDGET;
     }
 
     answer_members<T>(a, qi, qs, cpos, lo2, hi2, lim, member, n_ver, rounds, exit_kind, sh);
+    if (PASS == Pass::Ball && threadIdx.x == 0) a.q_flag[qi] = kDecided;
 }
 
 }  // namespace
@@ -2996,22 +3030,22 @@ int ann_lds_bytes(int d_pad) {
 
 namespace {
 
-template <int T, bool BALL = false>
+template <int T, Pass PASS = Pass::Budget>
 void launch_pool(AnnArgs& a, const AnnLaunch& L, int lds_cut, int lds_answer, hipStream_t stream) {
     // members of L per verify workgroup: enough workgroups to fill the chip a few
     // times over, at least the 64 rows that one has in flight
     const int64_t per = (L.budget * L.nq + 4095) / 4096;
     a.vslice = (int)std::min<int64_t>(512, std::max<int64_t>(64, (per + 63) / 64 * 64));
-    PMLSH_HIP(hipFuncSetAttribute((const void*)pool_cut_kernel<T, BALL>,
+    PMLSH_HIP(hipFuncSetAttribute((const void*)pool_cut_kernel<T, PASS>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_cut));
-    PMLSH_HIP(hipFuncSetAttribute((const void*)pool_answer_kernel<T>,
+    auto* answer = pool_answer_kernel<T, PASS == Pass::Ball ? PASS : Pass::Budget>;
+    PMLSH_HIP(hipFuncSetAttribute((const void*)answer,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_answer));
-    hipLaunchKernelGGL((pool_cut_kernel<T, BALL>), dim3((unsigned)L.nq), dim3(T), (unsigned)lds_cut,
+    hipLaunchKernelGGL((pool_cut_kernel<T, PASS>), dim3((unsigned)L.nq), dim3(T), (unsigned)lds_cut,
                        stream, a);
     const dim3 vgrid((unsigned)((L.budget + a.vslice - 1) / a.vslice), (unsigned)L.nq);
     hipLaunchKernelGGL(pool_verify_kernel, vgrid, dim3(WG), (unsigned)(4 * a.d16), stream, a);
-    hipLaunchKernelGGL(pool_answer_kernel<T>, dim3((unsigned)L.nq), dim3(T), (unsigned)lds_answer,
-                       stream, a);
+    hipLaunchKernelGGL(answer, dim3((unsigned)L.nq), dim3(T), (unsigned)lds_answer, stream, a);
 }
 
 template <int T>
@@ -3071,6 +3105,11 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
     a.t = L.t;
     a.r_min = L.r_min;
     a.max_rounds = L.max_rounds > 0 ? L.max_rounds : 0x7fffffff;
+    const bool ball = L.fast && L.ball_r > 0.0;
+    const double ball_rd = L.t * L.ball_r;
+    a.ball_r = L.ball_r;
+    a.ball2 = (float)(ball_rd * ball_rd);
+    a.staged = ball && a.max_rounds != 1;
     a.ws_front = L.ws_front;
     a.ws_cpos = L.ws_cpos;
     a.ws_cdist = L.ws_cdist;
@@ -3123,11 +3162,11 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             hipLaunchKernelGGL(dist_kernel, dgrid, dim3(WG), 0, stream, a);
             PMLSH_HIP(hipGetLastError());
         }
-        {
+        auto bound_and_mask = [&](Pass pass) {
             StageTimer tm(PMLSH_STAGE_TAU, stream);
             const int64_t ngr = (nchunk + 63) / 64;
             a.sample = ann_bound_sample(x);
-            a.ordered = L.nq >= 64 && L.budget > kLeanBudget && !L.ball;
+            a.ordered = L.nq >= 64 && L.budget > kLeanBudget && pass == Pass::Budget;
             a.sel_cap = (int)std::min<int64_t>(kSelMax, std::max<int64_t>(kSelCap, (a.sample * L.budget + 63) / 64 + 1));
             a.grp_cap = (int)std::min<int64_t>(kGrpCap, std::max<int64_t>(0, tune_get(PMLSH_TUNE_GROUP_LIST)));
             const size_t min_bytes = 2 * (size_t)((ngr + 7) & ~7);
@@ -3136,7 +3175,9 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             const size_t lds_t = std::max((size_t)lds0, offsetof(Smem, skey) +
                                           (a.glds ? min_bytes : 0) +
                                           4 * (size_t)(kGrpCap + a.sel_cap));
-            auto* tau_fn = L.ball ? tau_kernel<true> : tau_kernel<false>;
+            auto* tau_fn = pass == Pass::Ball   ? tau_kernel<Pass::Ball>
+                           : pass == Pass::Rest ? tau_kernel<Pass::Rest>
+                                                : tau_kernel<Pass::Budget>;
             PMLSH_HIP(hipFuncSetAttribute((const void*)tau_fn,
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_t));
             hipLaunchKernelGGL(tau_fn, dim3((unsigned)L.nq), dim3(WG), (unsigned)lds_t, stream, a);
@@ -3144,7 +3185,7 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
             dim3 mgrid((unsigned)((nchunk + MCH - 1) / MCH), (unsigned)((L.nq + MQB - 1) / MQB));
             hipLaunchKernelGGL(mask_kernel, mgrid, dim3(WG), 0, stream, a);
             PMLSH_HIP(hipGetLastError());
-        }
+        };
         // one resident wave of workgroups striding over the chunks, in the
         // block shape that suits the index's size
         const int64_t shape = tune_get(PMLSH_TUNE_SCAN_SHAPE);
@@ -3165,10 +3206,20 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         int64_t gx = std::max<int64_t>(1, slots / ny);
         gx = std::min(gx, nchunk);   // at least one chunk per workgroup on average
         dim3 sgrid((unsigned)gx, (unsigned)ny);
-        {
+        auto scan = [&] {
             StageTimer tm(PMLSH_STAGE_FILTER, stream);
             hipLaunchKernelGGL(scan_fn, sgrid, dim3((unsigned)swg), 0, stream, a);
             PMLSH_HIP(hipGetLastError());
+        };
+        if (ball) {
+            bound_and_mask(Pass::Ball);
+            scan();
+            StageTimer tm(PMLSH_STAGE_FINISH, stream);
+            launch_pool<1024, Pass::Ball>(a, L, lds0, lds, stream);
+        }
+        if (!ball || a.staged) {
+            bound_and_mask(ball ? Pass::Rest : Pass::Budget);
+            scan();
         }
         StageTimer tm(PMLSH_STAGE_FINISH, stream);
         // Which kernels finish a budget of at most kLeanBudget. One workgroup of
@@ -3195,8 +3246,10 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
         //   20,000 x 900         32 queries, B = 900   126 / 106 / 105 /  93
         // (*) data without contrast.
         const int64_t B = L.budget, nq = L.nq;
-        if (L.ball)
-            launch_pool<1024, true>(a, L, lds0, lds, stream);
+        if (a.staged)
+            launch_pool<1024, Pass::Rest>(a, L, lds0, lds, stream);
+        else if (ball)
+            ;
         else if (B > kLeanBudget)
             launch_pool<1024>(a, L, lds0, lds, stream);
         else if (nq <= 32 && B >= 768 && x.d16 >= 256)

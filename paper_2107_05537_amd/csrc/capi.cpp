@@ -212,7 +212,7 @@ struct AnnCall {
     const AnnQueryParams* qpar;
     int out_stride;
     int max_rounds;
-    bool ball = false;
+    double ball_r = 0.0;   // as in AnnLaunch
 };
 
 // The batches of one ANN call over the workspace region ws laid out by w.
@@ -273,7 +273,7 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
         L.qpar = call.qpar ? call.qpar + q0 : nullptr;
         L.out_stride = stride;
         L.fast = fast;
-        L.ball = fast && call.ball;
+        L.ball_r = call.ball_r;
         L.ws_front = front;
         L.front_slots = std::min<int64_t>(w.slots, nb);
         L.ws_cpos = cpos;
@@ -338,6 +338,38 @@ double ann_plan(const pmlsh_index* x, int k, double c, double confidence, double
     return r_min;
 }
 
+// The radius up to which the rounds of a large budget are answered from the points of
+// one ball (0: none): the ball that the sampled distances expect to hold fewer points.
+// (r,c)-BC has one round; of Algorithm 2 those that a small r_min puts before the
+// budget's radius, at most 0.3 of it where there are any, since queries with k
+// neighbours near by end there. The rule leaves room for queries whose balls hold many
+// more than the sample's: lists that outgrow the pools cost a second pass, or in
+// (r,c)-BC the per-query kernel.
+// us per call of 1,000 queries for the budget alone / with the ball / on the per-query
+// kernel, by the first radius in units of the budget's:
+//   (r,c)-BC   30,000 x 32, B = 2,902               0.25     239 /    136 /    126
+//                                                   0.5      245 /    145 /    161
+//              1M x 128, B = 96,695                 0.25   3,812 /    224 /  1,073
+//                                                   0.5    3,837 /    284 /  2,404
+//                                                   0.8    6,467 / 23,324 / 24,972
+//              1M x 128 without contrast, B = 3,001 0.5      643 /    227 / 16,668
+//                                                   0.65     700 / 23,720 / 29,888
+//   ANN        100,000 x 64, B = 9,680, copies of   0.01     393 /    149 /     82
+//              the queries among the points         0.1      390 /    154 /    101
+//              1M x 128, B = 96,704, the same       0.01   3,766 /    284 /    162
+//              ordinary queries                     0.01  19,697 /    440 /  1,069
+//                                                   0.6    3,981 /    555 /  4,339
+double ball_radius(const pmlsh_index* x, int64_t budget, double c, double r_min, int max_rounds) {
+    if (budget <= kLeanBudget) return 0.0;
+    const double full = index_default_r_min(x, budget);
+    double most = (budget * 100 >= x->n ? 0.7 : 0.6) * full;
+    if (max_rounds != 1 && r_min < 0.3 * full) most = 0.3 * full;
+    if (!(r_min < most)) return 0.0;
+    double r = r_min;
+    for (int i = 0; max_rounds != 1 && i < 64 && c * r <= most; ++i) r = c * r;
+    return r;
+}
+
 }  // namespace
 
 void run_ann(const pmlsh_index* x, const float* queries, int64_t nq, int k, double c,
@@ -346,25 +378,9 @@ void run_ann(const pmlsh_index* x, const float* queries, int64_t nq, int k, doub
     pmlsh_plan plan;
     r_min = ann_plan(x, k, c, confidence, beta, r_min, &plan);
     if (nq == 0) return;
-    // (r,c)-BC of a large budget whose ball the sampled distances expect to hold fewer
-    // points: the filter looks for the ball's points instead of for the budget's. The
-    // rule leaves room for queries whose balls hold many more than the sample's, since
-    // lists that outgrow the pools are the per-query kernel's after all. us per call of
-    // 1,000 queries, for the budget / for the ball / on the per-query kernel, by r in
-    // units of the radius whose ball is expected to hold the budget:
-    //   30,000 x 32, B = 2,902     r = 0.25   239 /   136 /    126
-    //                              r = 0.5    245 /   145 /    161
-    //   1M x 128, B = 96,695       r = 0.25 3,812 /   224 /  1,073
-    //                              r = 0.5  3,837 /   284 /  2,404
-    //                              r = 0.8  6,467 / 23,324 / 24,972
-    //   1M x 128 without contrast,
-    //             B = 3,001        r = 0.5    643 /   227 / 16,668
-    //                              r = 0.65   700 / 23,720 / 29,888
-    const double share = plan.budget * 100 >= x->n ? 0.7 : 0.6;
-    const bool ball = max_rounds == 1 && plan.budget > kLeanBudget &&
-                      r_min < share * index_default_r_min(x, plan.budget);
     AnnWorkspace w;
-    const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, max_rounds, ball};
+    const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, max_rounds,
+                       ball_radius(x, plan.budget, c, r_min, max_rounds)};
     void* ws = ann_workspace_alloc(x, nq, k, plan.budget, st, &w);
     try {
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, ws);
@@ -392,7 +408,8 @@ void run_ann_in(const pmlsh_index* x, const float* queries, int64_t nq, int k, d
              "one query of this index needs " + std::to_string(one.bytes) +
                  " bytes of workspace; the fixed region holds " + std::to_string(region_bytes));
     }
-    const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, 0};
+    const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, 0,
+                       ball_radius(x, plan.budget, c, r_min, 0)};
     run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, region_of_device());
 }
 
@@ -442,7 +459,8 @@ void run_ann_planned(const pmlsh_index* x, const float* queries, int64_t nq,
     if (nq == 0) return;
     const AnnWorkspace w = ann_workspace_region(x, nq, p.k, p.budget, region_bytes);
     if (w.batch < 1) fail(PMLSH_ENOMEM, "the workspace region holds no query");
-    const AnnCall call{p.k, p.budget, p.c, p.t, p.r_min, nullptr, p.k, 0};
+    const AnnCall call{p.k, p.budget, p.c, p.t, p.r_min, nullptr, p.k, 0,
+                       ball_radius(x, p.budget, p.c, p.r_min, 0)};
     run_ann_region(x, queries, nq, call, out_ids, out_dist, nullptr, st, w, region);
 }
 

@@ -425,7 +425,8 @@ struct AnnLaunch {
     const AnnQueryParams* qpar = nullptr;   // per-query parameters (then k, budget: the largest)
     int out_stride = 0;                     // output row stride (0: k)
     bool fast = false;                      // the batched path (its workspace fields are set)
-    bool ball = false;                      // one range query, of fewer points than a large budget
+    double ball_r = 0.0;                    // largest radius of a round answered from its ball's
+                                            // points alone before the budget's are looked for
 };
 void launch_ann(const AnnLaunch& a, hipStream_t stream);
 int ann_lds_bytes(int d_pad);
