@@ -86,10 +86,9 @@ struct AnnArgs {
     const AnnQueryParams* qpar;
     int out_stride;             // row stride of out_ids / out_dist (>= every k)
     int max_rounds;             // range queries per query at most ((r,c)-BC: 1)
-    // Pass::Ball: the largest radius of a round that the lists hold the ball of, the
-    // square of that ball's radius, and whether Pass::Rest follows
-    double ball_r;
-    float ball2;
+    // Pass::Ball: no round of a larger radius has its ball listed, and whether
+    // Pass::Rest follows
+    double ball_most;
     int staged;
     int32_t* ws_front;
     int32_t* ws_cpos;
@@ -1686,6 +1685,14 @@ __device__ __forceinline__ float budget_radius2(const AnnArgs& a, int64_t qi, co
 enum class Pass { Budget, Ball, Rest };
 constexpr int kDecided = -2, kUndecided = -3;   // in a query's flag, after Pass::Ball
 
+// The radius of the last round whose ball a query's list holds in Pass::Ball (0: of none).
+__device__ __forceinline__ double ball_radius(const AnnArgs& a, const AnnQueryParams& p) {
+    double r = p.r_min;
+    if (!(r < a.ball_most)) return 0.0;
+    for (int i = 0; a.max_rounds != 1 && i < 64 && p.c * r <= a.ball_most; ++i) r = p.c * r;
+    return r;
+}
+
 template <Pass PASS>
 __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1703,9 +1710,11 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
     QueryCtx qc;
     load_query(a, qi, nullptr, qc);
     float R2;
-    if constexpr (PASS == Pass::Ball)
-        R2 = a.ball2;
-    else
+    if constexpr (PASS == Pass::Ball) {
+        const AnnQueryParams p = query_params(a, qi);
+        const double rd = p.t * ball_radius(a, p);
+        R2 = rd > 0.0 ? (float)(rd * rd) : __int_as_float(0x7f800000);
+    } else
         R2 = budget_radius2(a, qi, qc, sh, smem_raw);
 
     // 4: the radius of the chunk-ball test, which mask_kernel applies: it
@@ -1768,7 +1777,7 @@ __global__ __launch_bounds__(WG) void tau_kernel(AnnArgs a) {
             w[19] = (_Float16)(v - (float)hi);
             w[20] = (_Float16)(-s * qn);
         } else {
-            // outside the FP16 range (or no finite bound): every product is
+            // outside the FP16 range (or no finite radius): every product is
             // +1, no candidate, and the per-query path answers the query
             w[18] = (_Float16)1.f;
             if constexpr (PASS == Pass::Ball) a.l_count[qi * a.l_stride] = 0xffffffffu;   // as a list too long
@@ -2908,6 +2917,7 @@ __global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
     // the others get theirs here when a second one is needed, and their pd^2
     // is computed again where it is asked for.
     double r = qpar.r_min;
+    const double last = PASS == Pass::Ball ? ball_radius(a, qpar) : 0.0;
     uint32_t cbits = first_radius_bits(qpar);
     int lim = n1, n_ver = n1, rounds = 1, exit_kind = n1 == B ? PMLSH_EXIT_BUDGET : 0;
     auto member = [&](int i) {
@@ -2948,7 +2958,7 @@ __global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
             sure = block_sum<T>(loc, sh);
         }
         if (sure >= k) { exit_kind = PMLSH_EXIT_NEAR; break; }
-        if (PASS == Pass::Ball && r > a.ball_r) {
+        if (PASS == Pass::Ball && r > last) {
             if (threadIdx.x == 0) a.q_flag[qi] = kUndecided;
             return;
         }
@@ -3105,10 +3115,8 @@ void launch_ann(const AnnLaunch& L, hipStream_t stream) {
     a.t = L.t;
     a.r_min = L.r_min;
     a.max_rounds = L.max_rounds > 0 ? L.max_rounds : 0x7fffffff;
-    const bool ball = L.fast && L.ball_r > 0.0;
-    const double ball_rd = L.t * L.ball_r;
-    a.ball_r = L.ball_r;
-    a.ball2 = (float)(ball_rd * ball_rd);
+    const bool ball = L.fast && L.ball_most > 0.0;
+    a.ball_most = L.ball_most;
     a.staged = ball && a.max_rounds != 1;
     a.ws_front = L.ws_front;
     a.ws_cpos = L.ws_cpos;

@@ -212,7 +212,7 @@ struct AnnCall {
     const AnnQueryParams* qpar;
     int out_stride;
     int max_rounds;
-    double ball_r = 0.0;   // as in AnnLaunch
+    double ball_most = 0.0;   // as in AnnLaunch
 };
 
 // The batches of one ANN call over the workspace region ws laid out by w.
@@ -273,7 +273,7 @@ void run_ann_region(const pmlsh_index* x, const float* queries, int64_t nq, cons
         L.qpar = call.qpar ? call.qpar + q0 : nullptr;
         L.out_stride = stride;
         L.fast = fast;
-        L.ball_r = call.ball_r;
+        L.ball_most = call.ball_most;
         L.ws_front = front;
         L.front_slots = std::min<int64_t>(w.slots, nb);
         L.ws_cpos = cpos;
@@ -359,15 +359,12 @@ double ann_plan(const pmlsh_index* x, int k, double c, double confidence, double
 //              1M x 128, B = 96,704, the same       0.01   3,766 /    284 /    162
 //              ordinary queries                     0.01  19,697 /    440 /  1,069
 //                                                   0.6    3,981 /    555 /  4,339
-double ball_radius(const pmlsh_index* x, int64_t budget, double c, double r_min, int max_rounds) {
+double ball_limit(const pmlsh_index* x, int64_t budget, double r_min, int max_rounds) {
     if (budget <= kLeanBudget) return 0.0;
     const double full = index_default_r_min(x, budget);
     double most = (budget * 100 >= x->n ? 0.7 : 0.6) * full;
     if (max_rounds != 1 && r_min < 0.3 * full) most = 0.3 * full;
-    if (!(r_min < most)) return 0.0;
-    double r = r_min;
-    for (int i = 0; max_rounds != 1 && i < 64 && c * r <= most; ++i) r = c * r;
-    return r;
+    return r_min < most ? most : 0.0;
 }
 
 }  // namespace
@@ -380,7 +377,7 @@ void run_ann(const pmlsh_index* x, const float* queries, int64_t nq, int k, doub
     if (nq == 0) return;
     AnnWorkspace w;
     const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, max_rounds,
-                       ball_radius(x, plan.budget, c, r_min, max_rounds)};
+                       ball_limit(x, plan.budget, r_min, max_rounds)};
     void* ws = ann_workspace_alloc(x, nq, k, plan.budget, st, &w);
     try {
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, ws);
@@ -409,15 +406,16 @@ void run_ann_in(const pmlsh_index* x, const float* queries, int64_t nq, int k, d
                  " bytes of workspace; the fixed region holds " + std::to_string(region_bytes));
     }
     const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, 0,
-                       ball_radius(x, plan.budget, c, r_min, 0)};
+                       ball_limit(x, plan.budget, r_min, 0)};
     run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, region_of_device());
 }
 
 void plan_queries(const pmlsh_index* x, const pmlsh_query_args* args, int64_t nq,
-                  std::vector<AnnQueryParams>* out, int* kmax, int64_t* bmax) {
+                  std::vector<AnnQueryParams>* out, int* kmax, int64_t* bmax, double* ball_most) {
     out->resize((size_t)nq);
     *kmax = 1;
     *bmax = 1;
+    *ball_most = 0.0;
     std::vector<int64_t> seen;   // the first queries of distinct parameters
     for (int64_t i = 0; i < nq; ++i) {
         const pmlsh_query_args& q = args[i];
@@ -447,6 +445,8 @@ void plan_queries(const pmlsh_index* x, const pmlsh_query_args* args, int64_t nq
             p.budget = (int32_t)plan.budget;
             *kmax = std::max(*kmax, q.k);
             *bmax = std::max<int64_t>(*bmax, plan.budget);
+            const double ball = ball_limit(x, plan.budget, r_min, 0);
+            if (ball > 0.0 && !(*ball_most > 0.0 && *ball_most < ball)) *ball_most = ball;
         } catch (const Error& e) {
             fail(e.code, "query " + std::to_string(i) + ": " + e.msg);
         }
@@ -460,7 +460,7 @@ void run_ann_planned(const pmlsh_index* x, const float* queries, int64_t nq,
     const AnnWorkspace w = ann_workspace_region(x, nq, p.k, p.budget, region_bytes);
     if (w.batch < 1) fail(PMLSH_ENOMEM, "the workspace region holds no query");
     const AnnCall call{p.k, p.budget, p.c, p.t, p.r_min, nullptr, p.k, 0,
-                       ball_radius(x, p.budget, p.c, p.r_min, 0)};
+                       ball_limit(x, p.budget, p.r_min, 0)};
     run_ann_region(x, queries, nq, call, out_ids, out_dist, nullptr, st, w, region);
 }
 
@@ -475,11 +475,11 @@ int64_t ann_workspace_bytes_least(const pmlsh_index* x, int kmax, int64_t bmax) 
 }
 
 void run_ann_mixed(const pmlsh_index* x, const float* queries, int64_t nq,
-                   const AnnQueryParams* qpar, int kmax, int64_t bmax, int out_stride,
+                   const AnnQueryParams* qpar, int kmax, int64_t bmax, double ball_most, int out_stride,
                    int64_t* out_ids, float* out_dist, int32_t* out_stats, hipStream_t st,
                    void* region, int64_t region_bytes) {
     if (nq == 0) return;
-    const AnnCall call{kmax, bmax, 0.0, 0.0, 0.0, qpar, out_stride, 0};
+    const AnnCall call{kmax, bmax, 0.0, 0.0, 0.0, qpar, out_stride, 0, ball_most};
     if (region) {
         const AnnWorkspace w = ann_workspace_region(x, nq, kmax, bmax, region_bytes);
         if (w.batch < 1) fail(PMLSH_ENOMEM, "the workspace region holds no query");
@@ -552,7 +552,8 @@ int pmlsh_ann_mixed(const pmlsh_index* index, const float* queries, int64_t nq,
         std::vector<AnnQueryParams> params;
         int kmax = 1;
         int64_t bmax = 1;
-        plan_queries(index, args, nq, &params, &kmax, &bmax);
+        double ball_most = 0.0;
+        plan_queries(index, args, nq, &params, &kmax, &bmax, &ball_most);
         if (out_stride < kmax) fail(PMLSH_EINVAL, "out_stride must be >= every k");
         hipStream_t st = static_cast<hipStream_t>(stream);
         // a captured graph would read the host parameters on every replay
@@ -564,7 +565,7 @@ int pmlsh_ann_mixed(const pmlsh_index* index, const float* queries, int64_t nq,
         try {
             fetch_params(params, static_cast<AnnQueryParams*>(dp), st);
             run_ann_mixed(index, queries, nq, static_cast<const AnnQueryParams*>(dp), kmax, bmax,
-                          out_stride, out_ids, out_dist, out_stats, st, nullptr, 0);
+                          ball_most, out_stride, out_ids, out_dist, out_stats, st, nullptr, 0);
         } catch (...) {
             ws_free(dp, st);
             throw;

@@ -159,11 +159,11 @@ void run_ann(const pmlsh_index* x, const float* queries, int64_t nq, int k, doub
              double confidence, double beta, double r_min, int64_t* out_ids,
              float* out_dist, int32_t* out_stats, hipStream_t st, int max_rounds = 0);
 // A batch of queries with per-query parameters: the device array qpar (nq
-// entries, from plan_queries), the largest k and budget among them, and the
-// row stride of the outputs (>= kmax). region / region_bytes: a fixed
+// entries, from plan_queries), the largest k and budget among them, their ball_most
+// and the row stride of the outputs (>= kmax). region / region_bytes: a fixed
 // device region for the workspace (null: the caching allocator).
 void run_ann_mixed(const pmlsh_index* x, const float* queries, int64_t nq,
-                   const AnnQueryParams* qpar, int kmax, int64_t bmax, int out_stride,
+                   const AnnQueryParams* qpar, int kmax, int64_t bmax, double ball_most, int out_stride,
                    int64_t* out_ids, float* out_dist, int32_t* out_stats, hipStream_t st,
                    void* region, int64_t region_bytes);
 // A batch of queries sharing one plan (from plan_queries), its answers
@@ -172,9 +172,10 @@ void run_ann_planned(const pmlsh_index* x, const float* queries, int64_t nq,
                      const AnnQueryParams& p, int64_t* out_ids, float* out_dist, hipStream_t st,
                      void* region, int64_t region_bytes);
 // Host plan of per-query parameters (t, B and the default r_min resolved);
-// throws EINVAL / EUNSUPPORTED like pmlsh_ann for an invalid entry.
+// throws EINVAL / EUNSUPPORTED like pmlsh_ann for an invalid entry. ball_most: the
+// smallest ball limit of its queries (0: none has one), see AnnLaunch.
 void plan_queries(const pmlsh_index* x, const pmlsh_query_args* args, int64_t nq,
-                  std::vector<AnnQueryParams>* out, int* kmax, int64_t* bmax);
+                  std::vector<AnnQueryParams>* out, int* kmax, int64_t* bmax, double* ball_most);
 // Workspace bytes of run_ann_mixed on nq queries with these largest k, B.
 int64_t ann_workspace_bytes_mixed(const pmlsh_index* x, int64_t nq, int kmax, int64_t bmax);
 // Bytes that any such launch runs in, a query at a time.
@@ -425,8 +426,8 @@ struct AnnLaunch {
     const AnnQueryParams* qpar = nullptr;   // per-query parameters (then k, budget: the largest)
     int out_stride = 0;                     // output row stride (0: k)
     bool fast = false;                      // the batched path (its workspace fields are set)
-    double ball_r = 0.0;                    // largest radius of a round answered from its ball's
-                                            // points alone before the budget's are looked for
+    double ball_most = 0.0;                 // radius up to which rounds are answered from a ball's
+                                            // points before the budget's are looked for
 };
 void launch_ann(const AnnLaunch& a, hipStream_t stream);
 int ann_lds_bytes(int d_pad);

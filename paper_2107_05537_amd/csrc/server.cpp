@@ -33,6 +33,7 @@ struct Request {
     int32_t k = 0;
     double c = 0, confidence = 0, beta = 0, r_min = 0;
     AnnQueryParams params{};      // the plan of every query of the request
+    double ball_most = 0;         // and its ball limit
     int64_t* out_ids = nullptr;
     float* out_dist = nullptr;
     hipEvent_t ready = nullptr;   // work of the submitting stream, or null
@@ -216,11 +217,12 @@ void untake(pmlsh_server* s, std::vector<Segment>& segs) {
                      });
 }
 
-// Shape of a launch: queries, largest k and budget.
+// Shape of a launch: queries, largest k and budget, smallest ball limit.
 struct Shape {
     int64_t nb = 0;
     int kmax = 1;
     int64_t bmax = 1;
+    double ball_most = 0.0;
 };
 
 Shape shape_of(const std::vector<Segment>& segs) {
@@ -229,6 +231,8 @@ Shape shape_of(const std::vector<Segment>& segs) {
         sh.nb += sg.count;
         sh.kmax = std::max(sh.kmax, sg.req->params.k);
         sh.bmax = std::max<int64_t>(sh.bmax, sg.req->params.budget);
+        const double ball = sg.req->ball_most;
+        if (ball > 0.0 && !(sh.ball_most > 0.0 && sh.ball_most < ball)) sh.ball_most = ball;
     }
     return sh;
 }
@@ -346,8 +350,8 @@ void issue(pmlsh_server* s, Launch& L, const Shape& shp) {
         hipLaunchKernelGGL(gather_queries_kernel, grid, dim3(64 * kRowWaves), 0, st,
                            sl.hdesc_dev, shp.nb, d, sl.desc, sl.params, sl.q);
         PMLSH_HIP(hipGetLastError());
-        run_ann_mixed(s->idx, sl.q, shp.nb, sl.params, shp.kmax, shp.bmax, shp.kmax, sl.ids,
-                      sl.dist, nullptr, st, sl.ws, sl.ws_bytes);
+        run_ann_mixed(s->idx, sl.q, shp.nb, sl.params, shp.kmax, shp.bmax, shp.ball_most, shp.kmax,
+                      sl.ids, sl.dist, nullptr, st, sl.ws, sl.ws_bytes);
         hipLaunchKernelGGL(scatter_answers_kernel, grid, dim3(64 * kRowWaves), 0, st,
                            sl.desc, shp.nb, (int64_t)shp.kmax, sl.ids, sl.dist);
         PMLSH_HIP(hipGetLastError());
@@ -494,9 +498,11 @@ int pmlsh_server_submit(pmlsh_server* server, const float* queries, int64_t nq, 
         std::vector<AnnQueryParams> plan;
         int kmax = 1;
         int64_t bmax = 1;
-        plan_queries(server->idx, &qa, 1, &plan, &kmax, &bmax);
+        double ball_most = 0.0;
+        plan_queries(server->idx, &qa, 1, &plan, &kmax, &bmax, &ball_most);
         auto r = std::make_shared<Request>();
         r->params = plan[0];
+        r->ball_most = ball_most;
         r->q = queries;
         r->nq = nq;
         r->k = k;

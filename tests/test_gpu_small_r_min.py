@@ -89,3 +89,38 @@ def test_lists_that_outgrow_the_pools():
     for f in (0.01, 0.2, 0.5):
         say(f"case: small r_min with lists of 18,000, r_min={f} of the budget's")
         _same(pm, idx, Q, 10, 1.5, (2_049 - 10) / n, f * idx.default_r_min(2_049))
+
+
+def test_mixed_launches():
+    """Queries with first radii of all sizes and budgets on both sides of 2,048 in one
+    launch, alone and through the server."""
+    pm = _gpu()
+    g = torch.Generator(device="cuda").manual_seed(15)
+    x = torch.randn(N, DIM, generator=g, device="cuda")
+    x = x + 4 * torch.randn(40, DIM, generator=g, device="cuda")[
+        torch.randint(40, (N,), generator=g, device="cuda")]
+    x[-4_000:] = x[:200].repeat_interleave(20, 0) + 1e-2 * torch.randn(
+        4_000, DIM, generator=g, device="cuda")
+    Q = torch.cat([x[:60] + 1e-3, 3 * torch.randn(60, DIM, generator=g, device="cuda")])
+    idx = pm.Index(x, torch.randn(15, DIM, generator=g, device="cuda"))
+    params = []
+    for i in range(120):
+        budget = (200, 2_049, 9_000)[i % 3]
+        k = (1, 10, 40)[i // 3 % 3]
+        p = {"k": k, "c": (1.2, 2.0)[i // 9 % 2], "beta": (budget - k) / N}
+        f = (0.0, 0.01, 0.25, 0.5, 1.5)[i // 18 % 5]
+        if f:
+            p["r_min"] = f * idx.default_r_min(budget)
+        params.append(p)
+    say("case: small r_min, mixed")
+    ids, dist = idx.ann_mixed(Q, params, out_stride=40)
+    server = pm.Server(idx)
+    pending = [server.submit(Q[i:i + 1].contiguous(), p["k"], c=p["c"], beta=p["beta"],
+                             r_min=p.get("r_min", 0.0)) for i, p in enumerate(params)]
+    for i, (p, t) in enumerate(zip(params, pending)):
+        t.wait()
+        a, b, _ = _same(pm, idx, Q[i:i + 1].contiguous().expand(4, DIM).contiguous(), p["k"], p["c"],
+                        p["beta"], p.get("r_min", 0.0))
+        assert torch.equal(ids[i, :p["k"]], a[0]) and torch.equal(dist[i, :p["k"]], b[0])
+        assert torch.equal(t.ids[0], a[0]) and torch.equal(t.dist[0], b[0])
+    server.close()
