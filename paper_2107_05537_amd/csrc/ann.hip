@@ -86,10 +86,6 @@ struct AnnArgs {
     const AnnQueryParams* qpar;
     int out_stride;             // row stride of out_ids / out_dist (>= every k)
     int max_rounds;             // range queries per query at most ((r,c)-BC: 1)
-    // Pass::Ball: no round of a larger radius has its ball listed, and whether
-    // Pass::Rest follows
-    double ball_most;
-    int staged;
     int32_t* ws_front;
     int32_t* ws_cpos;
     float* ws_cdist;
@@ -147,6 +143,10 @@ struct AnnArgs {
     int vslice;
     // bound kernel: points sampled per budget point, chunks it may choose
     int sample, sel_cap;
+    // Pass::Ball: no round of a larger radius has its ball listed, and whether
+    // Pass::Rest follows
+    double ball_most;
+    int staged;
 };
 
 // Element (query q, chunk c) of the blocked chunk-distance matrix.
