@@ -2987,17 +2987,18 @@ __global__ __launch_bounds__(T) void pool_answer_kernel(AnnArgs a) {
 // clustered data and 5 to 8 B on data without contrast (fewer for large B). The
 // radius that filter_gemm widens by its bounds passes more of them, and the
 // queries that overflow cost milliseconds on the per-query kernel. 1,024 queries of
-// a call, ms, with the entries of the exact filter / 2 / 4 / 8 times as many:
+// a call, ms, with the entries of the exact filter / 2 / 4 / 8 / 16 times as many:
 //   FP16, 1M x 256 without contrast, B = 2,500   19  / 1.0
 //   BF16, 1M x 256, B = 885                      1.4 / 1.4 / 0.32
 //                   B = 4,910                    33  / 14  / 1.6 / 1.6
-//   BF16, 1M x 256 without contrast, B = 1,010   63  / 63  / 63  / 19
-//                                    B = 5,010   105 / 64  / 19  / 3.7
-//   BF16, 1M x 960 without contrast, B = 2,010   73  / 74  / 74  / 74
+//   BF16, 1M x 256 without contrast, B = 1,010   63  / 63  / 63  / 19  / 2.2
+//                                    B = 5,010   105 / 64  / 19  / 3.7 / 4.3
+//   BF16, 1M x 960 without contrast, B = 2,010   73  / 74  / 74  / 74  / 56
+//                                    B = 5,010   108 / 68  / 68  / 63  / 11
 // least: the exact filter's, where memory is short.
 int64_t ann_pool_per_query(const pmlsh_index& x, int64_t budget, bool least) {
     const bool bf16 = x.filter_gemm == PMLSH_FILTER_GEMM_BF16;
-    const int64_t f = least || !x.filter_gemm ? 1 : !bf16 ? 2 : x.low_contrast ? 8 : 4;
+    const int64_t f = least || !x.filter_gemm ? 1 : !bf16 ? 2 : x.low_contrast ? 16 : 4;
     const int64_t want = std::max(std::min<int64_t>(f * 8 * budget, f * 65536),
                                   std::min<int64_t>(f + 2, 4) * budget);
     return std::min(x.n, std::max<int64_t>(want, 16384));
