@@ -111,8 +111,18 @@ void ann_workspace_size(const pmlsh_index* x, int64_t batch, AnnWorkspace* w) {
     w->bytes = (w->bytes + q - 1) / q * q;
 }
 
+// The layout that a launch of nq queries starts from. Budgets above kLeanBudget of a
+// few thousand points hold most of them: many such queries are faster one workgroup
+// each on the per-query kernel (batched / per-query, us: 2,500 x 256, B = 2,060, 1,000
+// queries 295 / 180, 30 queries 103 / 85; without contrast 320 / 389 and 101 / 162; 3,000
+// x 16, B = 3,000 315 / 261 and 99 / 127; 4,000 x 16, B = 2,500 289 / 282 and 98 / 159,
+// without contrast 305 / 305 and 100 / 149).
+Pools pools_of(const pmlsh_index* x, int64_t nq, int64_t B) {
+    return B > kLeanBudget && x->n <= 3072 && nq > 256 ? Pools::Short : Pools::All;
+}
+
 AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B) {
-    AnnWorkspace w = ann_workspace_base(x, k, B);
+    AnnWorkspace w = ann_workspace_base(x, k, B, pools_of(x, nq, B));
     // per query, with the distance blocks of a 64-query band spread over it
     const int64_t per_query_all =
         w.per_query + (w.fast ? 8 + 2 * (64 * cdist_groups(w.nchunk) + cdist_gmin_len(w.nchunk)) +
@@ -172,7 +182,7 @@ AnnWorkspace ann_workspace_in(const pmlsh_index* x, int64_t nq, int k, int64_t B
 // As ann_workspace_in for a region of a launch; shorter pools where those leave no
 // room for a single query.
 AnnWorkspace ann_workspace_region(const pmlsh_index* x, int64_t nq, int k, int64_t B, int64_t bytes,
-                                  Pools pools = Pools::All) {
+                                  Pools pools) {
     AnnWorkspace w = ann_workspace_in(x, nq, k, B, bytes, pools);
     if (w.batch < 1 && pools == Pools::All) w = ann_workspace_in(x, nq, k, B, bytes, Pools::Short);
     if (w.batch < 1) w = ann_workspace_in(x, nq, k, B, bytes, Pools::Least);
@@ -398,7 +408,7 @@ void run_ann_in(const pmlsh_index* x, const float* queries, int64_t nq, int k, d
     // a small fixed region holds most queries without the lists' pd^2 bits; a
     // large budget whose candidate pool does not fit takes the per-query path
     const AnnWorkspace w = ann_workspace_region(x, nq, k, plan.budget, region_bytes,
-                                                plan.budget > kLeanBudget ? Pools::All : Pools::Short);
+                                                plan.budget > kLeanBudget ? pools_of(x, nq, plan.budget) : Pools::Short);
     if (w.batch < 1) {
         const AnnWorkspace one = ann_workspace_in(x, 1, k, plan.budget, int64_t(1) << 62, Pools::Least);
         fail(PMLSH_EUNSUPPORTED,
@@ -457,7 +467,8 @@ void run_ann_planned(const pmlsh_index* x, const float* queries, int64_t nq,
                      const AnnQueryParams& p, int64_t* out_ids, float* out_dist, hipStream_t st,
                      void* region, int64_t region_bytes) {
     if (nq == 0) return;
-    const AnnWorkspace w = ann_workspace_region(x, nq, p.k, p.budget, region_bytes);
+    const AnnWorkspace w = ann_workspace_region(x, nq, p.k, p.budget, region_bytes,
+                                                pools_of(x, nq, p.budget));
     if (w.batch < 1) fail(PMLSH_ENOMEM, "the workspace region holds no query");
     const AnnCall call{p.k, p.budget, p.c, p.t, p.r_min, nullptr, p.k, 0,
                        ball_limit(x, p.budget, p.r_min, 0)};
@@ -481,7 +492,8 @@ void run_ann_mixed(const pmlsh_index* x, const float* queries, int64_t nq,
     if (nq == 0) return;
     const AnnCall call{kmax, bmax, 0.0, 0.0, 0.0, qpar, out_stride, 0, ball_most};
     if (region) {
-        const AnnWorkspace w = ann_workspace_region(x, nq, kmax, bmax, region_bytes);
+        const AnnWorkspace w = ann_workspace_region(x, nq, kmax, bmax, region_bytes,
+                                                    pools_of(x, nq, bmax));
         if (w.batch < 1) fail(PMLSH_ENOMEM, "the workspace region holds no query");
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, region);
         return;

@@ -144,3 +144,20 @@ def test_largest_budgets(n, budget, kind):
     for i, p in enumerate(params):
         a, b = idx.ann(Q[i:i + 1], p["k"], beta=p["beta"])
         assert torch.equal(ids[i, :p["k"]], a[0]) and torch.equal(dist[i, :p["k"]], b[0])
+
+
+@pytest.mark.parametrize("n,nq", [(2_060, 257), (3_072, 256), (3_072, 257), (3_073, 257)])
+def test_budgets_of_most_points(n, nq):
+    """A few thousand points, most of them in the budget: the same answers by the hundred
+    and one by one, whichever path takes them."""
+    pm = _gpu()
+    say(f"case: budgets of most points n={n} nq={nq}")
+    D, Q, A = _points(n, 20, "clusters", 7, nq)
+    idx = pm.Index(D, A)
+    beta = (2_052 - 10) / n
+    ref = [t.cpu().numpy() for t in idx.ann(Q, 10, beta=beta, stats=True)]
+    for i in (0, 17, nq - 1):
+        one = [t.cpu().numpy() for t in idx.ann(Q[i:i + 1].contiguous(), 10, beta=beta, stats=True)]
+        _same(one, [t[i:i + 1] for t in ref])
+    mixed = idx.ann_mixed(Q, [{"k": 10, "beta": beta}] * nq)
+    _same([t.cpu().numpy() for t in mixed], ref[:2])
