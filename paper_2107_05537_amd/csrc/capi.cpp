@@ -121,8 +121,8 @@ Pools pools_of(const pmlsh_index* x, int64_t nq, int64_t B) {
     return B > kLeanBudget && x->n <= 3072 && nq > 256 ? Pools::Short : Pools::All;
 }
 
-AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B) {
-    AnnWorkspace w = ann_workspace_base(x, k, B, pools_of(x, nq, B));
+AnnWorkspace ann_workspace(const pmlsh_index* x, int64_t nq, int k, int64_t B, Pools pools) {
+    AnnWorkspace w = ann_workspace_base(x, k, B, pools);
     // per query, with the distance blocks of a 64-query band spread over it
     const int64_t per_query_all =
         w.per_query + (w.fast ? 8 + 2 * (64 * cdist_groups(w.nchunk) + cdist_gmin_len(w.nchunk)) +
@@ -147,9 +147,9 @@ bool ann_workspace_smaller(const pmlsh_index* x, int k, AnnWorkspace* w) {
 }
 
 // The workspace of one call, as large a layout as the device has memory for.
-void* ann_workspace_alloc(const pmlsh_index* x, int64_t nq, int k, int64_t B, hipStream_t st,
-                          AnnWorkspace* w) {
-    *w = ann_workspace(x, nq, k, B);
+void* ann_workspace_alloc(const pmlsh_index* x, int64_t nq, int k, int64_t B, Pools pools,
+                          hipStream_t st, AnnWorkspace* w) {
+    *w = ann_workspace(x, nq, k, B, pools);
     return ws_alloc_least(
         w->bytes, st, [&](int64_t* bytes) {
             const bool more = ann_workspace_smaller(x, k, w);
@@ -208,7 +208,7 @@ int64_t ann_workspace_bytes(const pmlsh_index* x, int64_t nq, int k, double c,
                             double confidence, double beta) {
     pmlsh_plan plan;
     plan_params(x->n, x->m, k, c, confidence, beta, &plan);
-    return nq > 0 ? ann_workspace(x, nq, k, plan.budget).bytes : 0;
+    return nq > 0 ? ann_workspace(x, nq, k, plan.budget, pools_of(x, nq, plan.budget)).bytes : 0;
 }
 
 namespace {
@@ -385,10 +385,19 @@ void run_ann(const pmlsh_index* x, const float* queries, int64_t nq, int k, doub
     pmlsh_plan plan;
     r_min = ann_plan(x, k, c, confidence, beta, r_min, &plan);
     if (nq == 0) return;
+    // (r,c)-BC by a few queries with a ball far below the budget's in a small index with
+    // contrast: few nodes of the tree lie near it, and one launch finds them (batched /
+    // per-query, us: 30,000 x 32, B = 2,902, a tenth of the budget's radius, 1 query 54 / 41,
+    // 500 queries 80 / 53, 3,000 queries 186 / 187; 200,000 x 64, 500 queries 84 / 75; without
+    // contrast 69 / 699)
+    Pools pools = pools_of(x, nq, plan.budget);
+    if (max_rounds == 1 && plan.budget > kLeanBudget && nq <= 512 && x->n <= 65536 && !x->low_contrast &&
+        r_min < 0.2 * index_default_r_min(x, plan.budget))
+        pools = Pools::Short;
     AnnWorkspace w;
     const AnnCall call{k, plan.budget, c, plan.t, r_min, nullptr, k, max_rounds,
                        ball_limit(x, plan.budget, r_min, max_rounds)};
-    void* ws = ann_workspace_alloc(x, nq, k, plan.budget, st, &w);
+    void* ws = ann_workspace_alloc(x, nq, k, plan.budget, pools, st, &w);
     try {
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, ws);
     } catch (...) {
@@ -476,7 +485,7 @@ void run_ann_planned(const pmlsh_index* x, const float* queries, int64_t nq,
 }
 
 int64_t ann_workspace_bytes_mixed(const pmlsh_index* x, int64_t nq, int kmax, int64_t bmax) {
-    return nq > 0 ? ann_workspace(x, nq, kmax, bmax).bytes : 0;
+    return nq > 0 ? ann_workspace(x, nq, kmax, bmax, pools_of(x, nq, bmax)).bytes : 0;
 }
 
 int64_t ann_workspace_bytes_least(const pmlsh_index* x, int kmax, int64_t bmax) {
@@ -499,7 +508,7 @@ void run_ann_mixed(const pmlsh_index* x, const float* queries, int64_t nq,
         return;
     }
     AnnWorkspace w;
-    void* ws = ann_workspace_alloc(x, nq, kmax, bmax, st, &w);
+    void* ws = ann_workspace_alloc(x, nq, kmax, bmax, pools_of(x, nq, bmax), st, &w);
     try {
         run_ann_region(x, queries, nq, call, out_ids, out_dist, out_stats, st, w, ws);
     } catch (...) {

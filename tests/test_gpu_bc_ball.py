@@ -77,3 +77,17 @@ def test_balls_that_outgrow_the_pools():
     say(f"case: ball cover with lists of 18,000, r={r}")
     ref = _same(pm, idx, Q, r, 2_048 / n)
     assert (ref[2][:30, 2] == pm.EXIT_BUDGET).all()
+
+
+@pytest.mark.parametrize("nq", [512, 513])
+def test_balls_far_below_the_budgets(nq):
+    """Few and many queries of small balls: the routes on both sides of the rule agree."""
+    pm = _gpu()
+    g = torch.Generator(device="cuda").manual_seed(16)
+    x = torch.randn(N, DIM, generator=g, device="cuda") + 4 * torch.randn(
+        40, DIM, generator=g, device="cuda")[torch.randint(40, (N,), generator=g, device="cuda")]
+    Q = (x[:nq] + 1e-2).contiguous()
+    idx = pm.Index(x, torch.randn(15, DIM, generator=g, device="cuda"))
+    for f in (0.02, 0.1999, 0.2001):
+        say(f"case: ball cover nq={nq} r={f} of r_min")
+        _same(pm, idx, Q, f * idx.default_r_min(2_049), 2_048 / N)
